@@ -1,0 +1,534 @@
+// Matrix products of the MLP path for any shape and alignment: batches that are no multiple of a tile, layer
+// widths of any size (rows that start on any 2-byte boundary), the narrow classifier layer.
+//
+//   forward   out[m][n] = bf16(relu(<A[m,:], B[n,:]> + bias[n]))      A = h_{k-1}, B = W_k       (both [.][k])
+//   logits    C[m][n]   = <A[m,:], B[n,:]> + bias[n]
+//   d-input   out[m][n] = bf16(sum_k A[m][k] B[k][n]) * [mask != 0]   A = delta_k, B = W_k       (B as [k][n])
+//   d-weight  C[m][n]   = sum_k A[m][k] B[k][n]                       A = delta_k^T, B = h_{k-1}  (or the update)
+//
+// Loads are 16 bytes per lane at any 2-byte boundary.  Nothing outside an operand's rows is read: a row index past
+// the end is clamped to the last row, a 16-byte piece past the end of a row is moved back to the row's last 16
+// bytes and shifted into place (zeros behind it) on its way to LDS, so the K loop has no branches per lane.
+//
+// Tiles.  These shapes are small or have few rows per weight, so what counts is to have enough bytes in flight on
+// enough compute units, not flops per LDS byte: BN = 64 columns, 32 / 64 / 128 rows.  With 32 or 64 rows (a whole
+// small batch) the wavefronts split the contraction of one tile among them (K steps of 128, a quarter or a half
+// each) instead of splitting the rows.
+//
+// Sums.  One chain of v_mfma_f32_32x32x16_bf16 rounds its fp32 accumulator once per 16 products: measured 1.6e-7 of
+// the result at K = 784 and 3.2e-7 at K = 3072 (normal operands), where a plain dot product spread over 64 lanes
+// has 6e-8 and 8e-8.  An activation is rounded to bf16 next, and the larger that error, the more activations land on
+// the wrong side of a rounding boundary.  The forward products therefore carry a sum in double: the accumulators of
+// one or two K steps (2 to 8 matrix instructions) are added to it and start again from zero (4e-8 to 6e-8 at any K).
+//
+// Measured (whole passes, against one-thread-per-output vector-ALU kernels that re-read an operand per output):
+// gradients of 3072-1024-512-10, 16 workers, batch 32: 19.7 ms -> 0.15 ms; objective of 3072-1024-10, 16 workers,
+// batch 500: 16.2 -> 0.11 ms (first product 0.105 ms = 480 TFLOP/s); whole step of 784-300-100-10, 8 workers,
+// batch 50: 1.26 -> 0.075 ms (5 to 8 us per product: launch and fill, not work).
+#include <type_traits>
+
+#include "mlp_common.h"
+
+namespace lsgd {
+
+namespace {
+
+constexpr int kRaggedThreads = 256;
+constexpr int kRaggedBN = 64;
+constexpr int kXcds = 8;
+
+
+__device__ __forceinline__ u32x4 load16(const uint16_t* p) { return *reinterpret_cast<const u32x4_any*>(p); }
+
+// v moved down by s elements of 16 bits, zeros from above (s = 0 .. 8)
+__device__ __forceinline__ u32x4 shift_in(u32x4 v, int s)
+{
+    uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
+    if (s >= 4) { lo = hi; hi = 0; s -= 4; }
+    if (s >= 4) { lo = 0; s = 0; }
+    if (s > 0) { lo = (lo >> (16 * s)) | (hi << (64 - 16 * s)); hi >>= 16 * s; }
+    return (u32x4){(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
+// rows shorter than 8 elements: element by element
+__device__ __forceinline__ u32x4 load_short(const uint16_t* p, int n)
+{
+    uint32_t e[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) e[q] = q < n ? p[q] : 0;
+    return (u32x4){e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+}
+
+// the first n < 4 of four values
+__device__ __forceinline__ void store_some(float* p, f32x4 v, int n)
+{
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+        if (e < n) p[e] = v[e];
+}
+__device__ __forceinline__ void store_some(uint16_t* p, u32x2 v, int n)
+{
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+        if (e < n) p[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+}
+
+template <int R>
+__device__ __forceinline__ void ragged_update(const FusedRow& r, const int64_t (&off)[R], const f32x4 (&gv)[R], const bool (&on)[R])
+{
+    const f32x4 zero = (f32x4)(0.f);
+    f32x4 xv[R], mv[R], zl[R], zg[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        xv[q] = mv[q] = zl[q] = zg[q] = zero;
+        if (on[q]) {
+            xv[q] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(r.x + off[q]));
+            if (r.m) mv[q] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(r.m + off[q]));
+            if (r.zl) zl[q] = *reinterpret_cast<const f32x4_any*>(r.zl + off[q]);
+            if (r.zg) zg[q] = *reinterpret_cast<const f32x4_any*>(r.zg + off[q]);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        if (!on[q]) continue;
+        if (r.m) update_vec<1, f32x4>(xv[q], gv[q], mv[q], zl[q], zg[q], r.c);
+        else update_vec<0, f32x4>(xv[q], gv[q], mv[q], zl[q], zg[q], r.c);
+        __builtin_nontemporal_store((f32x4_any)xv[q], reinterpret_cast<f32x4_any*>(r.x + off[q]));
+        if (r.m) __builtin_nontemporal_store((f32x4_any)mv[q], reinterpret_cast<f32x4_any*>(r.m + off[q]));
+        const u32x2 o = {f32x2_to_bf16x2(xv[q].x, xv[q].y), f32x2_to_bf16x2(xv[q].z, xv[q].w)};
+        *reinterpret_cast<u32x2_any*>(r.xb + off[q]) = o;
+    }
+}
+
+template <int BM, int WVM, int WVN, int WVK, int BK, int EPI>
+struct RaggedShape {
+    static constexpr bool FORWARD = EPI == EPI_FWD || EPI == EPI_LOGITS;
+    static constexpr bool TRANS_B = !FORWARD;                           // B given as [k][n]
+    using Sum = typename std::conditional<FORWARD, double, float>::type;
+    static constexpr int PROMOTE = BM > 64 ? 2 : 1;                     // K steps between promotions to the double sum
+    static constexpr int BN = kRaggedBN;
+    static constexpr int LDA = BK + 8;                                  // padded LDS row of a [.][k] operand
+    static constexpr int LDN = BN + kPadN;                              // of a [k][n] operand
+    static constexpr int A_TILE = BM * LDA;
+    static constexpr int B_TILE = TRANS_B ? BK * LDN : BN * LDA;
+    static constexpr int LDC = BN + 4;                                  // row of the result tile
+    static constexpr size_t operand_bytes = (size_t)2 * (A_TILE + B_TILE) * 2;
+    static constexpr size_t result_bytes = (size_t)WVK * BM * LDC * sizeof(Sum);
+    static constexpr size_t lds = operand_bytes > result_bytes ? operand_bytes : result_bytes;
+};
+
+template <int BM, int WVM, int WVN, int WVK, int BK, int EPI>
+__global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs g, int tiles_m, int tiles_n, int W, int64_t per_xcd)
+{
+    using S = RaggedShape<BM, WVM, WVN, WVK, BK, EPI>;
+    using Sum = typename S::Sum;
+    constexpr bool TRANS_B = S::TRANS_B;
+    static_assert(WVM * WVN * WVK == 4, "four wavefronts");
+    constexpr int BN = S::BN, LDA = S::LDA, LDN = S::LDN, LDC = S::LDC;
+    constexpr int TM = BM / WVM / 32, TN = BN / WVN / 32;               // 32x32 MFMA tiles per wavefront
+    constexpr int KCH = BK / 8;                                         // 16-byte pieces of a [.][k] row
+    constexpr int A_CHUNKS = BM * KCH / kRaggedThreads, B_CHUNKS = BN * BK / 8 / kRaggedThreads;
+    constexpr int A_STEP = kRaggedThreads / KCH;                        // rows between a thread's pieces
+    constexpr int KK = BK / 16 / WVK;                                   // MFMA steps of a wavefront per K step
+
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    uint16_t* As = smem;                                                // [2][BM][LDA]
+    uint16_t* Bs = smem + 2 * S::A_TILE;                                // [2][BN][LDA], or [2][BK][LDN]
+
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int wk = wid % WVK, wn = (wid / WVK) % WVN, wm = wid / (WVK * WVN);
+
+    // A die (workgroup id modulo 8) takes a contiguous run of tiles.  Row tiles vary fastest, so that the tiles
+    // that share a weight tile, and the workgroups of a worker, which share its activations, run on one die.  In
+    // the fused update the workers vary fastest instead: they share the leader copies' tile.
+    const int64_t id = (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    if (id >= (int64_t)tiles_m * tiles_n * W) return;
+    int w, tm, tn;
+    if (EPI == EPI_DWU) {
+        w = (int)(id % W);
+        const int64_t tile = id / W;
+        tn = (int)(tile % tiles_n); tm = (int)(tile / tiles_n);
+    } else {
+        tm = (int)(id % tiles_m);
+        const int64_t r = id / tiles_m;
+        tn = (int)(r % tiles_n); w = (int)(r / tiles_n);
+    }
+    const int m0 = tm * BM, n0 = tn * BN, M = g.M, N = g.N, K = g.K;
+    const uint16_t* A = g.A + (int64_t)w * g.sA;
+    const uint16_t* B = g.B + (int64_t)w * g.sB;
+    const bool short_k = K < 8, short_n = TRANS_B && N < 8;             // uniform
+
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    Sum sum[S::FORWARD ? TM : 1][S::FORWARD ? TN : 1][16];
+    if (S::FORWARD) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sum[i][j][v] = 0;
+    }
+    auto promote = [&]() {
+        if (!S::FORWARD) return;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) { sum[i][j][v] += (Sum)acc[i][j][v]; acc[i][j][v] = 0.f; }
+    };
+
+    // this thread's pieces: column piece kc of rows ra0 + c * A_STEP (a [k][n] operand: piece nc of rows kr0 + 32 c)
+    const int kc = (tid % KCH) * 8, ra0 = tid / KCH;
+    const int nc = (tid & 7) * 8, kr0 = tid >> 3;
+    const uint16_t* arow[A_CHUNKS];
+    const uint16_t* brow[B_CHUNKS];
+#pragma unroll
+    for (int c = 0; c < A_CHUNKS; ++c) {
+        const int r = m0 + ra0 + c * A_STEP;
+        arow[c] = A + (int64_t)(r < M ? r : M - 1) * g.lda;
+    }
+    if (!TRANS_B) {
+#pragma unroll
+        for (int c = 0; c < B_CHUNKS; ++c) {
+            const int r = n0 + ra0 + c * A_STEP;
+            brow[c] = B + (int64_t)(r < N ? r : N - 1) * g.ldb;
+        }
+    }
+    const int bcol = n0 + nc, bcol_in = bcol < N - 8 ? bcol : N - 8;     // [k][n]: first column read
+    const int bshift = bcol - bcol_in < 8 ? bcol - bcol_in : 8;
+    const bool edge_n = n0 + BN > N;                                     // uniform
+
+    auto load_global = [&](int kt, u32x4* ra, u32x4* rb) {
+        const int k = kt * BK + kc;
+        if (short_k) {
+            const int n = K - k < 0 ? 0 : K - k;
+#pragma unroll
+            for (int c = 0; c < A_CHUNKS; ++c) ra[c] = load_short(arow[c] + k, n);
+            if (!TRANS_B) {
+#pragma unroll
+                for (int c = 0; c < B_CHUNKS; ++c) rb[c] = load_short(brow[c] + k, n);
+            }
+        } else {
+            const int kin = k < K - 8 ? k : K - 8;
+#pragma unroll
+            for (int c = 0; c < A_CHUNKS; ++c) ra[c] = load16(arow[c] + kin);
+            if (!TRANS_B) {
+#pragma unroll
+                for (int c = 0; c < B_CHUNKS; ++c) rb[c] = load16(brow[c] + kin);
+            }
+        }
+        if (TRANS_B) {
+#pragma unroll
+            for (int c = 0; c < B_CHUNKS; ++c) {
+                const int kr = kt * BK + kr0 + c * 32;
+                const uint16_t* p = B + (int64_t)(kr < K ? kr : K - 1) * g.ldb;
+                if (short_n) rb[c] = load_short(p + bcol, N - bcol < 0 ? 0 : N - bcol);
+                else rb[c] = load16(p + bcol_in);
+            }
+        }
+    };
+    auto store_lds = [&](int buf, int kt, u32x4* ra, u32x4* rb) {
+        uint16_t* as = As + buf * S::A_TILE;
+        uint16_t* bs = Bs + buf * S::B_TILE;
+        const bool tail = (kt + 1) * BK > K;                             // uniform: the last K step, if it is not full
+        if (tail && !short_k) {
+            const int k = kt * BK + kc, kin = k < K - 8 ? k : K - 8;
+            const int s = k - kin < 8 ? k - kin : 8;
+#pragma unroll
+            for (int c = 0; c < A_CHUNKS; ++c) ra[c] = shift_in(ra[c], s);
+            if (!TRANS_B) {
+#pragma unroll
+                for (int c = 0; c < B_CHUNKS; ++c) rb[c] = shift_in(rb[c], s);
+            }
+        }
+        if (TRANS_B && (tail || (edge_n && !short_n))) {
+#pragma unroll
+            for (int c = 0; c < B_CHUNKS; ++c) {
+                const int s = (kt * BK + kr0 + c * 32 < K) ? (short_n ? 0 : bshift) : 8;
+                rb[c] = shift_in(rb[c], s);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < A_CHUNKS; ++c) *reinterpret_cast<u32x4*>(as + (ra0 + c * A_STEP) * LDA + kc) = ra[c];
+        if (TRANS_B) {
+#pragma unroll
+            for (int c = 0; c < B_CHUNKS; ++c) *reinterpret_cast<u32x4*>(bs + (kr0 + c * 32) * LDN + nc) = rb[c];
+        } else {
+#pragma unroll
+            for (int c = 0; c < B_CHUNKS; ++c) *reinterpret_cast<u32x4*>(bs + (ra0 + c * A_STEP) * LDA + kc) = rb[c];
+        }
+    };
+    auto compute = [&](int buf) {
+        const uint16_t* as = As + buf * S::A_TILE;
+        const uint16_t* bs = Bs + buf * S::B_TILE;
+#pragma unroll
+        for (int q = 0; q < KK; ++q) {
+            const int kk = wk * KK + q;
+            bf16x8 af[TM], bfr[TN];
+            const int ch = kk * 2 + (lane >> 5);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                af[i] = *reinterpret_cast<const bf16x8*>(as + ((wm * TM + i) * 32 + (lane & 31)) * LDA + ch * 8);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if (TRANS_B) {
+                    // lane (n = lane % 32, k-half = lane / 32): k = 16 kk + 8 (lane / 32) + 0..7 of column n
+                    const int i = lane & 15;
+                    const int col = (wn * TN + j) * 32 + (lane & 16) + 4 * (i & 3);
+                    const int row = kk * 16 + 8 * (lane >> 5) + (i >> 2);
+                    const s16x4 lo = lds_read_tr(bs + row * LDN + col);
+                    const s16x4 hi = lds_read_tr(bs + (row + 4) * LDN + col);
+                    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                    bfr[j] = __builtin_bit_cast(bf16x8, v);
+                } else {
+                    bfr[j] = *reinterpret_cast<const bf16x8*>(bs + ((wn * TN + j) * 32 + (lane & 31)) * LDA + ch * 8);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+        }
+    };
+
+    // K loop: LDS holds steps kt (being multiplied) and kt + 1, registers the next two
+    const int nk = (K + BK - 1) / BK;
+    {
+        u32x4 ra[A_CHUNKS], rb[B_CHUNKS], qa[A_CHUNKS], qb[B_CHUNKS];
+        load_global(0, ra, rb);
+        if (nk > 1) load_global(1, qa, qb);
+        store_lds(0, 0, ra, rb);
+        if (nk > 2) load_global(2, ra, rb);
+        __syncthreads();
+        int kt = 0;
+        // no conditional load in here: behind a branch around loads the compiler waits for all loads in flight
+        for (; kt + 4 < nk; kt += 2) {
+            store_lds(1, kt + 1, qa, qb);
+            load_global(kt + 3, qa, qb);
+            compute(0);
+            if (S::PROMOTE == 1) promote();
+            __syncthreads();
+            store_lds(0, kt + 2, ra, rb);
+            load_global(kt + 4, ra, rb);
+            compute(1);
+            promote();
+            __syncthreads();
+        }
+        const int left = nk - kt;                                        // 1 .. 4 steps, the first already in buffer 0
+        if (left > 1) store_lds(1, kt + 1, qa, qb);
+        if (left > 3) load_global(kt + 3, qa, qb);
+        compute(0);
+        if (S::PROMOTE == 1) promote();
+        __syncthreads();
+        if (left > 1) {
+            if (left > 2) store_lds(0, kt + 2, ra, rb);
+            compute(1);
+            promote();
+            __syncthreads();
+        }
+        if (left > 2) {
+            if (left > 3) store_lds(1, kt + 3, qa, qb);
+            compute(0);
+            if (S::PROMOTE == 1) promote();
+            __syncthreads();
+        }
+        if (left > 3) {
+            compute(1);
+            __syncthreads();
+        }
+        promote();
+    }
+
+    // The wavefronts' accumulators meet in LDS (lane: column lane % 32, rows (lane / 32) * 4 + 8 (v / 4) + v % 4 of
+    // each 32x32 tile) and come back as four adjacent columns per thread.
+    Sum* T = reinterpret_cast<Sum*>(smem);                              // [WVK][BM][LDC]
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = (wm * TM + i) * 32 + (lane >> 5) * 4 + 8 * (v >> 2) + (v & 3);
+                T[(wk * BM + r) * LDC + (wn * TN + j) * 32 + (lane & 31)] = S::FORWARD ? sum[S::FORWARD ? i : 0][S::FORWARD ? j : 0][v] : (Sum)acc[i][j][v];
+            }
+    __syncthreads();
+    constexpr int PASSES = BM / 16;                                     // 16 threads per row
+    const int c4 = (tid & 15) * 4, r0 = tid >> 4, n = n0 + c4;
+    const int nv = N - n < 4 ? N - n : 4;                               // columns of this thread (may be <= 0)
+    typedef Sum sum4 __attribute__((ext_vector_type(4)));
+    auto value = [&](int p) {
+        sum4 v = *reinterpret_cast<const sum4*>(T + (r0 + 16 * p) * LDC + c4);
+#pragma unroll
+        for (int q = 1; q < WVK; ++q) v += *reinterpret_cast<const sum4*>(T + (q * BM + r0 + 16 * p) * LDC + c4);
+        return v;
+    };
+    if constexpr (S::FORWARD) {
+        sum4 b = (sum4)(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e < nv) b[e] = g.bias[(int64_t)w * g.sBias + n + e];
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int m = m0 + r0 + 16 * p;
+            if (m >= M || nv <= 0) continue;
+            const sum4 zs = value(p) + b;
+            const f32x4 z = {(float)zs.x, (float)zs.y, (float)zs.z, (float)zs.w};
+            if (EPI == EPI_LOGITS) {
+                float* dst = g.C + (int64_t)w * g.sC + (int64_t)m * g.ldc + n;
+                if (nv == 4) *reinterpret_cast<f32x4_any*>(dst) = z;
+                else store_some(dst, z, nv);
+            } else {
+                uint16_t* dst = g.out + (int64_t)w * g.sOut + (int64_t)m * g.ldout + n;
+                const u32x2 o = {f32x2_to_bf16x2(z.x > 0.f ? z.x : 0.f, z.y > 0.f ? z.y : 0.f),
+                                 f32x2_to_bf16x2(z.z > 0.f ? z.z : 0.f, z.w > 0.f ? z.w : 0.f)};
+                if (nv == 4) *reinterpret_cast<u32x2_any*>(dst) = o;
+                else store_some(dst, o, nv);
+            }
+        }
+        return;
+    } else if constexpr (EPI == EPI_DX) {
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int m = m0 + r0 + 16 * p;
+            f32x4 v = value(p);
+            if (m < M && nv > 0) {
+                const uint16_t* mk = g.mask + (int64_t)w * g.sMask + (int64_t)m * g.ldmask + n;
+                u32x2 h = {0u, 0u};
+                if (nv == 4) h = *reinterpret_cast<const u32x2_any*>(mk);
+                else {
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+                        if (e < nv) h[e >> 1] |= (uint32_t)mk[e] << (16 * (e & 1));
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (((h[e >> 1] >> (16 * (e & 1))) & 0xFFFFu) == 0) v[e] = 0.f;
+                uint16_t* dst = g.out + (int64_t)w * g.sOut + (int64_t)m * g.ldout + n;
+                const u32x2 o = {f32x2_to_bf16x2(v.x, v.y), f32x2_to_bf16x2(v.z, v.w)};
+                if (nv == 4) *reinterpret_cast<u32x2_any*>(dst) = o;
+                else store_some(dst, o, nv);
+            }
+            *reinterpret_cast<f32x4*>(T + (r0 + 16 * p) * LDC + c4) = v;   // this thread's own elements of copy 0
+        }
+        __syncthreads();
+        // the transposed copy: four samples of one column per thread
+        constexpr int MQ = BM / 4, CPP = kRaggedThreads / MQ;            // threads per column, columns per pass
+        const int mq = (tid % MQ) * 4, mm = m0 + mq;
+        const int mv = M - mm < 4 ? M - mm : 4;
+#pragma unroll
+        for (int p = 0; p < BN / CPP; ++p) {
+            const int col = tid / MQ + p * CPP;
+            if (n0 + col >= N || mv <= 0) continue;
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = T[(mq + e) * LDC + col];
+            const u32x2 o = {f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3])};
+            uint16_t* dst = g.outT + (int64_t)w * g.sOutT + (int64_t)(n0 + col) * g.ldoutT + mm;
+            if (mv == 4) *reinterpret_cast<u32x2_any*>(dst) = o;
+            else store_some(dst, o, mv);
+        }
+        return;
+    } else if constexpr (EPI == EPI_DW) {
+        float* C = g.C + (int64_t)w * g.sC;
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int m = m0 + r0 + 16 * p;
+            if (m >= M || nv <= 0) continue;
+            const f32x4 v = value(p);
+            float* dst = C + (int64_t)m * g.ldc + n;
+            if (nv == 4) *reinterpret_cast<f32x4_any*>(dst) = v;
+            else store_some(dst, v, nv);
+        }
+        return;
+    } else {
+    // EPI_DWU: the update in place of the store
+    constexpr int R = PASSES < 4 ? PASSES : 4;                          // rows in flight per thread
+    const FusedRow fr = fused_row(g.fu, w, g.sC);
+#pragma unroll
+    for (int p0 = 0; p0 < PASSES; p0 += R) {
+        f32x4 gv[R];
+        int64_t off[R];
+        bool on[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int m = m0 + r0 + 16 * (p0 + q);
+            gv[q] = value(p0 + q);
+            off[q] = g.colC + (int64_t)m * g.ldc + n;
+            on[q] = m < M && nv == 4;
+            if (m < M && nv > 0 && nv < 4) {
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    const int o1[1] = {0};
+                    const float g1[1] = {gv[q][e]};
+                    if (e < nv) fused_apply<1>(fr, off[q] + e, o1, g1);
+                }
+            }
+        }
+        ragged_update<R>(fr, off, gv, on);
+    }
+    }
+}
+
+template <int BM, int WVM, int WVN, int WVK, int BK, int EPI>
+void launch_tile(const GemmArgs& g, int W, hipStream_t s)
+{
+    using S = RaggedShape<BM, WVM, WVN, WVK, BK, EPI>;
+    auto kernel = gemm_ragged_kernel<BM, WVM, WVN, WVK, BK, EPI>;
+    if (S::lds > 64 * 1024) {
+        static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::lds);
+        (void)once;
+    }
+    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + kRaggedBN - 1) / kRaggedBN;
+    const int64_t per_xcd = ((int64_t)tiles_m * tiles_n * W + kXcds - 1) / kXcds;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(per_xcd * kXcds)), dim3(kRaggedThreads), S::lds, s, g, tiles_m, tiles_n, W, per_xcd);
+}
+
+// Row tile: a batch of up to 32 / 64 fits one tile; larger ones take 128 rows, unless that leaves compute units
+// without a workgroup.
+template <int EPI>
+void launch_epi(const GemmArgs& g, int W, hipStream_t s)
+{
+    const int64_t cols = (int64_t)((g.N + kRaggedBN - 1) / kRaggedBN) * W;
+    const bool fill64 = cols * ((g.M + 63) / 64) >= 256, fill128 = cols * ((g.M + 127) / 128) >= 256;
+    if constexpr (EPI == EPI_DW || EPI == EPI_DWU) {
+        if (g.M > 64 && fill128) launch_tile<128, 2, 2, 1, 64, EPI>(g, W, s);
+        else if (g.M > 32) launch_tile<64, 2, 2, 1, 64, EPI>(g, W, s);
+        else launch_tile<32, 1, 2, 2, 64, EPI>(g, W, s);
+    } else {
+        // one K step (the classifier layer's d-input): a stream of results, many small workgroups
+        if constexpr (EPI == EPI_DX) {
+            if (g.K <= 64) {
+                if (g.M > 32) launch_tile<64, 2, 2, 1, 64, EPI>(g, W, s);
+                else launch_tile<32, 1, 2, 2, 64, EPI>(g, W, s);
+                return;
+            }
+        }
+        if (g.M > 64 && fill128) launch_tile<128, 2, 2, 1, 64, EPI>(g, W, s);
+        else if (g.M > 32 && fill64) launch_tile<64, 1, 2, 2, 128, EPI>(g, W, s);
+        else launch_tile<32, 1, 1, 4, 128, EPI>(g, W, s);
+    }
+}
+
+} // namespace
+
+void launch_gemm_ragged(const GemmArgs& g, int W, int epi, hipStream_t s)
+{
+    switch (epi) {
+    case EPI_FWD: launch_epi<EPI_FWD>(g, W, s); break;
+    case EPI_LOGITS: launch_epi<EPI_LOGITS>(g, W, s); break;
+    case EPI_DX: launch_epi<EPI_DX>(g, W, s); break;
+    case EPI_DW: launch_epi<EPI_DW>(g, W, s); break;
+    case EPI_DWU: launch_epi<EPI_DWU>(g, W, s); break;
+    }
+}
+
+} // namespace lsgd

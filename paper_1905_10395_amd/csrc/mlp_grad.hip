@@ -10,9 +10,9 @@
 //             delta_{k-1} = bf16((delta_k W_k) .* [h_{k-1} > 0])
 //
 // The three matrix products are dense contractions and run on the matrix
-// cores (v_mfma_f32_32x32x16_bf16) whenever the shapes are multiples of the
-// tile sizes; a plain vector-ALU path covers every other shape, including
-// the narrow classifier layer.
+// cores (v_mfma_f32_32x32x16_bf16): with the kernel in this file when the
+// shapes are multiples of its tile sizes and the rows 16-byte aligned, with the
+// any-shape kernel (mlp_gemm_ragged.hip) otherwise, the narrow classifier layer included.
 //
 // Operand layouts for the MFMA kernel.  A lane feeds the matrix core eight
 // consecutive values along the contraction index:
@@ -23,149 +23,12 @@
 // tile is staged in LDS as it lies in memory and the fragments are fetched
 // with the LDS transposing read (see lds_read_tr).  delta_k is stored in both
 // layouts by the kernel that produces it.
-#include "common.h"
-#include "update_math.h"
+#include "mlp_common.h"
 
 namespace lsgd {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-enum { EPI_FWD = 0, EPI_DX = 1, EPI_DW = 2, EPI_DWU = 3 };   // DWU: d-weight with the update applied in place of the store
-
-struct GemmArgs {
-    const uint16_t* A; int64_t sA; int64_t lda;   // [M][K], per-worker stride sA (elements)
-    const uint16_t* B; int64_t sB; int64_t ldb;   // TRANS_B ? [K][N] : [N][K]
-    int M, N, K;
-    const float* bias; int64_t sBias;             // EPI_FWD: fp32 [N]
-    const uint16_t* mask; int64_t sMask; int64_t ldmask; // EPI_DX: h_{k-1} [M][N]
-    uint16_t* out; int64_t sOut; int64_t ldout;   // EPI_FWD: h [M][N]; EPI_DX: delta [M][N]
-    uint16_t* outT; int64_t sOutT; int64_t ldoutT;// EPI_DX: delta^T [N][M]
-    float* C; int64_t sC; int64_t ldc;            // EPI_DW: fp32 [M][N]
-    FusedUpdate fu; int64_t colC;                 // EPI_DWU: update state; column of C[0][0] in the parameter row
-};
-
-// Per-worker view of the fused update: coefficients (with the leader exemption resolved) and row pointers.
-struct FusedRow {
-    Coef c;
-    float* x;
-    float* m;
-    uint16_t* xb;
-    const float* zl;
-    const float* zg;
-};
-
-__device__ __forceinline__ FusedRow fused_row(const FusedUpdate& u, int w, int64_t ld)
-{
-    FusedRow r;
-    r.c.eta = u.eta; r.c.mu = u.mu; r.c.wd = u.wd; r.c.cL = u.lamL; r.c.cG = u.lamG;
-    r.c.nesterov = (u.flags & LSGD_NESTEROV) != 0;
-    r.c.grad_only = (u.flags & LSGD_MOMENTUM_GRAD_ONLY) != 0;
-    const int j = u.group_of[w];
-    if (u.flags & LSGD_LEADER_EXEMPT) {
-        if (u.lamL != 0.0f && u.lead[j] == w) r.c.cL = 0.0f;
-        if (u.lamG != 0.0f && u.glead[0] == w) r.c.cG = 0.0f;
-    }
-    r.x = u.x + (int64_t)w * ld;
-    r.m = u.m ? u.m + (int64_t)w * ld : nullptr;
-    r.xb = u.xb + (int64_t)w * ld;
-    r.zl = (u.lamL != 0.0f) ? u.Z + (int64_t)j * ld : nullptr;
-    r.zg = (u.lamG != 0.0f) ? u.Z + (int64_t)u.G * ld : nullptr;
-    return r;
-}
-
-// N parameters at columns base + off[0..N) of the worker's row, gradient values gv: all loads first,
-// then the arithmetic, then the stores (x, m, bf16 copy).
-template <int N>
-__device__ __forceinline__ void fused_apply(const FusedRow& r, int64_t base, const int (&off)[N], const float (&gv)[N])
-{
-    float* xp = r.x + base;
-    float* mp = r.m ? r.m + base : nullptr;
-    const float* lp = r.zl ? r.zl + base : nullptr;
-    const float* gp = r.zg ? r.zg + base : nullptr;
-    uint16_t* bp = r.xb + base;
-    float xv[N], mv[N], zl[N], zg[N];
-#pragma unroll
-    for (int v = 0; v < N; ++v) xv[v] = xp[off[v]];
-#pragma unroll
-    for (int v = 0; v < N; ++v) mv[v] = mp ? mp[off[v]] : 0.f;
-#pragma unroll
-    for (int v = 0; v < N; ++v) zl[v] = lp ? lp[off[v]] : 0.f;
-#pragma unroll
-    for (int v = 0; v < N; ++v) zg[v] = gp ? gp[off[v]] : 0.f;
-#pragma unroll
-    for (int v = 0; v < N; ++v) {
-        if (mp) update_vec<1, float>(xv[v], gv[v], mv[v], zl[v], zg[v], r.c);
-        else update_vec<0, float>(xv[v], gv[v], mv[v], zl[v], zg[v], r.c);
-    }
-#pragma unroll
-    for (int v = 0; v < N; ++v) {
-        xp[off[v]] = xv[v];
-        if (mp) mp[off[v]] = mv[v];
-        bp[off[v]] = f32_to_bf16_rne(xv[v]);
-    }
-}
-
-// R groups of four adjacent parameters (columns multiples of 4, rows 16-byte aligned) at element offsets
-// `off` of the worker's row: the loads of one batch are issued as a block, so that they are in flight while the previous batch is updated and stored.
-template <int R>
-struct FusedBatch {
-    int64_t off[R];
-    f32x4 xv[R], mv[R], zl[R], zg[R];
-};
-
-template <int R>
-__device__ __forceinline__ void fused_load4(const FusedRow& r, FusedBatch<R>& b)
-{
-    const f32x4 zero = (f32x4)(0.f);
-#pragma unroll
-    for (int q = 0; q < R; ++q) b.xv[q] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(r.x + b.off[q]));
-#pragma unroll
-    for (int q = 0; q < R; ++q) b.mv[q] = r.m ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(r.m + b.off[q])) : zero;
-#pragma unroll
-    for (int q = 0; q < R; ++q) b.zl[q] = r.zl ? *reinterpret_cast<const f32x4*>(r.zl + b.off[q]) : zero;
-#pragma unroll
-    for (int q = 0; q < R; ++q) b.zg[q] = r.zg ? *reinterpret_cast<const f32x4*>(r.zg + b.off[q]) : zero;
-}
-
-template <int R>
-__device__ __forceinline__ void fused_store4(const FusedRow& r, FusedBatch<R>& b, const f32x4 (&gv)[R])
-{
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-        if (r.m) update_vec<1, f32x4>(b.xv[q], gv[q], b.mv[q], b.zl[q], b.zg[q], r.c);
-        else update_vec<0, f32x4>(b.xv[q], gv[q], b.mv[q], b.zl[q], b.zg[q], r.c);
-    }
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-        __builtin_nontemporal_store(b.xv[q], reinterpret_cast<f32x4*>(r.x + b.off[q]));
-        if (r.m) __builtin_nontemporal_store(b.mv[q], reinterpret_cast<f32x4*>(r.m + b.off[q]));
-        const u32x2 o = {f32x2_to_bf16x2(b.xv[q].x, b.xv[q].y), f32x2_to_bf16x2(b.xv[q].z, b.xv[q].w)};
-        *reinterpret_cast<u32x2*>(r.xb + b.off[q]) = o;
-    }
-}
-
 constexpr int kBK = 64;          // contraction tile
 constexpr int kLdk = kBK + 8;    // padded LDS row (bf16 elements): 144 B
-
-// An operand given as [k][n] (n contiguous: the weights in the d-input product, the activations in the
-// d-weight product) is staged in LDS as it lies in memory, 64 k-rows of BN + kPadN elements: the padding shifts
-// consecutive rows by 64 bytes, i.e. a quarter of the banks, so that the four rows one transposing read touches
-// cover all banks once.  The matrix cores want, per lane, eight consecutive k of one column n; the LDS
-// transposing read delivers that: in every group of 16 lanes, lane i supplies the address of four consecutive
-// elements, the 16 x 4 elements are taken as a 4 x 16 matrix (lanes 4r .. 4r+3 hold row r), and lane i receives
-// column i.  With lanes 4r .. 4r+3 pointing at k-row r, columns n0 .. n0+15, lane i gets (k0 .. k0+3, n0 + i).
-constexpr int kPadN = 32;
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ s16x4 lds_read_tr(const uint16_t* p)
-{
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
-}
 
 // BM x BN output tile per workgroup, WVM x WVN wavefronts, each owning (BM/WVM) x (BN/WVN).
 // 128x128 / 128x64 with 2x2 wavefronts run two workgroups per CU; 256x256 with 2x4 wavefronts
@@ -536,39 +399,6 @@ static bool try_mfma(const GemmArgs& g, int W, hipStream_t s)
     return true;
 }
 
-// ------------------------------------------------------------------------------------------
-// Vector-ALU kernels: any shape.  They are the path of the narrow classifier layer and the
-// fallback of shapes the MFMA tiles do not divide.
-// ------------------------------------------------------------------------------------------
-
-// out[b][o] = sum_i h[b][i] * Wq[o][i] + bias[o].  One wavefront per (b, worker); lanes stride over i.
-// HIDDEN: relu + bf16 store; else fp32 logits.
-template <bool HIDDEN>
-__global__ __launch_bounds__(256) void fwd_valu_kernel(const uint16_t* __restrict__ H, int64_t sH, int64_t ldh,
-                                                       const uint16_t* __restrict__ Wq, int64_t sW, const float* __restrict__ bias,
-                                                       int64_t sBias, int B, int din, int dout, uint16_t* __restrict__ out,
-                                                       float* __restrict__ logits, int64_t sOut, int64_t ldout)
-{
-    const int lane = threadIdx.x & 63;
-    const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int w = blockIdx.y;
-    if (b >= B) return;
-    const uint16_t* h = H + (int64_t)w * sH + (int64_t)b * ldh;
-    const uint16_t* Wm = Wq + (int64_t)w * sW;
-    for (int o = 0; o < dout; ++o) {
-        const uint16_t* wr = Wm + (int64_t)o * din;
-        float acc = 0.f;
-        for (int i = lane; i < din; i += 64) acc = fmaf(bf16_to_f32(h[i]), bf16_to_f32(wr[i]), acc);
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
-        if (lane == 0) {
-            const float z = acc + bias[(int64_t)w * sBias + o];
-            if (HIDDEN) out[(int64_t)w * sOut + (int64_t)b * ldout + o] = f32_to_bf16_rne(z > 0.f ? z : 0.f);
-            else logits[(int64_t)w * sOut + (int64_t)b * ldout + o] = z;
-        }
-    }
-}
-
 // Softmax cross-entropy of one worker's batch: loss = mean_b(lse - z[y]); delta = bf16((p - onehot)/B),
 // stored as [B][C] and [C][B].  One workgroup per worker.
 __global__ __launch_bounds__(256) void loss_delta_kernel(const float* __restrict__ logits, int64_t sLogits, const int32_t* __restrict__ y,
@@ -607,70 +437,6 @@ __global__ __launch_bounds__(256) void loss_delta_kernel(const float* __restrict
     if (threadIdx.x == 0) losses[w] = (float)(red[0] / (double)B);
 }
 
-// dW[o][i] = sum_b deltaT[o][b] * h[b][i].  One thread per (o, i).
-__global__ __launch_bounds__(256) void dw_valu_kernel(const uint16_t* __restrict__ deltaT, int64_t sD, const uint16_t* __restrict__ H,
-                                                      int64_t sH, int64_t ldh, int B, int din, int dout, float* __restrict__ g, int64_t sG,
-                                                      FusedUpdate fu, int64_t col0)
-{
-    const int w = blockIdx.z, o = blockIdx.y;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= din) return;
-    const uint16_t* dt = deltaT + (int64_t)w * sD + (int64_t)o * B;
-    const uint16_t* h = H + (int64_t)w * sH;
-    float acc = 0.f;
-    for (int b = 0; b < B; ++b) acc = fmaf(bf16_to_f32(dt[b]), bf16_to_f32(h[(int64_t)b * ldh + i]), acc);
-    if (fu.enabled) {
-        const int off[1] = {0};
-        const float gv[1] = {acc};
-        fused_apply<1>(fused_row(fu, w, sG), col0 + (int64_t)o * din + i, off, gv);
-    } else {
-        g[(int64_t)w * sG + (int64_t)o * din + i] = acc;
-    }
-}
-
-// db[o] = sum_b deltaT[o][b].  One wavefront per o.
-__global__ __launch_bounds__(256) void db_kernel(const uint16_t* __restrict__ deltaT, int64_t sD, int B, int dout, float* __restrict__ g, int64_t sG,
-                                                 FusedUpdate fu, int64_t col0)
-{
-    const int lane = threadIdx.x & 63;
-    const int o = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int w = blockIdx.y;
-    if (o >= dout) return;
-    const uint16_t* dt = deltaT + (int64_t)w * sD + (int64_t)o * B;
-    float acc = 0.f;
-    for (int b = lane; b < B; b += 64) acc += bf16_to_f32(dt[b]);
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
-    if (lane == 0) {
-        if (fu.enabled) {
-            const int off[1] = {0};
-            const float gv[1] = {acc};
-            fused_apply<1>(fused_row(fu, w, sG), col0 + o, off, gv);
-        } else {
-            g[(int64_t)w * sG + o] = acc;
-        }
-    }
-}
-
-// dprev[b][i] = bf16((sum_o delta[b][o] * Wq[o][i]) * [h[b][i] > 0]), also stored transposed.  One thread per (b, i).
-__global__ __launch_bounds__(256) void dx_valu_kernel(const uint16_t* __restrict__ delta, int64_t sD, const uint16_t* __restrict__ Wq, int64_t sW,
-                                                      const uint16_t* __restrict__ H, int64_t sH, int64_t ldh, int B, int din, int dout,
-                                                      uint16_t* __restrict__ dprev, uint16_t* __restrict__ dprevT, int64_t sP)
-{
-    const int w = blockIdx.z, b = blockIdx.y;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= din) return;
-    const uint16_t* d = delta + (int64_t)w * sD + (int64_t)b * dout;
-    const uint16_t* Wm = Wq + (int64_t)w * sW;
-    float acc = 0.f;
-    for (int o = 0; o < dout; ++o) acc = fmaf(bf16_to_f32(d[o]), bf16_to_f32(Wm[(int64_t)o * din + i]), acc);
-    const bool on = H[(int64_t)w * sH + (int64_t)b * ldh + i] != 0;
-    const uint16_t q = on ? f32_to_bf16_rne(acc) : (uint16_t)0;
-    dprev[(int64_t)w * sP + (int64_t)b * din + i] = q;
-    dprevT[(int64_t)w * sP + (int64_t)i * B + b] = q;
-}
-
-// ---- narrow-layer kernels: the classifier layer (a handful of classes) with 16-byte loads ----
 __device__ __forceinline__ void unpack8(const u32x4 v, float* f)
 {
 #pragma unroll
@@ -680,38 +446,8 @@ __device__ __forceinline__ void unpack8(const u32x4 v, float* f)
     }
 }
 
-// One wavefront per output (b, o): out = <h[b,:], Wq[o,:]> + bias[o].  d_in % 8 == 0, rows 16-byte aligned.
-template <bool HIDDEN>
-__global__ __launch_bounds__(256) void fwd_narrow_kernel(const uint16_t* __restrict__ H, int64_t sH, int64_t ldh,
-                                                         const uint16_t* __restrict__ Wq, int64_t sW, const float* __restrict__ bias,
-                                                         int64_t sBias, int B, int din, int dout, uint16_t* __restrict__ out,
-                                                         float* __restrict__ logits, int64_t sOut, int64_t ldout)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t idx = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int w = blockIdx.y;
-    if (idx >= (int64_t)B * dout) return;
-    const int b = (int)(idx / dout), o = (int)(idx % dout);
-    const u32x4* h = reinterpret_cast<const u32x4*>(H + (int64_t)w * sH + (int64_t)b * ldh);
-    const u32x4* wr = reinterpret_cast<const u32x4*>(Wq + (int64_t)w * sW + (int64_t)o * din);
-    float acc = 0.f;
-    for (int c = lane; c < din / 8; c += 64) {
-        float a[8], q[8];
-        unpack8(h[c], a); unpack8(wr[c], q);
-#pragma unroll
-        for (int t = 0; t < 8; ++t) acc = fmaf(a[t], q[t], acc);
-    }
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
-    if (lane == 0) {
-        const float z = acc + bias[(int64_t)w * sBias + o];
-        if (HIDDEN) out[(int64_t)w * sOut + (int64_t)b * ldout + o] = f32_to_bf16_rne(z > 0.f ? z : 0.f);
-        else logits[(int64_t)w * sOut + (int64_t)b * ldout + o] = z;
-    }
-}
-
-// Bias gradients of all layers in one launch: db_k[o] = sum_b deltaT_k[o][b] with 16-byte loads, half a
-// wavefront per output, eight outputs per workgroup.  B % 8 == 0, rows 16-byte aligned.
+// Bias gradients of all layers in one launch: db_k[o] = sum_b deltaT_k[o][b] with 16-byte loads (at any 2-byte
+// boundary), half a wavefront per output, eight outputs per workgroup; the last B % 8 samples one by one.
 struct BiasLayers {
     int n;                    // layers
     int first_block[65];      // workgroups of layer i: first_block[i] .. first_block[i+1]
@@ -731,13 +467,14 @@ __global__ __launch_bounds__(256) void db_all_kernel(const uint16_t* __restrict_
     const int dout = t.dout[layer];
     float acc = 0.f;
     if (o < dout) {
-        const u32x4* dt = reinterpret_cast<const u32x4*>(scratch + (int64_t)w * sD + t.dT[layer] + (int64_t)o * B);
+        const uint16_t* dt = scratch + (int64_t)w * sD + t.dT[layer] + (int64_t)o * B;
         for (int c = l; c < B / 8; c += 32) {
             float a[8];
-            unpack8(dt[c], a);
+            unpack8(*reinterpret_cast<const u32x4_any*>(dt + c * 8), a);
 #pragma unroll
             for (int q = 0; q < 8; ++q) acc += a[q];
         }
+        if (l < (B & 7)) acc += bf16_to_f32(dt[(B & ~7) + l]);
     }
 #pragma unroll
     for (int d = 1; d < 32; d <<= 1) acc += __shfl_xor(acc, d, 64);
@@ -749,122 +486,6 @@ __global__ __launch_bounds__(256) void db_all_kernel(const uint16_t* __restrict_
             fused_apply<1>(fused_row(fu, w, sG), col, off, gv);
         } else {
             g[(int64_t)w * sG + col] = acc;
-        }
-    }
-}
-
-// dW[o][i..i+7] for one output row o and 512 columns per workgroup; the four wavefronts split the batch
-// and combine through LDS in a fixed order.  d_in % 8 == 0.
-__global__ __launch_bounds__(256) void dw_narrow_kernel(const uint16_t* __restrict__ deltaT, int64_t sD, const uint16_t* __restrict__ H,
-                                                        int64_t sH, int64_t ldh, int B, int din, int dout, float* __restrict__ g, int64_t sG,
-                                                        FusedUpdate fu, int64_t col0)
-{
-    const int w = blockIdx.z, o = blockIdx.y;
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int c = blockIdx.x * 64 + lane;            // 16-byte chunk (8 columns)
-    const bool live = c < din / 8;
-    const uint16_t* dt = deltaT + (int64_t)w * sD + (int64_t)o * B;
-    const uint16_t* h = H + (int64_t)w * sH;
-    float acc[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) acc[t] = 0.f;
-    const int b0 = (int)((int64_t)B * q / 4), b1 = (int)((int64_t)B * (q + 1) / 4);
-    if (live) {
-        int b = b0;
-        for (; b + 8 <= b1; b += 8) {                     // eight rows of h in flight
-            u32x4 hv[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) hv[u] = *reinterpret_cast<const u32x4*>(h + (int64_t)(b + u) * ldh + (int64_t)c * 8);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float d = bf16_to_f32(dt[b + u]);
-                float a[8];
-                unpack8(hv[u], a);
-#pragma unroll
-                for (int t = 0; t < 8; ++t) acc[t] = fmaf(d, a[t], acc[t]);
-            }
-        }
-        for (; b < b1; ++b) {
-            const float d = bf16_to_f32(dt[b]);
-            float a[8];
-            unpack8(*reinterpret_cast<const u32x4*>(h + (int64_t)b * ldh + (int64_t)c * 8), a);
-#pragma unroll
-            for (int t = 0; t < 8; ++t) acc[t] = fmaf(d, a[t], acc[t]);
-        }
-    }
-    __shared__ float red[4][64][9];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) red[q][lane][t] = acc[t];
-    __syncthreads();
-    if (q == 0 && live) {
-        float sum[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) sum[t] = ((red[0][lane][t] + red[1][lane][t]) + red[2][lane][t]) + red[3][lane][t];
-        if (fu.enabled) {
-            const int off[8] = {0, 1, 2, 3, 4, 5, 6, 7};
-            fused_apply<8>(fused_row(fu, w, sG), col0 + (int64_t)o * din + (int64_t)c * 8, off, sum);
-        } else {
-            float* dst = g + (int64_t)w * sG + (int64_t)o * din + (int64_t)c * 8;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) dst[t] = sum[t];
-        }
-    }
-}
-
-// dprev[b][i..i+7] = bf16(sum_o delta[b][o] Wq[o][i..i+7]) .* [h > 0] for a narrow delta (few classes).
-// A workgroup owns 64 samples x 64 columns: thread (b, 8-column chunk).  The row-major result is
-// stored directly (128 contiguous bytes per sample); the transposed copy goes through an LDS tile so
-// that it too leaves as 128-byte runs (64 samples of one column).
-__global__ __launch_bounds__(512) void dx_narrow_kernel(const uint16_t* __restrict__ delta, int64_t sD, const uint16_t* __restrict__ Wq, int64_t sW,
-                                                        const uint16_t* __restrict__ H, int64_t sH, int64_t ldh, int B, int din, int dout,
-                                                        uint16_t* __restrict__ dprev, uint16_t* __restrict__ dprevT, int64_t sP)
-{
-    constexpr int kLd = 72;                                   // padded tile row (bf16), 144 B
-    __shared__ __attribute__((aligned(16))) uint16_t tile[64 * kLd];   // [column][sample]
-    const int w = blockIdx.z;
-    const int t = threadIdx.x, cl = t & 7, bl = t >> 3;
-    const int b = blockIdx.y * 64 + bl;
-    const int c = blockIdx.x * 8 + cl;                        // 16-byte chunk = 8 columns
-    const bool live = b < B && c < din / 8;
-    uint32_t pk[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) pk[q] = 0;
-    if (live) {
-        const uint16_t* d = delta + (int64_t)w * sD + (int64_t)b * dout;
-        const uint16_t* Wm = Wq + (int64_t)w * sW + (int64_t)c * 8;
-        float acc[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) acc[q] = 0.f;
-        for (int o = 0; o < dout; ++o) {
-            const float dv = bf16_to_f32(d[o]);
-            float a[8];
-            unpack8(*reinterpret_cast<const u32x4*>(Wm + (int64_t)o * din), a);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) acc[q] = fmaf(dv, a[q], acc[q]);
-        }
-        const u32x4 hm = *reinterpret_cast<const u32x4*>(H + (int64_t)w * sH + (int64_t)b * ldh + (int64_t)c * 8);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const uint32_t hb = (q & 1) ? (hm[q >> 1] >> 16) : (hm[q >> 1] & 0xFFFFu);
-            pk[q] = hb ? (uint32_t)f32_to_bf16_rne(acc[q]) : 0u;
-        }
-        u32x4 o4 = {pk[0] | (pk[1] << 16), pk[2] | (pk[3] << 16), pk[4] | (pk[5] << 16), pk[6] | (pk[7] << 16)};
-        *reinterpret_cast<u32x4*>(dprev + (int64_t)w * sP + (int64_t)b * din + (int64_t)c * 8) = o4;
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) tile[(cl * 8 + q) * kLd + bl] = (uint16_t)pk[q];
-    __syncthreads();
-    // thread (column il, 8-sample chunk): 16 bytes of the transposed copy
-    const int il = t >> 3, bc = t & 7;
-    const int col = blockIdx.x * 64 + il;
-    const int b0 = blockIdx.y * 64 + bc * 8;
-    if (col < din && b0 < B) {
-        uint16_t* dst = dprevT + (int64_t)w * sP + (int64_t)col * B + b0;
-        const uint16_t* src = tile + il * kLd + bc * 8;
-        if (b0 + 8 <= B && (B & 7) == 0) {
-            *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(src);
-        } else {
-            for (int q = 0; q < 8 && b0 + q < B; ++q) dst[q] = src[q];
         }
     }
 }
@@ -969,36 +590,17 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* losses,
         const uint16_t* Hin = (k == 1) ? X0 : sc16 + p.h[k - 1];
         const int64_t sHin = (k == 1) ? sX0 : sW16;
         const float* bias = x + woff[k] + (int64_t)dout * din;
-        bool done = false;
+        GemmArgs a{};
+        a.A = Hin; a.sA = sHin; a.lda = din;
+        a.B = xb + woff[k]; a.sB = ld; a.ldb = din;
+        a.M = B; a.N = dout; a.K = din;
+        a.bias = bias; a.sBias = ld;
         if (k < L) {
-            GemmArgs a{};
-            a.A = Hin; a.sA = sHin; a.lda = din;
-            a.B = xb + woff[k]; a.sB = ld; a.ldb = din;
-            a.M = B; a.N = dout; a.K = din;
-            a.bias = bias; a.sBias = ld;
             a.out = sc16 + p.h[k]; a.sOut = sW16; a.ldout = dout;
-            done = try_mfma<false, EPI_FWD>(a, W, s);
-        }
-        auto a16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
-        const bool vec8 = din % 8 == 0 && ld % 8 == 0 && woff[k] % 8 == 0 && a16(xb) && a16(Hin) && sHin % 8 == 0;
-        if (!done && vec8 && dout <= 64) {
-            dim3 grid((unsigned)(((int64_t)B * dout + 3) / 4), (unsigned)W);
-            if (k < L)
-                hipLaunchKernelGGL(fwd_narrow_kernel<true>, grid, dim3(256), 0, s, Hin, sHin, (int64_t)din, xb + woff[k], ld, bias, ld,
-                                   B, din, dout, sc16 + p.h[k], (float*)nullptr, sW16, (int64_t)dout);
-            else
-                hipLaunchKernelGGL(fwd_narrow_kernel<false>, grid, dim3(256), 0, s, Hin, sHin, (int64_t)din, xb + woff[k], ld, bias, ld,
-                                   B, din, dout, (uint16_t*)nullptr, logits, sW32, (int64_t)dout);
-            done = true;
-        }
-        if (!done) {
-            dim3 grid((unsigned)((B + 3) / 4), (unsigned)W);
-            if (k < L)
-                hipLaunchKernelGGL(fwd_valu_kernel<true>, grid, dim3(256), 0, s, Hin, sHin, (int64_t)din, xb + woff[k], ld, bias, ld,
-                                   B, din, dout, sc16 + p.h[k], (float*)nullptr, sW16, (int64_t)dout);
-            else
-                hipLaunchKernelGGL(fwd_valu_kernel<false>, grid, dim3(256), 0, s, Hin, sHin, (int64_t)din, xb + woff[k], ld, bias, ld,
-                                   B, din, dout, (uint16_t*)nullptr, logits, sW32, (int64_t)dout);
+            if (!try_mfma<false, EPI_FWD>(a, W, s)) launch_gemm_ragged(a, W, EPI_FWD, s);
+        } else {
+            a.C = logits; a.sC = sW32; a.ldc = dout;
+            launch_gemm_ragged(a, W, EPI_LOGITS, s);
         }
     }
     // ---- loss and output delta ----
@@ -1039,18 +641,7 @@ hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int
             a.mask = Hin; a.sMask = sHin; a.ldmask = din;
             a.out = sc16 + p.d[k - 1]; a.sOut = sW16; a.ldout = din;
             a.outT = sc16 + p.dT[k - 1]; a.sOutT = sW16; a.ldoutT = B;
-            auto a16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
-            const bool vec8 = din % 8 == 0 && ld % 8 == 0 && woff[k] % 8 == 0 && a16(xb) && a16(Hin) && sHin % 8 == 0;
-            if (try_mfma<true, EPI_DX>(a, W, s)) {
-            } else if (vec8 && dout <= 64) {
-                dim3 grid((unsigned)((din / 8 + 7) / 8), (unsigned)((B + 63) / 64), (unsigned)W);
-                hipLaunchKernelGGL(dx_narrow_kernel, grid, dim3(512), 0, s, sc16 + p.d[k], sW16, xb + woff[k], ld, Hin, sHin,
-                                   (int64_t)din, B, din, dout, sc16 + p.d[k - 1], sc16 + p.dT[k - 1], sW16);
-            } else {
-                dim3 grid((unsigned)((din + 255) / 256), (unsigned)B, (unsigned)W);
-                hipLaunchKernelGGL(dx_valu_kernel, grid, dim3(256), 0, s, sc16 + p.d[k], sW16, xb + woff[k], ld, Hin, sHin,
-                                   (int64_t)din, B, din, dout, sc16 + p.d[k - 1], sc16 + p.dT[k - 1], sW16);
-            }
+            if (!try_mfma<true, EPI_DX>(a, W, s)) launch_gemm_ragged(a, W, EPI_DX, s);
         }
         // dW_k
         {
@@ -1060,42 +651,24 @@ hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int
             a.M = dout; a.N = din; a.K = B;
             a.C = g + woff[k]; a.sC = ld; a.ldc = din;
             a.fu = fu; a.colC = woff[k];
-            auto a16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
-            const bool vec8 = din % 8 == 0 && a16(Hin) && sHin % 8 == 0;
-            if (fused ? try_mfma<true, EPI_DWU>(a, W, s) : try_mfma<true, EPI_DW>(a, W, s)) {
-            } else if (vec8 && dout <= 64) {
-                dim3 grid((unsigned)((din / 8 + 63) / 64), (unsigned)dout, (unsigned)W);
-                hipLaunchKernelGGL(dw_narrow_kernel, grid, dim3(256), 0, s, sc16 + p.dT[k], sW16, Hin, sHin, (int64_t)din, B, din,
-                                   dout, g + woff[k], ld, fu, woff[k]);
-            } else {
-                dim3 grid((unsigned)((din + 255) / 256), (unsigned)dout, (unsigned)W);
-                hipLaunchKernelGGL(dw_valu_kernel, grid, dim3(256), 0, s, sc16 + p.dT[k], sW16, Hin, sHin, (int64_t)din, B, din,
-                                   dout, g + woff[k], ld, fu, woff[k]);
-            }
+            if (!(fused ? try_mfma<true, EPI_DWU>(a, W, s) : try_mfma<true, EPI_DW>(a, W, s)))
+                launch_gemm_ragged(a, W, fused ? EPI_DWU : EPI_DW, s);
         }
     }
     // db_k of every layer (delta^T_k is complete once layer k+1 has been processed; the biases' columns
-    // are nobody else's): one launch when the rows allow 16-byte loads, else one per layer
-    if (B % 8 == 0 && sW16 % 8 == 0 && (reinterpret_cast<uintptr_t>(sc16) & 15u) == 0) {
-        BiasLayers t{};
-        t.n = L;
-        int blocks = 0;
-        for (int k = 1; k <= L; ++k) {
-            t.first_block[k - 1] = blocks;
-            t.dout[k - 1] = b.dims[k];
-            t.dT[k - 1] = p.dT[k];
-            t.col[k - 1] = woff[k] + (int64_t)b.dims[k] * b.dims[k - 1];
-            blocks += (b.dims[k] + 7) / 8;
-        }
-        t.first_block[L] = blocks;
-        hipLaunchKernelGGL(db_all_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, sc16, sW16, B, t, g, ld, fu);
-    } else {
-        for (int k = L; k >= 1; --k) {
-            const int din = b.dims[k - 1], dout = b.dims[k];
-            hipLaunchKernelGGL(db_kernel, dim3((unsigned)((dout + 3) / 4), (unsigned)W), dim3(256), 0, s, sc16 + p.dT[k], sW16, B, dout,
-                               g + woff[k] + (int64_t)dout * din, ld, fu, woff[k] + (int64_t)dout * din);
-        }
+    // are nobody else's) in one launch
+    BiasLayers t{};
+    t.n = L;
+    int blocks = 0;
+    for (int k = 1; k <= L; ++k) {
+        t.first_block[k - 1] = blocks;
+        t.dout[k - 1] = b.dims[k];
+        t.dT[k - 1] = p.dT[k];
+        t.col[k - 1] = woff[k] + (int64_t)b.dims[k] * b.dims[k - 1];
+        blocks += (b.dims[k] + 7) / 8;
     }
+    t.first_block[L] = blocks;
+    hipLaunchKernelGGL(db_all_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, sc16, sW16, B, t, g, ld, fu);
     if (fused) return hipGetLastError();          // g is not written, so there is no padding to clear
     if (ld > P)
         hipLaunchKernelGGL(zero_pad_kernel, dim3((unsigned)((ld - P + 255) / 256), (unsigned)W), dim3(256), 0, s, g, P, ld);

@@ -1,0 +1,57 @@
+"""GPU parity of the any-shape matrix products behind the MLP path: sizes on both sides of every tile edge, rows on odd
+2-byte boundaries, contractions shorter than one 16-byte piece, each row-tile height, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1905_10395_amd as L
+from test_gpu_mlp import check_grads, make
+
+pytestmark = pytest.mark.gpu
+
+# one hidden layer, so that the tight gradient bar (1e-4 median, 2e-3 per worker and block) applies
+SHAPES = [
+    ([7, 5, 3], 2, 1),            # every contraction shorter than 8, one sample
+    ([8, 64, 8], 3, 32),          # exactly one tile and one 16-byte piece
+    ([9, 65, 2], 3, 33),          # one past the tile in every direction, two classes
+    ([63, 130, 7], 2, 31),        # odd rows: every row of W starts on another 2-byte boundary
+    ([136, 128, 16], 2, 64),      # multiples of 8 that are no multiples of a K step
+    ([257, 191, 10], 12, 65),     # 64-row tile, remainders in m, n and k
+    ([129, 1100, 65], 16, 127),   # 128-row tile, classes past one column tile
+    ([640, 2050, 10], 9, 130),    # five K steps, two row tiles
+    ([383, 515, 100], 5, 300),
+]
+
+
+@pytest.mark.parametrize("dims,W,B", SHAPES)
+def test_ragged_grad_loss_matches_oracle(dims, W, B):
+    pr, batch, Xb, y, P, _ = make(dims, W, B, seed=sum(dims) + B)
+    pr.g.fill_(float("nan"))
+    pr.ora.grad_loss_mlp(dims, Xb, y)
+    pr.pop.grad_loss(batch)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(pr.pop.get_losses(), pr.ora.losses, rtol=1e-5)
+    g = pr.g.cpu().numpy()
+    check_grads(g[:, :P], pr.ora.g[:, :P], dims)
+    assert np.all(g[:, P:] == 0)
+
+
+@pytest.mark.parametrize("dims,W,B", [SHAPES[0], SHAPES[2], SHAPES[3], SHAPES[5], SHAPES[7]])
+def test_ragged_fused_update_equals_the_three_call_step(dims, W, B):
+    """The update inside the d-weight kernels against gradient + update: the same expression up to the rounding of
+    its fused multiply-adds, element by element; nothing outside the parameters is written."""
+    res = []
+    for flags in (L.WRITE_BF16_SHADOW, L.WRITE_BF16_SHADOW | L.FUSED_MLP_UPDATE):
+        pr, batch, _, _, P, _ = make(dims, W, B, seed=5, momentum=0.9, flags=flags)
+        pr.x[:, P:] = 3.0
+        pr.m[:, P:] = 4.0
+        pr.pop.step(batch, 0.01, 0.1, 0.05)
+        torch.cuda.synchronize()
+        assert torch.all(pr.x[:, P:] == 3.0) and torch.all(pr.m[:, P:] == 4.0)
+        assert torch.equal(pr.xb[:, :P], pr.x[:, :P].to(torch.bfloat16))
+        res.append((pr.x[:, :P].clone(), pr.m[:, :P].clone(), pr.Z[:, :P].clone()))
+    (x0, m0, z0), (x1, m1, z1) = res
+    assert torch.equal(z0, z1)
+    # m = g + pulls: a few roundings of terms no larger than max|m|; x moves by eta m
+    assert (m1 - m0).abs().max() <= 8 * 2.0 ** -23 * m0.abs().max()
+    assert (x1 - x0).abs().max() <= 2.0 ** -23 * x0.abs().max() + 0.01 * 8 * 2.0 ** -23 * m0.abs().max()
