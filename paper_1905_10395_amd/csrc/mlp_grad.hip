@@ -183,18 +183,35 @@ __global__ __launch_bounds__(64 * WVM * WVN, (WVM * WVN > 4) ? 1 : 2) void gemm_
         if (nk > 2) load_global(2, ra0, rb0);
         __syncthreads();
         int kt = 0;
-        for (; kt + 1 < nk; kt += 2) {                    // both halves always run: no exit in the middle of the body
+        // No load in here is conditional: behind a branch that may or may not have issued loads, the compiler has to
+        // wait for every load in flight, and the second register stage would be worth nothing.
+        for (; kt + 4 < nk; kt += 2) {
             store_lds(1, ra1, rb1);
-            if (kt + 3 < nk) load_global(kt + 3, ra1, rb1);
+            load_global(kt + 3, ra1, rb1);
             compute(0);
             __syncthreads();
-            if (kt + 2 < nk) store_lds(0, ra0, rb0);
-            if (kt + 4 < nk) load_global(kt + 4, ra0, rb0);
+            store_lds(0, ra0, rb0);
+            load_global(kt + 4, ra0, rb0);
             compute(1);
             __syncthreads();
         }
-        if (kt < nk) {                                    // odd number of k-steps: the last one sits in buffer 0
+        const int left = nk - kt;                         // 1 .. 4 k-steps, the first already in buffer 0
+        if (left > 1) store_lds(1, ra1, rb1);
+        if (left > 3) load_global(kt + 3, ra1, rb1);
+        compute(0);
+        __syncthreads();
+        if (left > 1) {
+            if (left > 2) store_lds(0, ra0, rb0);
+            compute(1);
+            __syncthreads();
+        }
+        if (left > 2) {
+            if (left > 3) store_lds(1, ra1, rb1);
             compute(0);
+            __syncthreads();
+        }
+        if (left > 3) {
+            compute(1);
             __syncthreads();
         }
     } else {
