@@ -33,8 +33,6 @@ namespace lsgd {
 
 namespace {
 
-constexpr int kRaggedThreads = 256;
-constexpr int kRaggedBN = 64;
 constexpr int kXcds = 8;
 
 
@@ -100,13 +98,13 @@ __device__ __forceinline__ void ragged_update(const FusedRow& r, const int64_t (
     }
 }
 
-template <int BM, int WVM, int WVN, int WVK, int BK, int EPI>
+template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
 struct RaggedShape {
+    static constexpr int THREADS = 64 * WVM * WVN * WVK;
     static constexpr bool FORWARD = EPI == EPI_FWD || EPI == EPI_LOGITS;
     static constexpr bool TRANS_B = !FORWARD;                           // B given as [k][n]
     using Sum = typename std::conditional<FORWARD, double, float>::type;
     static constexpr int PROMOTE = BM > 64 ? 2 : 1;                     // K steps between promotions to the double sum
-    static constexpr int BN = kRaggedBN;
     static constexpr int LDA = BK + 8;                                  // padded LDS row of a [.][k] operand
     static constexpr int LDN = BN + kPadN;                              // of a [k][n] operand
     static constexpr int A_TILE = BM * LDA;
@@ -117,19 +115,19 @@ struct RaggedShape {
     static constexpr size_t lds = operand_bytes > result_bytes ? operand_bytes : result_bytes;
 };
 
-template <int BM, int WVM, int WVN, int WVK, int BK, int EPI>
-__global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs g, int tiles_m, int tiles_n, int W, int64_t per_xcd)
+template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
+__global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1) void gemm_ragged_kernel(GemmArgs g, int tiles_m, int tiles_n, int W, int64_t per_xcd)
 {
-    using S = RaggedShape<BM, WVM, WVN, WVK, BK, EPI>;
+    using S = RaggedShape<BM, BN, WVM, WVN, WVK, BK, EPI>;
     using Sum = typename S::Sum;
     constexpr bool TRANS_B = S::TRANS_B;
-    static_assert(WVM * WVN * WVK == 4, "four wavefronts");
-    constexpr int BN = S::BN, LDA = S::LDA, LDN = S::LDN, LDC = S::LDC;
+    constexpr int THREADS = S::THREADS, LDA = S::LDA, LDN = S::LDN, LDC = S::LDC;
     constexpr int TM = BM / WVM / 32, TN = BN / WVN / 32;               // 32x32 MFMA tiles per wavefront
     constexpr int KCH = BK / 8;                                         // 16-byte pieces of a [.][k] row
-    constexpr int A_CHUNKS = BM * KCH / kRaggedThreads, B_CHUNKS = BN * BK / 8 / kRaggedThreads;
-    constexpr int A_STEP = kRaggedThreads / KCH;                        // rows between a thread's pieces
+    constexpr int A_CHUNKS = BM * KCH / THREADS, B_CHUNKS = BN * BK / 8 / THREADS;
+    constexpr int A_STEP = THREADS / KCH;                               // rows between a thread's pieces
     constexpr int KK = BK / 16 / WVK;                                   // MFMA steps of a wavefront per K step
+    constexpr int NCH = BN / 8, B_STEP = THREADS / NCH;                 // [k][n]: pieces per row, rows between a thread's pieces
 
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     uint16_t* As = smem;                                                // [2][BM][LDA]
@@ -184,9 +182,9 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
                 for (int v = 0; v < 16; ++v) { sum[i][j][v] += (Sum)acc[i][j][v]; acc[i][j][v] = 0.f; }
     };
 
-    // this thread's pieces: column piece kc of rows ra0 + c * A_STEP (a [k][n] operand: piece nc of rows kr0 + 32 c)
+    // this thread's pieces: column piece kc of rows ra0 + c * A_STEP (a [k][n] operand: piece nc of rows kr0 + c * B_STEP)
     const int kc = (tid % KCH) * 8, ra0 = tid / KCH;
-    const int nc = (tid & 7) * 8, kr0 = tid >> 3;
+    const int nc = (tid % NCH) * 8, kr0 = tid / NCH;
     const uint16_t* arow[A_CHUNKS];
     const uint16_t* brow[B_CHUNKS];
 #pragma unroll
@@ -227,7 +225,7 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
         if (TRANS_B) {
 #pragma unroll
             for (int c = 0; c < B_CHUNKS; ++c) {
-                const int kr = kt * BK + kr0 + c * 32;
+                const int kr = kt * BK + kr0 + c * B_STEP;
                 const uint16_t* p = B + (int64_t)(kr < K ? kr : K - 1) * g.ldb;
                 if (short_n) rb[c] = load_short(p + bcol, N - bcol < 0 ? 0 : N - bcol);
                 else rb[c] = load16(p + bcol_in);
@@ -251,7 +249,7 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
         if (TRANS_B && (tail || (edge_n && !short_n))) {
 #pragma unroll
             for (int c = 0; c < B_CHUNKS; ++c) {
-                const int s = (kt * BK + kr0 + c * 32 < K) ? (short_n ? 0 : bshift) : 8;
+                const int s = (kt * BK + kr0 + c * B_STEP < K) ? (short_n ? 0 : bshift) : 8;
                 rb[c] = shift_in(rb[c], s);
             }
         }
@@ -259,7 +257,7 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
         for (int c = 0; c < A_CHUNKS; ++c) *reinterpret_cast<u32x4*>(as + (ra0 + c * A_STEP) * LDA + kc) = ra[c];
         if (TRANS_B) {
 #pragma unroll
-            for (int c = 0; c < B_CHUNKS; ++c) *reinterpret_cast<u32x4*>(bs + (kr0 + c * 32) * LDN + nc) = rb[c];
+            for (int c = 0; c < B_CHUNKS; ++c) *reinterpret_cast<u32x4*>(bs + (kr0 + c * B_STEP) * LDN + nc) = rb[c];
         } else {
 #pragma unroll
             for (int c = 0; c < B_CHUNKS; ++c) *reinterpret_cast<u32x4*>(bs + (ra0 + c * A_STEP) * LDA + kc) = rb[c];
@@ -360,14 +358,16 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
                 T[(wk * BM + r) * LDC + (wn * TN + j) * 32 + (lane & 31)] = S::FORWARD ? sum[S::FORWARD ? i : 0][S::FORWARD ? j : 0][v] : (Sum)acc[i][j][v];
             }
     __syncthreads();
-    constexpr int PASSES = BM / 16;                                     // 16 threads per row
-    const int c4 = (tid & 15) * 4, r0 = tid >> 4, n = n0 + c4;
+    constexpr int RPP = THREADS / (BN / 4) < BM ? THREADS / (BN / 4) : BM;   // rows per pass
+    constexpr int PASSES = BM / RPP;
+    if (THREADS / (BN / 4) > BM && tid >= BM * (BN / 4)) return;         // more threads than the tile has groups of four
+    const int c4 = (tid % (BN / 4)) * 4, r0 = tid / (BN / 4), n = n0 + c4;
     const int nv = N - n < 4 ? N - n : 4;                               // columns of this thread (may be <= 0)
     typedef Sum sum4 __attribute__((ext_vector_type(4)));
     auto value = [&](int p) {
-        sum4 v = *reinterpret_cast<const sum4*>(T + (r0 + 16 * p) * LDC + c4);
+        sum4 v = *reinterpret_cast<const sum4*>(T + (r0 + RPP * p) * LDC + c4);
 #pragma unroll
-        for (int q = 1; q < WVK; ++q) v += *reinterpret_cast<const sum4*>(T + (q * BM + r0 + 16 * p) * LDC + c4);
+        for (int q = 1; q < WVK; ++q) v += *reinterpret_cast<const sum4*>(T + (q * BM + r0 + RPP * p) * LDC + c4);
         return v;
     };
     if constexpr (S::FORWARD) {
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
             if (e < nv) b[e] = g.bias[(int64_t)w * g.sBias + n + e];
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
-            const int m = m0 + r0 + 16 * p;
+            const int m = m0 + r0 + RPP * p;
             if (m >= M || nv <= 0) continue;
             const sum4 zs = value(p) + b;
             const f32x4 z = {(float)zs.x, (float)zs.y, (float)zs.z, (float)zs.w};
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
     } else if constexpr (EPI == EPI_DX) {
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
-            const int m = m0 + r0 + 16 * p;
+            const int m = m0 + r0 + RPP * p;
             f32x4 v = value(p);
             if (m < M && nv > 0) {
                 const uint16_t* mk = g.mask + (int64_t)w * g.sMask + (int64_t)m * g.ldmask + n;
@@ -416,11 +416,11 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
                 if (nv == 4) *reinterpret_cast<u32x2_any*>(dst) = o;
                 else store_some(dst, o, nv);
             }
-            *reinterpret_cast<f32x4*>(T + (r0 + 16 * p) * LDC + c4) = v;   // this thread's own elements of copy 0
+            *reinterpret_cast<f32x4*>(T + (r0 + RPP * p) * LDC + c4) = v;   // this thread's own elements of copy 0
         }
         __syncthreads();
         // the transposed copy: four samples of one column per thread
-        constexpr int MQ = BM / 4, CPP = kRaggedThreads / MQ;            // threads per column, columns per pass
+        constexpr int MQ = BM / 4, CPP = THREADS / MQ;            // threads per column, columns per pass
         const int mq = (tid % MQ) * 4, mm = m0 + mq;
         const int mv = M - mm < 4 ? M - mm : 4;
 #pragma unroll
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
         float* C = g.C + (int64_t)w * g.sC;
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
-            const int m = m0 + r0 + 16 * p;
+            const int m = m0 + r0 + RPP * p;
             if (m >= M || nv <= 0) continue;
             const f32x4 v = value(p);
             float* dst = C + (int64_t)m * g.ldc + n;
@@ -459,7 +459,7 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
         bool on[R];
 #pragma unroll
         for (int q = 0; q < R; ++q) {
-            const int m = m0 + r0 + 16 * (p0 + q);
+            const int m = m0 + r0 + RPP * (p0 + q);
             gv[q] = value(p0 + q);
             off[q] = g.colC + (int64_t)m * g.ldc + n;
             on[q] = m < M && nv == 4;
@@ -477,44 +477,53 @@ __global__ __launch_bounds__(kRaggedThreads, 2) void gemm_ragged_kernel(GemmArgs
     }
 }
 
-template <int BM, int WVM, int WVN, int WVK, int BK, int EPI>
+template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
 void launch_tile(const GemmArgs& g, int W, hipStream_t s)
 {
-    using S = RaggedShape<BM, WVM, WVN, WVK, BK, EPI>;
-    auto kernel = gemm_ragged_kernel<BM, WVM, WVN, WVK, BK, EPI>;
+    using S = RaggedShape<BM, BN, WVM, WVN, WVK, BK, EPI>;
+    auto kernel = gemm_ragged_kernel<BM, BN, WVM, WVN, WVK, BK, EPI>;
+    static_assert(S::FORWARD || S::THREADS / (BN / 4) <= BM, "the other epilogues use every thread");
     if (S::lds > 64 * 1024) {
         static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::lds);
         (void)once;
     }
-    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + kRaggedBN - 1) / kRaggedBN;
+    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     const int64_t per_xcd = ((int64_t)tiles_m * tiles_n * W + kXcds - 1) / kXcds;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(per_xcd * kXcds)), dim3(kRaggedThreads), S::lds, s, g, tiles_m, tiles_n, W, per_xcd);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(per_xcd * kXcds)), dim3(S::THREADS), S::lds, s, g, tiles_m, tiles_n, W, per_xcd);
 }
 
 // Row tile: a batch of up to 32 / 64 fits one tile; larger ones take 128 rows, unless that leaves compute units
-// without a workgroup.
+// without a workgroup.  When there are few tiles and a long contraction (the classifier layer, a narrow first
+// layer), sixteen wavefronts split the contraction of a 32 x 32 tile, 64 KB of operands per K step: logits of
+// 4096 -> 10, 8 workers, batch 256 25 -> 17 us, of 1024 -> 10, 16 workers, batch 128 11 -> 8 us.
 template <int EPI>
 void launch_epi(const GemmArgs& g, int W, hipStream_t s)
 {
-    const int64_t cols = (int64_t)((g.N + kRaggedBN - 1) / kRaggedBN) * W;
+    const int64_t cols = (int64_t)((g.N + 63) / 64) * W;
     const bool fill64 = cols * ((g.M + 63) / 64) >= 256, fill128 = cols * ((g.M + 127) / 128) >= 256;
     if constexpr (EPI == EPI_DW || EPI == EPI_DWU) {
-        if (g.M > 64 && fill128) launch_tile<128, 2, 2, 1, 64, EPI>(g, W, s);
-        else if (g.M > 32) launch_tile<64, 2, 2, 1, 64, EPI>(g, W, s);
-        else launch_tile<32, 1, 2, 2, 64, EPI>(g, W, s);
+        if (g.M > 64 && fill128) launch_tile<128, 64, 2, 2, 1, 64, EPI>(g, W, s);
+        else if (g.M > 32) launch_tile<64, 64, 2, 2, 1, 64, EPI>(g, W, s);
+        else launch_tile<32, 64, 1, 2, 2, 64, EPI>(g, W, s);
     } else {
         // one K step (the classifier layer's d-input): a stream of results, many small workgroups
         if constexpr (EPI == EPI_DX) {
             if (g.K <= 64) {
-                if (g.M > 32) launch_tile<64, 2, 2, 1, 64, EPI>(g, W, s);
-                else launch_tile<32, 1, 2, 2, 64, EPI>(g, W, s);
+                if (g.M > 32) launch_tile<64, 64, 2, 2, 1, 64, EPI>(g, W, s);
+                else launch_tile<32, 64, 1, 2, 2, 64, EPI>(g, W, s);
                 return;
             }
         }
-        if (g.M > 64 && fill128) launch_tile<128, 2, 2, 1, 64, EPI>(g, W, s);
-        else if (g.M > 32 && fill64) launch_tile<64, 1, 2, 2, 128, EPI>(g, W, s);
-        else launch_tile<32, 1, 1, 4, 128, EPI>(g, W, s);
+        if constexpr (EPI == EPI_FWD || EPI == EPI_LOGITS) {
+            if (g.K >= 1024 && cols * ((g.M + 31) / 32) <= 128) {
+                launch_tile<32, 32, 1, 1, 16, 512, EPI>(g, W, s);
+                return;
+            }
+        }
+        if (g.M > 64 && fill128) launch_tile<128, 64, 2, 2, 1, 64, EPI>(g, W, s);
+        else if (g.M > 32 && fill64) launch_tile<64, 64, 1, 2, 2, 128, EPI>(g, W, s);
+        else launch_tile<32, 64, 1, 1, 4, 128, EPI>(g, W, s);
     }
 }
 
