@@ -371,23 +371,29 @@ lsgd_status check_pull_state(const lsgd_population* p, float eta, float lamL, fl
     return LSGD_OK;
 }
 
-lsgd_status do_select(lsgd_population* p, const float* losses, const uint8_t* refresh_local, int refresh_global)
+// Bookkeeping of a selection: which groups are re-selected (sel) and which count as re-selected since the last
+// update afterwards (cap).
+void note_selection(lsgd_population* p, const uint8_t* refresh_local, int refresh_global, RefreshBits* sel, RefreshBits* cap)
 {
-    const int G = p->cfg.n_groups;
-    RefreshBits sel, cap;
-    std::memset(&sel, 0, sizeof(sel));
-    std::memset(&cap, 0, sizeof(cap));
-    for (int j = 0; j < G; ++j) {
+    std::memset(sel, 0, sizeof(*sel));
+    std::memset(cap, 0, sizeof(*cap));
+    for (int j = 0; j < p->cfg.n_groups; ++j) {
         const bool r = !refresh_local || refresh_local[j];
         if (r) {
-            sel.w[j >> 6] |= 1ull << (j & 63);
+            sel->w[j >> 6] |= 1ull << (j & 63);
             p->pending_local[(size_t)j] = 1;
             p->local_selected[(size_t)j] = 1;
         }
-        if (p->pending_local[(size_t)j]) cap.w[j >> 6] |= 1ull << (j & 63);
+        if (p->pending_local[(size_t)j]) cap->w[j >> 6] |= 1ull << (j & 63);
     }
     if (refresh_global) { p->pending_global = true; p->global_selected = true; }
-    hipError_t e = launch_select_leaders(losses ? losses : p->st.losses, p->cfg.W, G, p->st, sel, cap,
+}
+
+lsgd_status do_select(lsgd_population* p, const float* losses, const uint8_t* refresh_local, int refresh_global)
+{
+    RefreshBits sel, cap;
+    note_selection(p, refresh_local, refresh_global, &sel, &cap);
+    hipError_t e = launch_select_leaders(losses ? losses : p->st.losses, p->cfg.W, p->cfg.n_groups, p->st, sel, cap,
                                          refresh_global != 0, p->pending_global, p->stream);
     if (e != hipSuccess) return fail(LSGD_ERR_HIP, "select_leaders: %s", hipGetErrorString(e));
     return LSGD_OK;
@@ -400,15 +406,26 @@ bool any_pending(const lsgd_population* p)
     return any;
 }
 
+// Whether the one-launch update by column owners is the faster one.  Up to about 300 MB read and written per update
+// the launches it saves weigh more than what workgroups that hop between rows lose against row streams (us, row
+// streams / column owners: 96 MB 31 / 22, 240 MB 62 / 44, 400 MB 82 / 81 to 86, 800 MB 148 / 160); a thread walks the
+// rows one after the other, so many rows with few columns are the other end (32 workers x 10 000: 16 / 11).
+// Elastic averaging reads every row twice there and has one launch less to save: 16 x 600 000 44 / 41,
+// 32 x 10 000 11.6 / 13, 16 x 1 250 000 85 / 87.
+bool column_step(const lsgd_population* p, bool easgd = false)
+{
+    const double bytes = (p->cfg.momentum != 0.0f ? 20.0 : 12.0) * (double)p->cfg.W * (double)p->cfg.P;
+    return easgd ? p->cfg.W <= 16 && bytes <= 200e6 : p->cfg.W <= 32 && bytes <= 300e6;
+}
+
 // comm: Algorithm 1's communication pull (lamL, lamG are its lambdas; eta unused).
 // unscaled: the pulls of a gradient step are not multiplied by eta.
-lsgd_status do_pull(lsgd_population* p, float eta, float lamL, float lamG, bool unscaled, bool comm)
+PullParams pull_params(const lsgd_population* p, float eta, float lamL, float lamG, bool unscaled, bool comm)
 {
-    const int G = p->cfg.n_groups;
     PullParams q;
     q.x = p->x; q.g = p->g; q.m = p->m; q.Z = p->Z;
     q.xb = (p->cfg.flags & LSGD_WRITE_BF16_SHADOW) ? p->xb : nullptr;
-    q.P = p->cfg.P; q.ld = p->cfg.ld; q.W = p->cfg.W; q.G = G;
+    q.P = p->cfg.P; q.ld = p->cfg.ld; q.W = p->cfg.W; q.G = p->cfg.n_groups;
     q.eta = eta; q.mu = p->cfg.momentum; q.wd = p->cfg.weight_decay;
     q.lamL = lamL; q.lamG = lamG;
     if (unscaled && !comm) {
@@ -420,12 +437,16 @@ lsgd_status do_pull(lsgd_population* p, float eta, float lamL, float lamG, bool 
     q.clear_refreshed = 0;
     q.group_size = p->group_size;
     q.comm_pull = comm ? 1 : 0;
-    hipError_t e = launch_pull_update(q, p->st, p->stream);
-    if (e != hipSuccess) return fail(LSGD_ERR_HIP, "%s: %s", comm ? "leader_pull" : "pull_update", hipGetErrorString(e));
-    // a refreshed leader whose term was active has now been captured (and kept, if Z exists);
-    // the communication pull captures every refreshed leader
-    // (a re-selected leader whose coefficient was exactly 0 was not captured: its kept copy, if any, still
-    // belongs to the previous leader, so it stops being valid until the next selection)
+    return q;
+}
+
+// Bookkeeping of an update: a refreshed leader whose term was active has now been captured (and kept, if Z exists);
+// the communication pull captures every refreshed leader
+// (a re-selected leader whose coefficient was exactly 0 was not captured: its kept copy, if any, still
+// belongs to the previous leader, so it stops being valid until the next selection)
+void note_pull(lsgd_population* p, float lamL, float lamG, bool comm)
+{
+    const int G = p->cfg.n_groups;
     for (int j = 0; j < G; ++j) {
         if (p->pending_local[(size_t)j]) p->z_valid[(size_t)j] = (comm || lamL != 0.0f) && p->Z != nullptr;
         p->pending_local[(size_t)j] = 0;
@@ -433,12 +454,42 @@ lsgd_status do_pull(lsgd_population* p, float eta, float lamL, float lamG, bool 
     if (p->pending_global) p->z_valid[(size_t)G] = (comm || lamG != 0.0f) && p->Z != nullptr;
     p->pending_global = false;
     if (!(p->cfg.flags & LSGD_WRITE_BF16_SHADOW)) p->shadow_valid = false;
+}
+
+lsgd_status do_pull(lsgd_population* p, float eta, float lamL, float lamG, bool unscaled, bool comm)
+{
+    const PullParams q = pull_params(p, eta, lamL, lamG, unscaled, comm);
+    hipError_t e;
+    if (column_step(p)) {
+        ColumnStep c{};
+        c.pull = q;
+        c.update = !comm; c.comm = comm; c.commL = lamL; c.commG = lamG;
+        e = launch_column_step(c, p->st, p->stream);
+    } else {
+        e = launch_pull_update(q, p->st, p->stream);
+    }
+    if (e != hipSuccess) return fail(LSGD_ERR_HIP, "%s: %s", comm ? "leader_pull" : "pull_update", hipGetErrorString(e));
+    note_pull(p, lamL, lamG, comm);
     return LSGD_OK;
 }
 
 lsgd_status do_pull(lsgd_population* p, float eta, float lamL, float lamG)
 {
     return do_pull(p, eta, lamL, lamG, (p->cfg.flags & LSGD_PULL_UNSCALED_BY_ETA) != 0, false);
+}
+
+// Losses of a step that goes through the one-launch update: an external batch's stay where they are (the update
+// kernel copies them to the population's buffer on the way), other batches leave theirs in that buffer.
+lsgd_status column_losses(lsgd_population* p, const lsgd_batch* batch, ColumnStep* c)
+{
+    if (batch->kind == LSGD_BATCH_EXTERNAL) {
+        c->losses = static_cast<const lsgd_external_batch*>(batch->desc)->losses;
+        c->losses_out = c->losses != p->st.losses ? p->st.losses : nullptr;
+        p->losses_valid = true;
+        return LSGD_OK;
+    }
+    c->losses = p->st.losses;
+    return do_grad_loss(p, batch, nullptr);
 }
 
 // forward + losses -> leaders -> kept copies brought up to date -> backward pass that applies the update
@@ -456,8 +507,25 @@ lsgd_status do_fused_mlp_step(lsgd_population* p, const lsgd_batch* batch, float
     e = launch_mlp_forward(p->xb, p->x, p->st.losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, p->stream);
     if (e != hipSuccess) return fail(LSGD_ERR_HIP, "mlp forward: %s", hipGetErrorString(e));
     p->losses_valid = true;
-    lsgd_status st = do_select(p, nullptr, refresh_local, refresh_global);
-    if (st != LSGD_OK) return st;
+    lsgd_status st = LSGD_OK;
+    if (p->cfg.W <= kColumnMaxWorkers && (lamL != 0.0f || lamG != 0.0f)) {
+        // selection and capture (nobody moves) in one launch
+        RefreshBits sel, cap;
+        note_selection(p, refresh_local, refresh_global, &sel, &cap);
+        if (any_pending(p)) {
+            ColumnStep c{};
+            c.pull = pull_params(p, 0.0f, 0.0f, 0.0f, false, true);
+            c.comm = 1;
+            c.select = 1; c.sel = sel.w[0]; c.cap = cap.w[0]; c.selG = refresh_global != 0; c.capG = p->pending_global;
+            c.losses = p->st.losses;
+            e = launch_column_step(c, p->st, p->stream);
+            if (e != hipSuccess) return fail(LSGD_ERR_HIP, "capture: %s", hipGetErrorString(e));
+            note_pull(p, 0.0f, 0.0f, true);
+        }
+    } else {
+        st = do_select(p, nullptr, refresh_local, refresh_global);
+        if (st != LSGD_OK) return st;
+    }
     if (any_pending(p)) {
         if (lamL != 0.0f || lamG != 0.0f) {
             st = do_pull(p, 0.0f, 0.0f, 0.0f, false, true);            // capture only: nobody moves
@@ -535,6 +603,20 @@ lsgd_status lsgd_step(lsgd_population* pop, const lsgd_batch* batch, float eta, 
     if (st != LSGD_OK) return st;
     if ((pop->cfg.flags & LSGD_FUSED_MLP_UPDATE) && batch->kind == LSGD_BATCH_MLP)
         return do_fused_mlp_step(pop, batch, eta, lambda_L, lambda_G, refresh_local, refresh_global);
+    if (column_step(pop)) {
+        ColumnStep c{};
+        st = column_losses(pop, batch, &c);
+        if (st != LSGD_OK) return st;
+        RefreshBits sel, cap;
+        note_selection(pop, refresh_local, refresh_global, &sel, &cap);
+        c.pull = pull_params(pop, eta, lambda_L, lambda_G, (pop->cfg.flags & LSGD_PULL_UNSCALED_BY_ETA) != 0, false);
+        c.update = 1;
+        c.select = 1; c.sel = sel.w[0]; c.cap = cap.w[0]; c.selG = refresh_global != 0; c.capG = pop->pending_global;
+        hipError_t e = launch_column_step(c, pop->st, pop->stream);
+        if (e != hipSuccess) return fail(LSGD_ERR_HIP, "step: %s", hipGetErrorString(e));
+        note_pull(pop, lambda_L, lambda_G, false);
+        return LSGD_OK;
+    }
     st = do_grad_loss(pop, batch, nullptr);
     if (st != LSGD_OK) return st;
     st = do_select(pop, nullptr, refresh_local, refresh_global);
@@ -572,17 +654,36 @@ lsgd_status lsgd_step_alg1(lsgd_population* pop, const lsgd_batch* batch, float 
     if (comm & LSGD_COMM_LOCAL) {
         for (int j = 0; j < G; ++j) any_local = any_local || !comm_local_mask || comm_local_mask[j];
     }
-    st = do_grad_loss(pop, batch, nullptr);
-    if (st != LSGD_OK) return st;
-    st = do_pull(pop, eta, gamma_L, gamma_G, true, false);
-    if (st != LSGD_OK) return st;
-    if (!any_local && !(comm & LSGD_COMM_GLOBAL)) return LSGD_OK;
+    const bool communicate = any_local || (comm & LSGD_COMM_GLOBAL);
     std::vector<uint8_t> none;
     const uint8_t* mask = comm_local_mask;
     if (!(comm & LSGD_COMM_LOCAL)) {
         none.assign((size_t)G, 0);
         mask = none.data();
     }
+    // one launch for update, selection and communication pull; the workgroups then read only leaders that this call
+    // does not re-record, so not while a selection is pending or the recorded leaders are exempt
+    if (communicate && column_step(pop) && !any_pending(pop) && !(pop->cfg.flags & LSGD_LEADER_EXEMPT)) {
+        ColumnStep c{};
+        st = column_losses(pop, batch, &c);
+        if (st != LSGD_OK) return st;
+        c.pull = pull_params(pop, eta, gamma_L, gamma_G, true, false);
+        note_pull(pop, gamma_L, gamma_G, false);
+        RefreshBits sel, cap;
+        note_selection(pop, mask, (comm & LSGD_COMM_GLOBAL) != 0, &sel, &cap);
+        c.update = c.comm = 1; c.commL = lambda_L; c.commG = lambda_G;
+        c.select = 2; c.sel = sel.w[0]; c.cap = cap.w[0];
+        c.selG = c.capG = (comm & LSGD_COMM_GLOBAL) != 0;
+        hipError_t e = launch_column_step(c, pop->st, pop->stream);
+        if (e != hipSuccess) return fail(LSGD_ERR_HIP, "step_alg1: %s", hipGetErrorString(e));
+        note_pull(pop, lambda_L, lambda_G, true);
+        return LSGD_OK;
+    }
+    st = do_grad_loss(pop, batch, nullptr);
+    if (st != LSGD_OK) return st;
+    st = do_pull(pop, eta, gamma_L, gamma_G, true, false);
+    if (st != LSGD_OK) return st;
+    if (!communicate) return LSGD_OK;
     st = do_select(pop, nullptr, mask, (comm & LSGD_COMM_GLOBAL) != 0);
     if (st != LSGD_OK) return st;
     return do_pull(pop, 0.0f, lambda_L, lambda_G, false, true);
@@ -621,22 +722,22 @@ lsgd_status lsgd_easgd_update(lsgd_population* pop, float* center, float eta, fl
     if (!pop->Z) return fail(LSGD_ERR_STATE, "easgd_update keeps the pre-update center in z_snapshot, which is NULL");
     if (any_pending(pop)) return fail(LSGD_ERR_STATE, "easgd_update: a leader selection is pending; elastic averaging uses no leaders");
     const int G = pop->cfg.n_groups;
-    // center first (it reads the workers before they move); the old center lands in the global row of Z
     const double a = (double)pop->cfg.W * (double)eta * (double)lambda;
-    hipError_t e = launch_easgd_center(pop->x, pop->cfg.W, pop->cfg.P, pop->cfg.ld, center, pop->Z + (int64_t)G * pop->cfg.ld, a, pop->stream);
-    if (e != hipSuccess) return fail(LSGD_ERR_HIP, "easgd_update: center: %s", hipGetErrorString(e));
-    pop->z_valid[(size_t)G] = 0;             // that row no longer holds a leader
-    PullParams q;
-    q.x = pop->x; q.g = pop->g; q.m = pop->m; q.Z = pop->Z;
-    q.xb = (pop->cfg.flags & LSGD_WRITE_BF16_SHADOW) ? pop->xb : nullptr;
-    q.P = pop->cfg.P; q.ld = pop->cfg.ld; q.W = pop->cfg.W; q.G = G;
-    q.eta = eta; q.mu = pop->cfg.momentum; q.wd = pop->cfg.weight_decay;
-    q.lamL = 0.0f; q.lamG = lambda;
-    q.flags = pop->cfg.flags & ~LSGD_LEADER_EXEMPT;        // nobody is a leader here
-    q.use_refreshed = 0; q.clear_refreshed = 0;
-    q.group_size = pop->group_size;
-    q.comm_pull = 0;
-    e = launch_pull_update(q, pop->st, pop->stream);
+    PullParams q = pull_params(pop, eta, 0.0f, lambda, false, false);
+    q.flags &= ~LSGD_LEADER_EXEMPT;          // nobody is a leader here
+    hipError_t e;
+    if (column_step(pop, true)) {
+        ColumnStep c{};
+        c.pull = q; c.update = 1; c.center = center; c.center_rate = a;
+        e = launch_column_step(c, pop->st, pop->stream);
+        pop->z_valid[(size_t)G] = 0;         // that row no longer holds a leader
+    } else {
+        // center first (it reads the workers before they move); the old center lands in the global row of Z
+        e = launch_easgd_center(pop->x, pop->cfg.W, pop->cfg.P, pop->cfg.ld, center, pop->Z + (int64_t)G * pop->cfg.ld, a, pop->stream);
+        if (e != hipSuccess) return fail(LSGD_ERR_HIP, "easgd_update: center: %s", hipGetErrorString(e));
+        pop->z_valid[(size_t)G] = 0;
+        e = launch_pull_update(q, pop->st, pop->stream);
+    }
     if (e != hipSuccess) return fail(LSGD_ERR_HIP, "easgd_update: %s", hipGetErrorString(e));
     if (!(pop->cfg.flags & LSGD_WRITE_BF16_SHADOW)) pop->shadow_valid = false;
     return LSGD_OK;

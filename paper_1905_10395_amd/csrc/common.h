@@ -72,6 +72,23 @@ struct PullParams {
 };
 hipError_t launch_pull_update(const PullParams& p, const DeviceState& st, hipStream_t s);
 
+// Selection and update of a small or medium population in one launch (column_step.hip).
+constexpr int kColumnMaxWorkers = 64;   // one wavefront selects
+struct ColumnStep {
+    PullParams pull;
+    int update;              // gradient step with pull's coefficients
+    int comm;                // Algorithm 1's communication pull with commL, commG, after the update
+    float commL, commG;
+    int select;              // 0: none, 1: before the update, 2: between the update and the communication pull
+    uint64_t sel, cap;       // groups to re-select / whose leader counts as re-selected afterwards
+    int selG, capG;
+    const float* losses;
+    float* losses_out;       // also receives the losses, or NULL
+    float* center;           // elastic averaging (old center to row G of Z), else NULL
+    double center_rate;
+};
+hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStream_t s);
+
 hipError_t launch_smooth_losses(float* window, int K, int64_t t, const float* losses, int W, float* out, hipStream_t s);
 hipError_t launch_easgd_center(const float* x, int W, int64_t P, int64_t ld, float* center, float* old_center, double a, hipStream_t s);
 hipError_t launch_center(const float* x, int W, int64_t P, int64_t ld, float* out, hipStream_t s);

@@ -1,0 +1,116 @@
+"""GPU parity of the two routes of the update: the one-launch update by column owners (up to 32 workers) and the row
+streams (more), on the same inputs against the CPU oracle, at the edges of column tiles, row batches and groups; and
+the one-launch step against the same step made by the separate calls."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1905_10395_amd as L
+import workloads as wl
+from gpu_util import Pair, dev
+
+pytestmark = pytest.mark.gpu
+
+# W, group offsets, P, ld
+SHAPES = [
+    (1, [0, 1], 1, 1),                               # one of everything
+    (2, [0, 1, 2], 255, 256),                        # one thread short of a workgroup, groups of one
+    (7, [0, 1, 7], 257, 257),                        # odd stride: one column per thread
+    (32, [0, 9, 17, 32], 1027, 1088),                # groups of 9, 8 and 15 rows: remainders of the row batch
+    (33, [0, 9, 17, 33], 1027, 1088),                # row streams
+    (9, [0, 4, 9], 500_003, 500_032),                # more columns per thread, ragged last one
+]
+OPTIONS = [(0.0, 0, 0.0), (0.9, L.NESTEROV, 1e-2), (0.9, L.LEADER_EXEMPT, 0.0), (0.5, L.MOMENTUM_GRAD_ONLY, 0.0),
+           (0.0, L.PULL_UNSCALED_BY_ETA, 0.0)]
+
+
+@pytest.mark.parametrize("mu,flags,wd", OPTIONS)
+@pytest.mark.parametrize("W,off,P,ld", SHAPES)
+def test_whole_step_matches_oracle(W, off, P, ld, mu, flags, wd):
+    G = len(off) - 1
+    x0, _, _ = wl.stress_state(W, P, ld, seed=W + P)
+    x0[:, P:] = 7.0
+    pr = Pair(x0, off, P=P, momentum=mu, flags=flags, weight_decay=wd)
+    for t in range(4):
+        pr.set_grad(wl.stress_grad(W, P, ld, t, seed=W), wl.stress_losses(W, t, seed=W + G))
+        rl, rg = wl.refresh_masks(t, 2, G, staggered=(G > 1), tau_G=3)
+        before = pr.follow_gpu()
+        pr.ora.select(rl, rg); pr.ora.update(0.05, 0.1, 0.05, rl, rg)
+        pr.pop.step(L.ExternalBatch(pr.losses_dev), 0.05, 0.1, 0.05, rl, rg)
+        lead, gl = pr.pop.get_leaders()
+        assert lead == pr.ora.lead.tolist() and gl == int(pr.ora.glead[0])
+        assert pr.pop.get_losses() == pr.losses_dev.tolist()
+        pr.check_step_elementwise(before, f"step {t}")
+        np.testing.assert_array_equal(pr.Z.cpu().numpy()[:, :P], pr.ora.Z[:, :P])
+
+
+@pytest.mark.parametrize("mu", [0.0, 0.9])
+@pytest.mark.parametrize("W,off,P,ld", SHAPES)
+def test_one_call_equals_separate_calls(W, off, P, ld, mu):
+    """lsgd_step and lsgd_step_alg1 against the calls they are made of: the same expressions on the same values, so
+    parameters, momentum, copies and leaders agree bit for bit."""
+    G = len(off) - 1
+    x0, g0, _ = wl.stress_state(W, P, ld, seed=W)
+    res = []
+    for fused in (False, True):
+        pr = Pair(x0, off, P=P, momentum=mu)
+        losses = [dev(wl.stress_losses(W, t, seed=G)) for t in range(5)]
+        pr.g.copy_(dev(g0))
+        batch = [L.ExternalBatch(v) for v in losses]
+        if fused:
+            pr.pop.step(batch[0], 0.05, 0.1, 0.05)
+        else:
+            pr.pop.select_leaders(losses[0]); pr.pop.pull_update(0.05, 0.1, 0.05)
+        masks = [None, [1] + [0] * (G - 1), [0] * G]
+        for t in range(1, 4):
+            comm = (L.COMM_LOCAL if t != 3 else 0) | (L.COMM_GLOBAL if t != 2 else 0)
+            if fused:
+                pr.pop.step_alg1(batch[t], 0.05, 0.02, 0.01, 0.1, 0.07, comm, masks[t - 1])
+            else:
+                pr.pop.step_alg1(batch[t], 0.05, 0.02, 0.01, 0.1, 0.07, 0)
+                pr.pop.select_leaders(None, masks[t - 1] if comm & L.COMM_LOCAL else [0] * G, 1 if comm & L.COMM_GLOBAL else 0)
+                pr.pop.leader_pull(0.1, 0.07)
+        pr.pop.select_leaders(losses[4], [0] * (G - 1) + [1], 0)      # records of the one-launch calls feed a separate update
+        pr.pop.pull_update(0.05, 0.1, 0.05)
+        torch.cuda.synchronize()
+        res.append((pr.x.clone(), pr.m.clone() if mu else pr.x.clone(), pr.Z[:, :P].clone(), pr.pop.get_leaders(), pr.pop.get_losses()))
+    a, b = res
+    assert all(torch.equal(a[k], b[k]) for k in range(3)) and a[3] == b[3]
+
+
+def test_ties_nan_and_infinite_losses_select_alike():
+    """Selection inside the one-launch step against the selection kernel: ties to the lowest index, NaN as +inf,
+    -0 = +0, whole groups without a finite loss."""
+    W, G, P = 16, 4, 65
+    x0, g0, _ = wl.stress_state(W, P, P, seed=3)
+    rows = [[1.0, 0.5, 0.5, 2.0] + [float("nan")] * 4 + [float("inf"), float("nan"), float("inf"), 3.0] + [0.0, -0.0, 0.0, -0.0],
+            [float("nan")] * 16, [-float("inf")] * 8 + [0.0] * 8]
+    for v in rows:
+        losses = torch.tensor(v, device="cuda:0")
+        one = Pair(x0, wl.equal_group_offsets(W, G)); two = Pair(x0, wl.equal_group_offsets(W, G))
+        one.pop.step(L.ExternalBatch(losses), 0.1, 0.1, 0.1)
+        two.pop.select_leaders(losses)
+        assert one.pop.get_leaders() == two.pop.get_leaders()
+
+
+@pytest.mark.parametrize("W", [5, 16, 17])
+def test_easgd_both_routes(W):
+    """Center and rows, one launch (16 workers at most) or two: center bit-exact (one order of the sum, one rounding)."""
+    P, ld = 1030, 1088
+    x0, g0, _ = wl.stress_state(W, P, ld, seed=W)
+    pr = Pair(x0, [0, W], P=P, momentum=0.9)
+    c0 = x0[0].astype(np.float32).copy()
+    center = dev(c0)
+    pr.set_grad(g0, wl.stress_losses(W, 0))
+    a = W * np.float64(np.float32(0.05)) * np.float64(np.float32(0.1))
+    mean = np.zeros(ld)
+    for i in range(W):
+        mean = mean + x0[i].astype(np.float64)
+    want = ((1.0 - a) * c0.astype(np.float64) + a * (mean / W)).astype(np.float32)
+    pr.pop.easgd_step(L.ExternalBatch(pr.losses_dev), center, 0.05, 0.1)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(center.cpu().numpy()[:P], want[:P])
+    np.testing.assert_array_equal(pr.Z.cpu().numpy()[1, :P], c0[:P])
+    step = g0.astype(np.float64) + np.float64(np.float32(0.1)) * (x0.astype(np.float64) - c0.astype(np.float64))
+    np.testing.assert_allclose(pr.x.cpu().numpy()[:, :P], (x0 - np.float64(np.float32(0.05)) * step)[:, :P], rtol=3e-7, atol=3e-9)
+    assert pr.pop.get_losses() == pr.losses_dev.tolist()
