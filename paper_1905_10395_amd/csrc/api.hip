@@ -246,7 +246,7 @@ lsgd_status lsgd_destroy_population(lsgd_population* pop)
 
 namespace {
 
-lsgd_status do_grad_loss(lsgd_population* p, const lsgd_batch* batch, float* losses_out)
+lsgd_status do_grad_loss(lsgd_population* p, const lsgd_batch* batch, float* losses_out, LossParts* parts = nullptr)
 {
     float* losses = losses_out ? losses_out : p->st.losses;
     hipError_t e = hipSuccess;
@@ -269,7 +269,7 @@ lsgd_status do_grad_loss(lsgd_population* p, const lsgd_batch* batch, float* los
         }
         st.scratch = p->st.scratch + used;
         st.scratch_bytes = p->st.scratch_bytes - used;
-        e = launch_mc_grad_loss(p->x, p->g, losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, st, p->stream);
+        e = launch_mc_grad_loss(p->x, p->g, losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, st, p->stream, parts);
         break;
     }
     case LSGD_BATCH_MLP: {
@@ -331,6 +331,7 @@ lsgd_status check_grad_loss(lsgd_population* p, const lsgd_batch* batch)
     lsgd_status st = check_batch(batch, p->cfg.W, p->cfg.P, &partials, &scratch);
     if (st != LSGD_OK) return st;
     if (batch->kind == LSGD_BATCH_MLP && !p->xb) return fail(LSGD_ERR_STATE, "MLP batches need the x_bf16 buffer");
+    if (batch->kind == LSGD_BATCH_MC) scratch = mc_scratch_required(p->cfg.W, *static_cast<const lsgd_mc_batch*>(batch->desc));
     size_t need = scratch;
     if (partials > (size_t)p->cfg.W) need += align_up(sizeof(float) * partials);
     if (need > p->st.scratch_bytes)
@@ -489,7 +490,9 @@ lsgd_status column_losses(lsgd_population* p, const lsgd_batch* batch, ColumnSte
         return LSGD_OK;
     }
     c->losses = p->st.losses;
-    return do_grad_loss(p, batch, nullptr);
+    const lsgd_status st = do_grad_loss(p, batch, nullptr, &c->parts);
+    if (c->parts.n > 0) c->losses_out = p->st.losses;
+    return st;
 }
 
 // forward + losses -> leaders -> kept copies brought up to date -> backward pass that applies the update

@@ -33,6 +33,7 @@ struct ColumnDev {
     int selG, capG;
     const float* losses;
     float* losses_out;           // the population's own loss buffer when the losses come from elsewhere, else NULL
+    LossParts parts;             // partial sums to finish instead
     int32_t *lead, *glead, *refreshed;
     RowPlan* plan;
     float* center;               // elastic averaging: the center takes the global leader's place
@@ -222,12 +223,35 @@ template <int VEC, int KIND>
 __global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
 {
     __shared__ Leaders now, chosen;
+    __shared__ float loss_s[kColumnMaxWorkers];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int W = s.a.W, G = s.a.G;
     const int64_t col = s.a.col0 + ((int64_t)blockIdx.x * kThreads + tid) * VEC;
     const bool whole = col + VEC <= s.a.col1;
     RowBatch<VEC> first;
     if (s.update && whole) load_rows<VEC, KIND>(s.a, 0, s.a.offsets[1], col, first);   // under way during the selection
+    if (s.parts.n > 0) {
+        // every workgroup adds up the partial sums itself: a team of 8 to 256 lanes per worker, in double, in a fixed order
+        int team = kThreads;
+        while (team * W > kThreads) team >>= 1;
+        const int w = tid / team, l = tid % team;
+        double acc = 0.0;
+        if (w < W)
+            for (int i = l; i < s.parts.n; i += team) acc += (double)s.parts.sums[(int64_t)w * s.parts.n + i];
+        if (team > kWave) {                              // one or two workers
+            __shared__ double cross[kThreads / kWave];
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) acc += __shfl_xor(acc, d, kWave);
+            if (lane == 0) cross[tid / kWave] = acc;
+            __syncthreads();
+            acc = 0.0;
+            for (int q = 0; q < team / kWave; ++q) acc += cross[(w * team) / kWave + q];
+        } else {
+            for (int d = 1; d < team; d <<= 1) acc += __shfl_xor(acc, d, kWave);
+        }
+        if (w < W && l == 0) loss_s[w] = (float)((double)s.parts.c * acc);
+        __syncthreads();
+    }
     if (tid < kWave) {
         if (lane < G) {                                  // as recorded by earlier calls
             now.lead[lane] = s.a.lead[lane];
@@ -241,7 +265,7 @@ __global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
             uint64_t key = ~0ull;
             int gid = -1;
             if (lane < W) {
-                key = loss_key(s.losses[lane], lane);
+                key = loss_key(s.parts.n > 0 ? loss_s[lane] : s.losses[lane], lane);
                 gid = s.a.group_of[lane];
             }
             uint64_t seg = key;                          // segmented inclusive minimum: keys of the lane's own group only
@@ -266,7 +290,7 @@ __global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
         }
     }
     __syncthreads();
-    if (s.losses_out && blockIdx.x == 0 && tid < W) s.losses_out[tid] = s.losses[tid];
+    if (s.losses_out && blockIdx.x == 0 && tid < W) s.losses_out[tid] = s.parts.n > 0 ? loss_s[tid] : s.losses[tid];
     if (s.select && blockIdx.x == 0) {                   // recorded for the calls that follow
         if (tid < G) {
             if ((s.sel >> tid) & 1ull) s.lead[tid] = chosen.lead[tid];
@@ -318,7 +342,7 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     a.offsets = st.offsets; a.group_of = st.group_of; a.lead = st.lead; a.glead = st.glead; a.refreshed = st.refreshed; a.plan = st.plan;
     s.update = q.update; s.comm = q.comm; s.commL = q.commL; s.commG = q.commG;
     s.select = q.select; s.sel = q.sel; s.cap = q.cap; s.selG = q.selG; s.capG = q.capG;
-    s.losses = q.losses; s.losses_out = q.losses_out;
+    s.losses = q.losses; s.losses_out = q.losses_out; s.parts = q.parts;
     s.lead = st.lead; s.glead = st.glead; s.refreshed = st.refreshed; s.plan = st.plan;
     s.center = q.center; s.center_rate = q.center_rate;
     const bool mom = q.update && p.mu != 0.0f;

@@ -72,6 +72,13 @@ struct PullParams {
 };
 hipError_t launch_pull_update(const PullParams& p, const DeviceState& st, hipStream_t s);
 
+// Losses left as partial sums: losses[w] = c * sum of sums[w][0 .. n) (n = 0: they are finished).
+constexpr int kLossPartsMax = 1024;     // workers x partial sums up to which the next launch adds them up itself
+struct LossParts {
+    const float* sums;
+    int n;
+    float c;
+};
 // Selection and update of a small or medium population in one launch (column_step.hip).
 constexpr int kColumnMaxWorkers = 64;   // one wavefront selects
 struct ColumnStep {
@@ -82,8 +89,9 @@ struct ColumnStep {
     int select;              // 0: none, 1: before the update, 2: between the update and the communication pull
     uint64_t sel, cap;       // groups to re-select / whose leader counts as re-selected afterwards
     int selG, capG;
-    const float* losses;
+    const float* losses;     // ignored when parts.n > 0
     float* losses_out;       // also receives the losses, or NULL
+    LossParts parts;
     float* center;           // elastic averaging (old center to row G of Z), else NULL
     double center_rate;
 };
@@ -96,9 +104,11 @@ hipError_t launch_center(const float* x, int W, int64_t P, int64_t ld, float* ou
 hipError_t launch_cast_shadow(const float* x, uint16_t* xb, int W, int64_t P, int64_t ld, hipStream_t s);
 
 size_t mc_scratch_bytes(int W, const lsgd_mc_batch& b);
+size_t mc_scratch_required(int W, const lsgd_mc_batch& b);   // without which a batch is refused
 size_t mc_partials(int W, const lsgd_mc_batch& b);
+// parts != NULL: the caller's next launch can finish the losses; if parts->n is 0 afterwards they are in `losses`
 hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
-                               const lsgd_mc_batch& b, const DeviceState& st, hipStream_t s);
+                               const lsgd_mc_batch& b, const DeviceState& st, hipStream_t s, LossParts* parts);
 // objective values only (no gradient); needs the same loss-partial slots as launch_mc_grad_loss
 hipError_t launch_mc_loss(const float* x, float* losses, int W, int64_t ld, const lsgd_mc_batch& b, const DeviceState& st,
                           hipStream_t s);

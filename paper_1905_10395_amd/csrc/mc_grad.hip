@@ -7,6 +7,8 @@
 //   dU[a] = 2c * sum_{k: a_k = a} e_k V[b_k] ;  dV[b] = 2c * sum_{k: b_k = b} e_k U[a_k]
 //
 // Worker row of x and of g: [U (m x r) | V (n x r)], row-major factors.
+#include <cmath>
+
 #include "common.h"
 
 namespace lsgd {
@@ -46,50 +48,78 @@ __device__ __forceinline__ void fetch_entry(const lsgd_mc_entry* __restrict__ en
 // General path: S lanes cooperate on one entry (S = power of two >= min(r, 64)),
 // residual by a lane butterfly, gradient rows accumulated with hardware fp32
 // atomics into the zero-filled g.  Any r, m, n.  GRAD = false evaluates the
-// squared residuals only (g may be NULL).
+// squared residuals only (g may be NULL).  What bounds it on small batches is the
+// chain index -> entry -> factor rows -> residual of an entry, so a lane group has
+// up to eight entries in flight, and wide groups come in larger workgroups (256
+// entries each): 4 workers x 3000 entries, rank 5, 13.9 -> 4 us; 4 x 256, rank 50,
+// whole gradient call 39 -> 18 us.
+constexpr int mc_atomic_threads(int S) { return S <= 8 ? 256 : S == 16 ? 512 : 1024; }
+
 template <int S, bool GRAD>
-__global__ __launch_bounds__(kMcThreads) void mc_grad_atomic_kernel(
+__global__ __launch_bounds__(mc_atomic_threads(S)) void mc_grad_atomic_kernel(
     const float* __restrict__ x, float* __restrict__ g, int64_t ld, int m, int n, int r,
     const int32_t* __restrict__ rows, const int32_t* __restrict__ cols, const float* __restrict__ vals,
     const int32_t* __restrict__ batch_idx, int64_t nb, float two_c, float* __restrict__ partials, int nblk,
     const lsgd_mc_entry* __restrict__ entries)
 {
+    constexpr int kThreads = mc_atomic_threads(S);
     const int w = blockIdx.y;
     const float* U = x + (int64_t)w * ld;
     const float* V = U + (int64_t)m * r;
     float* gU = GRAD ? g + (int64_t)w * ld : nullptr;
     float* gV = GRAD ? gU + (int64_t)m * r : nullptr;
     const int sub = threadIdx.x / S, q0 = threadIdx.x % S;
-    constexpr int kSubs = kMcThreads / S;
+    constexpr int kSubs = kThreads / S;
+    constexpr int kFly = S < 8 ? S : 8;              // entries of a lane group in flight 
     const int64_t k0 = (int64_t)blockIdx.x * kMcEntriesPerBlock;
     const int64_t k1 = (k0 + kMcEntriesPerBlock < nb) ? k0 + kMcEntriesPerBlock : nb;
     float sq = 0.f;
-    for (int64_t k = k0 + sub; k < k1; k += kSubs) {
-        const int64_t s = batch_idx ? (int64_t)batch_idx[(int64_t)w * nb + k] : k;
-        int a, b;
-        float mv;
-        fetch_entry(entries, rows, cols, vals, s, a, b, mv);
-        const float* ua = U + (int64_t)a * r;
-        const float* vb = V + (int64_t)b * r;
-        float dot = 0.f;
-        for (int q = q0; q < r; q += S) dot = fmaf(ua[q], vb[q], dot);
+    for (int64_t kb = k0 + sub; kb < k1; kb += (int64_t)kSubs * kFly) {
+        int a[kFly], b[kFly];
+        float mv[kFly], ua[kFly], vb[kFly];
+        bool live[kFly];
 #pragma unroll
-        for (int d = 1; d < S; d <<= 1) dot += __shfl_xor(dot, d, S);
-        const float e = dot - mv;
-        if (q0 == 0) sq = fmaf(e, e, sq);
-        if (GRAD) {
-            const float f = two_c * e;
-            for (int q = q0; q < r; q += S) {
-                unsafeAtomicAdd(gU + (int64_t)a * r + q, f * vb[q]);
-                unsafeAtomicAdd(gV + (int64_t)b * r + q, f * ua[q]);
+        for (int u = 0; u < kFly; ++u) {
+            const int64_t k = kb + (int64_t)u * kSubs;
+            live[u] = k < k1;
+            const int64_t kc = live[u] ? k : kb;     // past the end: the first entry again, its results dropped
+            const int64_t s = batch_idx ? (int64_t)batch_idx[(int64_t)w * nb + kc] : kc;
+            fetch_entry(entries, rows, cols, vals, s, a[u], b[u], mv[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+            ua[u] = q0 < r ? U[(int64_t)a[u] * r + q0] : 0.f;
+            vb[u] = q0 < r ? V[(int64_t)b[u] * r + q0] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+            const float* uu = U + (int64_t)a[u] * r;
+            const float* vv = V + (int64_t)b[u] * r;
+            float dot = ua[u] * vb[u];
+            for (int q = q0 + S; q < r; q += S) dot = fmaf(uu[q], vv[q], dot);
+#pragma unroll
+            for (int d = 1; d < S; d <<= 1) dot += __shfl_xor(dot, d, S);
+            const float e = dot - mv[u];
+            if (!live[u]) continue;
+            if (q0 == 0) sq = fmaf(e, e, sq);
+            if (GRAD) {
+                const float f = two_c * e;
+                if (q0 < r) {
+                    unsafeAtomicAdd(gU + (int64_t)a[u] * r + q0, f * vb[u]);
+                    unsafeAtomicAdd(gV + (int64_t)b[u] * r + q0, f * ua[u]);
+                }
+                for (int q = q0 + S; q < r; q += S) {
+                    unsafeAtomicAdd(gU + (int64_t)a[u] * r + q, f * vv[q]);
+                    unsafeAtomicAdd(gV + (int64_t)b[u] * r + q, f * uu[q]);
+                }
             }
         }
     }
     // block sum of squared residuals in a fixed order
-    __shared__ float red[kMcThreads];
+    __shared__ float red[kThreads];
     red[threadIdx.x] = sq;
     __syncthreads();
-    for (int d = kMcThreads / 2; d > 0; d >>= 1) {
+    for (int d = kThreads / 2; d > 0; d >>= 1) {
         if (threadIdx.x < d) red[threadIdx.x] += red[threadIdx.x + d];
         __syncthreads();
     }
@@ -173,7 +203,7 @@ __global__ __launch_bounds__(256) void mc_loss_finish_kernel(const float* __rest
 }
 
 // ------------------------------------------------------------------------------------------
-// Binned path (r % 4 == 0, 16-byte aligned rows): no global floating-point atomics, and each
+// Binned path (up to 64 column groups of 4, 2 or 1 in a row): no global floating-point atomics, and each
 // factor row an entry touches is gathered once per side.
 // Factor rows are grouped in bins of 128 consecutive rows (U bins, then V bins).
 //   1. prepare kernel (1024 threads, E = 1024..4096 entries per workgroup): fetches each entry's
@@ -194,11 +224,20 @@ __global__ __launch_bounds__(256) void mc_loss_finish_kernel(const float* __rest
 // there is no separate zero fill.  The order of a row's records follows LDS rank order, so the
 // last bits of a gradient row (fp32 sums) can differ between runs; the loss is summed in double,
 // where a different order changes the rounded fp32 result only in freak cases.
-// Workgroups of one worker are numbered so that they land on one die (workgroup id modulo 8),
+// Workgroups of one worker are numbered so that they land on one die, or few (workgroup id modulo 8),
 // which keeps the worker's factors, 5 MB at rank 32, in that die's L2.  This placement only
 // affects speed, never results.
 // ------------------------------------------------------------------------------------------
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+// a lane's part of a factor row: four, two or one of its columns, by the rank and the alignment of the rows
+template <int VW> struct Cols;
+template <> struct Cols<4> { using type = v4f; };
+template <> struct Cols<2> { using type = v2f; };
+template <> struct Cols<1> { using type = float; };
+__device__ __forceinline__ float col_dot(v4f a, v4f b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
+__device__ __forceinline__ float col_dot(v2f a, v2f b) { return a.x * b.x + a.y * b.y; }
+__device__ __forceinline__ float col_dot(float a, float b) { return a * b; }
 
 constexpr int kBinRows = 128;         // factor rows per bin (64, 128 or 256)
 constexpr int kKeyShift = (kBinRows == 64) ? 26 : (kBinRows == 128) ? 25 : 24;   // record key: row in bin above, other row below
@@ -214,13 +253,21 @@ struct McBinned {
     int nbinsU, nbins, nblk, E;
 };
 
-// maps a linear workgroup id to (worker, chunk) with all chunks of a worker on the same die
-__device__ __forceinline__ bool xcd_map(int64_t id, int W, int nchunk, int& w, int& chunk)
+// Maps a linear workgroup id to (worker, chunk), a die being id modulo 8.  Multiples of eight workers: worker w lives on
+// die w % 8, all dies work through workers 0 .. 7, then 8 .. 15 (144.3 -> 140.9 us for a whole step of 16 workers of
+// 20000 x 20000, rank 32, against contiguous runs).  Other numbers of workers: a die takes a contiguous run of all
+// workers' chunks, so that a worker's chunks share few dies and no die is left without work (per_die > 0).
+__device__ __forceinline__ bool xcd_map(int64_t id, int64_t per_die, int W, int nchunk, int& w, int& chunk)
 {
-    const int xcd = (int)(id % kXcd);
     const int64_t t = id / kXcd;
-    w = (int)(t / nchunk) * kXcd + xcd;
-    chunk = (int)(t % nchunk);
+    if (per_die > 0) {
+        const int64_t lin = (id % kXcd) * per_die + t;
+        w = (int)(lin / nchunk);
+        chunk = (int)(lin % nchunk);
+    } else {
+        w = (int)(t / nchunk) * kXcd + (int)(id % kXcd);
+        chunk = (int)(t % nchunk);
+    }
     return w < W;
 }
 
@@ -331,18 +378,20 @@ constexpr int kSideThreads = 256;
 constexpr int kRedCap = 1024;                     // records staged per pass
 constexpr int kSegCap = kSideThreads;             // segments collected at a time
 
-// EXACT: r == 4 * LPE, every lane of a group holds part of the row.
-template <int LPE, bool EXACT>
+// EXACT: r == VW * LPE, every lane of a group holds part of the row.
+template <int LPE, bool EXACT, int VW>
 __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __restrict__ x, float* __restrict__ g, int64_t ld,
                                                              int m, int n, int r, McBinned S, float two_c,
-                                                             float* __restrict__ partials, int W)
+                                                             float* __restrict__ partials, int W, int64_t per_die)
 {
+    using V = typename Cols<VW>::type;
     constexpr int kSubs = kSideThreads / LPE;                          // lane groups per workgroup
     constexpr int RPG = (kBinRows + kSubs - 1) / kSubs;              // rows per lane group
     constexpr int PER = kRedCap / kSideThreads;                        // records per thread and pass
     int w, gbin;
-    if (!xcd_map(blockIdx.x, W, S.nbins, w, gbin)) return;
-    extern __shared__ v4f tile[];                                     // the bin's own rows [kBinRows][r]
+    if (!xcd_map(blockIdx.x, per_die, W, S.nbins, w, gbin)) return;
+    extern __shared__ __attribute__((aligned(16))) char tile_mem[];   // the bin's own rows [kBinRows][r]
+    V* tile = reinterpret_cast<V*>(tile_mem);
     __shared__ int2 sorted[kRedCap];
     __shared__ int cnt[kBinRows], start[kBinRows + 1];
     __shared__ int segoff[kSegCap + 1], segbase[kSegCap], wtot[kSideThreads / 64];
@@ -354,20 +403,20 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
     const float* xw = x + (int64_t)w * ld;
     const float* own = uside ? xw : xw + (int64_t)m * r;
     const float* other = uside ? xw + (int64_t)m * r : xw;            // U rows gather V rows and vice versa
-    const int r4 = r >> 2;
+    const int rv = r / VW;
     {
-        const int live = (nrows - row0 < kBinRows ? nrows - row0 : kBinRows) * r4;
-        const v4f* src = reinterpret_cast<const v4f*>(own + (int64_t)row0 * r);
+        const int live = (nrows - row0 < kBinRows ? nrows - row0 : kBinRows) * rv;
+        const V* src = reinterpret_cast<const V*>(own + (int64_t)row0 * r);
         for (int i = t; i < live; i += kSideThreads) tile[i] = src[i];
     }
     const int2* rec = S.rec + (int64_t)w * S.nblk * (2 * S.E);
     const int32_t* segs = S.segs + (int64_t)w * S.nblk * (S.nbins + 1) + gbin;
     const int sub = t / LPE, q0 = t % LPE;
-    const bool lane_live = EXACT || q0 < r4;
-    const float* obase = other + q0 * 4;                              // this lane's four columns of a gathered row
-    v4f acc[RPG];
+    const bool lane_live = EXACT || q0 < rv;
+    const float* obase = other + q0 * VW;                             // this lane's columns of a gathered row
+    V acc[RPG];
 #pragma unroll
-    for (int i = 0; i < RPG; ++i) acc[i] = (v4f)(0.f);
+    for (int i = 0; i < RPG; ++i) acc[i] = V(0.f);
     double sq = 0.0;
 
     for (int blk0 = 0; blk0 < S.nblk; blk0 += kSegCap) {
@@ -441,22 +490,22 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
                 if (row < kBinRows) {
                     const int s0 = start[row], s1 = start[row + 1];
                     if (s0 < s1) {
-                        const v4f mine_row = lane_live ? tile[row * r4 + q0] : (v4f)(0.f);
+                        const V mine_row = lane_live ? tile[row * rv + q0] : V(0.f);
                         float rowsq = 0.f;
                         for (int sidx = s0; sidx < s1; sidx += 4) {
                             // straight-line body: slots past the row's end repeat its last record with weight zero
                             int2 rc[4];
-                            v4f ov[4];
+                            V ov[4];
 #pragma unroll
                             for (int u = 0; u < 4; ++u) rc[u] = sorted[(sidx + u < s1) ? sidx + u : s1 - 1];
 #pragma unroll
                             for (int u = 0; u < 4; ++u)
-                                ov[u] = lane_live ? *reinterpret_cast<const v4f*>(obase + (uint64_t)(uint32_t)(rc[u].x & kKeyMask) * (uint32_t)r)
-                                                  : (v4f)(0.f);
+                                ov[u] = lane_live ? *reinterpret_cast<const V*>(obase + (uint64_t)(uint32_t)(rc[u].x & kKeyMask) * (uint32_t)r)
+                                                  : V(0.f);
                             float d[4];
 #pragma unroll
                             for (int u = 0; u < 4; ++u)
-                                d[u] = group_sum<LPE>(mine_row.x * ov[u].x + mine_row.y * ov[u].y + mine_row.z * ov[u].z + mine_row.w * ov[u].w);
+                                d[u] = group_sum<LPE>(col_dot(mine_row, ov[u]));
 #pragma unroll
                             for (int u = 0; u < 4; ++u) {
                                 const float e = (sidx + u < s1) ? d[u] - __int_as_float(rc[u].y) : 0.f;
@@ -476,7 +525,7 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
     for (int i = 0; i < RPG; ++i) {
         const int row = sub + i * kSubs;
         if (row < kBinRows && row0 + row < nrows && lane_live)
-            reinterpret_cast<v4f*>(out + (int64_t)row * r)[q0] = two_c * acc[i];
+            reinterpret_cast<V*>(out + (int64_t)row * r)[q0] = two_c * acc[i];
     }
     if (uside) {                                                      // sum of squared residuals of this U bin
 #pragma unroll
@@ -537,10 +586,45 @@ static int mc_prep_blocks(int W, const lsgd_mc_batch& b)
     const int64_t E = (int64_t)mc_ept(W, b) * kPrepThreads;
     return (int)((mc_entries(b) + E - 1) / E);
 }
-static bool mc_binned_ok(int W, const lsgd_mc_batch& b)
+// Columns per lane in the side kernel by the rank alone.
+static int mc_cols(int r) { return r % 4 == 0 ? 4 : r % 2 == 0 ? 2 : 1; }
+
+// Which path is faster, from what bounds each (us; fitted to gradient calls of 100 x 100 to 20000 x 20000, ranks 1 to
+// 64, 256 to 50000 entries per worker, 3 to 16 workers: the choice costs 1 % on average, 26 % at worst):
+//   atomics   launches and one chain, plus the atomics themselves, which grow with entries x rank, plus the zero fill;
+//             ranks past 32 take a whole wavefront per entry
+//   binned    one launch more; then either the records of one bin, which one workgroup walks, or all records, and every
+//             factor row read and gradient row written, touched or not
+// Measured, atomics / binned: 100 x 100 (one bin a side), rank 5, 3000 entries, 3 workers 11 / 35; 6001 x 3517, rank 10,
+// 8 workers, 2048 entries 14 / 20, 8192 22 / 23, 32768 57 / 37; 20000 x 20000, rank 32, 16 workers, 32768 entries 148 / 91.
+static bool mc_binned_faster(int W, const lsgd_mc_batch& b)
+{
+    const double thousands = 1e-3 * (double)W * (double)mc_entries(b);
+    const double rows = (double)W * ((double)b.m + (double)b.n) * b.r * 4.0 / 5e6;      // one pass over all factor rows
+    const double side = (double)(b.m < b.n ? b.m : b.n) / kBinRows;
+    const double per_bin = (double)mc_entries(b) / (side > 1.0 ? ceil(side) : 1.0);
+    int lanes = 1;
+    while (lanes * mc_cols(b.r) < b.r) lanes <<= 1;
+    const double atomics = (b.r > 32 ? 15.0 : 7.2) + thousands * (0.136 + 0.0062 * b.r) + rows;
+    const double walk = per_bin * (0.0135 + 0.00038 * lanes), all = thousands * (0.079 + 0.0029 * b.r);
+    const double binned = 12.2 + (walk > all ? walk : all) + 3.4 * rows;
+    return binned < atomics;
+}
+
+// ... as wide as the rank and the alignment of the rows allow
+static int mc_cols(const float* x, const float* g, int64_t ld, int r)
+{
+    int vw = mc_cols(r);
+    auto ok = [&](int v) {
+        return (reinterpret_cast<uintptr_t>(x) & (4u * (unsigned)v - 1u)) == 0 && (reinterpret_cast<uintptr_t>(g) & (4u * (unsigned)v - 1u)) == 0 && ld % v == 0;
+    };
+    while (vw > 1 && !ok(vw)) vw >>= 1;
+    return vw;
+}
+static bool mc_binned_ok(int W, const lsgd_mc_batch& b, int vw)
 {
     const int64_t nb = mc_entries(b);
-    if (!(b.r % 4 == 0 && nb > 0 && nb < ((int64_t)1 << 30) && mc_bins(b) <= kMaxBins && b.m < (1 << kKeyShift) && b.n < (1 << kKeyShift) &&
+    if (!(b.r / vw <= 64 && nb > 0 && nb < ((int64_t)1 << 30) && mc_bins(b) <= kMaxBins && b.m < (1 << kKeyShift) && b.n < (1 << kKeyShift) &&
           (size_t)kBinRows * b.r * 4 <= 64 * 1024))
         return false;
     return (int64_t)mc_prep_blocks(W, b) * (mc_bins(b) + 1) <= ((int64_t)1 << 22);
@@ -555,16 +639,17 @@ size_t mc_partials(int W, const lsgd_mc_batch& b)
 
 size_t mc_scratch_bytes(int W, const lsgd_mc_batch& b)
 {
-    if (!mc_binned_ok(W, b)) return 0;
+    if (!mc_binned_ok(W, b, mc_cols(b.r)) || (b.r % 4 != 0 && !mc_binned_faster(W, b))) return 0;
     const size_t slots = (size_t)mc_prep_blocks(W, b) * mc_ept(W, b) * kPrepThreads;
     return up256((size_t)W * mc_prep_blocks(W, b) * (mc_bins(b) + 1) * 4) + up256((size_t)W * 2 * slots * 8);
 }
 
-template <int LPE>
-static void launch_binned(const float* x, float* g, int W, int64_t ld, const lsgd_mc_batch& b, int64_t nb,
-                          const McBinned& S, float* partials, hipStream_t s)
+// The binned path's scratch is a condition only for ranks that are multiples of four; with others a workspace
+// without room for it takes the general path.
+size_t mc_scratch_required(int W, const lsgd_mc_batch& b) { return b.r % 4 == 0 ? mc_scratch_bytes(W, b) : 0; }
+
+static void launch_prep(int W, const lsgd_mc_batch& b, int64_t nb, const McBinned& S, hipStream_t s)
 {
-    const int rounds = (W + kXcd - 1) / kXcd;
     const dim3 pgrid((unsigned)S.nblk, (unsigned)W);
     const size_t plds = (size_t)((S.nbins + 2) & ~1) * 4 + (size_t)2 * S.E * 8;     // counters, then the staged records
     static bool big_lds = false;
@@ -579,38 +664,63 @@ static void launch_binned(const float* x, float* g, int W, int64_t ld, const lsg
         hipLaunchKernelGGL((mc_prep_kernel<2>), pgrid, dim3(kPrepThreads), plds, s, b.rows, b.cols, b.vals, b.batch_idx, nb, S, b.entries);
     else
         hipLaunchKernelGGL((mc_prep_kernel<4>), pgrid, dim3(kPrepThreads), plds, s, b.rows, b.cols, b.vals, b.batch_idx, nb, S, b.entries);
-    if (b.r == 4 * LPE)
-        hipLaunchKernelGGL((mc_side_kernel<LPE, true>), dim3((unsigned)((int64_t)rounds * kXcd * S.nbins)), dim3(kSideThreads),
-                           (size_t)kBinRows * b.r * 4, s, x, g, ld, b.m, b.n, b.r, S, 2.0f * b.c, partials, W);
+}
+
+template <int LPE, int VW>
+static void launch_side(const float* x, float* g, int W, int64_t ld, const lsgd_mc_batch& b,
+                        const McBinned& S, float* partials, hipStream_t s)
+{
+    const int64_t groups = ((int64_t)W * S.nbins + kXcd - 1) / kXcd * kXcd, per_die = W % kXcd ? groups / kXcd : 0;
+    if (b.r == VW * LPE)
+        hipLaunchKernelGGL((mc_side_kernel<LPE, true, VW>), dim3((unsigned)groups), dim3(kSideThreads),
+                           (size_t)kBinRows * b.r * 4, s, x, g, ld, b.m, b.n, b.r, S, 2.0f * b.c, partials, W, per_die);
     else
-        hipLaunchKernelGGL((mc_side_kernel<LPE, false>), dim3((unsigned)((int64_t)rounds * kXcd * S.nbins)), dim3(kSideThreads),
-                           (size_t)kBinRows * b.r * 4, s, x, g, ld, b.m, b.n, b.r, S, 2.0f * b.c, partials, W);
+        hipLaunchKernelGGL((mc_side_kernel<LPE, false, VW>), dim3((unsigned)groups), dim3(kSideThreads),
+                           (size_t)kBinRows * b.r * 4, s, x, g, ld, b.m, b.n, b.r, S, 2.0f * b.c, partials, W, per_die);
+}
+
+template <int VW>
+static void launch_side_lanes(const float* x, float* g, int W, int64_t ld, const lsgd_mc_batch& b, const McBinned& S, float* partials,
+                              hipStream_t s)
+{
+    const int rv = b.r / VW;
+    if (rv <= 1) launch_side<1, VW>(x, g, W, ld, b, S, partials, s);
+    else if (rv <= 2) launch_side<2, VW>(x, g, W, ld, b, S, partials, s);
+    else if (rv <= 4) launch_side<4, VW>(x, g, W, ld, b, S, partials, s);
+    else if (rv <= 8) launch_side<8, VW>(x, g, W, ld, b, S, partials, s);
+    else if (rv <= 16) launch_side<16, VW>(x, g, W, ld, b, S, partials, s);
+    else if (rv <= 32) launch_side<32, VW>(x, g, W, ld, b, S, partials, s);
+    else launch_side<64, VW>(x, g, W, ld, b, S, partials, s);
 }
 
 hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
-                               const lsgd_mc_batch& b, const DeviceState& st, hipStream_t s)
+                               const lsgd_mc_batch& b, const DeviceState& st, hipStream_t s, LossParts* parts)
 {
     const int64_t nb = mc_entries(b);
-    const bool aligned = (reinterpret_cast<uintptr_t>(x) & 15u) == 0 && (reinterpret_cast<uintptr_t>(g) & 15u) == 0 && ld % 4 == 0;
-    const bool binned = mc_binned_ok(W, b) && aligned && st.scratch_bytes >= mc_scratch_bytes(W, b);
+    // the partial sums are added up by a launch of their own, or left to a caller that says it can
+    auto finish_loss = [&](int workers, int n) {
+        if (parts && n > 0 && (int64_t)workers * n <= kLossPartsMax) {
+            parts->sums = st.partials; parts->n = n; parts->c = b.c;
+        } else {
+            hipLaunchKernelGGL(mc_loss_finish_kernel, dim3((unsigned)workers), dim3(256), 0, s, st.partials, n, b.c, losses);
+        }
+        return hipGetLastError();
+    };
+    const int vw = mc_cols(x, g, ld, b.r);
+    const bool binned = mc_binned_faster(W, b) && mc_binned_ok(W, b, vw) && st.scratch_bytes >= mc_scratch_bytes(W, b);
     if (binned) {
         McBinned S;
         S.nbinsU = mc_bins_u(b); S.nbins = mc_bins(b); S.nblk = mc_prep_blocks(W, b); S.E = mc_ept(W, b) * kPrepThreads;
         char* p = st.scratch;
         S.segs = reinterpret_cast<int32_t*>(p); p += up256((size_t)W * S.nblk * (S.nbins + 1) * 4);
         S.rec = reinterpret_cast<int2*>(p);
-        const int r4 = b.r / 4;
-        if (r4 <= 1) launch_binned<1>(x, g, W, ld, b, nb, S, st.partials, s);
-        else if (r4 <= 2) launch_binned<2>(x, g, W, ld, b, nb, S, st.partials, s);
-        else if (r4 <= 4) launch_binned<4>(x, g, W, ld, b, nb, S, st.partials, s);
-        else if (r4 <= 8) launch_binned<8>(x, g, W, ld, b, nb, S, st.partials, s);
-        else if (r4 <= 16) launch_binned<16>(x, g, W, ld, b, nb, S, st.partials, s);
-        else if (r4 <= 32) launch_binned<32>(x, g, W, ld, b, nb, S, st.partials, s);
-        else launch_binned<64>(x, g, W, ld, b, nb, S, st.partials, s);
+        launch_prep(W, b, nb, S, s);
+        if (vw == 4) launch_side_lanes<4>(x, g, W, ld, b, S, st.partials, s);
+        else if (vw == 2) launch_side_lanes<2>(x, g, W, ld, b, S, st.partials, s);
+        else launch_side_lanes<1>(x, g, W, ld, b, S, st.partials, s);
         if (ld > P)
             hipLaunchKernelGGL(mc_zero_pad_kernel, dim3((unsigned)((ld - P + 255) / 256), (unsigned)W), dim3(256), 0, s, g, P, ld);
-        hipLaunchKernelGGL(mc_loss_finish_kernel, dim3((unsigned)W), dim3(256), 0, s, st.partials, S.nbinsU, b.c, losses);
-        return hipGetLastError();
+        return finish_loss(W, S.nbinsU);
     }
     const int nblk = (int)((nb + kMcEntriesPerBlock - 1) / kMcEntriesPerBlock);
     // general path: zero the whole rows (padding included), then atomics
@@ -626,7 +736,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         dim3 grid((unsigned)nblk, (unsigned)W);
         const float two_c = 2.0f * b.c;
 #define LSGD_MC_LAUNCH(S)                                                                                       \
-    hipLaunchKernelGGL((mc_grad_atomic_kernel<S, true>), grid, dim3(kMcThreads), 0, s, x, g, ld, b.m, b.n, b.r, \
+    hipLaunchKernelGGL((mc_grad_atomic_kernel<S, true>), grid, dim3(mc_atomic_threads(S)), 0, s, x, g, ld, b.m, b.n, b.r, \
                        b.rows, b.cols, b.vals, b.batch_idx, nb, two_c, st.partials, nblk, b.entries)
         if (b.r <= 1) LSGD_MC_LAUNCH(1);
         else if (b.r <= 2) LSGD_MC_LAUNCH(2);
@@ -637,8 +747,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         else LSGD_MC_LAUNCH(64);
 #undef LSGD_MC_LAUNCH
     }
-    hipLaunchKernelGGL(mc_loss_finish_kernel, dim3((unsigned)W), dim3(256), 0, s, st.partials, nblk, b.c, losses);
-    return hipGetLastError();
+    return finish_loss(W, nblk);
 }
 
 // Objective values only: the residual pass of the general path without its atomics, one partial sum per
@@ -666,7 +775,7 @@ hipError_t launch_mc_loss(const float* x, float* losses, int W, int64_t ld, cons
     } else if (nblk > 0) {
         dim3 grid((unsigned)nblk, (unsigned)W);
 #define LSGD_MC_LAUNCH(S)                                                                                              \
-    hipLaunchKernelGGL((mc_grad_atomic_kernel<S, false>), grid, dim3(kMcThreads), 0, s, x, (float*)nullptr, ld, b.m, b.n, \
+    hipLaunchKernelGGL((mc_grad_atomic_kernel<S, false>), grid, dim3(mc_atomic_threads(S)), 0, s, x, (float*)nullptr, ld, b.m, b.n, \
                        b.r, b.rows, b.cols, b.vals, b.batch_idx, nb, 0.0f, st.partials, nblk, b.entries)
         if (b.r <= 1) LSGD_MC_LAUNCH(1);
         else if (b.r <= 2) LSGD_MC_LAUNCH(2);

@@ -1,0 +1,89 @@
+"""GPU parity of the two routes of the matrix-completion gradient (binned, atomics) at every width of a lane's part of a
+factor row, on shapes that the size rule sends to either, and on workspaces without room for the binned route."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1905_10395_amd as L
+import workloads as wl
+from gpu_util import Pair, dev, rel_l2_rows
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(m, n, r, n_obs, W, B, seed, ld=None, pop_kw=None, G=1):
+    g = wl.stream("mc_routes", m, n, r, seed=seed)
+    rows = g.integers(0, m, n_obs).astype(np.int32); cols = g.integers(0, n, n_obs).astype(np.int32)
+    vals = g.standard_normal(n_obs).astype(np.float32)
+    idx = g.integers(0, n_obs, (W, B)).astype(np.int32)
+    P = (m + n) * r
+    ld = wl.padded_ld(P) if ld is None else ld(P)
+    x0 = np.zeros((W, ld), np.float32)
+    x0[:, :P] = g.standard_normal((W, P)).astype(np.float32) * np.float32(r ** -0.25)
+    c = 0.5 / B
+    batch = L.MCBatch(m, n, r, dev(rows), dev(cols), dev(vals), dev(idx), c)
+    pr = Pair(x0, wl.equal_group_offsets(W, G), P=P, largest_batch=batch)
+    pr.ora.grad_loss_mc(m, n, r, rows, cols, vals, idx, c)
+    return pr, batch, P
+
+
+# bins of 128 rows: one row past a bin, several bins; ranks with lanes of four, two and one column, exact and not;
+# 40000 entries per worker so that the binned route is the faster one by the rule, 300 so that it is not
+@pytest.mark.parametrize("B", [300, 40000])
+@pytest.mark.parametrize("r", [1, 2, 3, 4, 5, 6, 10, 12, 33, 50, 64])
+def test_both_routes_match_oracle(r, B):
+    W = 9
+    pr, batch, P = problem(4001, 3000, r, 60000, W, B, seed=r)
+    pr.g.fill_(float("nan"))
+    pr.pop.grad_loss(batch)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(pr.pop.get_losses(), pr.ora.losses, rtol=1e-5)
+    g = pr.g.cpu().numpy()
+    assert rel_l2_rows(g[:, :P], pr.ora.g[:, :P]).max() <= 1e-5
+    assert np.all(g[:, P:] == 0)
+
+
+@pytest.mark.parametrize("r", [4, 8, 10])
+def test_rows_that_are_not_aligned_for_the_widest_lanes(r):
+    """Odd row strides: the binned route with two or one column per lane."""
+    pr, batch, P = problem(4001, 3000, r, 60000, 9, 40000, seed=r, ld=lambda P: P + 2 if r != 8 else P + 1)
+    pr.g.fill_(float("nan"))
+    pr.pop.grad_loss(batch)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(pr.pop.get_losses(), pr.ora.losses, rtol=1e-5)
+    assert rel_l2_rows(pr.g.cpu().numpy()[:, :P], pr.ora.g[:, :P]).max() <= 1e-5
+
+
+def test_workspace_without_binned_scratch():
+    """A workspace that holds the loss sums but not the binned route's records: other ranks than multiples of four take
+    the atomics instead, multiples of four are refused as ever."""
+    for r in (5, 8):
+        pr, batch, P = problem(4001, 3000, r, 60000, 9, 40000, seed=r)
+        small = 9 * ((40000 + 255) // 256) * 4
+        need = L.workspace_bytes(9, P, pr.ld, 1) + (small + 255) // 256 * 256
+        assert need < L.workspace_bytes(9, P, pr.ld, 1, batch=batch)
+        ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+        g = torch.full_like(pr.x, float("nan"))
+        pop = L.Population(pr.x, g, 1, P=P, workspace=ws)
+        if r == 8:
+            with pytest.raises(L.LsgdError, match="workspace"):
+                pop.grad_loss(batch)
+            continue
+        pop.grad_loss(batch)
+        torch.cuda.synchronize()
+        assert rel_l2_rows(g.cpu().numpy()[:, :P], pr.ora.g[:, :P]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("W,B", [(1, 700), (2, 40000), (3, 300), (8, 300), (32, 300)])
+def test_step_finishes_the_loss_sums_in_the_update(W, B):
+    """lsgd_step leaves the partial loss sums to the update's launch: losses, leaders and the step as from the calls."""
+    pr, batch, P = problem(500, 300, 5, 20000, W, B, seed=W)
+    sep, _, _ = problem(500, 300, 5, 20000, W, B, seed=W)
+    sep.pop.grad_loss(batch); sep.pop.select_leaders()
+    pr.pop.step(batch, 0.01, 0.1, 0.05)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(pr.pop.get_losses(), pr.ora.losses, rtol=1e-5)
+    np.testing.assert_allclose(pr.pop.get_losses(), sep.pop.get_losses(), rtol=1e-6)
+    assert pr.pop.get_leaders() == sep.pop.get_leaders()
+    pr.ora.select(); pr.ora.update(0.01, 0.1, 0.05)
+    pr.check_state(1e-6)
