@@ -315,7 +315,7 @@ lsgd_status do_loss(lsgd_population* p, const lsgd_batch* batch, float* losses_o
             if (e != hipSuccess) break;
             p->shadow_valid = true;
         }
-        e = launch_mlp_forward(p->xb, p->x, losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, p->stream);
+        e = launch_mlp_forward(p->xb, p->x, nullptr, losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, p->stream);
         break;
     }
     default: break;
@@ -507,7 +507,7 @@ lsgd_status do_fused_mlp_step(lsgd_population* p, const lsgd_batch* batch, float
         if (e != hipSuccess) return fail(LSGD_ERR_HIP, "cast_shadow: %s", hipGetErrorString(e));
         p->shadow_valid = true;
     }
-    e = launch_mlp_forward(p->xb, p->x, p->st.losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, p->stream);
+    e = launch_mlp_forward(p->xb, p->x, nullptr, p->st.losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, p->stream);
     if (e != hipSuccess) return fail(LSGD_ERR_HIP, "mlp forward: %s", hipGetErrorString(e));
     p->losses_valid = true;
     lsgd_status st = LSGD_OK;

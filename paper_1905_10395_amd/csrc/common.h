@@ -139,7 +139,8 @@ hipError_t launch_mlp_grad_loss(const uint16_t* xb, const float* x, float* g, fl
                                 hipStream_t s);
 // the two halves of launch_mlp_grad_loss: forward pass + losses (+ output delta), then the backward pass,
 // which writes g, or applies the update when fu->enabled
-hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* losses, int W, int64_t P, int64_t ld,
+// (g != NULL: its padding columns are zeroed on the way, the gradient pass leaves them alone)
+hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
                               const lsgd_mlp_batch& b, const DeviceState& st, hipStream_t s);
 hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int W, int64_t P, int64_t ld,
                                const lsgd_mlp_batch& b, const DeviceState& st, const FusedUpdate* fu, hipStream_t s);

@@ -147,6 +147,58 @@ __device__ __forceinline__ s16x4 lds_read_tr(const uint16_t* p)
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
 }
 
+__device__ __forceinline__ void unpack8(const u32x4 v, float* f)
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        f[2 * q] = __uint_as_float(v[q] << 16);
+        f[2 * q + 1] = __uint_as_float(v[q] & 0xFFFF0000u);
+    }
+}
+
+// Sums over k of the rows of a [ROWS][K] operand as its tiles pass through LDS (rows of LD elements, BK of them live):
+// THREADS / ROWS adjacent threads per row, eight partial sums each, so that the chains stay short.
+template <int ROWS, int THREADS, int BK, int LD>
+struct BiasSum {
+    static constexpr int TPR = THREADS / ROWS, CHUNKS = BK / 8 / TPR;
+    static_assert(TPR >= 1 && CHUNKS >= 1 && TPR * ROWS == THREADS && CHUNKS * TPR * 8 == BK, "tile shape");
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    static __device__ __forceinline__ int row(int tid) { return tid / TPR; }
+    static __device__ __forceinline__ bool first(int tid) { return tid % TPR == 0; }
+    __device__ __forceinline__ void add(const uint16_t* tile, int tid)
+    {
+        const uint16_t* p = tile + row(tid) * LD + (tid % TPR) * 8;
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c) {
+            float a[8];
+            unpack8(*reinterpret_cast<const u32x4*>(p + c * TPR * 8), a);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s[q] += a[q];
+        }
+    }
+    // valid in the first thread of a row
+    __device__ __forceinline__ float row_sum() const
+    {
+        float v = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+#pragma unroll
+        for (int d = 1; d < TPR; d <<= 1) v += __shfl_xor(v, d, 64);
+        return v;
+    }
+};
+
+// Bias gradient m of a layer: the M x N weights start at C, or at column colC of the parameter row, the biases follow.
+template <int EPI>
+__device__ __forceinline__ void store_bias_grad(const GemmArgs& g, int w, int m, float db)
+{
+    if (EPI == EPI_DWU) {
+        const int off[1] = {0};
+        const float gv[1] = {db};
+        fused_apply<1>(fused_row(g.fu, w, g.sC), g.colC + (int64_t)g.M * g.N + m, off, gv);
+    } else {
+        g.C[(int64_t)w * g.sC + (int64_t)g.M * g.N + m] = db;
+    }
+}
+
 // Matrix products of any shape and alignment (mlp_gemm_ragged.hip).
 void launch_gemm_ragged(const GemmArgs& g, int W, int epi, hipStream_t s);
 

@@ -37,6 +37,8 @@ constexpr int kXcds = 8;
 
 
 __device__ __forceinline__ u32x4 load16(const uint16_t* p) { return *reinterpret_cast<const u32x4_any*>(p); }
+// weights: read by one tile row, or by a few workgroups of one die at a time, and not again in this launch
+__device__ __forceinline__ u32x4 load16_once(const uint16_t* p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(p)); }
 
 // v moved down by s elements of 16 bits, zeros from above (s = 0 .. 8)
 __device__ __forceinline__ u32x4 shift_in(u32x4 v, int s)
@@ -203,40 +205,40 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
     const int bshift = bcol - bcol_in < 8 ? bcol - bcol_in : 8;
     const bool edge_n = n0 + BN > N;                                     // uniform
 
-    auto load_global = [&](int kt, u32x4* ra, u32x4* rb) {
-        const int k = kt * BK + kc;
-        if (short_k) {
-            const int n = K - k < 0 ? 0 : K - k;
+    auto load_global = [&](int kt, u32x4* ra, u32x4* rb) {               // rows of at least 8 elements
+        const int k = kt * BK + kc, kin = k < K - 8 ? k : K - 8;
 #pragma unroll
-            for (int c = 0; c < A_CHUNKS; ++c) ra[c] = load_short(arow[c] + k, n);
-            if (!TRANS_B) {
+        for (int c = 0; c < A_CHUNKS; ++c) ra[c] = load16(arow[c] + kin);
 #pragma unroll
-                for (int c = 0; c < B_CHUNKS; ++c) rb[c] = load_short(brow[c] + k, n);
-            }
-        } else {
-            const int kin = k < K - 8 ? k : K - 8;
-#pragma unroll
-            for (int c = 0; c < A_CHUNKS; ++c) ra[c] = load16(arow[c] + kin);
-            if (!TRANS_B) {
-#pragma unroll
-                for (int c = 0; c < B_CHUNKS; ++c) rb[c] = load16(brow[c] + kin);
-            }
-        }
-        if (TRANS_B) {
-#pragma unroll
-            for (int c = 0; c < B_CHUNKS; ++c) {
+        for (int c = 0; c < B_CHUNKS; ++c) {
+            if (TRANS_B) {
                 const int kr = kt * BK + kr0 + c * B_STEP;
-                const uint16_t* p = B + (int64_t)(kr < K ? kr : K - 1) * g.ldb;
-                if (short_n) rb[c] = load_short(p + bcol, N - bcol < 0 ? 0 : N - bcol);
-                else rb[c] = load16(p + bcol_in);
+                const uint16_t* p = B + (int64_t)(kr < K ? kr : K - 1) * g.ldb + bcol_in;
+                rb[c] = EPI == EPI_DX ? load16_once(p) : load16(p);
+            } else {
+                rb[c] = load16_once(brow[c] + kin);
             }
         }
     };
-    auto store_lds = [&](int buf, int kt, u32x4* ra, u32x4* rb) {
+    auto load_global_short = [&](int kt, u32x4* ra, u32x4* rb) {         // any length
+        const int k = kt * BK + kc, n = K - k < 0 ? 0 : K - k;
+#pragma unroll
+        for (int c = 0; c < A_CHUNKS; ++c) ra[c] = load_short(arow[c] + k, n);
+#pragma unroll
+        for (int c = 0; c < B_CHUNKS; ++c) {
+            if (TRANS_B) {
+                const int kr = kt * BK + kr0 + c * B_STEP;
+                rb[c] = load_short(B + (int64_t)(kr < K ? kr : K - 1) * g.ldb + bcol, kr < K && N > bcol ? N - bcol : 0);
+            } else {
+                rb[c] = load_short(brow[c] + k, n);
+            }
+        }
+    };
+    auto store_lds = [&](int buf, int kt, u32x4* ra, u32x4* rb, bool shift) {
         uint16_t* as = As + buf * S::A_TILE;
         uint16_t* bs = Bs + buf * S::B_TILE;
-        const bool tail = (kt + 1) * BK > K;                             // uniform: the last K step, if it is not full
-        if (tail && !short_k) {
+        const bool tail = shift && (kt + 1) * BK > K;                    // uniform: the last K step, if it is not full
+        if (tail) {
             const int k = kt * BK + kc, kin = k < K - 8 ? k : K - 8;
             const int s = k - kin < 8 ? k - kin : 8;
 #pragma unroll
@@ -246,12 +248,9 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
                 for (int c = 0; c < B_CHUNKS; ++c) rb[c] = shift_in(rb[c], s);
             }
         }
-        if (TRANS_B && (tail || (edge_n && !short_n))) {
+        if (TRANS_B && (tail || (shift && edge_n))) {
 #pragma unroll
-            for (int c = 0; c < B_CHUNKS; ++c) {
-                const int s = (kt * BK + kr0 + c * B_STEP < K) ? (short_n ? 0 : bshift) : 8;
-                rb[c] = shift_in(rb[c], s);
-            }
+            for (int c = 0; c < B_CHUNKS; ++c) rb[c] = shift_in(rb[c], kt * BK + kr0 + c * B_STEP < K ? bshift : 8);
         }
 #pragma unroll
         for (int c = 0; c < A_CHUNKS; ++c) *reinterpret_cast<u32x4*>(as + (ra0 + c * A_STEP) * LDA + kc) = ra[c];
@@ -263,9 +262,14 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
             for (int c = 0; c < B_CHUNKS; ++c) *reinterpret_cast<u32x4*>(bs + (ra0 + c * A_STEP) * LDA + kc) = rb[c];
         }
     };
+    // the first tile column of a d-weight product also sums its rows of delta^T: the bias gradients
+    constexpr bool BIAS = EPI == EPI_DW || EPI == EPI_DWU;
+    const bool bias_rows = BIAS && tn == 0;                              // uniform
+    BiasSum<BM, BIAS ? THREADS : BM, BK, LDA> bsum;
     auto compute = [&](int buf) {
         const uint16_t* as = As + buf * S::A_TILE;
         const uint16_t* bs = Bs + buf * S::B_TILE;
+        if (BIAS && bias_rows) bsum.add(as, tid);
 #pragma unroll
         for (int q = 0; q < KK; ++q) {
             const int kk = wk * KK + q;
@@ -299,41 +303,59 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
 
     // K loop: LDS holds steps kt (being multiplied) and kt + 1, registers the next two
     const int nk = (K + BK - 1) / BK;
-    {
-        u32x4 ra[A_CHUNKS], rb[B_CHUNKS], qa[A_CHUNKS], qb[B_CHUNKS];
-        load_global(0, ra, rb);
-        if (nk > 1) load_global(1, qa, qb);
-        store_lds(0, 0, ra, rb);
-        if (nk > 2) load_global(2, ra, rb);
-        __syncthreads();
-        int kt = 0;
-        // no conditional load in here: behind a branch around loads the compiler waits for all loads in flight
-        for (; kt + 4 < nk; kt += 2) {
-            store_lds(1, kt + 1, qa, qb);
-            load_global(kt + 3, qa, qb);
-            compute(0);
-            if (S::PROMOTE == 1) promote();
+    if (short_k || short_n) {                                            // rows of fewer than 8 elements: nothing in flight
+        for (int kt = 0; kt < nk; ++kt) {
+            u32x4 ra[A_CHUNKS], rb[B_CHUNKS];
+            load_global_short(kt, ra, rb);
+            store_lds(0, kt, ra, rb, false);
             __syncthreads();
-            store_lds(0, kt + 2, ra, rb);
-            load_global(kt + 4, ra, rb);
-            compute(1);
+            compute(0);
             promote();
             __syncthreads();
         }
+    } else {
+        u32x4 ra[A_CHUNKS], rb[B_CHUNKS], qa[A_CHUNKS], qb[B_CHUNKS];
+        int kt = 0;
+        load_global(0, ra, rb);
+        if (nk > 4) {
+            load_global(1, qa, qb);
+            __builtin_amdgcn_sched_barrier(0);           // the two stages' loads in the order in which the loop waits for them
+            store_lds(0, 0, ra, rb, true);
+            load_global(2, ra, rb);
+            __syncthreads();
+            // no conditional load in here: behind a branch around loads the compiler waits for all loads in flight
+            for (; kt + 4 < nk; kt += 2) {
+                store_lds(1, kt + 1, qa, qb, true);
+                load_global(kt + 3, qa, qb);
+                compute(0);
+                if (S::PROMOTE == 1) promote();
+                __syncthreads();
+                store_lds(0, kt + 2, ra, rb, true);
+                load_global(kt + 4, ra, rb);
+                compute(1);
+                promote();
+                __syncthreads();
+            }
+        } else {
+            if (nk > 1) load_global(1, qa, qb);
+            store_lds(0, 0, ra, rb, true);
+            if (nk > 2) load_global(2, ra, rb);
+            __syncthreads();
+        }
         const int left = nk - kt;                                        // 1 .. 4 steps, the first already in buffer 0
-        if (left > 1) store_lds(1, kt + 1, qa, qb);
+        if (left > 1) store_lds(1, kt + 1, qa, qb, true);
         if (left > 3) load_global(kt + 3, qa, qb);
         compute(0);
         if (S::PROMOTE == 1) promote();
         __syncthreads();
         if (left > 1) {
-            if (left > 2) store_lds(0, kt + 2, ra, rb);
+            if (left > 2) store_lds(0, kt + 2, ra, rb, true);
             compute(1);
             promote();
             __syncthreads();
         }
         if (left > 2) {
-            if (left > 3) store_lds(1, kt + 3, qa, qb);
+            if (left > 3) store_lds(1, kt + 3, qa, qb, true);
             compute(0);
             if (S::PROMOTE == 1) promote();
             __syncthreads();
@@ -343,6 +365,12 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
             __syncthreads();
         }
         promote();
+    }
+
+    if (BIAS && bias_rows) {
+        const float db = bsum.row_sum();
+        const int m = m0 + bsum.row(tid);
+        if (bsum.first(tid) && m < M) store_bias_grad<EPI>(g, w, m, db);
     }
 
     // The wavefronts' accumulators meet in LDS (lane: column lane % 32, rows (lane / 32) * 4 + 8 (v / 4) + v % 4 of
@@ -444,7 +472,7 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
             if (m >= M || nv <= 0) continue;
             const f32x4 v = value(p);
             float* dst = C + (int64_t)m * g.ldc + n;
-            if (nv == 4) *reinterpret_cast<f32x4_any*>(dst) = v;
+            if (nv == 4) __builtin_nontemporal_store((f32x4_any)v, reinterpret_cast<f32x4_any*>(dst));
             else store_some(dst, v, nv);
         }
         return;

@@ -102,13 +102,14 @@ __global__ __launch_bounds__(64 * WVM * WVN, (WVM * WVN > 4) ? 1 : 2) void gemm_
 #pragma unroll
             for (int c = 0; c < B_CHUNKS; ++c) {
                 const int id = tid + c * kGemmThreads, row = id / (BN / 8), ch = id % (BN / 8);
-                rb[c] = *reinterpret_cast<const u32x4*>(B + (int64_t)(k0 + row) * g.ldb + n0 + ch * 8);
+                const u32x4* p = reinterpret_cast<const u32x4*>(B + (int64_t)(k0 + row) * g.ldb + n0 + ch * 8);
+                rb[c] = EPI == EPI_DX ? __builtin_nontemporal_load(p) : *p;      // weights: once per tile row
             }
         } else {
 #pragma unroll
             for (int c = 0; c < B_CHUNKS; ++c) {
                 const int id = tid + c * kGemmThreads, row = id >> 3, ch = id & 7;
-                rb[c] = *reinterpret_cast<const u32x4*>(B + (int64_t)(n0 + row) * g.ldb + k0 + ch * 8);
+                rb[c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(B + (int64_t)(n0 + row) * g.ldb + k0 + ch * 8));
             }
         }
     };
@@ -135,9 +136,14 @@ __global__ __launch_bounds__(64 * WVM * WVN, (WVM * WVN > 4) ? 1 : 2) void gemm_
         }
     };
 
+    // The first tile column of a d-weight product also sums its rows of delta^T: the bias gradients.
+    constexpr bool BIAS = EPI == EPI_DW || EPI == EPI_DWU;
+    const bool bias_rows = BIAS && tn == 0;               // uniform
+    BiasSum<BM, kGemmThreads, kBK, kLdk> bsum;
     auto compute = [&](int buf) {
         const uint16_t* as = As + buf * BM * kLdk;
         const uint16_t* bs = Bs + buf * B_TILE;
+        if (BIAS && bias_rows) bsum.add(as, tid);
 #pragma unroll
         for (int kk = 0; kk < kBK / 16; ++kk) {
             bf16x8 af[TM], bfr[TN];
@@ -226,6 +232,11 @@ __global__ __launch_bounds__(64 * WVM * WVN, (WVM * WVN > 4) ? 1 : 2) void gemm_
             compute(buf);
             __syncthreads();
         }
+    }
+
+    if (BIAS && bias_rows) {
+        const float db = bsum.row_sum();
+        if (bsum.first(tid)) store_bias_grad<EPI>(g, w, m0 + bsum.row(tid), db);
     }
 
     // epilogue: lane holds column n = lane%32 and rows (lane/32)*4 + 8*(v/4) + v%4 of each 32x32 tile
@@ -362,7 +373,7 @@ __global__ __launch_bounds__(64 * WVM * WVN, (WVM * WVN > 4) ? 1 : 2) void gemm_
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int m = mb + 8 * (v >> 2) + (v & 3);
-                C[(int64_t)m * g.ldc + n] = acc[i][j][v];
+                __builtin_nontemporal_store(acc[i][j][v], C + (int64_t)m * g.ldc + n);
             }
         }
 }
@@ -409,9 +420,13 @@ static bool try_mfma(const GemmArgs& g, int W, hipStream_t s)
     // the fused update keeps two batches of x, m and leader values in registers: no room beside a 256x256 tile
     // a 256-row tile covers a whole batch of 256: the weight operand is then read once instead of twice
     const int64_t blocks_tall = (g.M % 256 == 0 && g.N % 128 == 0) ? (int64_t)(g.M / 256) * (g.N / 128) * W : 0;
-    if (blocks256 >= 256 && EPI != EPI_DWU) launch_gemm<256, 256, 2, 4, TRANS_B, EPI>(g, W, s);
-    else if ((EPI == EPI_FWD || EPI == EPI_DX) && blocks_tall >= 256) launch_gemm<256, 128, 4, 2, TRANS_B, EPI>(g, W, s);
-    else if (g.N % 128 == 0 && blocks128 >= 256) launch_gemm<128, 128, 2, 2, TRANS_B, EPI>(g, W, s);
+    if constexpr (EPI != EPI_DWU) {
+        if (blocks256 >= 256) { launch_gemm<256, 256, 2, 4, TRANS_B, EPI>(g, W, s); return true; }
+    }
+    if constexpr (EPI == EPI_FWD || EPI == EPI_DX) {
+        if (blocks_tall >= 256) { launch_gemm<256, 128, 4, 2, TRANS_B, EPI>(g, W, s); return true; }
+    }
+    if (g.N % 128 == 0 && blocks128 >= 256) launch_gemm<128, 128, 2, 2, TRANS_B, EPI>(g, W, s);
     else launch_gemm<128, 64, 2, 2, TRANS_B, EPI>(g, W, s);
     return true;
 }
@@ -420,9 +435,12 @@ static bool try_mfma(const GemmArgs& g, int W, hipStream_t s)
 // stored as [B][C] and [C][B].  One workgroup per worker.
 __global__ __launch_bounds__(256) void loss_delta_kernel(const float* __restrict__ logits, int64_t sLogits, const int32_t* __restrict__ y,
                                                          int B, int C, uint16_t* __restrict__ delta, uint16_t* __restrict__ deltaT,
-                                                         int64_t sDelta, float* __restrict__ losses)
+                                                         int64_t sDelta, float* __restrict__ losses, float* __restrict__ g,
+                                                         int64_t P, int64_t ld)
 {
     const int w = blockIdx.x;
+    if (g)                                                 // a gradient pass follows: the padding columns of g are zero
+        for (int64_t c = P + threadIdx.x; c < ld; c += 256) g[(int64_t)w * ld + c] = 0.f;
     const float* lg = logits + (int64_t)w * sLogits;
     uint16_t* d = delta + (int64_t)w * sDelta;
     uint16_t* dT = deltaT + (int64_t)w * sDelta;
@@ -454,59 +472,6 @@ __global__ __launch_bounds__(256) void loss_delta_kernel(const float* __restrict
     if (threadIdx.x == 0) losses[w] = (float)(red[0] / (double)B);
 }
 
-__device__ __forceinline__ void unpack8(const u32x4 v, float* f)
-{
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        f[2 * q] = __uint_as_float(v[q] << 16);
-        f[2 * q + 1] = __uint_as_float(v[q] & 0xFFFF0000u);
-    }
-}
-
-// Bias gradients of all layers in one launch: db_k[o] = sum_b deltaT_k[o][b] with 16-byte loads (at any 2-byte
-// boundary), half a wavefront per output, eight outputs per workgroup; the last B % 8 samples one by one.
-struct BiasLayers {
-    int n;                    // layers
-    int first_block[65];      // workgroups of layer i: first_block[i] .. first_block[i+1]
-    int dout[64];
-    int64_t dT[64];           // delta^T of the layer, element offset in a worker's scratch
-    int64_t col[64];          // column of the layer's bias in the parameter row
-};
-
-__global__ __launch_bounds__(256) void db_all_kernel(const uint16_t* __restrict__ scratch, int64_t sD, int B, BiasLayers t,
-                                                     float* __restrict__ g, int64_t sG, FusedUpdate fu)
-{
-    int layer = 0;
-    while (layer + 1 < t.n && (int)blockIdx.x >= t.first_block[layer + 1]) ++layer;   // uniform
-    const int lane = threadIdx.x & 63, l = lane & 31;
-    const int o = (((int)blockIdx.x - t.first_block[layer]) * 4 + (threadIdx.x >> 6)) * 2 + (lane >> 5);
-    const int w = blockIdx.y;
-    const int dout = t.dout[layer];
-    float acc = 0.f;
-    if (o < dout) {
-        const uint16_t* dt = scratch + (int64_t)w * sD + t.dT[layer] + (int64_t)o * B;
-        for (int c = l; c < B / 8; c += 32) {
-            float a[8];
-            unpack8(*reinterpret_cast<const u32x4_any*>(dt + c * 8), a);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) acc += a[q];
-        }
-        if (l < (B & 7)) acc += bf16_to_f32(dt[(B & ~7) + l]);
-    }
-#pragma unroll
-    for (int d = 1; d < 32; d <<= 1) acc += __shfl_xor(acc, d, 64);
-    if (l == 0 && o < dout) {
-        const int64_t col = t.col[layer] + o;
-        if (fu.enabled) {
-            const int off[1] = {0};
-            const float gv[1] = {acc};
-            fused_apply<1>(fused_row(fu, w, sG), col, off, gv);
-        } else {
-            g[(int64_t)w * sG + col] = acc;
-        }
-    }
-}
-
 // h_0 = bf16(X) for fp32 inputs: n values per worker, rounded to nearest even
 __global__ __launch_bounds__(256) void cast_input_kernel(const float* __restrict__ X, int64_t n, uint16_t* __restrict__ out, int64_t sOut)
 {
@@ -514,12 +479,6 @@ __global__ __launch_bounds__(256) void cast_input_kernel(const float* __restrict
     const float* src = X + (int64_t)w * n;
     uint16_t* dst = out + (int64_t)w * sOut;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) dst[i] = f32_to_bf16_rne(src[i]);
-}
-
-__global__ __launch_bounds__(256) void zero_pad_kernel(float* __restrict__ g, int64_t P, int64_t ld)
-{
-    const int64_t c = P + (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (c < ld) g[(int64_t)blockIdx.y * ld + c] = 0.f;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -573,12 +532,12 @@ size_t mlp_scratch_bytes(int W, const lsgd_mlp_batch& b) { return make_plan(b, W
 hipError_t launch_mlp_grad_loss(const uint16_t* xb, const float* x, float* g, float* losses, int W, int64_t P,
                                 int64_t ld, const lsgd_mlp_batch& b, const DeviceState& st, hipStream_t s)
 {
-    hipError_t e = launch_mlp_forward(xb, x, losses, W, P, ld, b, st, s);
+    hipError_t e = launch_mlp_forward(xb, x, g, losses, W, P, ld, b, st, s);
     if (e != hipSuccess) return e;
     return launch_mlp_backward(xb, x, g, W, P, ld, b, st, nullptr, s);
 }
 
-hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* losses, int W, int64_t P, int64_t ld,
+hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
                               const lsgd_mlp_batch& b, const DeviceState& st, hipStream_t s)
 {
     const MlpPlan p = make_plan(b, W);
@@ -622,7 +581,7 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* losses,
     }
     // ---- loss and output delta ----
     hipLaunchKernelGGL(loss_delta_kernel, dim3((unsigned)W), dim3(256), 0, s, logits, sW32, b.y, B, b.dims[L],
-                       sc16 + p.d[L], sc16 + p.dT[L], sW16, losses);
+                       sc16 + p.d[L], sc16 + p.dT[L], sW16, losses, g, P, ld);
     return hipGetLastError();
 }
 
@@ -672,23 +631,6 @@ hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int
                 launch_gemm_ragged(a, W, fused ? EPI_DWU : EPI_DW, s);
         }
     }
-    // db_k of every layer (delta^T_k is complete once layer k+1 has been processed; the biases' columns
-    // are nobody else's) in one launch
-    BiasLayers t{};
-    t.n = L;
-    int blocks = 0;
-    for (int k = 1; k <= L; ++k) {
-        t.first_block[k - 1] = blocks;
-        t.dout[k - 1] = b.dims[k];
-        t.dT[k - 1] = p.dT[k];
-        t.col[k - 1] = woff[k] + (int64_t)b.dims[k] * b.dims[k - 1];
-        blocks += (b.dims[k] + 7) / 8;
-    }
-    t.first_block[L] = blocks;
-    hipLaunchKernelGGL(db_all_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, sc16, sW16, B, t, g, ld, fu);
-    if (fused) return hipGetLastError();          // g is not written, so there is no padding to clear
-    if (ld > P)
-        hipLaunchKernelGGL(zero_pad_kernel, dim3((unsigned)((ld - P + 255) / 256), (unsigned)W), dim3(256), 0, s, g, P, ld);
     return hipGetLastError();
 }
 
