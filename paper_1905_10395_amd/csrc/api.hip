@@ -279,7 +279,7 @@ lsgd_status do_grad_loss(lsgd_population* p, const lsgd_batch* batch, float* los
             if (e != hipSuccess) break;
             p->shadow_valid = true;
         }
-        e = launch_mlp_grad_loss(p->xb, p->x, p->g, losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, p->stream);
+        e = launch_mlp_grad_loss(p->xb, p->x, p->g, losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, parts, p->stream);
         break;
     }
     default: break;
@@ -315,7 +315,7 @@ lsgd_status do_loss(lsgd_population* p, const lsgd_batch* batch, float* losses_o
             if (e != hipSuccess) break;
             p->shadow_valid = true;
         }
-        e = launch_mlp_forward(p->xb, p->x, nullptr, losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, p->stream);
+        e = launch_mlp_forward(p->xb, p->x, nullptr, losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, false, nullptr, p->stream);
         break;
     }
     default: break;
@@ -507,24 +507,27 @@ lsgd_status do_fused_mlp_step(lsgd_population* p, const lsgd_batch* batch, float
         if (e != hipSuccess) return fail(LSGD_ERR_HIP, "cast_shadow: %s", hipGetErrorString(e));
         p->shadow_valid = true;
     }
-    e = launch_mlp_forward(p->xb, p->x, nullptr, p->st.losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, p->stream);
+    // with something re-selected, one launch finishes the losses, selects, and captures the leaders (nobody moves)
+    bool reselect = any_pending(p) || refresh_global != 0;
+    for (int j = 0; j < p->cfg.n_groups; ++j) reselect = reselect || !refresh_local || refresh_local[j];
+    const bool one_launch = reselect && p->cfg.W <= kColumnMaxWorkers && (lamL != 0.0f || lamG != 0.0f);
+    ColumnStep c{};
+    e = launch_mlp_forward(p->xb, p->x, nullptr, p->st.losses, p->cfg.W, p->cfg.P, p->cfg.ld, *d, p->st, true,
+                           one_launch ? &c.parts : nullptr, p->stream);
     if (e != hipSuccess) return fail(LSGD_ERR_HIP, "mlp forward: %s", hipGetErrorString(e));
     p->losses_valid = true;
     lsgd_status st = LSGD_OK;
-    if (p->cfg.W <= kColumnMaxWorkers && (lamL != 0.0f || lamG != 0.0f)) {
-        // selection and capture (nobody moves) in one launch
+    if (one_launch) {
         RefreshBits sel, cap;
         note_selection(p, refresh_local, refresh_global, &sel, &cap);
-        if (any_pending(p)) {
-            ColumnStep c{};
-            c.pull = pull_params(p, 0.0f, 0.0f, 0.0f, false, true);
-            c.comm = 1;
-            c.select = 1; c.sel = sel.w[0]; c.cap = cap.w[0]; c.selG = refresh_global != 0; c.capG = p->pending_global;
-            c.losses = p->st.losses;
-            e = launch_column_step(c, p->st, p->stream);
-            if (e != hipSuccess) return fail(LSGD_ERR_HIP, "capture: %s", hipGetErrorString(e));
-            note_pull(p, 0.0f, 0.0f, true);
-        }
+        c.pull = pull_params(p, 0.0f, 0.0f, 0.0f, false, true);
+        c.comm = 1;
+        c.select = 1; c.sel = sel.w[0]; c.cap = cap.w[0]; c.selG = refresh_global != 0; c.capG = p->pending_global;
+        c.losses = p->st.losses;
+        c.losses_out = c.parts.n > 0 ? p->st.losses : nullptr;
+        e = launch_column_step(c, p->st, p->stream);
+        if (e != hipSuccess) return fail(LSGD_ERR_HIP, "capture: %s", hipGetErrorString(e));
+        note_pull(p, 0.0f, 0.0f, true);
     } else {
         st = do_select(p, nullptr, refresh_local, refresh_global);
         if (st != LSGD_OK) return st;

@@ -149,7 +149,7 @@ __device__ __forceinline__ void comm_columns(const ColumnDev& s, const Leaders& 
     }
 }
 
-// The same with both coefficients zero: nobody moves, the re-selected leaders are copied to Z, four rows of loads in
+// The same with both coefficients zero: nobody moves, the re-selected leaders are copied to Z, eight rows of loads in
 // flight.
 template <int VEC>
 __device__ __forceinline__ void capture_columns(const ColumnDev& s, const Leaders& L, int64_t col)
@@ -159,18 +159,18 @@ __device__ __forceinline__ void capture_columns(const ColumnDev& s, const Leader
     if (!a.Z) return;
     int j = L.freshG ? -1 : 0;                           // -1: the global leader
     while (j < a.G) {
-        V v[4];
-        int to[4], n = 0;
-        for (; j < a.G && n < 4; ++j) {
+        V v[8];
+        int to[8], n = 0;
+        for (; j < a.G && n < 8; ++j) {
             if (j >= 0 && !L.fresh[j]) continue;
             to[n] = j < 0 ? a.G : j;
             ++n;
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 8; ++u)
             if (u < n) v[u] = ld_vec<VEC>(a.x + (int64_t)(to[u] == a.G ? L.gl : L.lead[to[u]]) * a.ld + col);
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 8; ++u)
             if (u < n) st_stream(a.Z + (int64_t)to[u] * a.ld + col, v[u]);
     }
 }
@@ -213,23 +213,16 @@ __device__ __forceinline__ void step_columns(const ColumnDev& s, const Leaders& 
 {
     if (s.center) easgd_columns<VEC>(s, col);
     if (s.update) update_columns<VEC, KIND>(s, before, col, first);
-    if (s.comm) {
-        if (s.commL == 0.0f && s.commG == 0.0f) capture_columns<VEC>(s, after, col);
-        else comm_columns<VEC>(s, after, col);
-    }
+    if (s.comm) comm_columns<VEC>(s, after, col);
 }
 
-template <int VEC, int KIND>
-__global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
+// Leaders as recorded by earlier calls (now) and, when the call selects, as they stand after the selection (chosen);
+// the first workgroup records the latter, and the losses.  All threads; ends behind a barrier.
+__device__ __forceinline__ void choose_leaders(const ColumnDev& s, Leaders& now, Leaders& chosen)
 {
-    __shared__ Leaders now, chosen;
     __shared__ float loss_s[kColumnMaxWorkers];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int W = s.a.W, G = s.a.G;
-    const int64_t col = s.a.col0 + ((int64_t)blockIdx.x * kThreads + tid) * VEC;
-    const bool whole = col + VEC <= s.a.col1;
-    RowBatch<VEC> first;
-    if (s.update && whole) load_rows<VEC, KIND>(s.a, 0, s.a.offsets[1], col, first);   // under way during the selection
     if (s.parts.n > 0) {
         // every workgroup adds up the partial sums itself: a team of 8 to 256 lanes per worker, in double, in a fixed order
         int team = kThreads;
@@ -237,7 +230,10 @@ __global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
         const int w = tid / team, l = tid % team;
         double acc = 0.0;
         if (w < W)
-            for (int i = l; i < s.parts.n; i += team) acc += (double)s.parts.sums[(int64_t)w * s.parts.n + i];
+            for (int i = l; i < s.parts.n; i += team) {
+                const int64_t at = (int64_t)w * s.parts.stride + i;
+                acc += s.parts.sums64 ? s.parts.sums64[at] : (double)s.parts.sums[at];
+            }
         if (team > kWave) {                              // one or two workers
             __shared__ double cross[kThreads / kWave];
 #pragma unroll
@@ -249,7 +245,7 @@ __global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
         } else {
             for (int d = 1; d < team; d <<= 1) acc += __shfl_xor(acc, d, kWave);
         }
-        if (w < W && l == 0) loss_s[w] = (float)((double)s.parts.c * acc);
+        if (w < W && l == 0) loss_s[w] = (float)(s.parts.c * acc);
         __syncthreads();
     }
     if (tid < kWave) {
@@ -308,6 +304,33 @@ __global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
             s.plan[tid] = r;
         }
     }
+}
+
+// Capture alone (nobody moves): few registers, so that enough workgroups are resident, and each walks several tiles so
+// that the selection is not repeated for every one of them.
+template <int VEC>
+__global__ __launch_bounds__(kThreads) void capture_kernel(ColumnDev s)
+{
+    __shared__ Leaders now, chosen;
+    choose_leaders(s, now, chosen);
+    const Leaders& L = s.select ? chosen : now;
+    for (int64_t col = s.a.col0 + ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VEC; col < s.a.col1;
+         col += (int64_t)gridDim.x * kThreads * VEC) {
+        if (col + VEC <= s.a.col1) capture_columns<VEC>(s, L, col);
+        else
+            for (int64_t cc = col; cc < s.a.col1; ++cc) capture_columns<1>(s, L, cc);
+    }
+}
+
+template <int VEC, int KIND>
+__global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
+{
+    __shared__ Leaders now, chosen;
+    const int64_t col = s.a.col0 + ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VEC;
+    const bool whole = col + VEC <= s.a.col1;
+    RowBatch<VEC> first;
+    if (s.update && whole) load_rows<VEC, KIND>(s.a, 0, s.a.offsets[1], col, first);   // under way during the selection
+    choose_leaders(s, now, chosen);
     const Leaders& before = s.select == 1 ? chosen : now;
     const Leaders& after = s.select ? chosen : now;
     if (whole) step_columns<VEC, KIND>(s, before, after, col, first);
@@ -358,6 +381,14 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     if (q.update && !mom && p.P >= 500000) vec = p.P >= 1000000 ? 4 : 2;
     if (!q.update) vec = 4;
     while (vec > 1 && !layout_ok((unsigned)vec)) vec >>= 1;
+    if (!q.update && q.comm && q.commL == 0.0f && q.commG == 0.0f) {
+        const int64_t tiles = (p.P + (int64_t)kThreads * vec - 1) / ((int64_t)kThreads * vec);
+        const dim3 grid((unsigned)(tiles < 2048 ? tiles : 2048));
+        if (vec == 4) hipLaunchKernelGGL((capture_kernel<4>), grid, dim3(kThreads), 0, stream, s);
+        else if (vec == 2) hipLaunchKernelGGL((capture_kernel<2>), grid, dim3(kThreads), 0, stream, s);
+        else hipLaunchKernelGGL((capture_kernel<1>), grid, dim3(kThreads), 0, stream, s);
+        return hipGetLastError();
+    }
     if (vec == 4) launch_vec<4>(s, mom, stream);
     else if (vec == 2) launch_vec<2>(s, mom, stream);
     else launch_vec<1>(s, mom, stream);

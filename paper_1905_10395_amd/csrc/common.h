@@ -44,6 +44,16 @@ struct RefreshBits {
 // Records the message lsgd_last_error() returns on this thread and hands the status back.
 lsgd_status set_error(lsgd_status st, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 
+// Losses left as partial sums: losses[w] = c * sum of sums[w * stride + 0 .. n) (n = 0: they are finished).
+constexpr int kLossPartsMax = 1024;     // workers x partial sums up to which the next launch adds them up itself
+struct LossParts {
+    const float* sums;      // or, when sums64 is not NULL:
+    const double* sums64;
+    int64_t stride;
+    int n;
+    double c;
+};
+
 // ---- kernels' host launchers (each returns the hipError_t of its launches) ----
 hipError_t launch_init_state(const DeviceState& st, int W, int G, hipStream_t s);
 // clears the "re-selected since the last update" flags
@@ -72,13 +82,6 @@ struct PullParams {
 };
 hipError_t launch_pull_update(const PullParams& p, const DeviceState& st, hipStream_t s);
 
-// Losses left as partial sums: losses[w] = c * sum of sums[w][0 .. n) (n = 0: they are finished).
-constexpr int kLossPartsMax = 1024;     // workers x partial sums up to which the next launch adds them up itself
-struct LossParts {
-    const float* sums;
-    int n;
-    float c;
-};
 // Selection and update of a small or medium population in one launch (column_step.hip).
 constexpr int kColumnMaxWorkers = 64;   // one wavefront selects
 struct ColumnStep {
@@ -136,12 +139,13 @@ size_t mlp_scratch_bytes(int W, const lsgd_mlp_batch& b);
 // returns LSGD_OK / LSGD_ERR_UNSUPPORTED through *status for shapes the kernels do not cover
 hipError_t launch_mlp_grad_loss(const uint16_t* xb, const float* x, float* g, float* losses, int W,
                                 int64_t P, int64_t ld, const lsgd_mlp_batch& b, const DeviceState& st,
-                                hipStream_t s);
+                                LossParts* parts, hipStream_t s);
 // the two halves of launch_mlp_grad_loss: forward pass + losses (+ output delta), then the backward pass,
 // which writes g, or applies the update when fu->enabled
 // (g != NULL: its padding columns are zeroed on the way, the gradient pass leaves them alone)
+// (parts as in launch_mc_grad_loss; backward: the output deltas are needed)
 hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
-                              const lsgd_mlp_batch& b, const DeviceState& st, hipStream_t s);
+                              const lsgd_mlp_batch& b, const DeviceState& st, bool backward, LossParts* parts, hipStream_t s);
 hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int W, int64_t P, int64_t ld,
                                const lsgd_mlp_batch& b, const DeviceState& st, const FusedUpdate* fu, hipStream_t s);
 bool mlp_shape_supported(const lsgd_mlp_batch& b, const char** why);

@@ -700,7 +700,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
     // the partial sums are added up by a launch of their own, or left to a caller that says it can
     auto finish_loss = [&](int workers, int n) {
         if (parts && n > 0 && (int64_t)workers * n <= kLossPartsMax) {
-            parts->sums = st.partials; parts->n = n; parts->c = b.c;
+            parts->sums = st.partials; parts->stride = n; parts->n = n; parts->c = (double)b.c;
         } else {
             hipLaunchKernelGGL(mc_loss_finish_kernel, dim3((unsigned)workers), dim3(256), 0, s, st.partials, n, b.c, losses);
         }

@@ -17,7 +17,7 @@ typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
-enum { EPI_FWD = 0, EPI_DX = 1, EPI_DW = 2, EPI_DWU = 3, EPI_LOGITS = 4 };   // DWU: d-weight with the update applied in place of the store
+enum { EPI_FWD = 0, EPI_DX = 1, EPI_DW = 2, EPI_DWU = 3, EPI_LOGITS = 4, EPI_HEAD = 5 };   // DWU: d-weight with the update applied in place of the store
 
 struct GemmArgs {
     const uint16_t* A; int64_t sA; int64_t lda;   // [M][K], per-worker stride sA (elements)
@@ -28,6 +28,10 @@ struct GemmArgs {
     uint16_t* out; int64_t sOut; int64_t ldout;   // EPI_FWD: h [M][N]; EPI_DX: delta [M][N]
     uint16_t* outT; int64_t sOutT; int64_t ldoutT;// EPI_DX: delta^T [N][M]
     float* C; int64_t sC; int64_t ldc;            // EPI_DW, EPI_LOGITS: fp32 [M][N]
+    // EPI_HEAD (out, outT: the output deltas [M][N] and [N][M], or NULL)
+    const int32_t* y;                             // [M] per worker
+    double* loss_parts; int64_t sLoss; float* losses; // loss sums of the row tiles (sLoss doubles between workers), or the losses when one tile holds the batch
+    float* pad; int64_t pad_from, pad_to;         // columns [pad_from, pad_to) of rows of pad_to floats to clear, or NULL
     FusedUpdate fu; int64_t colC;                 // EPI_DWU: update state; column of C[0][0] in the parameter row
 };
 

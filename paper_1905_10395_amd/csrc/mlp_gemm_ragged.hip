@@ -3,6 +3,7 @@
 //
 //   forward   out[m][n] = bf16(relu(<A[m,:], B[n,:]> + bias[n]))      A = h_{k-1}, B = W_k       (both [.][k])
 //   logits    C[m][n]   = <A[m,:], B[n,:]> + bias[n]
+//   head      the same for up to 64 classes, kept in LDS: softmax cross-entropy, its sum per row tile, output deltas
 //   d-input   out[m][n] = bf16(sum_k A[m][k] B[k][n]) * [mask != 0]   A = delta_k, B = W_k       (B as [k][n])
 //   d-weight  C[m][n]   = sum_k A[m][k] B[k][n]                       A = delta_k^T, B = h_{k-1}  (or the update)
 //
@@ -103,7 +104,7 @@ __device__ __forceinline__ void ragged_update(const FusedRow& r, const int64_t (
 template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
 struct RaggedShape {
     static constexpr int THREADS = 64 * WVM * WVN * WVK;
-    static constexpr bool FORWARD = EPI == EPI_FWD || EPI == EPI_LOGITS;
+    static constexpr bool FORWARD = EPI == EPI_FWD || EPI == EPI_LOGITS || EPI == EPI_HEAD;
     static constexpr bool TRANS_B = !FORWARD;                           // B given as [k][n]
     using Sum = typename std::conditional<FORWARD, double, float>::type;
     static constexpr int PROMOTE = BM > 64 ? 2 : 1;                     // K steps between promotions to the double sum
@@ -386,6 +387,60 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
                 T[(wk * BM + r) * LDC + (wn * TN + j) * 32 + (lane & 31)] = S::FORWARD ? sum[S::FORWARD ? i : 0][S::FORWARD ? j : 0][v] : (Sum)acc[i][j][v];
             }
     __syncthreads();
+    if constexpr (EPI == EPI_HEAD) {
+        static_assert(BM == 32 && THREADS >= 256, "eight lanes per sample");
+        __shared__ double row_loss[BM];
+        if (tid < 256) {
+            const int r = tid >> 3, l = tid & 7, m = m0 + r;             // lane l of the sample's eight: classes l, l + 8, ...
+            const int yb = m < M ? g.y[(int64_t)w * M + m] : -1;
+            float z[BN / 8];
+            float mx = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < BN / 8; ++j) {
+                const int c = l + 8 * j;
+                Sum v = T[r * LDC + c];
+#pragma unroll
+                for (int q = 1; q < WVK; ++q) v += T[(q * BM + r) * LDC + c];
+                z[j] = c < N ? (float)(v + (Sum)g.bias[(int64_t)w * g.sBias + c]) : -INFINITY;
+                mx = fmaxf(mx, z[j]);
+            }
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+            float se = 0.f, zy = 0.f;
+#pragma unroll
+            for (int j = 0; j < BN / 8; ++j) {
+                const int c = l + 8 * j;
+                if (c < N) se += expf(z[j] - mx);
+                if (c < N && c == yb) zy = z[j];
+            }
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) { se += __shfl_xor(se, d, 64); zy += __shfl_xor(zy, d, 64); }
+            const float lse = mx + logf(se);
+            if (l == 0) row_loss[r] = m < M ? (double)(lse - zy) : 0.0;
+            if (m < M && g.out) {
+                const float inv = 1.0f / (float)M;
+#pragma unroll
+                for (int j = 0; j < BN / 8; ++j) {
+                    const int c = l + 8 * j;
+                    if (c < N) {
+                        const uint16_t q = f32_to_bf16_rne((expf(z[j] - lse) - (c == yb ? 1.f : 0.f)) * inv);
+                        g.out[(int64_t)w * g.sOut + (int64_t)m * N + c] = q;
+                        g.outT[(int64_t)w * g.sOut + (int64_t)c * M + m] = q;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (tid == 0) {
+            double t = 0.0;
+            for (int r = 0; r < BM; ++r) t += row_loss[r];
+            if (tiles_m == 1) g.losses[w] = (float)(t / (double)M);
+            else g.loss_parts[(int64_t)w * g.sLoss + tm] = t;
+        }
+        if (g.pad && tm == 0)                                            // the padding columns of g are zero
+            for (int64_t c = g.pad_from + tid; c < g.pad_to; c += THREADS) g.pad[(int64_t)w * g.pad_to + c] = 0.f;
+        return;
+    } else {
     constexpr int RPP = THREADS / (BN / 4) < BM ? THREADS / (BN / 4) : BM;   // rows per pass
     constexpr int PASSES = BM / RPP;
     if (THREADS / (BN / 4) > BM && tid >= BM * (BN / 4)) return;         // more threads than the tile has groups of four
@@ -503,6 +558,7 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
         ragged_update<R>(fr, off, gv, on);
     }
     }
+    }
 }
 
 template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
@@ -525,6 +581,14 @@ void launch_tile(const GemmArgs& g, int W, hipStream_t s)
 // without a workgroup.  When there are few tiles and a long contraction (the classifier layer, a narrow first
 // layer), sixteen wavefronts split the contraction of a 32 x 32 tile, 64 KB of operands per K step: logits of
 // 4096 -> 10, 8 workers, batch 256 25 -> 17 us, of 1024 -> 10, 16 workers, batch 128 11 -> 8 us.
+void launch_head(const GemmArgs& g, int W, hipStream_t s)
+{
+    const int64_t tiles = (int64_t)W * ((g.M + 31) / 32);
+    if (g.N <= 32 && g.K >= 512 && tiles <= 512) launch_tile<32, 32, 1, 1, 16, 512, EPI_HEAD>(g, W, s);
+    else if (g.N <= 32) launch_tile<32, 32, 1, 1, 4, 128, EPI_HEAD>(g, W, s);
+    else launch_tile<32, 64, 1, 1, 4, 128, EPI_HEAD>(g, W, s);
+}
+
 template <int EPI>
 void launch_epi(const GemmArgs& g, int W, hipStream_t s)
 {
@@ -562,6 +626,7 @@ void launch_gemm_ragged(const GemmArgs& g, int W, int epi, hipStream_t s)
     switch (epi) {
     case EPI_FWD: launch_epi<EPI_FWD>(g, W, s); break;
     case EPI_LOGITS: launch_epi<EPI_LOGITS>(g, W, s); break;
+    case EPI_HEAD: launch_head(g, W, s); break;
     case EPI_DX: launch_epi<EPI_DX>(g, W, s); break;
     case EPI_DW: launch_epi<EPI_DW>(g, W, s); break;
     case EPI_DWU: launch_epi<EPI_DWU>(g, W, s); break;

@@ -472,6 +472,19 @@ __global__ __launch_bounds__(256) void loss_delta_kernel(const float* __restrict
     if (threadIdx.x == 0) losses[w] = (float)(red[0] / (double)B);
 }
 
+// losses[w] = sum of the head's row-tile sums / B.  One wavefront per worker.
+__global__ __launch_bounds__(256) void loss_finish_kernel(const double* __restrict__ sums, int64_t stride, int n, int W, double B,
+                                                          float* __restrict__ losses)
+{
+    const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (w >= W) return;
+    double acc = 0.0;
+    for (int i = lane; i < n; i += 64) acc += sums[(int64_t)w * stride + i];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
+    if (lane == 0) losses[w] = (float)(acc / B);
+}
+
 // h_0 = bf16(X) for fp32 inputs: n values per worker, rounded to nearest even
 __global__ __launch_bounds__(256) void cast_input_kernel(const float* __restrict__ X, int64_t n, uint16_t* __restrict__ out, int64_t sOut)
 {
@@ -530,15 +543,15 @@ bool mlp_shape_supported(const lsgd_mlp_batch& b, const char** why)
 size_t mlp_scratch_bytes(int W, const lsgd_mlp_batch& b) { return make_plan(b, W).bytes; }
 
 hipError_t launch_mlp_grad_loss(const uint16_t* xb, const float* x, float* g, float* losses, int W, int64_t P,
-                                int64_t ld, const lsgd_mlp_batch& b, const DeviceState& st, hipStream_t s)
+                                int64_t ld, const lsgd_mlp_batch& b, const DeviceState& st, LossParts* parts, hipStream_t s)
 {
-    hipError_t e = launch_mlp_forward(xb, x, g, losses, W, P, ld, b, st, s);
+    hipError_t e = launch_mlp_forward(xb, x, g, losses, W, P, ld, b, st, true, parts, s);
     if (e != hipSuccess) return e;
     return launch_mlp_backward(xb, x, g, W, P, ld, b, st, nullptr, s);
 }
 
 hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
-                              const lsgd_mlp_batch& b, const DeviceState& st, hipStream_t s)
+                              const lsgd_mlp_batch& b, const DeviceState& st, bool backward, LossParts* parts, hipStream_t s)
 {
     const MlpPlan p = make_plan(b, W);
     const int L = p.L, B = b.B;
@@ -574,6 +587,23 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, floa
         if (k < L) {
             a.out = sc16 + p.h[k]; a.sOut = sW16; a.ldout = dout;
             if (!try_mfma<false, EPI_FWD>(a, W, s)) launch_gemm_ragged(a, W, EPI_FWD, s);
+        } else if (dout <= 64) {                               // logits, loss and output delta in one launch
+            const int tiles = (B + 31) / 32;
+            a.y = b.y;
+            a.losses = losses;
+            // the tiles' loss sums lie where the worker's logits would (4 B C bytes hold B / 32 doubles)
+            a.loss_parts = reinterpret_cast<double*>(logits); a.sLoss = p.per_worker / 8;
+            if (backward) { a.out = sc16 + p.d[L]; a.outT = sc16 + p.dT[L]; a.sOut = sW16; }
+            a.pad = ld > P ? g : nullptr; a.pad_from = P; a.pad_to = ld;
+            launch_gemm_ragged(a, W, EPI_HEAD, s);
+            if (tiles > 1) {
+                if (parts && (int64_t)W * tiles <= kLossPartsMax) {
+                    parts->sums64 = a.loss_parts; parts->stride = a.sLoss; parts->n = tiles; parts->c = 1.0 / (double)B;
+                } else {
+                    hipLaunchKernelGGL(loss_finish_kernel, dim3((unsigned)((W + 3) / 4)), dim3(256), 0, s, a.loss_parts, a.sLoss, tiles, W, (double)B, losses);
+                }
+            }
+            return hipGetLastError();
         } else {
             a.C = logits; a.sC = sW32; a.ldc = dout;
             launch_gemm_ragged(a, W, EPI_LOGITS, s);
