@@ -372,6 +372,13 @@ lsgd_status check_pull_state(const lsgd_population* p, float eta, float lamL, fl
     return LSGD_OK;
 }
 
+bool any_pending(const lsgd_population* p)
+{
+    bool any = p->pending_global;
+    for (int j = 0; j < p->cfg.n_groups; ++j) any = any || p->pending_local[(size_t)j];
+    return any;
+}
+
 // Bookkeeping of a selection: which groups are re-selected (sel) and which count as re-selected since the last
 // update afterwards (cap).
 void note_selection(lsgd_population* p, const uint8_t* refresh_local, int refresh_global, RefreshBits* sel, RefreshBits* cap)
@@ -394,17 +401,11 @@ lsgd_status do_select(lsgd_population* p, const float* losses, const uint8_t* re
 {
     RefreshBits sel, cap;
     note_selection(p, refresh_local, refresh_global, &sel, &cap);
+    if (!any_pending(p)) return LSGD_OK;     // nothing re-selected now or since the last update: no flag is read until there is
     hipError_t e = launch_select_leaders(losses ? losses : p->st.losses, p->cfg.W, p->cfg.n_groups, p->st, sel, cap,
                                          refresh_global != 0, p->pending_global, p->stream);
     if (e != hipSuccess) return fail(LSGD_ERR_HIP, "select_leaders: %s", hipGetErrorString(e));
     return LSGD_OK;
-}
-
-bool any_pending(const lsgd_population* p)
-{
-    bool any = p->pending_global;
-    for (int j = 0; j < p->cfg.n_groups; ++j) any = any || p->pending_local[(size_t)j];
-    return any;
 }
 
 // Whether the one-launch update by column owners is the faster one.  Up to about 300 MB read and written per update

@@ -171,7 +171,7 @@ __device__ __forceinline__ void capture_columns(const ColumnDev& s, const Leader
             if (u < n) v[u] = ld_vec<VEC>(a.x + (int64_t)(to[u] == a.G ? L.gl : L.lead[to[u]]) * a.ld + col);
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if (u < n) st_stream(a.Z + (int64_t)to[u] * a.ld + col, v[u]);
+            if (u < n) st_vec(a.Z + (int64_t)to[u] * a.ld + col, v[u]);
     }
 }
 

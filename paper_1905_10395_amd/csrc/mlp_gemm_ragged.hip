@@ -613,6 +613,13 @@ void launch_epi(const GemmArgs& g, int W, hipStream_t s)
                 return;
             }
         }
+        if constexpr (EPI == EPI_FWD) {
+            // large batches are bound by what reaches the compute units through L2: fewer bytes per product
+            if (g.M > 128 && (int64_t)((g.N + 127) / 128) * ((g.M + 127) / 128) * W >= 256) {
+                launch_tile<128, 128, 2, 4, 1, 64, EPI>(g, W, s);
+                return;
+            }
+        }
         if (g.M > 64 && fill128) launch_tile<128, 64, 2, 2, 1, 64, EPI>(g, W, s);
         else if (g.M > 32 && fill64) launch_tile<64, 64, 1, 2, 2, 128, EPI>(g, W, s);
         else launch_tile<32, 64, 1, 1, 4, 128, EPI>(g, W, s);
