@@ -18,9 +18,11 @@
 //
 // Sums.  One chain of v_mfma_f32_32x32x16_bf16 rounds its fp32 accumulator once per 16 products: measured 1.6e-7 of
 // the result at K = 784 and 3.2e-7 at K = 3072 (normal operands), where a plain dot product spread over 64 lanes
-// has 6e-8 and 8e-8.  An activation is rounded to bf16 next, and the larger that error, the more activations land on
-// the wrong side of a rounding boundary.  The forward products therefore carry a sum in double: the accumulators of
-// one or two K steps (2 to 8 matrix instructions) are added to it and start again from zero (4e-8 to 6e-8 at any K).
+// has 6e-8 and 8e-8.  Activations and back-propagated deltas are rounded to bf16 next, and the larger that error, the
+// more of them land on the wrong side of a rounding boundary.  The forward and d-input products therefore carry a sum
+// in double, to which the accumulators are added before they start again from zero: after every matrix instruction
+// with 32-row tiles (1.6e-8 at any K), every two with 64 (2.7e-8), every eight with 128, where the vector units would
+// become the limit (5.7e-8; 105 against 81 us without sums on 500 x 3072 x 1024, 16 workers).
 //
 // Measured (whole passes, against one-thread-per-output vector-ALU kernels that re-read an operand per output):
 // gradients of 3072-1024-512-10, 16 workers, batch 32: 19.7 ms -> 0.15 ms; objective of 3072-1024-10, 16 workers,
@@ -106,8 +108,9 @@ struct RaggedShape {
     static constexpr int THREADS = 64 * WVM * WVN * WVK;
     static constexpr bool FORWARD = EPI == EPI_FWD || EPI == EPI_LOGITS || EPI == EPI_HEAD;
     static constexpr bool TRANS_B = !FORWARD;                           // B given as [k][n]
-    using Sum = typename std::conditional<FORWARD, double, float>::type;
-    static constexpr int PROMOTE = BM > 64 ? 2 : 1;                     // K steps between promotions to the double sum
+    static constexpr bool WIDE = FORWARD || (EPI == EPI_DX && (BK == 128 || BM == 128));   // (one K step: the chain is short)
+    using Sum = typename std::conditional<WIDE, double, float>::type;
+    static constexpr int EVERY = BM == 32 ? 1 : BM == 64 ? 2 : 8;       // matrix instructions between additions to the sum
     static constexpr int LDA = BK + 8;                                  // padded LDS row of a [.][k] operand
     static constexpr int LDN = BN + kPadN;                              // of a [k][n] operand
     static constexpr int A_TILE = BM * LDA;
@@ -166,8 +169,8 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    Sum sum[S::FORWARD ? TM : 1][S::FORWARD ? TN : 1][16];
-    if (S::FORWARD) {
+    Sum sum[S::WIDE ? TM : 1][S::WIDE ? TN : 1][16];
+    if (S::WIDE) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -176,7 +179,7 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
                 for (int v = 0; v < 16; ++v) sum[i][j][v] = 0;
     }
     auto promote = [&]() {
-        if (!S::FORWARD) return;
+        if (!S::WIDE) return;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -184,6 +187,11 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) { sum[i][j][v] += (Sum)acc[i][j][v]; acc[i][j][v] = 0.f; }
     };
+
+    auto promote_pair = [&]() {                                          // after two K steps
+        if (S::EVERY > KK) promote();
+    };
+    static_assert(S::EVERY <= KK || S::EVERY == 2 * KK || !S::WIDE, "sum cadence");
 
     // this thread's pieces: column piece kc of rows ra0 + c * A_STEP (a [k][n] operand: piece nc of rows kr0 + c * B_STEP)
     const int kc = (tid % KCH) * 8, ra0 = tid / KCH;
@@ -299,6 +307,7 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+            if (S::EVERY <= KK && (q + 1) % S::EVERY == 0) promote();
         }
     };
 
@@ -311,7 +320,7 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
             store_lds(0, kt, ra, rb, false);
             __syncthreads();
             compute(0);
-            promote();
+            promote_pair();
             __syncthreads();
         }
     } else {
@@ -329,12 +338,11 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
                 store_lds(1, kt + 1, qa, qb, true);
                 load_global(kt + 3, qa, qb);
                 compute(0);
-                if (S::PROMOTE == 1) promote();
-                __syncthreads();
+                    __syncthreads();
                 store_lds(0, kt + 2, ra, rb, true);
                 load_global(kt + 4, ra, rb);
                 compute(1);
-                promote();
+                promote_pair();
                 __syncthreads();
             }
         } else {
@@ -347,25 +355,23 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
         if (left > 1) store_lds(1, kt + 1, qa, qb, true);
         if (left > 3) load_global(kt + 3, qa, qb);
         compute(0);
-        if (S::PROMOTE == 1) promote();
         __syncthreads();
         if (left > 1) {
             if (left > 2) store_lds(0, kt + 2, ra, rb, true);
             compute(1);
-            promote();
+            promote_pair();
             __syncthreads();
         }
         if (left > 2) {
             if (left > 3) store_lds(1, kt + 3, qa, qb, true);
             compute(0);
-            if (S::PROMOTE == 1) promote();
             __syncthreads();
         }
         if (left > 3) {
             compute(1);
             __syncthreads();
         }
-        promote();
+        promote_pair();
     }
 
     if (BIAS && bias_rows) {
@@ -384,7 +390,7 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int r = (wm * TM + i) * 32 + (lane >> 5) * 4 + 8 * (v >> 2) + (v & 3);
-                T[(wk * BM + r) * LDC + (wn * TN + j) * 32 + (lane & 31)] = S::FORWARD ? sum[S::FORWARD ? i : 0][S::FORWARD ? j : 0][v] : (Sum)acc[i][j][v];
+                T[(wk * BM + r) * LDC + (wn * TN + j) * 32 + (lane & 31)] = S::WIDE ? sum[S::WIDE ? i : 0][S::WIDE ? j : 0][v] : (Sum)acc[i][j][v];
             }
     __syncthreads();
     if constexpr (EPI == EPI_HEAD) {
@@ -481,7 +487,7 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int m = m0 + r0 + RPP * p;
-            f32x4 v = value(p);
+            sum4 v = value(p);
             if (m < M && nv > 0) {
                 const uint16_t* mk = g.mask + (int64_t)w * g.sMask + (int64_t)m * g.ldmask + n;
                 u32x2 h = {0u, 0u};
@@ -493,13 +499,13 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (((h[e >> 1] >> (16 * (e & 1))) & 0xFFFFu) == 0) v[e] = 0.f;
+                    if (((h[e >> 1] >> (16 * (e & 1))) & 0xFFFFu) == 0) v[e] = 0;
                 uint16_t* dst = g.out + (int64_t)w * g.sOut + (int64_t)m * g.ldout + n;
-                const u32x2 o = {f32x2_to_bf16x2(v.x, v.y), f32x2_to_bf16x2(v.z, v.w)};
+                const u32x2 o = {f32x2_to_bf16x2((float)v.x, (float)v.y), f32x2_to_bf16x2((float)v.z, (float)v.w)};
                 if (nv == 4) *reinterpret_cast<u32x2_any*>(dst) = o;
                 else store_some(dst, o, nv);
             }
-            *reinterpret_cast<f32x4*>(T + (r0 + RPP * p) * LDC + c4) = v;   // this thread's own elements of copy 0
+            *reinterpret_cast<sum4*>(T + (r0 + RPP * p) * LDC + c4) = v;   // this thread's own elements of copy 0
         }
         __syncthreads();
         // the transposed copy: four samples of one column per thread
@@ -512,7 +518,7 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
             if (n0 + col >= N || mv <= 0) continue;
             float v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = T[(mq + e) * LDC + col];
+            for (int e = 0; e < 4; ++e) v[e] = (float)T[(mq + e) * LDC + col];
             const u32x2 o = {f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3])};
             uint16_t* dst = g.outT + (int64_t)w * g.sOutT + (int64_t)(n0 + col) * g.ldoutT + mm;
             if (mv == 4) *reinterpret_cast<u32x2_any*>(dst) = o;
