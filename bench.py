@@ -35,9 +35,9 @@ import workloads as wl
 # Bytes between the L2 caches and memory per launch, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by
 # reference kernels of known size (profiles/*_hbm_traffic.md).  Valid only for the kernel source they were
 # taken on: reported as null once that file's code (comments and white space aside) differs.
-PULL_TRAFFIC = {"file": "pull_update.hip", "code_sha256_16": "ce89fd10d8336956", "bytes_per_launch": 7.666e9,
+PULL_TRAFFIC = {"file": "pull_update.hip", "code_sha256_16": "0c447222cfc3c9dd", "bytes_per_launch": 7.666e9,
                 "key": (32, 11_689_512)}
-MC_TRAFFIC = {"file": "mc_grad.hip", "code_sha256_16": "39a5db2ab05460a9", "bytes_per_launch": 3.936e8,
+MC_TRAFFIC = {"file": "mc_grad.hip", "code_sha256_16": "bd8ef4362cfe623f", "bytes_per_launch": 3.929e8,
               "key": (16, 65536, 20000, 20000, 32)}
 
 
@@ -404,7 +404,7 @@ def run_mlp(L, steps, warmup, cfg, data, fused=True, measured_bw_gbs=None):
     # the gradient stage as a contraction: fraction of the bf16 matrix-core peak, and of what its arithmetic
     # intensity allows (flops per byte of unavoidable traffic x memory bandwidth, datasheet and measured)
     intensity = flops / min_bytes
-    grad_stage = {"kernel": "lsgd_grad_loss (MLP): gemm_bf16_kernel launches + narrow-layer kernels", "bound": "mfma", "achieved": tf,
+    grad_stage = {"kernel": "lsgd_grad_loss (MLP): gemm_bf16_kernel launches + gemm_ragged_kernel for the classifier layer", "bound": "mfma", "achieved": tf,
                   "peak": 2500.0, "unit": "TFLOP/s", "frac": tf / 2500.0, "flops_per_launch": flops, "ms_per_launch": ms_grad,
                   "min_bytes_per_launch": min_bytes, "intensity_flop_per_byte": intensity,
                   "intensity_roofline_TFLOPs": min(2500.0, intensity * HBM_PEAK_GBS / 1e3),
