@@ -408,16 +408,29 @@ lsgd_status do_select(lsgd_population* p, const float* losses, const uint8_t* re
     return LSGD_OK;
 }
 
-// Whether the one-launch update by column owners is the faster one.  Up to about 300 MB read and written per update
-// the launches it saves weigh more than what workgroups that hop between rows lose against row streams (us, row
-// streams / column owners: 96 MB 31 / 22, 240 MB 62 / 44, 400 MB 82 / 81 to 86, 800 MB 148 / 160); a thread walks the
-// rows one after the other, so many rows with few columns are the other end (32 workers x 10 000: 16 / 11).
-// Elastic averaging reads every row twice there and has one launch less to save: 16 x 600 000 44 / 41,
-// 32 x 10 000 11.6 / 13, 16 x 1 250 000 85 / 87.
-bool column_step(const lsgd_population* p, bool easgd = false)
+// Whether the one-launch update by column owners is the faster one.  Up to 300 MB read and written per update the
+// launches it saves weigh more than what workgroups that hop between rows lose against row streams (whole step, all
+// leaders re-selected, us, row streams / column owners: 96 MB 31 / 22, 240 MB 62 / 45; 384 MB 81 / 74 but 66 / 75 with
+// none re-selected, 640 MB 137 / 142).  A thread walks the groups one after the other, at most four rows in flight, so
+// groups of one worker are the other end (16 x 250 000 with momentum, half of the leaders re-selected, 16 groups
+// 30 / 35, 4 groups 23 / 18), and so are pairs of many workers or with nothing re-selected (16 x 250 000, 8 groups: half
+// re-selected 27 / 24, none 20 / 21; 32 x 100 000, 16 groups: 28 / 31, 17 / 27).
+bool column_step(const lsgd_population* p, bool selects)
+{
+    const int W = p->cfg.W, G = p->cfg.n_groups;
+    const double bytes = (p->cfg.momentum != 0.0f ? 20.0 : 12.0) * (double)W * (double)p->cfg.P;
+    if (W > 32 || bytes > 300e6) return false;
+    if (selects) return W >= 4 * G || (W <= 16 && W >= 2 * G);
+    return W >= 4 * G && (W <= 16 || bytes >= 30e6);                   // 32 x 30 000, 8 groups: 12.3 / 13.5
+}
+
+// The same for elastic averaging, whose rows are one group: 16 x 250 000 with momentum 21 / 16, 16 x 1 250 000 (400 MB)
+// 85 / 73, 32 x 300 000 (192 MB) 43 / 42, 32 x 600 000 (384 MB) 76 / 82,
+// 16 x 2 500 000 158 / 165, 32 x 10 000 11.6 / 12.2.
+bool column_easgd(const lsgd_population* p)
 {
     const double bytes = (p->cfg.momentum != 0.0f ? 20.0 : 12.0) * (double)p->cfg.W * (double)p->cfg.P;
-    return easgd ? p->cfg.W <= 16 && bytes <= 200e6 : p->cfg.W <= 32 && bytes <= 300e6;
+    return p->cfg.W <= 16 ? bytes <= 450e6 : p->cfg.W <= 32 && bytes >= 80e6 && bytes <= 250e6;
 }
 
 // comm: Algorithm 1's communication pull (lamL, lamG are its lambdas; eta unused).
@@ -462,7 +475,10 @@ lsgd_status do_pull(lsgd_population* p, float eta, float lamL, float lamG, bool 
 {
     const PullParams q = pull_params(p, eta, lamL, lamG, unscaled, comm);
     hipError_t e;
-    if (column_step(p)) {
+    // One launch where row streams take two: re-selected leaders are to be captured (16 x 60 000 behind a selection of its
+    // own, us, row streams / column owners: 13.9 / 13.1, 32 x 10 000 10.4 / 13.1, 32 x 140 000 23 / 19; without any 6.8 / 10).
+    const double bytes = 12.0 * (double)p->cfg.W * (double)p->cfg.P;
+    if (any_pending(p) && column_step(p, true) && (p->cfg.W <= 16 || bytes >= 30e6)) {
         ColumnStep c{};
         c.pull = q;
         c.update = !comm; c.comm = comm; c.commL = lamL; c.commG = lamG;
@@ -610,7 +626,9 @@ lsgd_status lsgd_step(lsgd_population* pop, const lsgd_batch* batch, float eta, 
     if (st != LSGD_OK) return st;
     if ((pop->cfg.flags & LSGD_FUSED_MLP_UPDATE) && batch->kind == LSGD_BATCH_MLP)
         return do_fused_mlp_step(pop, batch, eta, lambda_L, lambda_G, refresh_local, refresh_global);
-    if (column_step(pop)) {
+    bool selects = any_pending(pop) || refresh_global != 0 || !refresh_local;
+    for (int j = 0; j < pop->cfg.n_groups && !selects; ++j) selects = refresh_local[j] != 0;
+    if (column_step(pop, selects)) {
         ColumnStep c{};
         st = column_losses(pop, batch, &c);
         if (st != LSGD_OK) return st;
@@ -670,7 +688,7 @@ lsgd_status lsgd_step_alg1(lsgd_population* pop, const lsgd_batch* batch, float 
     }
     // one launch for update, selection and communication pull; the workgroups then read only leaders that this call
     // does not re-record, so not while a selection is pending or the recorded leaders are exempt
-    if (communicate && column_step(pop) && !any_pending(pop) && !(pop->cfg.flags & LSGD_LEADER_EXEMPT)) {
+    if (communicate && column_step(pop, true) && !any_pending(pop) && !(pop->cfg.flags & LSGD_LEADER_EXEMPT)) {
         ColumnStep c{};
         st = column_losses(pop, batch, &c);
         if (st != LSGD_OK) return st;
@@ -733,7 +751,7 @@ lsgd_status lsgd_easgd_update(lsgd_population* pop, float* center, float eta, fl
     PullParams q = pull_params(pop, eta, 0.0f, lambda, false, false);
     q.flags &= ~LSGD_LEADER_EXEMPT;          // nobody is a leader here
     hipError_t e;
-    if (column_step(pop, true)) {
+    if (column_easgd(pop)) {
         ColumnStep c{};
         c.pull = q; c.update = 1; c.center = center; c.center_rate = a;
         e = launch_column_step(c, pop->st, pop->stream);

@@ -9,13 +9,15 @@
 // one also records its result for the calls that follow.
 //
 // Which path.  A launch costs about 3 to 5 us here whatever it does, while a workgroup that hops between W rows gets
-// less out of HBM than the row-streaming kernels (5.1 against 5.9 TB/s at 7.5 GB per update); up to about 300 MB read
+// less out of HBM than the row-streaming kernels (5.2 against 5.9 TB/s at 1.6 GB per update); up to about 300 MB read
 // and written per update (the caller's rule) the saved launches weigh more.  Measured, whole lsgd_step on external
 // gradients, row streams -> this kernel, us: 4 x 1003 14.6 -> 4.5; 12 x 271 117 with momentum and kept leaders
-// 24.6 -> 16.5; 16 x 250 000 with momentum 30.0 -> 18.4; 16 x 1 250 000 without 62.5 -> 41.5, with momentum (400 MB)
-// 82.7 -> 80.7, with kept leaders 82.1 -> 86.3.
+// 24.6 -> 16.5; 16 x 250 000 with momentum 30.0 -> 17.3;
+// 16 x 1 250 000 without 62.5 -> 41.5; elastic averaging, 16 x 1 250 000 with momentum 85.3 -> 73.3.
 #include "pull_common.h"
 #include "select_common.h"
+
+#include <type_traits>
 
 namespace lsgd {
 
@@ -52,7 +54,7 @@ struct RowBatch {
     typename Vec<VEC>::type x[kRowsInFlight<VEC>], g[kRowsInFlight<VEC>], m[kRowsInFlight<VEC>];
 };
 
-template <int VEC, int KIND>
+template <int VEC, int KIND, bool NT>
 __device__ __forceinline__ void load_rows(const PullDev& a, int i, int end, int64_t col, RowBatch<VEC>& b)
 {
     using V = typename Vec<VEC>::type;
@@ -60,15 +62,21 @@ __device__ __forceinline__ void load_rows(const PullDev& a, int i, int end, int6
     for (int u = 0; u < kRowsInFlight<VEC>; ++u)
         if (i + u < end) {
             const int64_t o = (int64_t)(i + u) * a.ld + col;
-            b.x[u] = ld_vec<VEC>(a.x + o);
+            b.x[u] = NT ? ld_stream<VEC>(a.x + o) : ld_vec<VEC>(a.x + o);
             b.g[u] = ld_stream<VEC>(a.g + o);
-            b.m[u] = (KIND == 1) ? ld_vec<VEC>(a.m + o) : zero_of(V());
+            b.m[u] = (KIND == 1) ? (NT ? ld_stream<VEC>(a.m + o) : ld_vec<VEC>(a.m + o)) : zero_of(V());
         }
 }
 
+// Rows that one pass treats alike: a group, or all of them where the center is what they are pulled to (no local pull
+// then; asked at run time all the same: a loop known to have one pass keeps twice the registers, 84 us instead of 73 for
+// 16 x 1 250 000).
+template <bool CENTER>
+__device__ __forceinline__ int pass_end(const PullDev& a, int j) { return CENTER && a.lamL == 0.0f ? a.W : a.offsets[j + 1]; }
+
 // The rows in order, the loads of the next few under way while a few are updated and stored.  `first` holds the first
-// rows of the first group, loaded before the leaders were known.
-template <int VEC, int KIND>
+// rows of the first pass, loaded before the leaders were known.
+template <int VEC, int KIND, bool NT, bool CENTER>
 __device__ __forceinline__ void update_columns(const ColumnDev& s, const Leaders& L, int64_t col, const RowBatch<VEC>& first)
 {
     using V = typename Vec<VEC>::type;
@@ -84,16 +92,17 @@ __device__ __forceinline__ void update_columns(const ColumnDev& s, const Leaders
     if (pullL) zl = local_leader(0);
     if (pullG && L.freshG && a.Z) st_vec(a.Z + (int64_t)a.G * a.ld + col, zg);
     RowBatch<VEC> cur = first, next;
-    int j = 0, i = 0, end = a.offsets[1];
+    const int passes = CENTER && !pullL ? 1 : a.G;
+    int j = 0, i = 0, end = pass_end<CENTER>(a, 0);
     while (true) {
         int nj = j, ni = i + kRowsInFlight<VEC>, nend = end;
         if (ni >= end) {
             nj = j + 1; ni = end;
-            nend = nj < a.G ? a.offsets[nj + 1] : end;
+            nend = nj < passes ? pass_end<CENTER>(a, nj) : end;
         }
         V nzl = zl;
-        if (nj < a.G) {
-            load_rows<VEC, KIND>(a, ni, nend, col, next);
+        if (nj < passes) {
+            load_rows<VEC, KIND, NT>(a, ni, nend, col, next);
             if (pullL && nj != j) nzl = local_leader(nj);
         }
         if (pullL && L.fresh[j] && a.Z && i == a.offsets[j]) st_vec(a.Z + (int64_t)j * a.ld + col, zl);
@@ -105,11 +114,11 @@ __device__ __forceinline__ void update_columns(const ColumnDev& s, const Leaders
                 if (exempt && pullL && i + u == L.lead[j]) cr.cL = 0.0f;
                 if (exempt && pullG && i + u == L.gl) cr.cG = 0.0f;
                 update_vec<KIND, V>(cur.x[u], cur.g[u], cur.m[u], zl, zg, cr);
-                st_vec(a.x + o, cur.x[u]);
-                if (KIND == 1) st_vec(a.m + o, cur.m[u]);
+                if (NT) st_stream(a.x + o, cur.x[u]); else st_vec(a.x + o, cur.x[u]);
+                if (KIND == 1) { if (NT) st_stream(a.m + o, cur.m[u]); else st_vec(a.m + o, cur.m[u]); }
                 if (a.xb) st_bf16(a.xb + o, cur.x[u]);
             }
-        if (nj >= a.G) break;
+        if (nj >= passes) break;
         cur = next; zl = nzl; j = nj; i = ni; end = nend;
     }
 }
@@ -208,12 +217,12 @@ __device__ __forceinline__ void easgd_columns(const ColumnDev& s, int64_t col)
     st_vec(s.center + col, next);
 }
 
-template <int VEC, int KIND>
+template <int VEC, int KIND, bool NT, bool CENTER>
 __device__ __forceinline__ void step_columns(const ColumnDev& s, const Leaders& before, const Leaders& after, int64_t col, const RowBatch<VEC>& first)
 {
-    if (s.center) easgd_columns<VEC>(s, col);
-    if (s.update) update_columns<VEC, KIND>(s, before, col, first);
-    if (s.comm) comm_columns<VEC>(s, after, col);
+    if (CENTER) easgd_columns<VEC>(s, col);
+    if (CENTER || s.update) update_columns<VEC, KIND, NT, CENTER>(s, before, col, first);
+    if (!CENTER && s.comm) comm_columns<VEC>(s, after, col);
 }
 
 // Leaders as recorded by earlier calls (now) and, when the call selects, as they stand after the selection (chosen);
@@ -322,33 +331,45 @@ __global__ __launch_bounds__(kThreads) void capture_kernel(ColumnDev s)
     }
 }
 
-template <int VEC, int KIND>
+template <int VEC, int KIND, bool NT, bool CENTER>
 __global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
 {
     __shared__ Leaders now, chosen;
     const int64_t col = s.a.col0 + ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VEC;
     const bool whole = col + VEC <= s.a.col1;
     RowBatch<VEC> first;
-    if (s.update && whole) load_rows<VEC, KIND>(s.a, 0, s.a.offsets[1], col, first);   // under way during the selection
+    if (s.update && whole) load_rows<VEC, KIND, NT>(s.a, 0, pass_end<CENTER>(s.a, 0), col, first);   // under way during the selection
     choose_leaders(s, now, chosen);
     const Leaders& before = s.select == 1 ? chosen : now;
     const Leaders& after = s.select ? chosen : now;
-    if (whole) step_columns<VEC, KIND>(s, before, after, col, first);
+    if (whole) step_columns<VEC, KIND, NT, CENTER>(s, before, after, col, first);
     else
         for (int64_t cc = col; cc < s.a.col1; ++cc) {
             RowBatch<1> one;
-            if (s.update) load_rows<1, KIND>(s.a, 0, s.a.offsets[1], cc, one);
-            step_columns<1, KIND>(s, before, after, cc, one);
+            if (s.update) load_rows<1, KIND, NT>(s.a, 0, pass_end<CENTER>(s.a, 0), cc, one);
+            step_columns<1, KIND, NT, CENTER>(s, before, after, cc, one);
         }
 }
 
 template <int VEC>
-void launch_vec(const ColumnDev& s, bool mom, hipStream_t st)
+void launch_vec(const ColumnDev& s, bool mom, bool nt, hipStream_t st)
 {
     const int64_t cols = s.a.col1 - s.a.col0, per = (int64_t)kThreads * VEC;
     const dim3 grid((unsigned)((cols + per - 1) / per));
-    if (mom) hipLaunchKernelGGL((column_step_kernel<VEC, 1>), grid, dim3(kThreads), 0, st, s);
-    else hipLaunchKernelGGL((column_step_kernel<VEC, 0>), grid, dim3(kThreads), 0, st, s);
+    auto go = [&](auto kind, auto stream, auto center) {
+        hipLaunchKernelGGL((column_step_kernel<VEC, decltype(kind)::value, decltype(stream)::value, decltype(center)::value>),
+                           grid, dim3(kThreads), 0, st, s);
+    };
+    auto with_kind = [&](auto stream, auto center) {
+        if (mom) go(std::integral_constant<int, 1>{}, stream, center);
+        else go(std::integral_constant<int, 0>{}, stream, center);
+    };
+    auto with_stream = [&](auto center) {
+        if (nt) with_kind(std::true_type{}, center);
+        else with_kind(std::false_type{}, center);
+    };
+    if (s.center) with_stream(std::true_type{});
+    else with_stream(std::false_type{});
 }
 
 } // namespace
@@ -383,6 +404,13 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     if (q.update && p.xb && p.P >= 100000 && vec < 2) vec = 2;
     if (!q.update) vec = 4;
     while (vec > 1 && !layout_ok((unsigned)vec)) vec >>= 1;
+    // Streaming accesses (x, m past the caches) where the population neither lives in the L2s from step to step nor in
+    // the memory-side cache as it is: plain / streaming, us: 16 workers with momentum, 250 000 columns (80 MB) 18.9 / 17.3,
+    // 600 000 (192 MB) 37.3 / 39.1, 1 250 000 (400 MB) 80.3 / 73.7, elastic averaging there 86.4 / 73.3; pairs of workers,
+    // 16 x 250 000, 26.8 / 25.3.
+    // Not before a communication pull, which reads x again.
+    const double bytes = (mom ? 20.0 : 12.0) * (double)p.W * (double)p.P;
+    const bool nt = !q.comm && bytes >= 16e6 && (bytes < 90e6 || bytes > 280e6);
     if (!q.update && q.comm && q.commL == 0.0f && q.commG == 0.0f) {
         const int64_t tiles = (p.P + (int64_t)kThreads * vec - 1) / ((int64_t)kThreads * vec);
         const dim3 grid((unsigned)(tiles < 2048 ? tiles : 2048));
@@ -391,9 +419,9 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
         else hipLaunchKernelGGL((capture_kernel<1>), grid, dim3(kThreads), 0, stream, s);
         return hipGetLastError();
     }
-    if (vec == 4) launch_vec<4>(s, mom, stream);
-    else if (vec == 2) launch_vec<2>(s, mom, stream);
-    else launch_vec<1>(s, mom, stream);
+    if (vec == 4) launch_vec<4>(s, mom, nt, stream);
+    else if (vec == 2) launch_vec<2>(s, mom, nt, stream);
+    else launch_vec<1>(s, mom, nt, stream);
     return hipGetLastError();
 }
 

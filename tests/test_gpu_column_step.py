@@ -15,10 +15,11 @@ pytestmark = pytest.mark.gpu
 SHAPES = [
     (1, [0, 1], 1, 1),                               # one of everything
     (2, [0, 1, 2], 255, 256),                        # one thread short of a workgroup, groups of one
+    (6, [0, 2, 4, 6], 301, 320),                     # pairs: one launch only where something is re-selected
     (7, [0, 1, 7], 257, 257),                        # odd stride: one column per thread
     (32, [0, 9, 17, 32], 1027, 1088),                # groups of 9, 8 and 15 rows: remainders of the row batch
     (33, [0, 9, 17, 33], 1027, 1088),                # row streams
-    (9, [0, 4, 9], 500_003, 500_032),                # more columns per thread, ragged last one
+    (9, [0, 4, 9], 500_003, 500_032),                # more columns per thread, ragged last one; streaming accesses without momentum
 ]
 OPTIONS = [(0.0, 0, 0.0), (0.9, L.NESTEROV, 1e-2), (0.9, L.LEADER_EXEMPT, 0.0), (0.5, L.MOMENTUM_GRAD_ONLY, 0.0),
            (0.0, L.PULL_UNSCALED_BY_ETA, 0.0)]
@@ -93,10 +94,10 @@ def test_ties_nan_and_infinite_losses_select_alike():
         assert one.pop.get_leaders() == two.pop.get_leaders()
 
 
-@pytest.mark.parametrize("W", [5, 16, 17])
-def test_easgd_both_routes(W):
-    """Center and rows, one launch (16 workers at most) or two: center bit-exact (one order of the sum, one rounding)."""
-    P, ld = 1030, 1088
+@pytest.mark.parametrize("W,P,ld", [(5, 1030, 1088), (16, 1030, 1088), (17, 1030, 1088), (16, 60_001, 60_032)])
+def test_easgd_both_routes(W, P, ld):
+    """Center and rows, one launch (small populations; streaming accesses at 60 001 columns) or two: center bit-exact
+    (one order of the sum, one rounding)."""
     x0, g0, _ = wl.stress_state(W, P, ld, seed=W)
     pr = Pair(x0, [0, W], P=P, momentum=0.9)
     c0 = x0[0].astype(np.float32).copy()
