@@ -45,21 +45,48 @@ __device__ __forceinline__ void fetch_entry(const lsgd_mc_entry* __restrict__ en
     }
 }
 
+// Sum over the LPE adjacent lanes of a lane group, result in every lane of the group.  Steps inside a
+// row of 16 lanes are data-parallel-primitive adds (swap neighbours, swap pairs, mirror 8, mirror 16:
+// after the first two steps every lane of a quad holds the quad's sum, and a mirror maps each quad onto
+// a different one); wider groups finish with lane shuffles.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v)
+{
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+template <int LPE>
+__device__ __forceinline__ float group_sum(float v)
+{
+    if (LPE >= 2) v = dpp_add<0xB1>(v);       // quad_perm [1,0,3,2]
+    if (LPE >= 4) v = dpp_add<0x4E>(v);       // quad_perm [2,3,0,1]
+    if (LPE >= 8) v = dpp_add<0x141>(v);      // row_half_mirror
+    if (LPE >= 16) v = dpp_add<0x140>(v);     // row_mirror
+    if (LPE >= 32) v += __shfl_xor(v, 16, 64);
+    if (LPE >= 64) v += __shfl_xor(v, 32, 64);
+    return v;
+}
+
 // General path: S lanes cooperate on one entry (S = power of two >= min(r, 64)),
-// residual by a lane butterfly, gradient rows accumulated with hardware fp32
+// residual by a sum over the lanes, gradient rows accumulated with hardware fp32
 // atomics into the zero-filled g.  Any r, m, n.  GRAD = false evaluates the
 // squared residuals only (g may be NULL).  What bounds it on small batches is the
 // chain index -> entry -> factor rows -> residual of an entry, so a lane group has
 // up to eight entries in flight, and wide groups come in larger workgroups (256
 // entries each): 4 workers x 3000 entries, rank 5, 13.9 -> 4 us; 4 x 256, rank 50,
 // whole gradient call 39 -> 18 us.
+// Sums are no less exact than the binned path's: squared residuals are added in double,
+// per lane and over the workgroup, products of a residual keep what their rounding
+// drops (a lane of the binned path fuses several columns), and a term of the gradient
+// is rounded once.  Relative error of gradient / losses, 8 workers x 256 entries on
+// 1000 x 800, rank 8: 5.6e-8 / 1.6e-8, binned 5.8e-8 / 1.8e-8, with all of it in
+// 32 bits 6.2e-8 / 3.9e-8, at the same time per call.
 constexpr int mc_atomic_threads(int S) { return S <= 8 ? 256 : S == 16 ? 512 : 1024; }
 
 template <int S, bool GRAD>
 __global__ __launch_bounds__(mc_atomic_threads(S)) void mc_grad_atomic_kernel(
     const float* __restrict__ x, float* __restrict__ g, int64_t ld, int m, int n, int r,
     const int32_t* __restrict__ rows, const int32_t* __restrict__ cols, const float* __restrict__ vals,
-    const int32_t* __restrict__ batch_idx, int64_t nb, float two_c, float* __restrict__ partials, int nblk,
+    const int32_t* __restrict__ batch_idx, int64_t nb, float two_c, float* __restrict__ partials, double* __restrict__ partials64, int nblk,
     const lsgd_mc_entry* __restrict__ entries)
 {
     constexpr int kThreads = mc_atomic_threads(S);
@@ -70,10 +97,10 @@ __global__ __launch_bounds__(mc_atomic_threads(S)) void mc_grad_atomic_kernel(
     float* gV = GRAD ? gU + (int64_t)m * r : nullptr;
     const int sub = threadIdx.x / S, q0 = threadIdx.x % S;
     constexpr int kSubs = kThreads / S;
-    constexpr int kFly = S < 8 ? S : 8;              // entries of a lane group in flight 
+    constexpr int kFly = S < 8 ? S : 8;              // entries of a lane group in flight
     const int64_t k0 = (int64_t)blockIdx.x * kMcEntriesPerBlock;
     const int64_t k1 = (k0 + kMcEntriesPerBlock < nb) ? k0 + kMcEntriesPerBlock : nb;
-    float sq = 0.f;
+    double sq = 0.0;
     for (int64_t kb = k0 + sub; kb < k1; kb += (int64_t)kSubs * kFly) {
         int a[kFly], b[kFly];
         float mv[kFly], ua[kFly], vb[kFly];
@@ -96,34 +123,36 @@ __global__ __launch_bounds__(mc_atomic_threads(S)) void mc_grad_atomic_kernel(
             const float* uu = U + (int64_t)a[u] * r;
             const float* vv = V + (int64_t)b[u] * r;
             float dot = ua[u] * vb[u];
+            float low = fmaf(ua[u], vb[u], -dot);            // what the product's rounding dropped
+            low = fabsf(low) < INFINITY ? low : 0.f;         // (nothing, where the product is infinite)
             for (int q = q0 + S; q < r; q += S) dot = fmaf(uu[q], vv[q], dot);
-#pragma unroll
-            for (int d = 1; d < S; d <<= 1) dot += __shfl_xor(dot, d, S);
-            const float e = dot - mv[u];
+            const float e = (group_sum<S>(dot) - mv[u]) + group_sum<S>(low);
             if (!live[u]) continue;
-            if (q0 == 0) sq = fmaf(e, e, sq);
+            if (q0 == 0) sq += (double)e * (double)e;
             if (GRAD) {
-                const float f = two_c * e;
+                const double f = (double)two_c * (double)e;
                 if (q0 < r) {
-                    unsafeAtomicAdd(gU + (int64_t)a[u] * r + q0, f * vb[u]);
-                    unsafeAtomicAdd(gV + (int64_t)b[u] * r + q0, f * ua[u]);
+                    unsafeAtomicAdd(gU + (int64_t)a[u] * r + q0, (float)(f * (double)vb[u]));
+                    unsafeAtomicAdd(gV + (int64_t)b[u] * r + q0, (float)(f * (double)ua[u]));
                 }
                 for (int q = q0 + S; q < r; q += S) {
-                    unsafeAtomicAdd(gU + (int64_t)a[u] * r + q, f * vv[q]);
-                    unsafeAtomicAdd(gV + (int64_t)b[u] * r + q, f * uu[q]);
+                    unsafeAtomicAdd(gU + (int64_t)a[u] * r + q, (float)(f * (double)vv[q]));
+                    unsafeAtomicAdd(gV + (int64_t)b[u] * r + q, (float)(f * (double)uu[q]));
                 }
             }
         }
     }
-    // block sum of squared residuals in a fixed order
-    __shared__ float red[kThreads];
-    red[threadIdx.x] = sq;
+    // block sum of squared residuals in a fixed order (one lane of a group holds its sum)
+#pragma unroll
+    for (int d = S; d < kWave; d <<= 1) sq += __shfl_xor(sq, d, kWave);
+    __shared__ double red[kThreads / kWave];
+    if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = sq;
     __syncthreads();
-    for (int d = kThreads / 2; d > 0; d >>= 1) {
-        if (threadIdx.x < d) red[threadIdx.x] += red[threadIdx.x + d];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kThreads / kWave; ++q) red[0] += red[q];
+        if (partials64) partials64[(int64_t)w * nblk + blockIdx.x] = red[0];
+        else partials[(int64_t)w * nblk + blockIdx.x] = (float)red[0];
     }
-    if (threadIdx.x == 0) partials[(int64_t)w * nblk + blockIdx.x] = red[0];
 }
 
 // Objective only, rank a multiple of 4 and 16-byte aligned rows: LPE lanes share an entry with one float4
@@ -186,7 +215,8 @@ __global__ __launch_bounds__(kMcThreads) void mc_loss_vec_kernel(
 }
 
 // losses[w] = c * sum of the worker's partial sums, accumulated in fp64 in a fixed order.
-__global__ __launch_bounds__(256) void mc_loss_finish_kernel(const float* __restrict__ partials, int nblk, float c,
+template <class T>
+__global__ __launch_bounds__(256) void mc_loss_finish_kernel(const T* __restrict__ partials, int nblk, float c,
                                                              float* __restrict__ losses)
 {
     const int w = blockIdx.x;
@@ -346,27 +376,6 @@ __global__ __launch_bounds__(kPrepThreads) void mc_prep_kernel(
     __syncthreads();
     int2* rec = S.rec + ((int64_t)w * S.nblk + blk) * (2 * E);
     for (int i = t; i < 2 * cnt_here; i += kPrepThreads) rec[i] = stage[i];
-}
-
-// Sum over the LPE adjacent lanes of a lane group, result in every lane of the group.  Steps inside a
-// row of 16 lanes are data-parallel-primitive adds (swap neighbours, swap pairs, mirror 8, mirror 16:
-// after the first two steps every lane of a quad holds the quad's sum, and a mirror maps each quad onto
-// a different one); wider groups finish with lane shuffles.
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v)
-{
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-template <int LPE>
-__device__ __forceinline__ float group_sum(float v)
-{
-    if (LPE >= 2) v = dpp_add<0xB1>(v);       // quad_perm [1,0,3,2]
-    if (LPE >= 4) v = dpp_add<0x4E>(v);       // quad_perm [2,3,0,1]
-    if (LPE >= 8) v = dpp_add<0x141>(v);      // row_half_mirror
-    if (LPE >= 16) v = dpp_add<0x140>(v);     // row_mirror
-    if (LPE >= 32) v += __shfl_xor(v, 16, 64);
-    if (LPE >= 64) v += __shfl_xor(v, 32, 64);
-    return v;
 }
 
 // One workgroup per (worker, bin).  The bin's records (one segment per prepare workgroup) are
@@ -698,11 +707,13 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
 {
     const int64_t nb = mc_entries(b);
     // the partial sums are added up by a launch of their own, or left to a caller that says it can
-    auto finish_loss = [&](int workers, int n) {
+    auto finish_loss = [&](int workers, int n, const double* sums64) {
         if (parts && n > 0 && (int64_t)workers * n <= kLossPartsMax) {
-            parts->sums = st.partials; parts->stride = n; parts->n = n; parts->c = (double)b.c;
+            parts->sums = st.partials; parts->sums64 = sums64; parts->stride = n; parts->n = n; parts->c = (double)b.c;
+        } else if (sums64) {
+            hipLaunchKernelGGL((mc_loss_finish_kernel<double>), dim3((unsigned)workers), dim3(256), 0, s, sums64, n, b.c, losses);
         } else {
-            hipLaunchKernelGGL(mc_loss_finish_kernel, dim3((unsigned)workers), dim3(256), 0, s, st.partials, n, b.c, losses);
+            hipLaunchKernelGGL((mc_loss_finish_kernel<float>), dim3((unsigned)workers), dim3(256), 0, s, st.partials, n, b.c, losses);
         }
         return hipGetLastError();
     };
@@ -720,9 +731,12 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         else launch_side_lanes<1>(x, g, W, ld, b, S, st.partials, s);
         if (ld > P)
             hipLaunchKernelGGL(mc_zero_pad_kernel, dim3((unsigned)((ld - P + 255) / 256), (unsigned)W), dim3(256), 0, s, g, P, ld);
-        return finish_loss(W, S.nbinsU);
+        return finish_loss(W, S.nbinsU, nullptr);
     }
     const int nblk = (int)((nb + kMcEntriesPerBlock - 1) / kMcEntriesPerBlock);
+    // the block sums of squares stay in double where the binned path's scratch, idle now, has room for them (always for
+    // ranks that are multiples of four and could have taken that path)
+    double* sums64 = st.scratch_bytes >= sizeof(double) * (size_t)W * (size_t)nblk ? reinterpret_cast<double*>(st.scratch) : nullptr;
     // general path: zero the whole rows (padding included), then atomics
     {
         const bool v4 = (reinterpret_cast<uintptr_t>(g) & 15u) == 0 && (ld % 4 == 0);
@@ -737,7 +751,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         const float two_c = 2.0f * b.c;
 #define LSGD_MC_LAUNCH(S)                                                                                       \
     hipLaunchKernelGGL((mc_grad_atomic_kernel<S, true>), grid, dim3(mc_atomic_threads(S)), 0, s, x, g, ld, b.m, b.n, b.r, \
-                       b.rows, b.cols, b.vals, b.batch_idx, nb, two_c, st.partials, nblk, b.entries)
+                       b.rows, b.cols, b.vals, b.batch_idx, nb, two_c, st.partials, sums64, nblk, b.entries)
         if (b.r <= 1) LSGD_MC_LAUNCH(1);
         else if (b.r <= 2) LSGD_MC_LAUNCH(2);
         else if (b.r <= 4) LSGD_MC_LAUNCH(4);
@@ -747,7 +761,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         else LSGD_MC_LAUNCH(64);
 #undef LSGD_MC_LAUNCH
     }
-    return finish_loss(W, nblk);
+    return finish_loss(W, nblk, sums64);
 }
 
 // Objective values only: the residual pass of the general path without its atomics, one partial sum per
@@ -776,7 +790,7 @@ hipError_t launch_mc_loss(const float* x, float* losses, int W, int64_t ld, cons
         dim3 grid((unsigned)nblk, (unsigned)W);
 #define LSGD_MC_LAUNCH(S)                                                                                              \
     hipLaunchKernelGGL((mc_grad_atomic_kernel<S, false>), grid, dim3(mc_atomic_threads(S)), 0, s, x, (float*)nullptr, ld, b.m, b.n, \
-                       b.r, b.rows, b.cols, b.vals, b.batch_idx, nb, 0.0f, st.partials, nblk, b.entries)
+                       b.r, b.rows, b.cols, b.vals, b.batch_idx, nb, 0.0f, st.partials, (double*)nullptr, nblk, b.entries)
         if (b.r <= 1) LSGD_MC_LAUNCH(1);
         else if (b.r <= 2) LSGD_MC_LAUNCH(2);
         else if (b.r <= 4) LSGD_MC_LAUNCH(4);
@@ -786,7 +800,7 @@ hipError_t launch_mc_loss(const float* x, float* losses, int W, int64_t ld, cons
         else LSGD_MC_LAUNCH(64);
 #undef LSGD_MC_LAUNCH
     }
-    hipLaunchKernelGGL(mc_loss_finish_kernel, dim3((unsigned)W), dim3(256), 0, s, st.partials, nblk, b.c, losses);
+    hipLaunchKernelGGL((mc_loss_finish_kernel<float>), dim3((unsigned)W), dim3(256), 0, s, st.partials, nblk, b.c, losses);
     return hipGetLastError();
 }
 

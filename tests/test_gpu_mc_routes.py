@@ -87,3 +87,57 @@ def test_step_finishes_the_loss_sums_in_the_update(W, B):
     assert pr.pop.get_leaders() == sep.pop.get_leaders()
     pr.ora.select(); pr.ora.update(0.01, 0.1, 0.05)
     pr.check_state(1e-6)
+
+
+def exact_problem(r, m, vals, c, U, V):
+    """Entry k couples rows k of both factors, every worker takes all of them; the factors are those given."""
+    W, P, k = 2, 2 * m * r, np.arange(len(vals), dtype=np.int32)
+    x0 = np.zeros((W, wl.padded_ld(P)), np.float32)
+    x0[:, :P] = np.concatenate([U.reshape(-1), V.reshape(-1)])
+    batch = L.MCBatch(m, m, r, dev(k), dev(k), dev(vals.astype(np.float32)), None, c)
+    return Pair(x0, [0, W], P=P, largest_batch=batch), batch
+
+
+@pytest.mark.parametrize("call", ["grad_loss", "step"])
+@pytest.mark.parametrize("r", [1, 4, 5, 8, 50, 64])
+def test_small_batch_sums_squares_in_double(r, call):
+    """64 squares of 2^24 and 192 below one: an fp32 chain drops the latter (its unit there is 2), the sum in double,
+    2^30 + 168.75, rounds to 2^30 + 128.  Everything else is exact."""
+    vals = np.where(np.arange(256) < 64, 4096.0, 0.9375)
+    pr, batch = exact_problem(r, 300, vals, 1.0, np.zeros((300, r)), np.zeros((300, r)))
+    if call == "step":
+        pr.pop.step(batch, 0.0, 0.0, 0.0)
+    else:
+        pr.pop.grad_loss(batch)
+    assert pr.pop.get_losses() == [2.0 ** 30 + 128] * 2
+
+
+@pytest.mark.parametrize("r", [1, 4, 5, 8, 50, 64])
+def test_small_batch_rounds_a_gradient_term_once(r):
+    """One entry per factor row, residuals and factors small integers: the gradient is 2c e v rounded once."""
+    g = wl.stream("mc_exact", r)
+    U, V = g.integers(-7, 8, (300, r)).astype(np.float64), g.integers(-7, 8, (300, r)).astype(np.float64)
+    vals = g.integers(-200, 201, 256).astype(np.float64)
+    c = np.float32(0.3)
+    pr, batch = exact_problem(r, 300, vals, float(c), U, V)
+    pr.pop.grad_loss(batch)
+    torch.cuda.synchronize()
+    e = (U * V).sum(1)[:256] - vals
+    want = np.zeros((2, 300, r), np.float32)
+    two_c = np.float64(np.float32(2) * c)
+    want[0, :256] = (two_c * e[:, None] * V[:256]).astype(np.float32)      # exact in 64 bits up to here
+    want[1, :256] = (two_c * e[:, None] * U[:256]).astype(np.float32)
+    np.testing.assert_array_equal(pr.g.cpu().numpy()[0, :600 * r], want.reshape(-1))
+
+
+@pytest.mark.parametrize("r", [1, 4, 5, 50])
+def test_small_batch_overflow_stays_infinite(r):
+    """A product past the largest float makes that residual, and with it the loss and its gradient rows, infinite, not NaN."""
+    U = np.ones((300, r)); V = np.ones((300, r))
+    U[7], V[7] = 1e30, 1e30
+    pr, batch = exact_problem(r, 300, np.zeros(256), 1.0, U, V)
+    pr.pop.grad_loss(batch)
+    torch.cuda.synchronize()
+    assert pr.pop.get_losses() == [float("inf")] * 2
+    g = pr.g.cpu().numpy()[0, :600 * r].reshape(600, r)
+    assert np.all(np.isposinf(g[[7, 307]])) and np.all(np.isfinite(np.delete(g, [7, 307], 0)))
