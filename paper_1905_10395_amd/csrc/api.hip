@@ -328,10 +328,11 @@ lsgd_status do_loss(lsgd_population* p, const lsgd_batch* batch, float* losses_o
 lsgd_status check_grad_loss(lsgd_population* p, const lsgd_batch* batch)
 {
     size_t partials = 0, scratch = 0;
-    lsgd_status st = check_batch(batch, p->cfg.W, p->cfg.P, &partials, &scratch);
+    const bool mc = batch && batch->kind == LSGD_BATCH_MC;       // what it could use is more than what it cannot do without
+    lsgd_status st = check_batch(batch, p->cfg.W, p->cfg.P, &partials, mc ? nullptr : &scratch);
     if (st != LSGD_OK) return st;
     if (batch->kind == LSGD_BATCH_MLP && !p->xb) return fail(LSGD_ERR_STATE, "MLP batches need the x_bf16 buffer");
-    if (batch->kind == LSGD_BATCH_MC) scratch = mc_scratch_required(p->cfg.W, *static_cast<const lsgd_mc_batch*>(batch->desc));
+    if (mc) scratch = mc_scratch_required(p->cfg.W, *static_cast<const lsgd_mc_batch*>(batch->desc));
     size_t need = scratch;
     if (partials > (size_t)p->cfg.W) need += align_up(sizeof(float) * partials);
     if (need > p->st.scratch_bytes)

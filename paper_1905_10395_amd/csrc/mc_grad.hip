@@ -69,27 +69,32 @@ __device__ __forceinline__ float group_sum(float v)
 // General path: S lanes cooperate on one entry (S = power of two >= min(r, 64)),
 // residual by a sum over the lanes, gradient rows accumulated with hardware fp32
 // atomics into the zero-filled g.  Any r, m, n.  GRAD = false evaluates the
-// squared residuals only (g may be NULL).  What bounds it on small batches is the
-// chain index -> entry -> factor rows -> residual of an entry, so a lane group has
-// up to eight entries in flight, and wide groups come in larger workgroups (256
-// entries each): 4 workers x 3000 entries, rank 5, 13.9 -> 4 us; 4 x 256, rank 50,
-// whole gradient call 39 -> 18 us.
+// squared residuals only (g may be NULL).  Two loops:
+//   FLY   small batches are bound by the chain index -> entry -> factor rows ->
+//         residual of an entry, so a lane group has up to eight entries in flight,
+//         and wide groups come in larger workgroups (256 entries each): 4 workers x
+//         3000 entries of 100 x 100, rank 5, 13.9 -> 4 us; 4 x 256, rank 50, whole
+//         gradient call 39 -> 18 us.
+//   !FLY  one entry at a time, for batches that fill the chip: these are bound by the
+//         atomics, and bursts of eight only queue up behind each other where rows are
+//         hot (4 workers x 62000 entries, rank 5: 100 x 20000 145 -> 83 us, 3000 x
+//         4001 47 -> 41).
 // Sums are no less exact than the binned path's: squared residuals are added in double,
 // per lane and over the workgroup, products of a residual keep what their rounding
 // drops (a lane of the binned path fuses several columns), and a term of the gradient
 // is rounded once.  Relative error of gradient / losses, 8 workers x 256 entries on
 // 1000 x 800, rank 8: 5.6e-8 / 1.6e-8, binned 5.8e-8 / 1.8e-8, with all of it in
 // 32 bits 6.2e-8 / 3.9e-8, at the same time per call.
-constexpr int mc_atomic_threads(int S) { return S <= 8 ? 256 : S == 16 ? 512 : 1024; }
+constexpr int mc_atomic_threads(int S, bool FLY) { return !FLY || S <= 8 ? 256 : S == 16 ? 512 : 1024; }
 
-template <int S, bool GRAD>
-__global__ __launch_bounds__(mc_atomic_threads(S)) void mc_grad_atomic_kernel(
+template <int S, bool GRAD, bool FLY>
+__global__ __launch_bounds__(mc_atomic_threads(S, FLY)) void mc_grad_atomic_kernel(
     const float* __restrict__ x, float* __restrict__ g, int64_t ld, int m, int n, int r,
     const int32_t* __restrict__ rows, const int32_t* __restrict__ cols, const float* __restrict__ vals,
     const int32_t* __restrict__ batch_idx, int64_t nb, float two_c, float* __restrict__ partials, double* __restrict__ partials64, int nblk,
     const lsgd_mc_entry* __restrict__ entries)
 {
-    constexpr int kThreads = mc_atomic_threads(S);
+    constexpr int kThreads = mc_atomic_threads(S, FLY);
     const int w = blockIdx.y;
     const float* U = x + (int64_t)w * ld;
     const float* V = U + (int64_t)m * r;
@@ -97,47 +102,76 @@ __global__ __launch_bounds__(mc_atomic_threads(S)) void mc_grad_atomic_kernel(
     float* gV = GRAD ? gU + (int64_t)m * r : nullptr;
     const int sub = threadIdx.x / S, q0 = threadIdx.x % S;
     constexpr int kSubs = kThreads / S;
-    constexpr int kFly = S < 8 ? S : 8;              // entries of a lane group in flight
     const int64_t k0 = (int64_t)blockIdx.x * kMcEntriesPerBlock;
     const int64_t k1 = (k0 + kMcEntriesPerBlock < nb) ? k0 + kMcEntriesPerBlock : nb;
     double sq = 0.0;
-    for (int64_t kb = k0 + sub; kb < k1; kb += (int64_t)kSubs * kFly) {
-        int a[kFly], b[kFly];
-        float mv[kFly], ua[kFly], vb[kFly];
-        bool live[kFly];
-#pragma unroll
-        for (int u = 0; u < kFly; ++u) {
-            const int64_t k = kb + (int64_t)u * kSubs;
-            live[u] = k < k1;
-            const int64_t kc = live[u] ? k : kb;     // past the end: the first entry again, its results dropped
-            const int64_t s = batch_idx ? (int64_t)batch_idx[(int64_t)w * nb + kc] : kc;
-            fetch_entry(entries, rows, cols, vals, s, a[u], b[u], mv[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < kFly; ++u) {
-            ua[u] = q0 < r ? U[(int64_t)a[u] * r + q0] : 0.f;
-            vb[u] = q0 < r ? V[(int64_t)b[u] * r + q0] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < kFly; ++u) {
-            const float* uu = U + (int64_t)a[u] * r;
-            const float* vv = V + (int64_t)b[u] * r;
-            float dot = ua[u] * vb[u];
-            float low = fmaf(ua[u], vb[u], -dot);            // what the product's rounding dropped
-            low = fabsf(low) < INFINITY ? low : 0.f;         // (nothing, where the product is infinite)
-            for (int q = q0 + S; q < r; q += S) dot = fmaf(uu[q], vv[q], dot);
-            const float e = (group_sum<S>(dot) - mv[u]) + group_sum<S>(low);
-            if (!live[u]) continue;
+    auto residual = [&](float dot, float low, float v) {
+        low = fabsf(low) < INFINITY ? low : 0.f;         // (nothing, where the product is infinite)
+        return (group_sum<S>(dot) - v) + group_sum<S>(low);
+    };
+    if constexpr (!FLY) {
+        for (int64_t k = k0 + sub; k < k1; k += kSubs) {
+            const int64_t s = batch_idx ? (int64_t)batch_idx[(int64_t)w * nb + k] : k;
+            int a, b;
+            float mv;
+            fetch_entry(entries, rows, cols, vals, s, a, b, mv);
+            const float* ua = U + (int64_t)a * r;
+            const float* vb = V + (int64_t)b * r;
+            float dot = 0.f, low = 0.f;
+            for (int q = q0; q < r; q += S) {
+                const float p = ua[q] * vb[q];
+                if (q == q0) { dot = p; low = fmaf(ua[q], vb[q], -p); }
+                else dot = fmaf(ua[q], vb[q], dot);
+            }
+            const float e = residual(dot, low, mv);
             if (q0 == 0) sq += (double)e * (double)e;
             if (GRAD) {
                 const double f = (double)two_c * (double)e;
-                if (q0 < r) {
-                    unsafeAtomicAdd(gU + (int64_t)a[u] * r + q0, (float)(f * (double)vb[u]));
-                    unsafeAtomicAdd(gV + (int64_t)b[u] * r + q0, (float)(f * (double)ua[u]));
+                for (int q = q0; q < r; q += S) {
+                    unsafeAtomicAdd(gU + (int64_t)a * r + q, (float)(f * (double)vb[q]));
+                    unsafeAtomicAdd(gV + (int64_t)b * r + q, (float)(f * (double)ua[q]));
                 }
-                for (int q = q0 + S; q < r; q += S) {
-                    unsafeAtomicAdd(gU + (int64_t)a[u] * r + q, (float)(f * (double)vv[q]));
-                    unsafeAtomicAdd(gV + (int64_t)b[u] * r + q, (float)(f * (double)uu[q]));
+            }
+        }
+    } else {
+        constexpr int kFly = S < 8 ? S : 8;              // entries of a lane group in flight
+        for (int64_t kb = k0 + sub; kb < k1; kb += (int64_t)kSubs * kFly) {
+            int a[kFly], b[kFly];
+            float mv[kFly], ua[kFly], vb[kFly];
+            bool live[kFly];
+#pragma unroll
+            for (int u = 0; u < kFly; ++u) {
+                const int64_t k = kb + (int64_t)u * kSubs;
+                live[u] = k < k1;
+                const int64_t kc = live[u] ? k : kb;     // past the end: the first entry again, its results dropped
+                const int64_t s = batch_idx ? (int64_t)batch_idx[(int64_t)w * nb + kc] : kc;
+                fetch_entry(entries, rows, cols, vals, s, a[u], b[u], mv[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kFly; ++u) {
+                ua[u] = q0 < r ? U[(int64_t)a[u] * r + q0] : 0.f;
+                vb[u] = q0 < r ? V[(int64_t)b[u] * r + q0] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < kFly; ++u) {
+                const float* uu = U + (int64_t)a[u] * r;
+                const float* vv = V + (int64_t)b[u] * r;
+                float dot = ua[u] * vb[u];
+                const float low = fmaf(ua[u], vb[u], -dot);      // what the product's rounding dropped
+                for (int q = q0 + S; q < r; q += S) dot = fmaf(uu[q], vv[q], dot);
+                const float e = residual(dot, low, mv[u]);
+                if (!live[u]) continue;
+                if (q0 == 0) sq += (double)e * (double)e;
+                if (GRAD) {
+                    const double f = (double)two_c * (double)e;
+                    if (q0 < r) {
+                        unsafeAtomicAdd(gU + (int64_t)a[u] * r + q0, (float)(f * (double)vb[u]));
+                        unsafeAtomicAdd(gV + (int64_t)b[u] * r + q0, (float)(f * (double)ua[u]));
+                    }
+                    for (int q = q0 + S; q < r; q += S) {
+                        unsafeAtomicAdd(gU + (int64_t)a[u] * r + q, (float)(f * (double)vv[q]));
+                        unsafeAtomicAdd(gV + (int64_t)b[u] * r + q, (float)(f * (double)uu[q]));
+                    }
                 }
             }
         }
@@ -283,10 +317,9 @@ struct McBinned {
     int nbinsU, nbins, nblk, E;
 };
 
-// Maps a linear workgroup id to (worker, chunk), a die being id modulo 8.  Multiples of eight workers: worker w lives on
-// die w % 8, all dies work through workers 0 .. 7, then 8 .. 15 (144.3 -> 140.9 us for a whole step of 16 workers of
-// 20000 x 20000, rank 32, against contiguous runs).  Other numbers of workers: a die takes a contiguous run of all
-// workers' chunks, so that a worker's chunks share few dies and no die is left without work (per_die > 0).
+// Maps a linear workgroup id to (worker, chunk), a die being id modulo 8.  per_die = 0: worker w lives on die w % 8, all
+// dies work through workers 0 .. 7, then 8 .. 15.  Else a die takes a contiguous run of per_die chunks of all workers,
+// so that no die is left without work when the number of workers is no multiple of eight.
 __device__ __forceinline__ bool xcd_map(int64_t id, int64_t per_die, int W, int nchunk, int& w, int& chunk)
 {
     const int64_t t = id / kXcd;
@@ -598,26 +631,50 @@ static int mc_prep_blocks(int W, const lsgd_mc_batch& b)
 // Columns per lane in the side kernel by the rank alone.
 static int mc_cols(int r) { return r % 4 == 0 ? 4 : r % 2 == 0 ? 2 : 1; }
 
-// Which path is faster, from what bounds each (us; fitted to gradient calls of 100 x 100 to 20000 x 20000, ranks 1 to
-// 64, 256 to 50000 entries per worker, 3 to 16 workers: the choice costs 1 % on average, 26 % at worst):
-//   atomics   launches and one chain, plus the atomics themselves, which grow with entries x rank, plus the zero fill;
-//             ranks past 32 take a whole wavefront per entry
-//   binned    one launch more; then either the records of one bin, which one workgroup walks, or all records, and every
-//             factor row read and gradient row written, touched or not
-// Measured, atomics / binned: 100 x 100 (one bin a side), rank 5, 3000 entries, 3 workers 11 / 35; 6001 x 3517, rank 10,
-// 8 workers, 2048 entries 14 / 20, 8192 22 / 23, 32768 57 / 37; 20000 x 20000, rank 32, 16 workers, 32768 entries 148 / 91.
-static bool mc_binned_faster(int W, const lsgd_mc_batch& b)
+// Time of one gradient call, us, from what bounds each route.  The constants are those that choose best over 2038 shapes,
+// each timed on every route: 60 to 20000 rows a side, ranks 1 to 128, 100 to 66000 entries per worker, 1 to 32 workers.
+struct McCost {
+    double one, flight, binned; // atomics an entry at a time, atomics with entries in flight, binned
+};
+static double dominant(double a, double b, double c = 0.0) { return sqrt(sqrt(a * a * a * a + b * b * b * b + c * c * c * c)); }
+static McCost mc_cost(int W, const lsgd_mc_batch& b, int vw)
 {
-    const double thousands = 1e-3 * (double)W * (double)mc_entries(b);
-    const double rows = (double)W * ((double)b.m + (double)b.n) * b.r * 4.0 / 5e6;      // one pass over all factor rows
-    const double side = (double)(b.m < b.n ? b.m : b.n) / kBinRows;
-    const double per_bin = (double)mc_entries(b) / (side > 1.0 ? ceil(side) : 1.0);
+    const double nb = (double)mc_entries(b), thousands = 1e-3 * (double)W * nb, r = b.r;
+    const double lo = b.m < b.n ? b.m : b.n, hi = b.m < b.n ? b.n : b.m;
+    const double rows = (double)W * (lo + hi) * r * 4.0 / 5e6;          // one pass over all factor rows
+    // Atomics: requests of 64 bytes and, where one side is narrow, their queues at its few channels; or the requests of
+    // one worker that meet in the same 64 bytes; or the latency of the entries that a lane group takes one after the other.
+    const double pieces = b.r % 16 == 0 || 16 % b.r == 0 ? (r > 16 ? r / 16 : 1.0) : 1.0 + (r - 1) / 16;
+    const double queue = thousands * (0.093 * pieces + 0.017 * log(hi / lo) / (1 + 0.14 * r));
+    const double meet = nb / (lo * r > 16 ? lo * r / 16 : 1.0) * (0.0068 + 0.0045 * (r < 16 ? r : 16));
+    int group = 1;                                                      // lanes per entry
+    while (group < b.r && group < kWave) group <<= 1;
+    const double turns = (b.r + group - 1) / group;
+    McCost c;
+    c.one = 5.7 + dominant(queue, meet, 1.3 * group * turns) + 1.1 * rows;
+    c.flight = 5.7 + dominant(1.1 * queue, meet, 4.3 * (group > 32 ? group / 32 : 1) * turns) + 1.1 * rows;
+    // Binned: one launch more; the records; and every factor row read and gradient row written, touched or not.
     int lanes = 1;
-    while (lanes * mc_cols(b.r) < b.r) lanes <<= 1;
-    const double atomics = (b.r > 32 ? 15.0 : 7.2) + thousands * (0.136 + 0.0062 * b.r) + rows;
-    const double walk = per_bin * (0.0135 + 0.00038 * lanes), all = thousands * (0.079 + 0.0029 * b.r);
-    const double binned = 12.2 + (walk > all ? walk : all) + 3.4 * rows;
-    return binned < atomics;
+    while (lanes * vw < b.r) lanes <<= 1;
+    const double walk = nb * (lo > kBinRows ? kBinRows / lo : 1.0) * (0.0046 + 0.00044 * lanes);
+    const double records = thousands * (0.026 + 0.0027 * lanes);
+    c.binned = 12.0 + dominant(walk, records) + 2.0 * rows;
+    return c;
+}
+
+// The route of a gradient call.  Between binned and atomics the usual one of the rank keeps the call (binned for multiples
+// of four on aligned rows, 16 bytes per lane) unless the other's estimate is 7 % lower.  Over the shapes above the choice
+// costs 0.6 % against the best route of each; 6 are more than 10 % slower than on the usual route (at most 1.28 times),
+// all together 31 % faster.  Measured, us, one at a time / in flight / binned:
+//   100 x 20000   rank 5    4 x 62000   84 / 144 / 605      9468 x 466      rank 2   16 x 62000  180 / 194 / 134
+//   6001 x 3517   rank 10   8 x  4096   34 /  16 /  20      6001 x 3517     rank 10   8 x 16384   38 /  34 /  26
+//   1000 x 800    rank 64   8 x   256   89 /  18 /  15      20000 x 20000   rank 32  16 x 32768  128 / 136 /  77
+enum McRoute { kMcOne, kMcFlight, kMcBinned };
+static McRoute mc_route(const McCost& c, int vw, bool binned_ok)
+{
+    const double atomics = c.flight < c.one ? c.flight : c.one;
+    if (binned_ok && (vw == 4 ? c.binned < 1.07 * atomics : 1.07 * c.binned < atomics)) return kMcBinned;
+    return c.flight < c.one ? kMcFlight : kMcOne;
 }
 
 // ... as wide as the rank and the alignment of the rows allow
@@ -646,11 +703,17 @@ size_t mc_partials(int W, const lsgd_mc_batch& b)
     return (size_t)W * (size_t)(nblk > 0 ? nblk : 1);
 }
 
-size_t mc_scratch_bytes(int W, const lsgd_mc_batch& b)
+static size_t mc_binned_bytes(int W, const lsgd_mc_batch& b)
 {
-    if (!mc_binned_ok(W, b, mc_cols(b.r)) || (b.r % 4 != 0 && !mc_binned_faster(W, b))) return 0;
     const size_t slots = (size_t)mc_prep_blocks(W, b) * mc_ept(W, b) * kPrepThreads;
     return up256((size_t)W * mc_prep_blocks(W, b) * (mc_bins(b) + 1) * 4) + up256((size_t)W * 2 * slots * 8);
+}
+
+size_t mc_scratch_bytes(int W, const lsgd_mc_batch& b)
+{
+    const int vw = mc_cols(b.r);
+    if (!mc_binned_ok(W, b, vw) || (b.r % 4 != 0 && mc_route(mc_cost(W, b, vw), vw, true) != kMcBinned)) return 0;
+    return mc_binned_bytes(W, b);
 }
 
 // The binned path's scratch is a condition only for ranks that are multiples of four; with others a workspace
@@ -679,7 +742,8 @@ template <int LPE, int VW>
 static void launch_side(const float* x, float* g, int W, int64_t ld, const lsgd_mc_batch& b,
                         const McBinned& S, float* partials, hipStream_t s)
 {
-    const int64_t groups = ((int64_t)W * S.nbins + kXcd - 1) / kXcd * kXcd, per_die = W % kXcd ? groups / kXcd : 0;
+    const int64_t run = ((int64_t)W * S.nbins + kXcd - 1) / kXcd, per_die = W % kXcd ? run : 0;
+    const int64_t groups = per_die ? run * kXcd : (int64_t)((W + kXcd - 1) / kXcd) * kXcd * S.nbins;
     if (b.r == VW * LPE)
         hipLaunchKernelGGL((mc_side_kernel<LPE, true, VW>), dim3((unsigned)groups), dim3(kSideThreads),
                            (size_t)kBinRows * b.r * 4, s, x, g, ld, b.m, b.n, b.r, S, 2.0f * b.c, partials, W, per_die);
@@ -718,8 +782,9 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         return hipGetLastError();
     };
     const int vw = mc_cols(x, g, ld, b.r);
-    const bool binned = mc_binned_faster(W, b) && mc_binned_ok(W, b, vw) && st.scratch_bytes >= mc_scratch_bytes(W, b);
-    if (binned) {
+    const McCost cost = mc_cost(W, b, vw);
+    const McRoute route = mc_route(cost, vw, mc_binned_ok(W, b, vw) && st.scratch_bytes >= mc_binned_bytes(W, b));
+    if (route == kMcBinned) {
         McBinned S;
         S.nbinsU = mc_bins_u(b); S.nbins = mc_bins(b); S.nblk = mc_prep_blocks(W, b); S.E = mc_ept(W, b) * kPrepThreads;
         char* p = st.scratch;
@@ -749,9 +814,10 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
     if (nblk > 0) {
         dim3 grid((unsigned)nblk, (unsigned)W);
         const float two_c = 2.0f * b.c;
-#define LSGD_MC_LAUNCH(S)                                                                                       \
-    hipLaunchKernelGGL((mc_grad_atomic_kernel<S, true>), grid, dim3(mc_atomic_threads(S)), 0, s, x, g, ld, b.m, b.n, b.r, \
+#define LSGD_MC_LAUNCH_AS(S, FLY)                                                                               \
+    hipLaunchKernelGGL((mc_grad_atomic_kernel<S, true, FLY>), grid, dim3(mc_atomic_threads(S, FLY)), 0, s, x, g, ld, b.m, b.n, b.r, \
                        b.rows, b.cols, b.vals, b.batch_idx, nb, two_c, st.partials, sums64, nblk, b.entries)
+#define LSGD_MC_LAUNCH(S) do { if (route == kMcFlight) LSGD_MC_LAUNCH_AS(S, true); else LSGD_MC_LAUNCH_AS(S, false); } while (0)
         if (b.r <= 1) LSGD_MC_LAUNCH(1);
         else if (b.r <= 2) LSGD_MC_LAUNCH(2);
         else if (b.r <= 4) LSGD_MC_LAUNCH(4);
@@ -760,6 +826,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         else if (b.r <= 32) LSGD_MC_LAUNCH(32);
         else LSGD_MC_LAUNCH(64);
 #undef LSGD_MC_LAUNCH
+#undef LSGD_MC_LAUNCH_AS
     }
     return finish_loss(W, nblk, sums64);
 }
@@ -789,7 +856,7 @@ hipError_t launch_mc_loss(const float* x, float* losses, int W, int64_t ld, cons
     } else if (nblk > 0) {
         dim3 grid((unsigned)nblk, (unsigned)W);
 #define LSGD_MC_LAUNCH(S)                                                                                              \
-    hipLaunchKernelGGL((mc_grad_atomic_kernel<S, false>), grid, dim3(mc_atomic_threads(S)), 0, s, x, (float*)nullptr, ld, b.m, b.n, \
+    hipLaunchKernelGGL((mc_grad_atomic_kernel<S, false, true>), grid, dim3(mc_atomic_threads(S, true)), 0, s, x, (float*)nullptr, ld, b.m, b.n, \
                        b.r, b.rows, b.cols, b.vals, b.batch_idx, nb, 0.0f, st.partials, (double*)nullptr, nblk, b.entries)
         if (b.r <= 1) LSGD_MC_LAUNCH(1);
         else if (b.r <= 2) LSGD_MC_LAUNCH(2);

@@ -43,6 +43,20 @@ def test_both_routes_match_oracle(r, B):
     assert np.all(g[:, P:] == 0)
 
 
+# one side of few rows, many entries: the atomics an entry at a time
+@pytest.mark.parametrize("m,n", [(90, 4000), (4000, 61)])
+@pytest.mark.parametrize("r", [1, 2, 3, 5, 6, 7, 9, 16, 17, 33, 64, 67])
+def test_narrow_side_matches_oracle(r, m, n):
+    pr, batch, P = problem(m, n, r, 60000, 4, 40000, seed=r)
+    pr.g.fill_(float("nan"))
+    pr.pop.grad_loss(batch)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(pr.pop.get_losses(), pr.ora.losses, rtol=1e-5)
+    g = pr.g.cpu().numpy()
+    assert rel_l2_rows(g[:, :P], pr.ora.g[:, :P]).max() <= 1e-5
+    assert np.all(g[:, P:] == 0)
+
+
 @pytest.mark.parametrize("r", [4, 8, 10])
 def test_rows_that_are_not_aligned_for_the_widest_lanes(r):
     """Odd row strides: the binned route with two or one column per lane."""
