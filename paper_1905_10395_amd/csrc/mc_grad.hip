@@ -319,7 +319,7 @@ struct McBinned {
 
 // Maps a linear workgroup id to (worker, chunk), a die being id modulo 8.  per_die = 0: worker w lives on die w % 8, all
 // dies work through workers 0 .. 7, then 8 .. 15.  Else a die takes a contiguous run of per_die chunks of all workers,
-// so that no die is left without work when the number of workers is no multiple of eight.
+// so that no die is left without work when the number of workers is no multiple of eight (see mc_runs).
 __device__ __forceinline__ bool xcd_map(int64_t id, int64_t per_die, int W, int nchunk, int& w, int& chunk)
 {
     const int64_t t = id / kXcd;
@@ -635,6 +635,7 @@ static int mc_cols(int r) { return r % 4 == 0 ? 4 : r % 2 == 0 ? 2 : 1; }
 // each timed on every route: 60 to 20000 rows a side, ranks 1 to 128, 100 to 66000 entries per worker, 1 to 32 workers.
 struct McCost {
     double one, flight, binned; // atomics an entry at a time, atomics with entries in flight, binned
+    double walk, stream;        // binned: the fullest bin's records, which one workgroup walks; all records and rows
 };
 static double dominant(double a, double b, double c = 0.0) { return sqrt(sqrt(a * a * a * a + b * b * b * b + c * c * c * c)); }
 static McCost mc_cost(int W, const lsgd_mc_batch& b, int vw)
@@ -656,9 +657,10 @@ static McCost mc_cost(int W, const lsgd_mc_batch& b, int vw)
     // Binned: one launch more; the records; and every factor row read and gradient row written, touched or not.
     int lanes = 1;
     while (lanes * vw < b.r) lanes <<= 1;
-    const double walk = nb * (lo > kBinRows ? kBinRows / lo : 1.0) * (0.0046 + 0.00044 * lanes);
+    c.walk = nb * (lo > kBinRows ? kBinRows / lo : 1.0) * (0.0046 + 0.00044 * lanes);
     const double records = thousands * (0.026 + 0.0027 * lanes);
-    c.binned = 12.0 + dominant(walk, records) + 2.0 * rows;
+    c.stream = records + 2.0 * rows;
+    c.binned = 12.0 + dominant(c.walk, records) + 2.0 * rows;
     return c;
 }
 
@@ -675,6 +677,19 @@ static McRoute mc_route(const McCost& c, int vw, bool binned_ok)
     const double atomics = c.flight < c.one ? c.flight : c.one;
     if (binned_ok && (vw == 4 ? c.binned < 1.07 * atomics : 1.07 * c.binned < atomics)) return kMcBinned;
     return c.flight < c.one ? kMcFlight : kMcOne;
+}
+
+// Whether dies take contiguous runs of bins (xcd_map).  With a worker per die and W no multiple of eight the busiest die
+// has 8 ceil(W / 8) / W times the average; runs even that out, but spread a worker over dies, so that the fullest bin's
+// records, if that is what the launch waits for, find less of the other factor in their die's L2 (up to 29 % longer).
+// Over 1359 shapes of 1 to 28 workers 5 are more than 10 % slower than with a worker per die (at most 1.16 times), 14 than
+// with runs (1.27).  Measured, us, worker per die / runs: 20000 x 20000, rank 64, 4 workers x 16384 entries 59 / 38,
+// 9 workers 99 / 68; 3000 x 4001, rank 64, 12 x 2000 33 / 25; 466 x 9468, rank 32, 4 x 16384 52 / 64; 100 x 5000, rank 32,
+// 9 x 16384 152 / 192.
+static bool mc_runs(const McCost& c, int W)
+{
+    const double excess = (double)kXcd * ((W + kXcd - 1) / kXcd) / W - 1.0;
+    return c.walk < 2.0 * excess * c.stream;
 }
 
 // ... as wide as the rank and the alignment of the rows allow
@@ -740,9 +755,9 @@ static void launch_prep(int W, const lsgd_mc_batch& b, int64_t nb, const McBinne
 
 template <int LPE, int VW>
 static void launch_side(const float* x, float* g, int W, int64_t ld, const lsgd_mc_batch& b,
-                        const McBinned& S, float* partials, hipStream_t s)
+                        const McBinned& S, float* partials, bool runs, hipStream_t s)
 {
-    const int64_t run = ((int64_t)W * S.nbins + kXcd - 1) / kXcd, per_die = W % kXcd ? run : 0;
+    const int64_t run = ((int64_t)W * S.nbins + kXcd - 1) / kXcd, per_die = runs ? run : 0;
     const int64_t groups = per_die ? run * kXcd : (int64_t)((W + kXcd - 1) / kXcd) * kXcd * S.nbins;
     if (b.r == VW * LPE)
         hipLaunchKernelGGL((mc_side_kernel<LPE, true, VW>), dim3((unsigned)groups), dim3(kSideThreads),
@@ -754,16 +769,16 @@ static void launch_side(const float* x, float* g, int W, int64_t ld, const lsgd_
 
 template <int VW>
 static void launch_side_lanes(const float* x, float* g, int W, int64_t ld, const lsgd_mc_batch& b, const McBinned& S, float* partials,
-                              hipStream_t s)
+                              bool runs, hipStream_t s)
 {
     const int rv = b.r / VW;
-    if (rv <= 1) launch_side<1, VW>(x, g, W, ld, b, S, partials, s);
-    else if (rv <= 2) launch_side<2, VW>(x, g, W, ld, b, S, partials, s);
-    else if (rv <= 4) launch_side<4, VW>(x, g, W, ld, b, S, partials, s);
-    else if (rv <= 8) launch_side<8, VW>(x, g, W, ld, b, S, partials, s);
-    else if (rv <= 16) launch_side<16, VW>(x, g, W, ld, b, S, partials, s);
-    else if (rv <= 32) launch_side<32, VW>(x, g, W, ld, b, S, partials, s);
-    else launch_side<64, VW>(x, g, W, ld, b, S, partials, s);
+    if (rv <= 1) launch_side<1, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else if (rv <= 2) launch_side<2, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else if (rv <= 4) launch_side<4, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else if (rv <= 8) launch_side<8, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else if (rv <= 16) launch_side<16, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else if (rv <= 32) launch_side<32, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else launch_side<64, VW>(x, g, W, ld, b, S, partials, runs, s);
 }
 
 hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
@@ -791,9 +806,9 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         S.segs = reinterpret_cast<int32_t*>(p); p += up256((size_t)W * S.nblk * (S.nbins + 1) * 4);
         S.rec = reinterpret_cast<int2*>(p);
         launch_prep(W, b, nb, S, s);
-        if (vw == 4) launch_side_lanes<4>(x, g, W, ld, b, S, st.partials, s);
-        else if (vw == 2) launch_side_lanes<2>(x, g, W, ld, b, S, st.partials, s);
-        else launch_side_lanes<1>(x, g, W, ld, b, S, st.partials, s);
+        if (vw == 4) launch_side_lanes<4>(x, g, W, ld, b, S, st.partials, mc_runs(cost, W), s);
+        else if (vw == 2) launch_side_lanes<2>(x, g, W, ld, b, S, st.partials, mc_runs(cost, W), s);
+        else launch_side_lanes<1>(x, g, W, ld, b, S, st.partials, mc_runs(cost, W), s);
         if (ld > P)
             hipLaunchKernelGGL(mc_zero_pad_kernel, dim3((unsigned)((ld - P + 255) / 256), (unsigned)W), dim3(256), 0, s, g, P, ld);
         return finish_loss(W, S.nbinsU, nullptr);

@@ -57,6 +57,19 @@ def test_narrow_side_matches_oracle(r, m, n):
     assert np.all(g[:, P:] == 0)
 
 
+# worker counts that are no multiples of the eight dies, binned: contiguous runs of bins per die, and a worker per die
+# where the fullest bin's records are what the launch waits for
+@pytest.mark.parametrize("W,m,n,B", [(2, 5000, 4000, 20000), (3, 5000, 4000, 20000), (9, 5000, 4000, 20000),
+                                     (3, 3000, 2500, 20000), (9, 700, 3000, 30000), (12, 1000, 800, 20000)])
+def test_bins_on_dies_match_oracle(W, m, n, B):
+    pr, batch, P = problem(m, n, 64, 60000, W, B, seed=W)
+    pr.g.fill_(float("nan"))
+    pr.pop.grad_loss(batch)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(pr.pop.get_losses(), pr.ora.losses, rtol=1e-5)
+    assert rel_l2_rows(pr.g.cpu().numpy()[:, :P], pr.ora.g[:, :P]).max() <= 1e-5
+
+
 @pytest.mark.parametrize("r", [4, 8, 10])
 def test_rows_that_are_not_aligned_for_the_widest_lanes(r):
     """Odd row strides: the binned route with two or one column per lane."""
