@@ -225,6 +225,36 @@ __device__ __forceinline__ void step_columns(const ColumnDev& s, const Leaders& 
     if (!CENTER && s.comm) comm_columns<VEC>(s, after, col);
 }
 
+// The losses from their partial sums: a team of 4 to 256 lanes per worker, in double, in an order that depends on the
+// number of workers alone.  All kThreads threads; at most kColumnMaxWorkers workers.
+__device__ __forceinline__ void finish_losses(const LossParts& parts, int W, float* losses)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    int team = kThreads;
+    while (team * W > kThreads) team >>= 1;
+    const int w = tid / team, l = tid % team;
+    double acc = 0.0;
+    if (w < W)
+        for (int i = l; i < parts.n; i += team) {
+            const int64_t at = (int64_t)w * parts.stride + i;
+            acc += parts.sums64 ? parts.sums64[at] : (double)parts.sums[at];
+        }
+    if (team > kWave) {                                  // one or two workers
+        __shared__ double cross[kThreads / kWave];
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) acc += __shfl_xor(acc, d, kWave);
+        if (lane == 0) cross[tid / kWave] = acc;
+        __syncthreads();
+        acc = 0.0;
+        for (int q = 0; q < team / kWave; ++q) acc += cross[(w * team) / kWave + q];
+    } else {
+        for (int d = 1; d < team; d <<= 1) acc += __shfl_xor(acc, d, kWave);
+    }
+    if (w < W && l == 0) losses[w] = (float)(parts.c * acc / parts.div);
+}
+
+__global__ __launch_bounds__(kThreads) void loss_parts_kernel(LossParts parts, int W, float* losses) { finish_losses(parts, W, losses); }
+
 // Leaders as recorded by earlier calls (now) and, when the call selects, as they stand after the selection (chosen);
 // the first workgroup records the latter, and the losses.  All threads; ends behind a barrier.
 __device__ __forceinline__ void choose_leaders(const ColumnDev& s, Leaders& now, Leaders& chosen)
@@ -232,29 +262,8 @@ __device__ __forceinline__ void choose_leaders(const ColumnDev& s, Leaders& now,
     __shared__ float loss_s[kColumnMaxWorkers];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int W = s.a.W, G = s.a.G;
-    if (s.parts.n > 0) {
-        // every workgroup adds up the partial sums itself: a team of 8 to 256 lanes per worker, in double, in a fixed order
-        int team = kThreads;
-        while (team * W > kThreads) team >>= 1;
-        const int w = tid / team, l = tid % team;
-        double acc = 0.0;
-        if (w < W)
-            for (int i = l; i < s.parts.n; i += team) {
-                const int64_t at = (int64_t)w * s.parts.stride + i;
-                acc += s.parts.sums64 ? s.parts.sums64[at] : (double)s.parts.sums[at];
-            }
-        if (team > kWave) {                              // one or two workers
-            __shared__ double cross[kThreads / kWave];
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) acc += __shfl_xor(acc, d, kWave);
-            if (lane == 0) cross[tid / kWave] = acc;
-            __syncthreads();
-            acc = 0.0;
-            for (int q = 0; q < team / kWave; ++q) acc += cross[(w * team) / kWave + q];
-        } else {
-            for (int d = 1; d < team; d <<= 1) acc += __shfl_xor(acc, d, kWave);
-        }
-        if (w < W && l == 0) loss_s[w] = (float)(s.parts.c * acc);
+    if (s.parts.n > 0) {                                 // every workgroup adds up the partial sums itself
+        finish_losses(s.parts, W, loss_s);
         __syncthreads();
     }
     if (tid < kWave) {
@@ -373,6 +382,12 @@ void launch_vec(const ColumnDev& s, bool mom, bool nt, hipStream_t st)
 }
 
 } // namespace
+
+hipError_t launch_loss_parts(const LossParts& parts, int W, float* losses, hipStream_t stream)
+{
+    hipLaunchKernelGGL(loss_parts_kernel, dim3(1), dim3(kThreads), 0, stream, parts, W, losses);
+    return hipGetLastError();
+}
 
 hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStream_t stream)
 {

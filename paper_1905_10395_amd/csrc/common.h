@@ -44,15 +44,18 @@ struct RefreshBits {
 // Records the message lsgd_last_error() returns on this thread and hands the status back.
 lsgd_status set_error(lsgd_status st, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 
-// Losses left as partial sums: losses[w] = c * sum of sums[w * stride + 0 .. n) (n = 0: they are finished).
+constexpr int kColumnMaxWorkers = 64;   // one wavefront selects (column_step.hip)
+
+// Losses left as partial sums: losses[w] = c * (sum of sums[w * stride + 0 .. n)) / div  (n = 0: they are finished).
 constexpr int kLossPartsMax = 1024;     // workers x partial sums up to which the next launch adds them up itself
 struct LossParts {
     const float* sums;      // or, when sums64 is not NULL:
     const double* sums64;
     int64_t stride;
     int n;
-    double c;
+    double c, div;
 };
+inline bool loss_parts_ok(int W, int n) { return n > 0 && W <= kColumnMaxWorkers && (int64_t)W * n <= kLossPartsMax; }
 
 // ---- kernels' host launchers (each returns the hipError_t of its launches) ----
 hipError_t launch_init_state(const DeviceState& st, int W, int G, hipStream_t s);
@@ -83,7 +86,6 @@ struct PullParams {
 hipError_t launch_pull_update(const PullParams& p, const DeviceState& st, hipStream_t s);
 
 // Selection and update of a small or medium population in one launch (column_step.hip).
-constexpr int kColumnMaxWorkers = 64;   // one wavefront selects
 struct ColumnStep {
     PullParams pull;
     int update;              // gradient step with pull's coefficients
@@ -99,6 +101,8 @@ struct ColumnStep {
     double center_rate;
 };
 hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStream_t s);
+// The losses alone, bit for bit as the launch above finishes them (loss_parts_ok).
+hipError_t launch_loss_parts(const LossParts& parts, int W, float* losses, hipStream_t s);
 
 hipError_t launch_smooth_losses(float* window, int K, int64_t t, const float* losses, int W, float* out, hipStream_t s);
 hipError_t launch_easgd_center(const float* x, int W, int64_t P, int64_t ld, float* center, float* old_center, double a, hipStream_t s);

@@ -785,14 +785,18 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
                                const lsgd_mc_batch& b, const DeviceState& st, hipStream_t s, LossParts* parts)
 {
     const int64_t nb = mc_entries(b);
-    // the partial sums are added up by a launch of their own, or left to a caller that says it can
-    auto finish_loss = [&](int workers, int n, const double* sums64) {
-        if (parts && n > 0 && (int64_t)workers * n <= kLossPartsMax) {
-            parts->sums = st.partials; parts->sums64 = sums64; parts->stride = n; parts->n = n; parts->c = (double)b.c;
+    // the partial sums are added up by a launch of their own, or left to a caller that says it can; few of them in one
+    // order either way, so that a step and the calls it is made of find the same losses
+    auto finish_loss = [&](int n, const double* sums64) {
+        if (loss_parts_ok(W, n)) {
+            LossParts p;
+            p.sums = st.partials; p.sums64 = sums64; p.stride = n; p.n = n; p.c = (double)b.c; p.div = 1.0;
+            if (!parts) return launch_loss_parts(p, W, losses, s);
+            *parts = p;
         } else if (sums64) {
-            hipLaunchKernelGGL((mc_loss_finish_kernel<double>), dim3((unsigned)workers), dim3(256), 0, s, sums64, n, b.c, losses);
+            hipLaunchKernelGGL((mc_loss_finish_kernel<double>), dim3((unsigned)W), dim3(256), 0, s, sums64, n, b.c, losses);
         } else {
-            hipLaunchKernelGGL((mc_loss_finish_kernel<float>), dim3((unsigned)workers), dim3(256), 0, s, st.partials, n, b.c, losses);
+            hipLaunchKernelGGL((mc_loss_finish_kernel<float>), dim3((unsigned)W), dim3(256), 0, s, st.partials, n, b.c, losses);
         }
         return hipGetLastError();
     };
@@ -811,7 +815,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         else launch_side_lanes<1>(x, g, W, ld, b, S, st.partials, mc_runs(cost, W), s);
         if (ld > P)
             hipLaunchKernelGGL(mc_zero_pad_kernel, dim3((unsigned)((ld - P + 255) / 256), (unsigned)W), dim3(256), 0, s, g, P, ld);
-        return finish_loss(W, S.nbinsU, nullptr);
+        return finish_loss(S.nbinsU, nullptr);
     }
     const int nblk = (int)((nb + kMcEntriesPerBlock - 1) / kMcEntriesPerBlock);
     // the block sums of squares stay in double where the binned path's scratch, idle now, has room for them (always for
@@ -843,7 +847,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
 #undef LSGD_MC_LAUNCH
 #undef LSGD_MC_LAUNCH_AS
     }
-    return finish_loss(W, nblk, sums64);
+    return finish_loss(nblk, sums64);
 }
 
 // Objective values only: the residual pass of the general path without its atomics, one partial sum per

@@ -604,12 +604,13 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, floa
             if (backward) { a.out = sc16 + p.d[L]; a.outT = sc16 + p.dT[L]; a.sOut = sW16; }
             a.pad = ld > P ? g : nullptr; a.pad_from = P; a.pad_to = ld;
             launch_gemm_ragged(a, W, EPI_HEAD, s);
-            if (tiles > 1) {
-                if (parts && (int64_t)W * tiles <= kLossPartsMax) {
-                    parts->sums64 = a.loss_parts; parts->stride = a.sLoss; parts->n = tiles; parts->c = 1.0 / (double)B;
-                } else {
-                    hipLaunchKernelGGL(loss_finish_kernel, dim3((unsigned)((W + 3) / 4)), dim3(256), 0, s, a.loss_parts, a.sLoss, tiles, W, (double)B, losses);
-                }
+            if (tiles > 1 && loss_parts_ok(W, tiles)) {        // one order, whoever adds them up
+                LossParts q;
+                q.sums = nullptr; q.sums64 = a.loss_parts; q.stride = a.sLoss; q.n = tiles; q.c = 1.0; q.div = (double)B;
+                if (!parts) return launch_loss_parts(q, W, losses, s);
+                *parts = q;
+            } else if (tiles > 1) {
+                hipLaunchKernelGGL(loss_finish_kernel, dim3((unsigned)((W + 3) / 4)), dim3(256), 0, s, a.loss_parts, a.sLoss, tiles, W, (double)B, losses);
             }
             return hipGetLastError();
         } else {

@@ -115,3 +115,23 @@ def test_easgd_both_routes(W, P, ld):
     step = g0.astype(np.float64) + np.float64(np.float32(0.1)) * (x0.astype(np.float64) - c0.astype(np.float64))
     np.testing.assert_allclose(pr.x.cpu().numpy()[:, :P], (x0 - np.float64(np.float32(0.05)) * step)[:, :P], rtol=3e-7, atol=3e-9)
     assert pr.pop.get_losses() == pr.losses_dev.tolist()
+
+
+def test_step_and_separate_calls_find_the_same_mlp_losses():
+    """Partial loss sums are added up by the update's launch or by a launch of their own: the same bits.  Half of the 150
+    samples lose 62, the others the next float: the mean is a tie that rounds to 62 unless it comes out a bit too high."""
+    W, B, dims = 2, 150, [8, 2]
+    P = 18
+    x0 = np.zeros((W, 64), np.float32)
+    x0[:, 8] = 2.0 ** -18                            # class 1's first weight; its bias:
+    x0[:, 17] = 62.0
+    X = np.zeros((W, B, 8), np.float32)
+    X[:, ::2, 0] = 1.0
+    batch = L.MLPBatch(dims, dev(X).to(torch.bfloat16), dev(np.zeros((W, B), np.int32)))
+    for call in ("step", "grad_loss", "loss"):
+        pr = Pair(x0, [0, W], P=P, shadow=True, largest_batch=batch)
+        if call == "step":
+            pr.pop.step(batch, 0.0, 0.0, 0.0)
+        else:
+            getattr(pr.pop, call)(batch)
+        assert pr.pop.get_losses() == [62.0] * W, call

@@ -110,7 +110,7 @@ def test_step_finishes_the_loss_sums_in_the_update(W, B):
     pr.pop.step(batch, 0.01, 0.1, 0.05)
     torch.cuda.synchronize()
     np.testing.assert_allclose(pr.pop.get_losses(), pr.ora.losses, rtol=1e-5)
-    np.testing.assert_allclose(pr.pop.get_losses(), sep.pop.get_losses(), rtol=1e-6)
+    assert pr.pop.get_losses() == sep.pop.get_losses()       # few sums: one order, whoever adds them up
     assert pr.pop.get_leaders() == sep.pop.get_leaders()
     pr.ora.select(); pr.ora.update(0.01, 0.1, 0.05)
     pr.check_state(1e-6)
