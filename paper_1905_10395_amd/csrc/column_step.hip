@@ -370,8 +370,10 @@ void launch_vec(const ColumnDev& s, bool mom, bool nt, hipStream_t st)
                            grid, dim3(kThreads), 0, st, s);
     };
     auto with_kind = [&](auto stream, auto center) {
-        if (mom) go(std::integral_constant<int, 1>{}, stream, center);
-        else go(std::integral_constant<int, 0>{}, stream, center);
+        if constexpr (VEC < 4) {                             // four columns per thread: without momentum only
+            if (mom) { go(std::integral_constant<int, 1>{}, stream, center); return; }
+        }
+        go(std::integral_constant<int, 0>{}, stream, center);
     };
     auto with_stream = [&](auto center) {
         if (nt) with_kind(std::true_type{}, center);
