@@ -1,6 +1,7 @@
-"""GPU parity of the two routes of the update: the one-launch update by column owners (up to 32 workers) and the row
-streams (more), on the same inputs against the CPU oracle, at the edges of column tiles, row batches and groups; and
-the one-launch step against the same step made by the separate calls."""
+"""GPU parity of the two routes of the update: the one-launch update by column owners (small and medium populations of up to
+32 workers in groups of a few) and the row streams (all others), on the same inputs against the CPU oracle, at the edges
+of column tiles, row batches and groups; the one-launch step against the same step by row streams, and against the calls
+it is made of."""
 import numpy as np
 import pytest
 import torch
@@ -13,13 +14,19 @@ pytestmark = pytest.mark.gpu
 
 # W, group offsets, P, ld
 SHAPES = [
-    (1, [0, 1], 1, 1),                               # one of everything
-    (2, [0, 1, 2], 255, 256),                        # one thread short of a workgroup, groups of one
+    (1, [0, 1], 1, 1),                               # row streams: one worker, one column
+    (2, [0, 1, 2], 255, 256),                        # row streams: groups of one
+    (2, [0, 2], 1, 1),                               # one column
+    (4, [0, 4], 255, 256),                           # one thread short of a workgroup
+    (2, [0, 2], 257, 257),                           # one thread past it, odd stride: one column per thread
     (6, [0, 2, 4, 6], 301, 320),                     # pairs: one launch only where something is re-selected
-    (7, [0, 1, 7], 257, 257),                        # odd stride: one column per thread
+    (7, [0, 1, 7], 257, 257),                        # groups of one and six
+    (20, [0, 9, 20], 1, 1),                          # separate calls by row streams: small, more than 16 workers
+    (20, [0, 9, 20], 255, 256),
     (32, [0, 9, 17, 32], 1027, 1088),                # groups of 9, 8 and 15 rows: remainders of the row batch
     (33, [0, 9, 17, 33], 1027, 1088),                # row streams
-    (9, [0, 4, 9], 500_003, 500_032),                # more columns per thread, ragged last one; streaming accesses without momentum
+    (9, [0, 4, 9], 500_003, 500_032),                # two columns per thread without momentum, ragged last one; streaming accesses
+    (2, [0, 2], 1_000_003, 1_000_064),               # four columns per thread without momentum, three left over
 ]
 OPTIONS = [(0.0, 0, 0.0), (0.9, L.NESTEROV, 1e-2), (0.9, L.LEADER_EXEMPT, 0.0), (0.5, L.MOMENTUM_GRAD_ONLY, 0.0),
            (0.0, L.PULL_UNSCALED_BY_ETA, 0.0)]
@@ -49,7 +56,8 @@ def test_whole_step_matches_oracle(W, off, P, ld, mu, flags, wd):
 @pytest.mark.parametrize("W,off,P,ld", SHAPES)
 def test_one_call_equals_separate_calls(W, off, P, ld, mu):
     """lsgd_step and lsgd_step_alg1 against the calls they are made of: the same expressions on the same values, so
-    parameters, momentum, copies and leaders agree bit for bit."""
+    parameters, momentum, copies and leaders agree bit for bit.  (Up to 16 workers the pull that follows a selection of its
+    own is by column owners too; with 20, 32 and 33 it is by row streams.)"""
     G = len(off) - 1
     x0, g0, _ = wl.stress_state(W, P, ld, seed=W)
     res = []
@@ -79,6 +87,27 @@ def test_one_call_equals_separate_calls(W, off, P, ld, mu):
     assert all(torch.equal(a[k], b[k]) for k in range(3)) and a[3] == b[3]
 
 
+@pytest.mark.parametrize("mu,flags,wd", OPTIONS)
+@pytest.mark.parametrize("W,off,P,ld", SHAPES)
+def test_step_equals_row_streams(W, off, P, ld, mu, flags, wd):
+    """lsgd_step against lsgd_select_pull_static, which has the row streams whatever the size: bit for bit."""
+    G = len(off) - 1
+    x0, g0, _ = wl.stress_state(W, P, ld, seed=W + 1)
+    one = Pair(x0, off, P=P, momentum=mu, flags=flags, weight_decay=wd)
+    one.g.copy_(dev(g0))
+    x, g, m = one.x.clone(), one.g.clone(), (None if one.m is None else one.m.clone())
+    lead = torch.zeros(G + 1, dtype=torch.int32, device="cuda:0")
+    for t in range(2):
+        losses = dev(wl.stress_losses(W, t, seed=G))
+        one.pop.step(L.ExternalBatch(losses), 0.05, 0.1, 0.05)
+        L.select_pull_static(x, g, losses, G, 0.05, 0.1, 0.05, m=m, P=P, group_offsets=off, momentum=mu, weight_decay=wd,
+                             flags=flags, leaders=lead)
+        torch.cuda.synchronize()
+        local, gl = one.pop.get_leaders()
+        assert local + [gl] == lead.tolist()
+        assert torch.equal(one.x, x) and (m is None or torch.equal(one.m, m))
+
+
 def test_ties_nan_and_infinite_losses_select_alike():
     """Selection inside the one-launch step against the selection kernel: ties to the lowest index, NaN as +inf,
     -0 = +0, whole groups without a finite loss."""
@@ -94,10 +123,10 @@ def test_ties_nan_and_infinite_losses_select_alike():
         assert one.pop.get_leaders() == two.pop.get_leaders()
 
 
-@pytest.mark.parametrize("W,P,ld", [(5, 1030, 1088), (16, 1030, 1088), (17, 1030, 1088), (16, 60_001, 60_032)])
+@pytest.mark.parametrize("W,P,ld", [(5, 1030, 1088), (16, 1030, 1088), (17, 1030, 1088), (16, 60_001, 60_032), (17, 240_001, 240_064), (20, 220_003, 220_032)])
 def test_easgd_both_routes(W, P, ld):
-    """Center and rows, one launch (small populations; streaming accesses at 60 001 columns) or two: center bit-exact
-    (one order of the sum, one rounding)."""
+    """Center and rows, one launch (up to 16 workers; more between 80 and 250 MB; streaming accesses at 60 001 columns) or
+    two: center bit-exact (one order of the sum, one rounding)."""
     x0, g0, _ = wl.stress_state(W, P, ld, seed=W)
     pr = Pair(x0, [0, W], P=P, momentum=0.9)
     c0 = x0[0].astype(np.float32).copy()

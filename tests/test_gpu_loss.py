@@ -57,7 +57,7 @@ def test_mc_loss_of_an_empty_batch_is_zero():
 
 
 @pytest.mark.parametrize("dims,W,B", [
-    ([12, 16, 5], 2, 9),                      # vector-ALU path
+    ([12, 16, 5], 2, 9),                      # any-shape kernel
     ([192, 256, 128, 10], 3, 128),            # MFMA tiles
     ([64, 512, 10], 64, 256),                 # whole batch per tile
     ([3072, 512, 512, 10], 4, 256),

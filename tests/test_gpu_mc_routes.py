@@ -103,7 +103,8 @@ def test_workspace_without_binned_scratch():
 
 @pytest.mark.parametrize("W,B", [(1, 700), (2, 40000), (3, 300), (8, 300), (32, 300)])
 def test_step_finishes_the_loss_sums_in_the_update(W, B):
-    """lsgd_step leaves the partial loss sums to the update's launch: losses, leaders and the step as from the calls."""
+    """lsgd_step leaves the partial loss sums to the update's launch (not with one worker, nor with more sums than that
+    adds up): losses, leaders and the step as from the calls."""
     pr, batch, P = problem(500, 300, 5, 20000, W, B, seed=W)
     sep, _, _ = problem(500, 300, 5, 20000, W, B, seed=W)
     sep.pop.grad_loss(batch); sep.pop.select_leaders()

@@ -64,7 +64,7 @@ def check_grads(g_gpu, g_ora, dims):
 
 
 SHAPES = [
-    ([12, 16, 5], 2, 9),                      # tiny, vector-ALU path everywhere
+    ([12, 16, 5], 2, 9),                      # tiny, any-shape kernel everywhere
     ([20, 24, 16, 8, 4], 3, 13),              # 4 layers, ragged
     ([192, 256, 128, 10], 3, 128),            # MFMA 128x64 tiles: forward, d-input, d-weight
     ([512, 1024, 10], 8, 128),                # d-weight on 128x128 tiles
@@ -268,7 +268,7 @@ FUSED_CASES = [
     ([192, 256, 10], 8, 2, 128, 0.5, L.MOMENTUM_GRAD_ONLY | L.NESTEROV, 1e-3),
     ([192, 256, 10], 8, 2, 128, 0.9, L.LEADER_EXEMPT, 0.0),
     ([192, 256, 10], 8, 2, 128, 0.0, L.PULL_UNSCALED_BY_ETA, 0.0),
-    ([100, 70, 10], 6, 3, 50, 0.9, 0, 0.0),                                     # vector-ALU kernels only
+    ([100, 70, 10], 6, 3, 50, 0.9, 0, 0.0),                                     # any-shape kernels only
     ([512, 512, 10], 64, 8, 64, 0.9, 0, 0.0),                                   # 256x256 tiles
     ([256, 128, 128, 10], 8, 2, 64, 0.9, 0, 0.0),                               # two hidden layers
 ]

@@ -16,10 +16,18 @@ SHAPES = [
     ([9, 65, 2], 3, 33),          # one past the tile in every direction, two classes
     ([63, 130, 7], 2, 31),        # odd rows: every row of W starts on another 2-byte boundary
     ([136, 128, 16], 2, 64),      # multiples of 8 that are no multiples of a K step
-    ([257, 191, 10], 12, 65),     # 64-row tile, remainders in m, n and k
+    ([257, 191, 10], 12, 65),     # 32-row tiles (few of them), remainders in m, n and k
     ([129, 1100, 65], 16, 127),   # 128-row tile, classes past one column tile
-    ([640, 2050, 10], 9, 130),    # five K steps, two row tiles
+    ([640, 2050, 10], 9, 130),    # five K steps, 128 x 128 forward tiles, two of rows
     ([383, 515, 100], 5, 300),
+    ([96, 70, 33], 3, 32),        # classifier of 33 to 64 classes: 64-column head, one row tile,
+    ([200, 150, 50], 4, 33),      # two,
+    ([130, 257, 64], 5, 100),     # four, all columns used
+    ([1030, 40, 10], 2, 33),      # hidden layer on 32 x 32 tiles of sixteen wavefronts: long contraction, few tiles
+    ([2050, 33, 40], 3, 31),
+    ([257, 1030, 100], 16, 50),   # 64-row tiles, forward and d-input (double sums every other instruction)
+    ([300, 1030], 16, 50),        # logits of more than 64 classes: 64-row tiles
+    ([137, 1030], 16, 130),       # ... 128-row tiles, two of them
 ]
 
 
@@ -36,7 +44,7 @@ def test_ragged_grad_loss_matches_oracle(dims, W, B):
     assert np.all(g[:, P:] == 0)
 
 
-@pytest.mark.parametrize("dims,W,B", [SHAPES[0], SHAPES[2], SHAPES[3], SHAPES[5], SHAPES[7]])
+@pytest.mark.parametrize("dims,W,B", [SHAPES[0], SHAPES[2], SHAPES[3], SHAPES[5], SHAPES[7], SHAPES[10], SHAPES[12], SHAPES[14]])
 def test_ragged_fused_update_equals_the_three_call_step(dims, W, B):
     """The update inside the d-weight kernels against gradient + update: the same expression up to the rounding of
     its fused multiply-adds, element by element; nothing outside the parameters is written."""
