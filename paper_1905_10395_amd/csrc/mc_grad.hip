@@ -836,7 +836,8 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
 #define LSGD_MC_LAUNCH_AS(S, FLY)                                                                               \
     hipLaunchKernelGGL((mc_grad_atomic_kernel<S, true, FLY>), grid, dim3(mc_atomic_threads(S, FLY)), 0, s, x, g, ld, b.m, b.n, b.r, \
                        b.rows, b.cols, b.vals, b.batch_idx, nb, two_c, st.partials, sums64, nblk, b.entries)
-#define LSGD_MC_LAUNCH(S) do { if (route == kMcFlight) LSGD_MC_LAUNCH_AS(S, true); else LSGD_MC_LAUNCH_AS(S, false); } while (0)
+// (ranks 1 and 2 have short chains anyway: the estimate never gives them entries in flight)
+#define LSGD_MC_LAUNCH(S) do { if (route == kMcFlight) LSGD_MC_LAUNCH_AS(S, (S > 2)); else LSGD_MC_LAUNCH_AS(S, false); } while (0)
         if (b.r <= 1) LSGD_MC_LAUNCH(1);
         else if (b.r <= 2) LSGD_MC_LAUNCH(2);
         else if (b.r <= 4) LSGD_MC_LAUNCH(4);

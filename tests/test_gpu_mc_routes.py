@@ -44,10 +44,10 @@ def test_both_routes_match_oracle(r, B):
 
 
 # one side of few rows, many entries: the atomics an entry at a time
-@pytest.mark.parametrize("m,n", [(90, 4000), (4000, 61)])
+@pytest.mark.parametrize("W,m,n", [(4, 90, 4000), (9, 4000, 61)])     # (628 and 1413 loss sums)
 @pytest.mark.parametrize("r", [1, 2, 3, 5, 6, 7, 9, 16, 17, 33, 64, 67])
-def test_narrow_side_matches_oracle(r, m, n):
-    pr, batch, P = problem(m, n, r, 60000, 4, 40000, seed=r)
+def test_narrow_side_matches_oracle(r, W, m, n):
+    pr, batch, P = problem(m, n, r, 60000, W, 40000, seed=r)
     pr.g.fill_(float("nan"))
     pr.pop.grad_loss(batch)
     torch.cuda.synchronize()
