@@ -12,9 +12,11 @@
 // bytes and shifted into place (zeros behind it) on its way to LDS, so the K loop has no branches per lane.
 //
 // Tiles.  These shapes are small or have few rows per weight, so what counts is to have enough bytes in flight on
-// enough compute units, not flops per LDS byte: BN = 64 columns, 32 / 64 / 128 rows.  With 32 or 64 rows (a whole
-// small batch) the wavefronts split the contraction of one tile among them (K steps of 128, a quarter or a half
-// each) instead of splitting the rows.
+// enough compute units, not flops per LDS byte: BN = 64 columns, 32 / 64 / 128 rows.  With 32 rows, and in the forward
+// and d-input products with 64 (a whole small batch), the wavefronts split the contraction of one tile among them (K
+// steps of 128, a quarter or a half each; 64 where the contraction is one step) instead of splitting the rows.  Few tiles
+// with a long contraction take 32 x 32 tiles of sixteen wavefronts and K steps of 512, large forward batches 128 x 128
+// tiles (launch_head, launch_epi).
 //
 // Sums.  One chain of v_mfma_f32_32x32x16_bf16 rounds its fp32 accumulator once per 16 products: measured 1.6e-7 of
 // the result at K = 784 and 3.2e-7 at K = 3072 (normal operands), where a plain dot product spread over 64 lanes
@@ -25,9 +27,9 @@
 // become the limit (5.7e-8; 105 against 81 us without sums on 500 x 3072 x 1024, 16 workers).
 //
 // Measured (whole passes, against one-thread-per-output vector-ALU kernels that re-read an operand per output):
-// gradients of 3072-1024-512-10, 16 workers, batch 32: 19.7 ms -> 0.15 ms; objective of 3072-1024-10, 16 workers,
-// batch 500: 16.2 -> 0.11 ms (first product 0.105 ms = 480 TFLOP/s); whole step of 784-300-100-10, 8 workers,
-// batch 50: 1.26 -> 0.075 ms (5 to 8 us per product: launch and fill, not work).
+// gradients of 3072-1024-512-10, 16 workers, batch 32: 19.7 ms -> 0.10 ms; objective of 3072-1024-10, 16 workers,
+// batch 500: 16.2 -> 0.09 ms (first product 0.087 ms = 570 TFLOP/s); whole step of 784-300-100-10, 8 workers,
+// batch 50: 1.26 -> 0.062 ms (3 to 6 us per product: launch and fill, not work).
 #include <type_traits>
 
 #include "mlp_common.h"
@@ -37,7 +39,6 @@ namespace lsgd {
 namespace {
 
 constexpr int kXcds = 8;
-
 
 __device__ __forceinline__ u32x4 load16(const uint16_t* p) { return *reinterpret_cast<const u32x4_any*>(p); }
 // weights: read by one tile row, or by a few workgroups of one die at a time, and not again in this launch
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
                 store_lds(1, kt + 1, qa, qb, true);
                 load_global(kt + 3, qa, qb);
                 compute(0);
-                    __syncthreads();
+                __syncthreads();
                 store_lds(0, kt + 2, ra, rb, true);
                 load_global(kt + 4, ra, rb);
                 compute(1);
