@@ -33,29 +33,32 @@ import torch
 import workloads as wl
 
 # Bytes between the L2 caches and memory per launch, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by
-# reference kernels of known size (profiles/*_hbm_traffic.md).  Valid only for the kernel source they were
-# taken on: reported as null once that file's code (comments and white space aside) differs.
-PULL_TRAFFIC = {"file": "pull_update.hip", "code_sha256_16": "0c447222cfc3c9dd", "bytes_per_launch": 7.666e9,
+# reference kernels of known size (profiles/*_hbm_traffic.md).  Valid only for the kernel sources they were
+# taken on: reported as null once the code of any of these files (comments and white space aside) differs.
+PULL_TRAFFIC = {"files": ("pull_update.hip", "pull_common.h", "update_math.h"), "code_sha256_16": "32c416ddd7e5bca5", "bytes_per_launch": 7.666e9,
                 "key": (32, 11_689_512)}
-MC_TRAFFIC = {"file": "mc_grad.hip", "code_sha256_16": "bd8ef4362cfe623f", "bytes_per_launch": 3.929e8,
+MC_TRAFFIC = {"files": ("mc_grad.hip",), "code_sha256_16": "17d30dada7d4797a", "bytes_per_launch": 3.935e8,
               "key": (16, 65536, 20000, 20000, 32)}
+CSRC = os.path.join(ROOT, "paper_1905_10395_amd", "csrc")
 
 
-def _code_fingerprint(path):
-    """sha256 of a source file with comments and white space removed (a reworded comment keeps the counters valid)"""
+def _code_fingerprint(paths):
+    """sha256 of source files with comments and white space removed (a reworded comment keeps the counters valid)"""
     import hashlib
     import re
-    text = open(path, "r").read()
-    text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
-    text = re.sub(r"//[^\n]*", "", text)
-    text = re.sub(r"\s+", "", text)
-    return hashlib.sha256(text.encode()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for path in paths:
+        text = open(path, "r").read()
+        text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
+        text = re.sub(r"//[^\n]*", "", text)
+        text = re.sub(r"\s+", "", text)
+        h.update(text.encode())
+    return h.hexdigest()[:16]
 
 
 def _traffic(rec, key):
-    src = os.path.join(ROOT, "paper_1905_10395_amd", "csrc", rec["file"])
     try:
-        cur = _code_fingerprint(src)
+        cur = _code_fingerprint(os.path.join(CSRC, f) for f in rec["files"])
     except OSError:
         return None
     if cur != rec["code_sha256_16"] or tuple(key) != tuple(rec["key"]):
