@@ -250,7 +250,7 @@ __device__ __forceinline__ void finish_losses(const LossParts& parts, int W, flo
     } else {
         for (int d = 1; d < team; d <<= 1) acc += __shfl_xor(acc, d, kWave);
     }
-    if (w < W && l == 0) losses[w] = (float)(parts.c * acc / parts.div);
+    if (w < W && l == 0) losses[w] = (float)(parts.c * acc / (double)parts.div);
 }
 
 __global__ __launch_bounds__(kThreads) void loss_parts_kernel(LossParts parts, int W, float* losses) { finish_losses(parts, W, losses); }

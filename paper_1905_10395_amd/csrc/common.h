@@ -52,8 +52,8 @@ struct LossParts {
     const float* sums;      // or, when sums64 is not NULL:
     const double* sums64;
     int64_t stride;
-    int n;
-    double c, div;
+    int n, div;
+    double c;
 };
 inline bool loss_parts_ok(int W, int n) { return n > 0 && W <= kColumnMaxWorkers && (int64_t)W * n <= kLossPartsMax; }
 

@@ -790,7 +790,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
     auto finish_loss = [&](int n, const double* sums64) {
         if (loss_parts_ok(W, n)) {
             LossParts p;
-            p.sums = st.partials; p.sums64 = sums64; p.stride = n; p.n = n; p.c = (double)b.c; p.div = 1.0;
+            p.sums = st.partials; p.sums64 = sums64; p.stride = n; p.n = n; p.c = (double)b.c; p.div = 1;
             if (!parts) return launch_loss_parts(p, W, losses, s);
             *parts = p;
         } else if (sums64) {

@@ -606,7 +606,7 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, floa
             launch_gemm_ragged(a, W, EPI_HEAD, s);
             if (tiles > 1 && loss_parts_ok(W, tiles)) {        // one order, whoever adds them up
                 LossParts q;
-                q.sums = nullptr; q.sums64 = a.loss_parts; q.stride = a.sLoss; q.n = tiles; q.c = 1.0; q.div = (double)B;
+                q.sums = nullptr; q.sums64 = a.loss_parts; q.stride = a.sLoss; q.n = tiles; q.c = 1.0; q.div = B;
                 if (!parts) return launch_loss_parts(q, W, losses, s);
                 *parts = q;
             } else if (tiles > 1) {
