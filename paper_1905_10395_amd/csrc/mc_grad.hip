@@ -650,15 +650,15 @@ static McCost mc_cost(int W, const lsgd_mc_batch& b, int vw)
     const double meet = nb / (lo * r > 16 ? lo * r / 16 : 1.0) * (0.0068 + 0.0045 * (r < 16 ? r : 16));
     int group = 1;                                                      // lanes per entry
     while (group < b.r && group < kWave) group <<= 1;
-    const double turns = (b.r + group - 1) / group;
+    const double turns = ceil(r / group);
     McCost c;
     c.one = 5.7 + dominant(queue, meet, 1.3 * group * turns) + 1.1 * rows;
     c.flight = 5.7 + dominant(1.1 * queue, meet, 4.3 * (group > 32 ? group / 32 : 1) * turns) + 1.1 * rows;
     // Binned: one launch more; the records; and every factor row read and gradient row written, touched or not.
-    int lanes = 1;
+    int64_t lanes = 1;
     while (lanes * vw < b.r) lanes <<= 1;
-    c.walk = nb * (lo > kBinRows ? kBinRows / lo : 1.0) * (0.0046 + 0.00044 * lanes);
-    const double records = thousands * (0.026 + 0.0027 * lanes);
+    c.walk = nb * (lo > kBinRows ? kBinRows / lo : 1.0) * (0.0046 + 0.00044 * (double)lanes);
+    const double records = thousands * (0.026 + 0.0027 * (double)lanes);
     c.stream = records + 2.0 * rows;
     c.binned = 12.0 + dominant(c.walk, records) + 2.0 * rows;
     return c;
