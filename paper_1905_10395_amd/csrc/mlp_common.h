@@ -203,6 +203,11 @@ __device__ __forceinline__ void store_bias_grad(const GemmArgs& g, int w, int m,
     }
 }
 
+// Forward and d-input products of 16-byte aligned operands (mlp_gemm_direct.hip): M a multiple of 128, N and K of 64;
+// or, if it returns true, other sizes.
+void launch_gemm_direct(const GemmArgs& g, int W, int epi, hipStream_t s);
+bool launch_gemm_direct_any(const GemmArgs& g, int W, int epi, hipStream_t s);
+
 // Matrix products of any shape and alignment (mlp_gemm_ragged.hip).
 void launch_gemm_ragged(const GemmArgs& g, int W, int epi, hipStream_t s);
 

@@ -426,17 +426,17 @@ static bool try_mfma(const GemmArgs& g, int W, hipStream_t s)
     const int64_t blocks256 = (g.M % 256 == 0 && g.N % 256 == 0) ? (int64_t)(g.M / 256) * (g.N / 256) * W : 0;
     const int64_t blocks128 = (int64_t)(g.M / 128) * (g.N / 128) * W;
     // the fused update keeps two batches of x, m and leader values in registers: no room beside a 256x256 tile
-    // a 256-row tile covers a whole batch of 256: the weight operand is then read once instead of twice
-    const int64_t blocks_tall = (g.M % 256 == 0 && g.N % 128 == 0) ? (int64_t)(g.M / 256) * (g.N / 128) * W : 0;
     if constexpr (EPI != EPI_DWU) {
         if (blocks256 >= 256) { launch_gemm<256, 256, 2, 4, TRANS_B, EPI>(g, W, s); return true; }
     }
     if constexpr (EPI == EPI_FWD || EPI == EPI_DX) {
-        if (blocks_tall >= 256) { launch_gemm<256, 128, 4, 2, TRANS_B, EPI>(g, W, s); return true; }
-    }
+        launch_gemm_direct(g, W, EPI, s);
+        return true;
+    } else {
     if (g.N % 128 == 0 && blocks128 >= 256) launch_gemm<128, 128, 2, 2, TRANS_B, EPI>(g, W, s);
     else launch_gemm<128, 64, 2, 2, TRANS_B, EPI>(g, W, s);
     return true;
+    }
 }
 
 // Softmax cross-entropy of one worker's batch: loss = mean_b(lse - z[y]); delta = bf16((p - onehot)/B),
@@ -594,7 +594,7 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, floa
         a.bias = bias; a.sBias = ld;
         if (k < L) {
             a.out = sc16 + p.h[k]; a.sOut = sW16; a.ldout = dout;
-            if (!try_mfma<false, EPI_FWD>(a, W, s)) launch_gemm_ragged(a, W, EPI_FWD, s);
+            if (!try_mfma<false, EPI_FWD>(a, W, s) && !launch_gemm_direct_any(a, W, EPI_FWD, s)) launch_gemm_ragged(a, W, EPI_FWD, s);
         } else if (dout <= 64) {                               // logits, loss and output delta in one launch
             const int tiles = (B + 31) / 32;
             a.y = b.y;
@@ -656,7 +656,7 @@ hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int
             a.mask = Hin; a.sMask = sHin; a.ldmask = din;
             a.out = sc16 + p.d[k - 1]; a.sOut = sW16; a.ldout = din;
             a.outT = sc16 + p.dT[k - 1]; a.sOutT = sW16; a.ldoutT = B;
-            if (!try_mfma<true, EPI_DX>(a, W, s)) launch_gemm_ragged(a, W, EPI_DX, s);
+            if (!try_mfma<true, EPI_DX>(a, W, s) && !launch_gemm_direct_any(a, W, EPI_DX, s)) launch_gemm_ragged(a, W, EPI_DX, s);
         }
         // dW_k
         {
