@@ -418,22 +418,34 @@ lsgd_status do_select(lsgd_population* p, const float* losses, const uint8_t* re
 // re-selected 27 / 24, none 20 / 21; 32 x 100 000, 16 groups: 28 / 31, 17 / 27).  Between these sizes
 // the lines are interpolated; 240 drawn populations (1 to 64 workers, 500 to 8 million columns, all the calls that come
 // this way) against row streams alone: half of them change, by a third on average, and none gets more than 5 % slower.
+// Groups of one worker are walked together instead: 16 x 140 001 36 / 16 us, 16 x 1 250 001 with momentum (400 MB) 126 / 90,
+// half of the leaders kept 90 / 88, none re-selected 43 / 46 (8 x 1 250 001).
 bool column_step(const lsgd_population* p, bool selects)
 {
     const int W = p->cfg.W, G = p->cfg.n_groups;
     const double bytes = (p->cfg.momentum != 0.0f ? 20.0 : 12.0) * (double)W * (double)p->cfg.P;
+    if (W == G && W > 1) return selects && W <= 32 && bytes <= (W >= 8 ? 450e6 : 300e6);   // 4 x 5 000 000, three kept: 94 / 105
     if (W > 32 || bytes > 300e6) return false;
     if (selects) return W >= 4 * G || (W <= 16 && W >= 2 * G);
     return W >= 4 * G && (W <= 16 || bytes >= 30e6);                   // 32 x 30 000, 8 groups: 12.3 / 13.5
 }
 
-// The same for elastic averaging, whose rows are one group: 16 x 250 000 with momentum 21 / 16, 16 x 1 250 000 (400 MB)
-// 85 / 73, 32 x 300 000 (192 MB) 43 / 42, 32 x 600 000 (384 MB) 76 / 82,
-// 16 x 2 500 000 158 / 165, 32 x 10 000 11.6 / 12.2.
+// The same for an iteration of Algorithm 1 that communicates, which takes four launches otherwise: 16 x 1 250 001, 4 groups,
+// 105 / 62 us, 24 x 1 250 001 (360 MB) 145 / 79, 12 x 2 500 000 (360 MB) 144 / 89; of any group size (8 groups of one x
+// 1 250 001 75 / 44).
+bool column_alg1(const lsgd_population* p)
+{
+    const double bytes = (p->cfg.momentum != 0.0f ? 20.0 : 12.0) * (double)p->cfg.W * (double)p->cfg.P;
+    return p->cfg.W <= 32 && bytes <= 450e6;
+}
+
+// The same for elastic averaging, two launches and a copy of the losses otherwise: 4 x 1003 11.5 / 4.0, 16 x 271 117 with
+// momentum 27.8 / 18.3, 32 x 140 001 33.7 / 17.2, 32 x 600 000 with momentum (384 MB) 79.5 / 78.2, 24 x 1 250 001 with
+// (600 MB) 127 / 115.
 bool column_easgd(const lsgd_population* p)
 {
     const double bytes = (p->cfg.momentum != 0.0f ? 20.0 : 12.0) * (double)p->cfg.W * (double)p->cfg.P;
-    return p->cfg.W <= 16 ? bytes <= 450e6 : p->cfg.W <= 32 && bytes >= 80e6 && bytes <= 250e6;
+    return p->cfg.W <= 32 && bytes <= 650e6;
 }
 
 // comm: Algorithm 1's communication pull (lamL, lamG are its lambdas; eta unused).
@@ -691,7 +703,7 @@ lsgd_status lsgd_step_alg1(lsgd_population* pop, const lsgd_batch* batch, float 
     }
     // one launch for update, selection and communication pull; the workgroups then read only leaders that this call
     // does not re-record, so not while a selection is pending or the recorded leaders are exempt
-    if (communicate && column_step(pop, true) && !any_pending(pop) && !(pop->cfg.flags & LSGD_LEADER_EXEMPT)) {
+    if (communicate && column_alg1(pop) && !any_pending(pop) && !(pop->cfg.flags & LSGD_LEADER_EXEMPT)) {
         ColumnStep c{};
         st = column_losses(pop, batch, &c);
         if (st != LSGD_OK) return st;
@@ -741,21 +753,16 @@ lsgd_status lsgd_center(lsgd_population* pop, float* out)
     return LSGD_OK;
 }
 
-lsgd_status lsgd_easgd_update(lsgd_population* pop, float* center, float eta, float lambda)
+// losses: what the one-launch update does about this step's losses on the way (column_losses).
+static lsgd_status do_easgd(lsgd_population* pop, float* center, float eta, float lambda, const ColumnStep& losses)
 {
-    if (!pop) return fail(LSGD_ERR_INVALID_ARG, "population is NULL");
-    if (!center) return fail(LSGD_ERR_INVALID_ARG, "easgd_update: center is NULL");
-    lsgd_status st = check_scalars(eta, lambda, 0.0f);
-    if (st != LSGD_OK) return st;
-    if (!pop->Z) return fail(LSGD_ERR_STATE, "easgd_update keeps the pre-update center in z_snapshot, which is NULL");
-    if (any_pending(pop)) return fail(LSGD_ERR_STATE, "easgd_update: a leader selection is pending; elastic averaging uses no leaders");
     const int G = pop->cfg.n_groups;
     const double a = (double)pop->cfg.W * (double)eta * (double)lambda;
     PullParams q = pull_params(pop, eta, 0.0f, lambda, false, false);
     q.flags &= ~LSGD_LEADER_EXEMPT;          // nobody is a leader here
     hipError_t e;
     if (column_easgd(pop)) {
-        ColumnStep c{};
+        ColumnStep c = losses;
         c.pull = q; c.update = 1; c.center = center; c.center_rate = a;
         e = launch_column_step(c, pop->st, pop->stream);
         pop->z_valid[(size_t)G] = 0;         // that row no longer holds a leader
@@ -771,6 +778,17 @@ lsgd_status lsgd_easgd_update(lsgd_population* pop, float* center, float eta, fl
     return LSGD_OK;
 }
 
+lsgd_status lsgd_easgd_update(lsgd_population* pop, float* center, float eta, float lambda)
+{
+    if (!pop) return fail(LSGD_ERR_INVALID_ARG, "population is NULL");
+    if (!center) return fail(LSGD_ERR_INVALID_ARG, "easgd_update: center is NULL");
+    lsgd_status st = check_scalars(eta, lambda, 0.0f);
+    if (st != LSGD_OK) return st;
+    if (!pop->Z) return fail(LSGD_ERR_STATE, "easgd_update keeps the pre-update center in z_snapshot, which is NULL");
+    if (any_pending(pop)) return fail(LSGD_ERR_STATE, "easgd_update: a leader selection is pending; elastic averaging uses no leaders");
+    return do_easgd(pop, center, eta, lambda, ColumnStep{});
+}
+
 lsgd_status lsgd_easgd_step(lsgd_population* pop, const lsgd_batch* batch, float* center, float eta, float lambda)
 {
     if (!pop) return fail(LSGD_ERR_INVALID_ARG, "population is NULL");
@@ -781,9 +799,10 @@ lsgd_status lsgd_easgd_step(lsgd_population* pop, const lsgd_batch* batch, float
     if (any_pending(pop)) return fail(LSGD_ERR_STATE, "easgd_step: a leader selection is pending; elastic averaging uses no leaders");
     st = check_grad_loss(pop, batch);
     if (st != LSGD_OK) return st;
-    st = do_grad_loss(pop, batch, nullptr);
+    ColumnStep losses{};
+    st = column_easgd(pop) ? column_losses(pop, batch, &losses) : do_grad_loss(pop, batch, nullptr);
     if (st != LSGD_OK) return st;
-    return lsgd_easgd_update(pop, center, eta, lambda);
+    return do_easgd(pop, center, eta, lambda, losses);
 }
 
 lsgd_status lsgd_mc_pack_entries(const int32_t* rows, const int32_t* cols, const float* vals, int64_t n_obs,

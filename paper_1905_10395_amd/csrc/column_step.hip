@@ -14,6 +14,19 @@
 // gradients, row streams -> this kernel, us: 4 x 1003 14.6 -> 4.5; 12 x 271 117 with momentum and kept leaders
 // 24.6 -> 16.5; 16 x 250 000 with momentum 30.0 -> 17.3;
 // 16 x 1 250 000 without 62.5 -> 41.5; elastic averaging, 16 x 1 250 000 with momentum 85.3 -> 73.3.
+//
+// Four ways through the rows (launch_column_step), by what a thread has to wait for:
+//   the update of groups of several workers     group by group, the next rows' loads under way (update_columns)
+//   ... of groups of one, and Algorithm 1's     one pass over all rows, two batches ahead, whatever group they are in
+//   iterations of more than 8 workers           (stream_columns): groups one after the other would leave a single row in
+//                                               flight, and a communication pull behind the update would read x again.
+//                                               16 groups of one x 140 001 36 -> 16 us, x 1 250 001 102 -> 67; iteration of
+//                                               16 workers in 4 groups x 1 250 001 74 -> 60, of 24 144 -> 79
+//   Algorithm 1's iterations of up to 8         every row in registers (regs_update, regs_comm): 8 workers in 2 groups x
+//                                               2 500 000 81 -> 57
+//   elastic averaging                           every row in registers, x read once: 4 x 1003 6.5 -> 4.0, 16 x 1 250 001
+//                                               without momentum 54 -> 46, 32 x 140 001 34 -> 17 (but for many rows with
+//                                               momentum out of HBM: two passes)
 #include "pull_common.h"
 #include "select_common.h"
 
@@ -123,10 +136,198 @@ __device__ __forceinline__ void update_columns(const ColumnDev& s, const Leaders
     }
 }
 
-// Algorithm 1's communication pull: every re-selected leader is captured, groups that communicate are pulled to
-// their leader, then everyone to the global leader if that was re-selected.
-template <int VEC>
-__device__ __forceinline__ void comm_columns(const ColumnDev& s, const Leaders& L, int64_t col)
+// A thread's columns of row i of p: the row's address is the same in every lane, the column's is an offset of 32 bits
+// (launch_column_step sees to that), which keeps addresses out of the vector registers.
+template <class T>
+__device__ __forceinline__ T* at(T* p, int64_t ld, int i, uint32_t col)
+{
+    T* const row = p + (int64_t)i * ld;
+    return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(row) + (uintptr_t)(col * (uint32_t)sizeof(T)));
+}
+
+// Every row's values at a thread's columns.
+template <int VEC, int NR>
+struct Rows {
+    typename Vec<VEC>::type x[NR], g[NR], m[NR];
+};
+
+template <int VEC, int KIND, bool NT, int NR>
+__device__ __forceinline__ void load_rows(const ColumnDev& s, uint32_t col, Rows<VEC, NR>& r)
+{
+    using V = typename Vec<VEC>::type;
+    const PullDev& a = s.a;
+#pragma unroll
+    for (int u = 0; u < NR; ++u)
+        if (u < a.W) {
+            r.x[u] = NT ? ld_stream<VEC>(at(a.x, a.ld, u, col)) : ld_vec<VEC>(at(a.x, a.ld, u, col));
+            r.g[u] = s.update ? ld_stream<VEC>(at(a.g, a.ld, u, col)) : zero_of(V());
+            r.m[u] = (KIND == 1) ? (NT ? ld_stream<VEC>(at(a.m, a.ld, u, col)) : ld_vec<VEC>(at(a.m, a.ld, u, col))) : zero_of(V());
+        }
+}
+
+// Row `i` (the same in every lane).
+template <int VEC, int NR>
+__device__ __forceinline__ typename Vec<VEC>::type row_of(const Rows<VEC, NR>& r, int i)
+{
+    typename Vec<VEC>::type v = r.x[0];
+#pragma unroll
+    for (int u = 1; u < NR; ++u) {
+        const typename Vec<VEC>::type at = r.x[u];
+        v = u == i ? at : v;
+    }
+    return v;
+}
+
+template <int VEC, int KIND, bool NT>
+__device__ __forceinline__ void load_row(const ColumnDev& s, int i, uint32_t col, typename Vec<VEC>::type& x, typename Vec<VEC>::type& g,
+                                         typename Vec<VEC>::type& m)
+{
+    using V = typename Vec<VEC>::type;
+    const PullDev& a = s.a;
+    x = NT ? ld_stream<VEC>(at(a.x, a.ld, i, col)) : ld_vec<VEC>(at(a.x, a.ld, i, col));
+    g = s.update ? ld_stream<VEC>(at(a.g, a.ld, i, col)) : zero_of(V());
+    m = (KIND == 1) ? (NT ? ld_stream<VEC>(at(a.m, a.ld, i, col)) : ld_vec<VEC>(at(a.m, a.ld, i, col))) : zero_of(V());
+}
+
+template <int VEC, int KIND, bool NT>
+__device__ __forceinline__ void load_batch(const ColumnDev& s, int i, uint32_t col, RowBatch<VEC>& b)
+{
+#pragma unroll
+    for (int u = 0; u < kRowsInFlight<VEC>; ++u)
+        if (i + u < s.a.W) load_row<VEC, KIND, NT>(s, i + u, col, b.x[u], b.g[u], b.m[u]);
+}
+
+// !COMM: the update of groups of one worker.  COMM: the update, if there is one, and Algorithm 1's communication pull
+// behind it: every leader re-selected by then is captured, groups that communicate are pulled to their leader, then
+// everyone to the global leader if that was re-selected.  One pass over the rows, two batches of loads ahead; what the
+// pull needs of a leader's row is its value after the update, which is worked out from that row when its group begins.
+// `before`: the leaders that the update pulls to, `after`: those of the communication pull.
+template <int VEC, int KIND, bool NT, bool COMM>
+__device__ __forceinline__ void stream_columns(const ColumnDev& s, const Leaders& before, const Leaders& after, uint32_t col, RowBatch<VEC>& cur,
+                                               RowBatch<VEC>& next)
+{
+    using V = typename Vec<VEC>::type;
+    constexpr int R = kRowsInFlight<VEC>;
+    const PullDev& a = s.a;
+    const bool pullL = a.lamL != 0.0f && s.update, pullG = a.lamG != 0.0f && s.update;
+    const bool exempt = !COMM && (a.flags & LSGD_LEADER_EXEMPT) != 0;
+    const Coef c = make_coef<V>(a);
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    // a re-selected leader's row belongs to the group that reads it, and the global leader's is read before any row
+    // is written: both are as they were
+    auto local_leader = [&](int j, int lead, int fresh) { return ld_vec<VEC>(fresh ? at(a.x, a.ld, lead, col) : at(a.Z, a.ld, j, col)); };
+    const int gl = uni(before.gl), freshG = uni(before.freshG);
+    V zg = zero_of(V());
+    if (pullG) zg = ld_vec<VEC>(freshG ? at(a.x, a.ld, gl, col) : at(a.Z, a.ld, a.G, col));
+    int lead = uni(before.lead[0]), fresh = uni(before.fresh[0]);
+    const bool own = !COMM;                              // groups of one: a re-selected leader is the row itself
+    V nzl = zero_of(V());
+    if (pullL && !(own && fresh)) nzl = local_leader(0, lead, fresh);
+    // communication pull: the leaders' values after the update
+    V zgc = zero_of(V()), nlx = zero_of(V()), nlg = zero_of(V()), nlm = zero_of(V());
+    int clead = 0, cfresh = 0, cfreshG = 0;
+    if (COMM) {
+        cfreshG = uni(after.freshG);
+        if (cfreshG) {
+            const int cgl = uni(after.gl), j = uni(a.group_of[cgl]);
+            V g, m, zl = zero_of(V());
+            load_row<VEC, KIND, false>(s, cgl, col, zgc, g, m);
+            if (pullL) zl = local_leader(j, uni(before.lead[j]), uni(before.fresh[j]));
+            if (s.update) update_vec<KIND, V>(zgc, g, m, zl, zg, c);
+        }
+        clead = uni(after.lead[0]); cfresh = uni(after.fresh[0]);
+        if (cfresh) load_row<VEC, KIND, false>(s, clead, col, nlx, nlg, nlm);
+    }
+    if (pullG && freshG && a.Z) st_vec(at(a.Z, a.ld, a.G, col), zg);
+    if (COMM && cfreshG && a.Z) st_vec(at(a.Z, a.ld, a.G, col), zgc);
+    V zl = zero_of(V()), zlc = zero_of(V());
+    Coef cc = c;
+    cc.cG = cfreshG ? s.commG : 0.0f;
+    int j = -1, end = 0, crow = -1;                      // group, its end, and (COMM) the leader its rows are pulled to
+    for (int at_row = 0; at_row < a.W; at_row += R) {
+        int i = at_row;
+        asm("" : "+s"(i));                               // (or every row's address becomes a loop variable of its own: scalar registers spill)
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int row = i + u;
+            if (row >= a.W) break;
+            if (row == end) {                            // a group begins
+                ++j; end = a.offsets[j + 1];
+                zl = own && fresh ? cur.x[u] : nzl;
+                if (pullL && fresh && a.Z) st_vec(at(a.Z, a.ld, j, col), zl);
+                if (COMM) {
+                    crow = cfresh ? clead : -1;
+                    cc.cL = cfresh ? s.commL : 0.0f;
+                    if (cfresh) {
+                        zlc = nlx;
+                        if (s.update) update_vec<KIND, V>(zlc, nlg, nlm, zl, zg, c);
+                        if (a.Z) st_vec(at(a.Z, a.ld, j, col), zlc);
+                    }
+                }
+                if (j + 1 < a.G) {
+                    lead = uni(before.lead[j + 1]); fresh = uni(before.fresh[j + 1]);
+                    if (pullL && !(own && fresh)) nzl = local_leader(j + 1, lead, fresh);
+                    if (COMM) {
+                        clead = uni(after.lead[j + 1]); cfresh = uni(after.fresh[j + 1]);
+                        if (cfresh) load_row<VEC, KIND, false>(s, clead, col, nlx, nlg, nlm);
+                    }
+                }
+            }
+                        if (s.update) {
+                Coef cr = c;
+                if (exempt) {
+                    if (pullL && row == uni(before.lead[j])) cr.cL = 0.0f;
+                    if (pullG && row == gl) cr.cG = 0.0f;
+                }
+                update_vec<KIND, V>(cur.x[u], cur.g[u], cur.m[u], zl, zg, cr);
+                if (KIND == 1) { if (NT) st_stream(at(a.m, a.ld, row, col), cur.m[u]); else st_vec(at(a.m, a.ld, row, col), cur.m[u]); }
+            }
+            bool store = s.update;
+            if (COMM && ((cc.cL != 0.0f && row != crow) || cc.cG != 0.0f)) {   // (a leader's pull to itself is zero)
+                V none = zero_of(V());
+                update_vec<2, V>(cur.x[u], none, none, zlc, zgc, cc);
+                store = true;
+            }
+            if (store) {
+                if (NT) st_stream(at(a.x, a.ld, row, col), cur.x[u]); else st_vec(at(a.x, a.ld, row, col), cur.x[u]);
+                if (a.xb) st_bf16(at(a.xb, a.ld, row, col), cur.x[u]);
+            }
+        }
+        if (i + R < a.W) {
+            cur = next;
+            load_batch<VEC, KIND, NT>(s, i + 2 * R, col, next);
+        }
+    }
+}
+
+// Algorithm 1's iteration, or a communication pull alone, with every row in registers.  The update's leaders are kept copies.
+template <int VEC, int KIND, bool NT, int NR>
+__device__ __forceinline__ void regs_update(const ColumnDev& s, uint32_t col, Rows<VEC, NR>& r)
+{
+    using V = typename Vec<VEC>::type;
+    const PullDev& a = s.a;
+    const bool pullL = a.lamL != 0.0f, pullG = a.lamG != 0.0f;
+    const Coef c = make_coef<V>(a);
+    V zg = zero_of(V()), zl = zero_of(V()), nzl = zero_of(V());
+    if (pullG) zg = ld_vec<VEC>(at(a.Z, a.ld, a.G, col));
+    if (pullL) zl = ld_vec<VEC>(at(a.Z, a.ld, 0, col));
+    if (pullL && a.G > 1) nzl = ld_vec<VEC>(at(a.Z, a.ld, 1, col));
+    int j = 0, end = a.offsets[1];
+#pragma unroll
+    for (int u = 0; u < NR; ++u)
+        if (u < a.W) {
+            if (u == end) {                              // the next group
+                ++j; end = a.offsets[j + 1];
+                zl = nzl;
+                if (pullL && j + 1 < a.G) nzl = ld_vec<VEC>(at(a.Z, a.ld, j + 1, col));
+            }
+            update_vec<KIND, V>(r.x[u], r.g[u], r.m[u], zl, zg, c);
+            if (KIND == 1) { if (NT) st_stream(at(a.m, a.ld, u, col), r.m[u]); else st_vec(at(a.m, a.ld, u, col), r.m[u]); }
+        }
+}
+
+template <int VEC, bool NT, int NR>
+__device__ __forceinline__ void regs_comm(const ColumnDev& s, const Leaders& L, uint32_t col, Rows<VEC, NR>& r)
 {
     using V = typename Vec<VEC>::type;
     const PullDev& a = s.a;
@@ -134,31 +335,36 @@ __device__ __forceinline__ void comm_columns(const ColumnDev& s, const Leaders& 
     c.cG = L.freshG ? s.commG : 0.0f;
     V zg = zero_of(V());
     if (L.freshG) {
-        zg = ld_vec<VEC>(a.x + (int64_t)L.gl * a.ld + col);
-        if (a.Z) st_vec(a.Z + (int64_t)a.G * a.ld + col, zg);
+        zg = row_of<VEC, NR>(r, __builtin_amdgcn_readfirstlane(L.gl));
+        if (a.Z) st_vec(at(a.Z, a.ld, a.G, col), zg);
     }
-    for (int j = 0; j < a.G; ++j) {
-        const int ll = L.lead[j];
-        const bool fresh = L.fresh[j] != 0;
-        V zl = zero_of(V());
-        if (fresh) {
-            zl = ld_vec<VEC>(a.x + (int64_t)ll * a.ld + col);
-            if (a.Z) st_vec(a.Z + (int64_t)j * a.ld + col, zl);
+    int j = -1, end = 0, lead = 0;
+    bool fresh = false;
+    V zl = zero_of(V());
+#pragma unroll
+    for (int u = 0; u < NR; ++u)
+        if (u < a.W) {
+            if (u == end) {
+                ++j; end = a.offsets[j + 1];
+                lead = __builtin_amdgcn_readfirstlane(L.lead[j]);
+                fresh = L.fresh[j] != 0;
+                c.cL = fresh ? s.commL : 0.0f;
+                if (fresh) {                             // (no row of the group has moved yet)
+                    zl = row_of<VEC, NR>(r, lead);
+                    if (a.Z) st_vec(at(a.Z, a.ld, j, col), zl);
+                }
+            }
+            const bool moves = (c.cL != 0.0f && !(fresh && u == lead)) || c.cG != 0.0f;   // (a leader's pull to itself is zero)
+            V none = zero_of(V());
+            if (moves) update_vec<2, V>(r.x[u], none, none, zl, zg, c);
+            if (moves || s.update) {
+                if (NT) st_stream(at(a.x, a.ld, u, col), r.x[u]); else st_vec(at(a.x, a.ld, u, col), r.x[u]);
+                if (a.xb) st_bf16(at(a.xb, a.ld, u, col), r.x[u]);
+            }
         }
-        c.cL = fresh ? s.commL : 0.0f;
-        if (c.cL == 0.0f && c.cG == 0.0f) continue;
-        for (int i = a.offsets[j]; i < a.offsets[j + 1]; ++i) {
-            if (fresh && i == ll && c.cG == 0.0f) continue;          // a leader's pull to itself is zero
-            const int64_t o = (int64_t)i * a.ld + col;
-            V xv = ld_vec<VEC>(a.x + o), none = zero_of(V());
-            update_vec<2, V>(xv, none, none, zl, zg, c);
-            st_vec(a.x + o, xv);
-            if (a.xb) st_bf16(a.xb + o, xv);
-        }
-    }
 }
 
-// The same with both coefficients zero: nobody moves, the re-selected leaders are copied to Z, eight rows of loads in
+// A communication pull with both coefficients zero: nobody moves, the re-selected leaders are copied to Z, eight rows of loads in
 // flight.
 template <int VEC>
 __device__ __forceinline__ void capture_columns(const ColumnDev& s, const Leaders& L, int64_t col)
@@ -184,10 +390,10 @@ __device__ __forceinline__ void capture_columns(const ColumnDev& s, const Leader
     }
 }
 
-// The center's step (mean in double, rows in order, rounded once) and the update that pulls every row to the center
-// as it was, which also goes to the global leader's row of Z.
+// Elastic averaging in two passes: the center's step (mean in double, rows in order, rounded once), the center as it was,
+// which the update pulls every row to, to the global leader's row of Z; then update_columns.
 template <int VEC>
-__device__ __forceinline__ void easgd_columns(const ColumnDev& s, int64_t col)
+__device__ __forceinline__ void center_columns(const ColumnDev& s, int64_t col)
 {
 #pragma clang fp contract(off)      // (1-a)*c + a*mean as two products and a sum, rounded like the plain expression
     using V = typename Vec<VEC>::type;
@@ -217,12 +423,39 @@ __device__ __forceinline__ void easgd_columns(const ColumnDev& s, int64_t col)
     st_vec(s.center + col, next);
 }
 
-template <int VEC, int KIND, bool NT, bool CENTER>
-__device__ __forceinline__ void step_columns(const ColumnDev& s, const Leaders& before, const Leaders& after, int64_t col, const RowBatch<VEC>& first)
+// The same with every row's values in registers.
+template <int VEC, int KIND, bool NT, int NR>
+__device__ __forceinline__ void regs_easgd(const ColumnDev& s, uint32_t col, Rows<VEC, NR>& r)
 {
-    if (CENTER) easgd_columns<VEC>(s, col);
-    if (CENTER || s.update) update_columns<VEC, KIND, NT, CENTER>(s, before, col, first);
-    if (!CENTER && s.comm) comm_columns<VEC>(s, after, col);
+    using V = typename Vec<VEC>::type;
+    const PullDev& a = s.a;
+    const V old = ld_vec<VEC>(at(s.center, 0, 0, col));
+    V next;
+    {
+#pragma clang fp contract(off)      // (1-a)*c + a*mean as two products and a sum, rounded like the plain expression
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            double sum = 0.0;
+#pragma unroll
+            for (int u = 0; u < NR; ++u)
+                if (u < a.W) sum += (double)reinterpret_cast<const float*>(&r.x[u])[v];
+            reinterpret_cast<float*>(&next)[v] =
+                (float)((1.0 - s.center_rate) * (double)reinterpret_cast<const float*>(&old)[v] + s.center_rate * (sum / (double)a.W));
+        }
+    }
+    st_vec(at(a.Z, a.ld, a.G, col), old);
+    st_vec(at(s.center, 0, 0, col), next);
+    const Coef c = make_coef<V>(a);
+    const V none = zero_of(V());
+    const V zg = a.lamG != 0.0f ? old : none;
+#pragma unroll
+    for (int u = 0; u < NR; ++u)
+        if (u < a.W) {
+                        update_vec<KIND, V>(r.x[u], r.g[u], r.m[u], none, zg, c);
+            if (NT) st_stream(at(a.x, a.ld, u, col), r.x[u]); else st_vec(at(a.x, a.ld, u, col), r.x[u]);
+            if (KIND == 1) { if (NT) st_stream(at(a.m, a.ld, u, col), r.m[u]); else st_vec(at(a.m, a.ld, u, col), r.m[u]); }
+            if (a.xb) st_bf16(at(a.xb, a.ld, u, col), r.x[u]);
+        }
 }
 
 // The losses from their partial sums: a team of 4 to 256 lanes per worker, in double, in an order that depends on the
@@ -340,47 +573,84 @@ __global__ __launch_bounds__(kThreads) void capture_kernel(ColumnDev s)
     }
 }
 
-template <int VEC, int KIND, bool NT, bool CENTER>
+enum { kUpdate, kUpdateOnes, kComm, kCommRegs, kCenter, kCenterRegs };
+
+// What one thread does at its columns.  Loads are under way during the selection.  NR: rows in registers (*Regs).
+template <int VEC, int KIND, bool NT, int MODE, int NR>
+__device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Leaders& chosen, int64_t col, bool live)
+{
+    const Leaders& before = s.select == 1 ? chosen : now;
+    const Leaders& after = s.select ? chosen : now;
+    if constexpr (MODE == kUpdate || MODE == kCenter) {
+        constexpr bool CENTER = MODE == kCenter;
+        RowBatch<VEC> first;
+        if (live) load_rows<VEC, KIND, NT>(s.a, 0, pass_end<CENTER>(s.a, 0), col, first);
+        choose_leaders(s, now, chosen);
+        if (!live) return;
+        if (CENTER) center_columns<VEC>(s, col);
+        update_columns<VEC, KIND, NT, CENTER>(s, before, col, first);
+    } else if constexpr (MODE == kUpdateOnes || MODE == kComm) {
+        RowBatch<VEC> cur, next;
+        if (live) {
+            load_batch<VEC, KIND, NT>(s, 0, (uint32_t)col, cur);
+            load_batch<VEC, KIND, NT>(s, kRowsInFlight<VEC>, (uint32_t)col, next);
+        }
+        choose_leaders(s, now, chosen);
+        if (live) stream_columns<VEC, KIND, NT, MODE == kComm>(s, before, after, (uint32_t)col, cur, next);
+    } else {
+        Rows<VEC, NR> r;
+        if (live) load_rows<VEC, KIND, NT, NR>(s, (uint32_t)col, r);
+        choose_leaders(s, now, chosen);
+        if (!live) return;
+        if (MODE == kCenterRegs) {
+            regs_easgd<VEC, KIND, NT, NR>(s, (uint32_t)col, r);
+        } else {
+            if (s.update) regs_update<VEC, KIND, NT, NR>(s, (uint32_t)col, r);
+            regs_comm<VEC, NT, NR>(s, after, (uint32_t)col, r);
+        }
+    }
+}
+
+// The last workgroup takes the columns that are left over, one per thread, if there are any.
+template <int VEC, int KIND, bool NT, int MODE, int NR>
 __global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
 {
     __shared__ Leaders now, chosen;
-    const int64_t col = s.a.col0 + ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VEC;
-    const bool whole = col + VEC <= s.a.col1;
-    RowBatch<VEC> first;
-    if (s.update && whole) load_rows<VEC, KIND, NT>(s.a, 0, pass_end<CENTER>(s.a, 0), col, first);   // under way during the selection
-    choose_leaders(s, now, chosen);
-    const Leaders& before = s.select == 1 ? chosen : now;
-    const Leaders& after = s.select ? chosen : now;
-    if (whole) step_columns<VEC, KIND, NT, CENTER>(s, before, after, col, first);
-    else
-        for (int64_t cc = col; cc < s.a.col1; ++cc) {
-            RowBatch<1> one;
-            if (s.update) load_rows<1, KIND, NT>(s.a, 0, pass_end<CENTER>(s.a, 0), cc, one);
-            step_columns<1, KIND, NT, CENTER>(s, before, after, cc, one);
-        }
+    const int64_t whole = s.a.col1 - (s.a.col1 - s.a.col0) % VEC, first = s.a.col0 + (int64_t)blockIdx.x * kThreads * VEC;
+    if (VEC == 1 || first < whole) {
+        const int64_t col = first + threadIdx.x * VEC;
+        step_thread<VEC, KIND, NT, MODE, NR>(s, now, chosen, col, col < whole);
+    } else {
+        const int64_t col = whole + threadIdx.x;
+        step_thread<1, KIND, NT, MODE, NR>(s, now, chosen, col, col < s.a.col1);
+    }
 }
 
-template <int VEC>
-void launch_vec(const ColumnDev& s, bool mom, bool nt, hipStream_t st)
+template <int VEC, int KIND, int MODE, int NR>
+void launch_vec(const ColumnDev& s, bool nt, hipStream_t st)
 {
-    const int64_t cols = s.a.col1 - s.a.col0, per = (int64_t)kThreads * VEC;
-    const dim3 grid((unsigned)((cols + per - 1) / per));
-    auto go = [&](auto kind, auto stream, auto center) {
-        hipLaunchKernelGGL((column_step_kernel<VEC, decltype(kind)::value, decltype(stream)::value, decltype(center)::value>),
-                           grid, dim3(kThreads), 0, st, s);
-    };
-    auto with_kind = [&](auto stream, auto center) {
-        if constexpr (VEC < 4) {                             // four columns per thread: without momentum only
-            if (mom) { go(std::integral_constant<int, 1>{}, stream, center); return; }
+    const int64_t cols = s.a.col1 - s.a.col0, per = (int64_t)kThreads * VEC, whole = cols / VEC * VEC;
+    const dim3 grid((unsigned)((whole + per - 1) / per + (whole < cols)));
+    if (nt) hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR>), grid, dim3(kThreads), 0, st, s);
+    else hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR>), grid, dim3(kThreads), 0, st, s);
+}
+
+// vec: columns per thread wished for; no more than the registers hold.
+template <int MODE, int NR = 0>
+void launch_mode(const ColumnDev& s, int vec, bool mom, bool nt, hipStream_t st)
+{
+    if (mom) {
+        if constexpr (NR <= 16) {
+            if (vec >= 2) { launch_vec<2, 1, MODE, NR>(s, nt, st); return; }
         }
-        go(std::integral_constant<int, 0>{}, stream, center);
-    };
-    auto with_stream = [&](auto center) {
-        if (nt) with_kind(std::true_type{}, center);
-        else with_kind(std::false_type{}, center);
-    };
-    if (s.center) with_stream(std::true_type{});
-    else with_stream(std::false_type{});
+        launch_vec<1, 1, MODE, NR>(s, nt, st);
+    } else {
+        if constexpr (NR <= 16) {
+            if (vec == 4) { launch_vec<4, 0, MODE, NR>(s, nt, st); return; }
+        }
+        if (vec >= 2) launch_vec<2, 0, MODE, NR>(s, nt, st);
+        else launch_vec<1, 0, MODE, NR>(s, nt, st);
+    }
 }
 
 } // namespace
@@ -412,22 +682,36 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
         return p.ld % v == 0 && aligned(p.x, 4 * v) && (!q.update || aligned(p.g, 4 * v)) && (!mom || aligned(p.m, 4 * v)) &&
                (!p.Z || aligned(p.Z, 4 * v)) && (!p.xb || aligned(p.xb, 2 * v)) && (!q.center || aligned(q.center, 4 * v));
     };
-    // Columns per thread: one, so that small rows still make enough wavefronts; more once there are plenty (16 workers
-    // without momentum: 600 000 columns 27.0 / 25.6 / 24.5 us with 1 / 2 / 4, 250 000 columns 13.8 / 13.7 / 14.1;
-    // with momentum two columns are never more than 2 % ahead, four mostly behind)
+    const double bytes = (mom ? 20.0 : 12.0) * (double)p.W * (double)p.P;
+    // Many rows with momentum out of HBM: reading x twice costs less than registers for sixteen rows of three values (16 x
+    // 1 250 001, 400 MB: 71 us against 78; 12 x 1 250 001, 300 MB, 60 against 59, 8 x 2 500 000, 400 MB, 83 against 76).
+    const int mode = q.center ? (mom && p.W > 12 && bytes > 300e6 && p.W <= 16 ? kCenter : kCenterRegs)
+                   : q.comm ? (p.W <= 8 ? kCommRegs : kComm) : p.W == p.G ? kUpdateOnes : kUpdate;
+    // Columns per thread: one, so that small rows still make enough wavefronts; more once there are plenty.  Update: 16
+    // workers without momentum, 600 000 columns 27.0 / 25.6 / 24.5 us with 1 / 2 / 4, 250 000 columns 13.8 / 13.7 / 14.1;
+    // with momentum two columns are never more than 2 % ahead, four mostly behind.  Algorithm 1's iteration, 8 workers in 2
+    // groups: 140 001 columns 8.8 / 9.4 / 10.0, 1 250 001 37 / 35 / 32.  Groups of one, 8 x 271 117, 13.6 / 12.8 / 12.5.
+    // Elastic averaging, 16 x 271 117 with momentum, 18.3 / 21.1, 4 x 1 250 001 without 18.8 / 17.8 / 16.3.
     int vec = 1;
-    if (q.update && !mom && p.P >= 500000) vec = p.P >= 1000000 ? 4 : 2;
-    // (a bf16 copy is written two bytes per lane with one column: 8 workers x 266 610 columns, whole step 62.9 -> 61.0 us)
-    if (q.update && p.xb && p.P >= 100000 && vec < 2) vec = 2;
+    if (mode == kUpdate || mode == kCenter) {
+        if (!mom && p.P >= 500000) vec = p.P >= 1000000 ? 4 : 2;
+        // (a bf16 copy is written two bytes per lane with one column: 8 workers x 266 610 columns, whole step 62.9 -> 61.0 us)
+        if (p.xb && p.P >= 100000 && vec < 2) vec = 2;
+    } else if (mode == kCenterRegs) {
+        vec = p.P < 500000 ? 1 : p.P < 1000000 ? 2 : 4;
+    } else {
+        vec = p.P < (mode == kComm ? 100000 : 200000) ? 1 : p.P < 500000 ? 2 : 4;
+    }
     if (!q.update) vec = 4;
     while (vec > 1 && !layout_ok((unsigned)vec)) vec >>= 1;
     // Streaming accesses (x, m past the caches) where the population neither lives in the L2s from step to step nor in
     // the memory-side cache as it is: plain / streaming, us: 16 workers with momentum, 250 000 columns (80 MB) 18.9 / 17.3,
     // 600 000 (192 MB) 37.3 / 39.1, 1 250 000 (400 MB) 80.3 / 73.7, elastic averaging there 86.4 / 73.3; pairs of workers,
-    // 16 x 250 000, 26.8 / 25.3.
-    // Not before a communication pull, which reads x again.
-    const double bytes = (mom ? 20.0 : 12.0) * (double)p.W * (double)p.P;
-    const bool nt = !q.comm && bytes >= 16e6 && (bytes < 90e6 || bytes > 280e6);
+    // 16 x 250 000, 26.8 / 25.3.  Groups of one with their leaders re-selected write a copy of every row as well: 8 x 271 117
+    // (26 MB) 13.6 / 17.3, 16 x 1 250 001 with momentum (400 MB) 106 / 90; with most of them kept 8 x 1 250 001 (120 MB) 43 / 39.
+    const bool all_fresh = q.select == 1 && (q.cap & (~0ull >> (64 - p.G))) == (~0ull >> (64 - p.G));
+    const bool nt = mode == kUpdateOnes ? (all_fresh ? bytes > 200e6 : true)
+                  : mode == kCommRegs ? true : bytes >= 16e6 && (bytes < 90e6 || bytes > 280e6);
     if (!q.update && q.comm && q.commL == 0.0f && q.commG == 0.0f) {
         const int64_t tiles = (p.P + (int64_t)kThreads * vec - 1) / ((int64_t)kThreads * vec);
         const dim3 grid((unsigned)(tiles < 2048 ? tiles : 2048));
@@ -436,9 +720,21 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
         else hipLaunchKernelGGL((capture_kernel<1>), grid, dim3(kThreads), 0, stream, s);
         return hipGetLastError();
     }
-    if (vec == 4) launch_vec<4>(s, mom, nt, stream);
-    else if (vec == 2) launch_vec<2>(s, mom, nt, stream);
-    else launch_vec<1>(s, mom, nt, stream);
+    switch (mode) {
+    case kUpdate: launch_mode<kUpdate>(s, vec, mom, nt, stream); break;
+    case kUpdateOnes: launch_mode<kUpdateOnes>(s, vec, mom, nt, stream); break;
+    case kComm: launch_mode<kComm>(s, vec, mom, nt, stream); break;
+    case kCommRegs:
+        if (p.W <= 4) launch_mode<kCommRegs, 4>(s, vec, mom, nt, stream);
+        else launch_mode<kCommRegs, 8>(s, vec, mom, nt, stream);
+        break;
+    case kCenter: launch_vec<1, 1, kCenter, 0>(s, true, stream); break;
+    case kCenterRegs:
+        if (p.W <= 8) launch_mode<kCenterRegs, 8>(s, vec, mom, nt, stream);
+        else if (p.W <= 16) launch_mode<kCenterRegs, 16>(s, vec, mom, nt, stream);
+        else launch_mode<kCenterRegs, 32>(s, vec, mom, nt, stream);
+        break;
+    }
     return hipGetLastError();
 }
 

@@ -10,35 +10,40 @@ struct Coef {
     int nesterov, grad_only;
 };
 
-// One parameter (V = float) or four (V = a 4-wide vector), element-wise.  Written with plain
-// operators so that the compiler forms the fused multiply-adds itself.
+// One parameter (V = float) or several (V = a vector), element-wise.  The fused multiply-adds are written out, so that
+// every kernel rounds alike wherever this is inlined: the one-launch update works out a leader's new value a second time
+// and the paths are compared bit for bit.
 // KIND 0: gradient step, 1: gradient step with momentum, 2: Algorithm 1's communication pull
 // (x <- x - cL (x - zl), then x <- x - cG (x - zg); no gradient, momentum untouched).
+template <class V>
+__device__ __forceinline__ V mul_add(float a, V b, V c) { return __builtin_elementwise_fma((V)(a), b, c); }
+
 template <int KIND, class V>
 __device__ __forceinline__ void update_vec(V& x, const V g, V& m, const V zl, const V zg, const Coef& c)
 {
+#pragma clang fp contract(off)
     constexpr bool MOM = KIND == 1;
     if (KIND == 2) {
-        const V y = x - c.cL * (x - zl);
-        x = y - c.cG * (y - zg);
+        const V y = mul_add(-c.cL, x - zl, x);
+        x = mul_add(-c.cG, y - zg, y);
         return;
     }
-    V d = g + c.wd * x;
-    const V pull = c.cL * (x - zl) + c.cG * (x - zg);
+    V d = mul_add(c.wd, x, g);
+    const V pull = mul_add(c.cG, x - zg, c.cL * (x - zl));
     V step;
     if (MOM) {
         if (c.grad_only) {
-            m = c.mu * m + d;
-            step = (c.nesterov ? d + c.mu * m : m) + pull;
+            m = mul_add(c.mu, m, d);
+            step = (c.nesterov ? mul_add(c.mu, m, d) : m) + pull;
         } else {
             d += pull;
-            m = c.mu * m + d;
-            step = c.nesterov ? d + c.mu * m : m;
+            m = mul_add(c.mu, m, d);
+            step = c.nesterov ? mul_add(c.mu, m, d) : m;
         }
     } else {
         step = d + pull;
     }
-    x = x - c.eta * step;
+    x = mul_add(-c.eta, step, x);
 }
 
 } // namespace lsgd

@@ -1,0 +1,65 @@
+"""The ways through the rows of the one-launch update at their edges: groups of one and iterations of Algorithm 1 whose
+rows stream whatever group they are in (batches of 8 rows at one column per thread, of 4 at two or four), iterations with up
+to 4 or 8 rows in registers, elastic averaging with up to 8, 16 or 32, columns left over for the last workgroup.  Bit for bit
+against row streams and against the calls that a step is made of; elastic averaging against the oracle."""
+import pytest
+
+import paper_1905_10395_amd as L
+import test_gpu_column_step as column
+import test_gpu_easgd as easgd
+
+pytestmark = pytest.mark.gpu
+
+
+def ones(W):
+    return list(range(W + 1))
+
+
+GROUPS_OF_ONE = [
+    (5, ones(5), 1031, 1031),                        # odd stride: one column per thread
+    (8, ones(8), 257, 320),                          # one whole batch
+    (9, ones(9), 255, 256),                          # a row in the second
+    (17, ones(17), 301, 320),                        # ... in the third
+    (32, ones(32), 64, 64),
+    (5, ones(5), 200_003, 200_064),                  # two columns per thread, one left over
+    (3, ones(3), 500_003, 500_032),                  # four (two with momentum), three left over
+]
+ALG1 = GROUPS_OF_ONE + [
+    (2, [0, 2], 1031, 1031),                         # rows in registers: up to four
+    (4, [0, 1, 4], 200_001, 200_064),
+    (5, [0, 3, 5], 257, 320),                        # ... up to eight
+    (8, [0, 3, 8], 500_003, 500_032),
+    (9, [0, 4, 9], 100_001, 100_032),                # streamed: two columns per thread, one left over
+    (13, [0, 5, 6, 13], 1030, 1088),                 # groups that begin inside a batch
+    (16, [0, 16], 500_003, 500_032),
+    (32, [0, 9, 17, 32], 301, 320),
+]
+
+
+@pytest.mark.parametrize("mu,flags,wd", column.OPTIONS)
+@pytest.mark.parametrize("W,off,P,ld", GROUPS_OF_ONE)
+def test_groups_of_one_equal_row_streams(W, off, P, ld, mu, flags, wd):
+    column.test_step_equals_row_streams(W, off, P, ld, mu, flags, wd)
+
+
+@pytest.mark.parametrize("mu,flags,wd", [(0.0, 0, 0.0), (0.9, L.NESTEROV, 1e-2)])
+@pytest.mark.parametrize("W,off,P,ld", GROUPS_OF_ONE[:5])
+def test_groups_of_one_match_the_oracle(W, off, P, ld, mu, flags, wd):
+    column.test_whole_step_matches_oracle(W, off, P, ld, mu, flags, wd)
+
+
+@pytest.mark.parametrize("mu", [0.0, 0.9])
+@pytest.mark.parametrize("W,off,P,ld", ALG1)
+def test_one_call_equals_separate_calls(W, off, P, ld, mu):
+    column.test_one_call_equals_separate_calls(W, off, P, ld, mu)
+
+
+@pytest.mark.parametrize("W,P,ld", [(1, 257, 257), (8, 1031, 1031), (9, 257, 320), (32, 301, 320), (33, 301, 320), (3, 500_003, 500_032),
+                                    (10, 500_003, 500_032), (16, 940_003, 940_032)])
+def test_easgd_rows_in_registers_or_twice(W, P, ld):
+    column.test_easgd_both_routes(W, P, ld)          # 16 x 940 003: two passes (301 MB)
+
+
+@pytest.mark.parametrize("W,G,P,ld", [(6, 2, 1_000_003, 1_000_064), (13, 1, 500_003, 500_032), (20, 4, 500_003, 500_032), (32, 4, 1031, 1031)])
+def test_easgd_without_momentum(W, G, P, ld):
+    easgd.test_easgd_update_matches_oracle(W, G, P, ld, 0.0, 0, 1e-4)
