@@ -8,6 +8,7 @@
 //
 // Worker row of x and of g: [U (m x r) | V (n x r)], row-major factors.
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 
@@ -302,6 +303,9 @@ template <> struct Cols<1> { using type = float; };
 __device__ __forceinline__ float col_dot(v4f a, v4f b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
 __device__ __forceinline__ float col_dot(v2f a, v2f b) { return a.x * b.x + a.y * b.y; }
 __device__ __forceinline__ float col_dot(float a, float b) { return a * b; }
+__device__ __forceinline__ float col_dot_add(v4f a, v4f b, float c) { return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, fmaf(a.x, b.x, c)))); }
+__device__ __forceinline__ float col_dot_add(v2f a, v2f b, float c) { return fmaf(a.y, b.y, fmaf(a.x, b.x, c)); }
+__device__ __forceinline__ float col_dot_add(float a, float b, float c) { return fmaf(a, b, c); }
 
 constexpr int kBinRows = 128;         // factor rows per bin (64, 128 or 256)
 constexpr int kKeyShift = (kBinRows == 64) ? 26 : (kBinRows == 128) ? 25 : 24;   // record key: row in bin above, other row below
@@ -315,7 +319,9 @@ struct McBinned {
                      // (U bins fill [0, count), V bins [count, 2 count); entry nbins = 2 count)
     int2* rec;       // [W][nblk][2E] (row-in-bin << kKeyShift | other factor's row, M bits)
     int nbinsU, nbins, nblk, E;
+    double* sums;    // [W][kLossSlots] squared residuals of the U bins, added up by atomics; or NULL: one sum per bin
 };
+constexpr int kLossSlots = 8;
 
 // Maps a linear workgroup id to (worker, chunk), a die being id modulo 8.  per_die = 0: worker w lives on die w % 8, all
 // dies work through workers 0 .. 7, then 8 .. 15.  Else a die takes a contiguous run of per_die chunks of all workers,
@@ -344,6 +350,7 @@ __global__ __launch_bounds__(kPrepThreads) void mc_prep_kernel(
     extern __shared__ int lhist[];                 // [nbins + 1]
     __shared__ int wsum[kPrepThreads / 64];
     for (int i = t; i <= S.nbins; i += kPrepThreads) lhist[i] = 0;
+    if (S.sums && blk == 0 && t < kLossSlots) S.sums[w * kLossSlots + t] = 0.0;
     const int64_t k0 = (int64_t)blk * E;
     const int cnt_here = (int)((nb - k0 < E) ? nb - k0 : E);
     // every index chase of the workgroup is in flight at once
@@ -420,8 +427,8 @@ constexpr int kSideThreads = 256;
 constexpr int kRedCap = 1024;                     // records staged per pass
 constexpr int kSegCap = kSideThreads;             // segments collected at a time
 
-// EXACT: r == VW * LPE, every lane of a group holds part of the row.
-template <int LPE, bool EXACT, int VW>
+// LPE lanes share a row, NV vectors each (vectors q0, q0 + LPE, ...).  EXACT: r == VW * LPE * NV, every lane holds NV of them.
+template <int LPE, int NV, bool EXACT, int VW>
 __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __restrict__ x, float* __restrict__ g, int64_t ld,
                                                              int m, int n, int r, McBinned S, float two_c,
                                                              float* __restrict__ partials, int W, int64_t per_die)
@@ -438,6 +445,7 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
     __shared__ int cnt[kBinRows], start[kBinRows + 1];
     __shared__ int segoff[kSegCap + 1], segbase[kSegCap], wtot[kSideThreads / 64];
     __shared__ double sqred[kSideThreads / 64];
+    __shared__ int crowded;                                           // some segment does not fit its team's registers
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const bool uside = gbin < S.nbinsU;
     const int row0 = (uside ? gbin : gbin - S.nbinsU) * kBinRows;     // first factor row of the bin
@@ -446,22 +454,133 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
     const float* own = uside ? xw : xw + (int64_t)m * r;
     const float* other = uside ? xw + (int64_t)m * r : xw;            // U rows gather V rows and vice versa
     const int rv = r / VW;
+    if (gbin == 0)                                                    // padding columns are zero
+        for (int64_t c = (int64_t)(m + (int64_t)n) * r + t; c < ld; c += kSideThreads) g[(int64_t)w * ld + c] = 0.f;
+    const int2* rec = S.rec + (int64_t)w * S.nblk * (2 * S.E);
+    const int32_t* segs = S.segs + (int64_t)w * S.nblk * (S.nbins + 1) + gbin;
+    const int sub = t / LPE, q0 = t % LPE;
+    bool on[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) on[k] = EXACT || q0 + k * LPE < rv;
+    V acc[RPG][NV];
+#pragma unroll
+    for (int i = 0; i < RPG; ++i)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) acc[i][k] = V(0.f);
+    double sq = 0.0;
+
+    // exclusive scan of the row counts (all threads; ends without a barrier)
+    auto scan_rows = [&]() {
+        if (kBinRows > 64 || t < 64) {
+            const int cc = (t < kBinRows) ? cnt[t] : 0;
+            int in2 = cc;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(in2, d, 64); if (lane >= d) in2 += v; }
+            if (kBinRows > 64) {
+                if (lane == 63) wtot[wv] = in2;
+                __syncthreads();
+                for (int q = 0; q < wv; ++q) in2 += wtot[q];
+            }
+            if (t < kBinRows) start[t] = in2 - cc;
+            if (t == kBinRows - 1) start[kBinRows] = in2;
+        }
+    };
+    // rows of the other factor: at most kMaxBins * kBinRows rows of 128 values, so an offset has fewer than 32 bits
+    const uint32_t row_bytes = 4u * (uint32_t)r;
+    // the sorted records of one pass
+    auto walk = [&]() {
+#pragma unroll
+        for (int i = 0; i < RPG; ++i) {
+            const int row = sub + i * kSubs;
+            if (row < kBinRows) {
+                const int s0 = start[row], s1 = start[row + 1];
+                if (s0 < s1) {
+                    V mine_row[NV];
+#pragma unroll
+                    for (int k = 0; k < NV; ++k) mine_row[k] = on[k] ? tile[row * rv + q0 + k * LPE] : V(0.f);
+                    float rowsq = 0.f;
+                    for (int sidx = s0; sidx < s1; sidx += 4) {
+                        // straight-line body: slots past the row's end repeat its last record with weight zero
+                        int2 rc[4];
+                        V ov[4][NV];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) rc[u] = sorted[(sidx + u < s1) ? sidx + u : s1 - 1];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const uint32_t off = __umul24((uint32_t)(rc[u].x & kKeyMask), row_bytes) + (uint32_t)(q0 * VW * 4);
+#pragma unroll
+                            for (int k = 0; k < NV; ++k)
+                                ov[u][k] = on[k] ? *reinterpret_cast<const V*>(reinterpret_cast<const char*>(other) + off + (uint32_t)(k * LPE * VW * 4)) : V(0.f);
+                        }
+                        float d[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            float dot = col_dot(mine_row[0], ov[u][0]);
+#pragma unroll
+                            for (int k = 1; k < NV; ++k) dot = col_dot_add(mine_row[k], ov[u][k], dot);
+                            d[u] = group_sum<LPE>(dot);
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const float e = (sidx + u < s1) ? d[u] - __int_as_float(rc[u].y) : 0.f;
+#pragma unroll
+                            for (int k = 0; k < NV; ++k) acc[i][k] += e * ov[u][k];
+                            rowsq = fmaf(e, e, rowsq);
+                        }
+                    }
+                    if (q0 == 0) sq += (double)rowsq;
+                }
+            }
+        }
+    };
+
+    // A team of lanes per segment reads its bounds and its records, as many as the registers hold; no list of all records
+    // in between.
+    int team = kSideThreads;
+    while (team > 1 && team * S.nblk > kSideThreads) team >>= 1;
+    bool teams = team * S.nblk <= kSideThreads && (int64_t)S.nblk * S.E * kBinRows <= (int64_t)kRedCap * nrows;   // uniform; on average they fit
+    int2 mine[PER];
+    int len = 0;                                                      // records of this lane
+    if (teams) {
+        const int blk = t / team, l = t % team;
+        if (blk < S.nblk) {
+            const int32_t* sp = segs + (int64_t)blk * (S.nbins + 1);
+            const int s0 = sp[0], left = sp[1] - s0 - l;
+            const int2* src = rec + (int64_t)blk * (2 * S.E) + s0 + l;
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+                if (u * team < left) mine[u] = src[u * team];
+            len = left > 0 ? (left + team - 1) / team : 0;
+        }
+    }
     {
         const int live = (nrows - row0 < kBinRows ? nrows - row0 : kBinRows) * rv;
         const V* src = reinterpret_cast<const V*>(own + (int64_t)row0 * r);
         for (int i = t; i < live; i += kSideThreads) tile[i] = src[i];
     }
-    const int2* rec = S.rec + (int64_t)w * S.nblk * (2 * S.E);
-    const int32_t* segs = S.segs + (int64_t)w * S.nblk * (S.nbins + 1) + gbin;
-    const int sub = t / LPE, q0 = t % LPE;
-    const bool lane_live = EXACT || q0 < rv;
-    const float* obase = other + q0 * VW;                             // this lane's columns of a gathered row
-    V acc[RPG];
+    if (t < kBinRows) cnt[t] = 0;
+    if (t == 0) crowded = 0;
+    __syncthreads();
+    if (teams) {
+        if (len > PER) crowded = 1;
+        int rank[PER];
 #pragma unroll
-    for (int i = 0; i < RPG; ++i) acc[i] = V(0.f);
-    double sq = 0.0;
-
-    for (int blk0 = 0; blk0 < S.nblk; blk0 += kSegCap) {
+        for (int u = 0; u < PER; ++u)
+            if (u < len) rank[u] = atomicAdd(&cnt[(uint32_t)mine[u].x >> kKeyShift], 1);
+        __syncthreads();
+        teams = crowded == 0;
+        if (teams) {
+            scan_rows();
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+                if (u < len) sorted[start[(uint32_t)mine[u].x >> kKeyShift] + rank[u]] = mine[u];
+            __syncthreads();
+            walk();
+        }
+    }
+    // More records: all segments' are numbered through, kRedCap at a time.
+    for (int blk0 = 0; blk0 < S.nblk && !teams; blk0 += kSegCap) {
         const int nseg = (S.nblk - blk0 < kSegCap) ? S.nblk - blk0 : kSegCap;
         // these segments: thread t takes segment t, counts are scanned into segoff
         int c = 0;
@@ -488,7 +607,6 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
             const int nrec = (total - c0 < kRedCap) ? total - c0 : kRedCap;
             if (t < kBinRows) cnt[t] = 0;
             __syncthreads();
-            int2 mine[PER];
             int rank[PER];
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
@@ -506,19 +624,7 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
                 }
             }
             __syncthreads();
-            if (kBinRows > 64 || t < 64) {                            // exclusive scan of the row counts
-                const int cc = (t < kBinRows) ? cnt[t] : 0;
-                int in2 = cc;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(in2, d, 64); if (lane >= d) in2 += v; }
-                if (kBinRows > 64) {
-                    if (lane == 63) wtot[wv] = in2;
-                    __syncthreads();
-                    for (int q = 0; q < wv; ++q) in2 += wtot[q];
-                }
-                if (t < kBinRows) start[t] = in2 - cc;
-                if (t == kBinRows - 1) start[kBinRows] = in2;
-            }
+            scan_rows();
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
@@ -526,39 +632,7 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
                 if (i < nrec) sorted[start[(uint32_t)mine[u].x >> kKeyShift] + rank[u]] = mine[u];
             }
             __syncthreads();
-#pragma unroll
-            for (int i = 0; i < RPG; ++i) {
-                const int row = sub + i * kSubs;
-                if (row < kBinRows) {
-                    const int s0 = start[row], s1 = start[row + 1];
-                    if (s0 < s1) {
-                        const V mine_row = lane_live ? tile[row * rv + q0] : V(0.f);
-                        float rowsq = 0.f;
-                        for (int sidx = s0; sidx < s1; sidx += 4) {
-                            // straight-line body: slots past the row's end repeat its last record with weight zero
-                            int2 rc[4];
-                            V ov[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) rc[u] = sorted[(sidx + u < s1) ? sidx + u : s1 - 1];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                ov[u] = lane_live ? *reinterpret_cast<const V*>(obase + (uint64_t)(uint32_t)(rc[u].x & kKeyMask) * (uint32_t)r)
-                                                  : V(0.f);
-                            float d[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                d[u] = group_sum<LPE>(col_dot(mine_row, ov[u]));
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                const float e = (sidx + u < s1) ? d[u] - __int_as_float(rc[u].y) : 0.f;
-                                acc[i] += e * ov[u];
-                                rowsq = fmaf(e, e, rowsq);
-                            }
-                        }
-                        if (q0 == 0) sq += (double)rowsq;
-                    }
-                }
-            }
+            walk();
             __syncthreads();
         }
     }
@@ -566,8 +640,10 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
 #pragma unroll
     for (int i = 0; i < RPG; ++i) {
         const int row = sub + i * kSubs;
-        if (row < kBinRows && row0 + row < nrows && lane_live)
-            reinterpret_cast<V*>(out + (int64_t)row * r)[q0] = two_c * acc[i];
+        if (row < kBinRows && row0 + row < nrows)
+#pragma unroll
+            for (int k = 0; k < NV; ++k)
+                if (on[k]) reinterpret_cast<V*>(out + (int64_t)row * r)[q0 + k * LPE] = two_c * acc[i][k];
     }
     if (uside) {                                                      // sum of squared residuals of this U bin
 #pragma unroll
@@ -577,15 +653,10 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
         if (t == 0) {
             double tot = 0.0;
             for (int q = 0; q < kSideThreads / 64; ++q) tot += sqred[q];
-            partials[(int64_t)w * S.nbinsU + gbin] = (float)tot;
+            if (S.sums) unsafeAtomicAdd(S.sums + w * kLossSlots + gbin % kLossSlots, tot);
+            else partials[(int64_t)w * S.nbinsU + gbin] = (float)tot;
         }
     }
-}
-
-__global__ __launch_bounds__(256) void mc_zero_pad_kernel(float* __restrict__ g, int64_t P, int64_t ld)
-{
-    const int64_t c = P + (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (c < ld) g[(int64_t)blockIdx.y * ld + c] = 0.f;
 }
 
 __global__ __launch_bounds__(256) void mc_pack_kernel(const int32_t* __restrict__ rows, const int32_t* __restrict__ cols,
@@ -753,18 +824,18 @@ static void launch_prep(int W, const lsgd_mc_batch& b, int64_t nb, const McBinne
         hipLaunchKernelGGL((mc_prep_kernel<4>), pgrid, dim3(kPrepThreads), plds, s, b.rows, b.cols, b.vals, b.batch_idx, nb, S, b.entries);
 }
 
-template <int LPE, int VW>
+template <int LPE, int NV, int VW>
 static void launch_side(const float* x, float* g, int W, int64_t ld, const lsgd_mc_batch& b,
                         const McBinned& S, float* partials, bool runs, hipStream_t s)
 {
     const int64_t run = ((int64_t)W * S.nbins + kXcd - 1) / kXcd, per_die = runs ? run : 0;
     const int64_t groups = per_die ? run * kXcd : (int64_t)((W + kXcd - 1) / kXcd) * kXcd * S.nbins;
-    if (b.r == VW * LPE)
-        hipLaunchKernelGGL((mc_side_kernel<LPE, true, VW>), dim3((unsigned)groups), dim3(kSideThreads),
+    auto go = [&](auto exact) {
+        hipLaunchKernelGGL((mc_side_kernel<LPE, NV, decltype(exact)::value, VW>), dim3((unsigned)groups), dim3(kSideThreads),
                            (size_t)kBinRows * b.r * 4, s, x, g, ld, b.m, b.n, b.r, S, 2.0f * b.c, partials, W, per_die);
-    else
-        hipLaunchKernelGGL((mc_side_kernel<LPE, false, VW>), dim3((unsigned)groups), dim3(kSideThreads),
-                           (size_t)kBinRows * b.r * 4, s, x, g, ld, b.m, b.n, b.r, S, 2.0f * b.c, partials, W, per_die);
+    };
+    if (b.r == VW * LPE * NV) go(std::true_type{});
+    else go(std::false_type{});
 }
 
 template <int VW>
@@ -772,13 +843,18 @@ static void launch_side_lanes(const float* x, float* g, int W, int64_t ld, const
                               bool runs, hipStream_t s)
 {
     const int rv = b.r / VW;
-    if (rv <= 1) launch_side<1, VW>(x, g, W, ld, b, S, partials, runs, s);
-    else if (rv <= 2) launch_side<2, VW>(x, g, W, ld, b, S, partials, runs, s);
-    else if (rv <= 4) launch_side<4, VW>(x, g, W, ld, b, S, partials, runs, s);
-    else if (rv <= 8) launch_side<8, VW>(x, g, W, ld, b, S, partials, runs, s);
-    else if (rv <= 16) launch_side<16, VW>(x, g, W, ld, b, S, partials, runs, s);
-    else if (rv <= 32) launch_side<32, VW>(x, g, W, ld, b, S, partials, runs, s);
-    else launch_side<64, VW>(x, g, W, ld, b, S, partials, runs, s);
+    // Two vectors per lane where that many lanes would mostly repeat each other's work on a record (its address, residual and
+    // place in the row): from sixteen lanes, from eight with narrow vectors.  One / two, gradient call, us: 20000 x 20000, rank
+    // 64, 8 workers x 32768 entries 85 / 79; 9468 x 5000, rank 50, 48 / 43; 20000 x 20000, rank 5, 16 x 65536 80 / 72; but rank
+    // 32 there 90 / 92, rank 16 66 / 71.
+    constexpr bool wide = VW == 4;
+    if (rv <= 1) launch_side<1, 1, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else if (rv <= 2) launch_side<2, 1, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else if (rv <= 4) launch_side<4, 1, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else if (rv <= 8) launch_side<wide ? 8 : 4, wide ? 1 : 2, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else if (rv <= 16) launch_side<8, 2, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else if (rv <= 32) launch_side<16, 2, VW>(x, g, W, ld, b, S, partials, runs, s);
+    else launch_side<32, 2, VW>(x, g, W, ld, b, S, partials, runs, s);
 }
 
 hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
@@ -809,13 +885,15 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         char* p = st.scratch;
         S.segs = reinterpret_cast<int32_t*>(p); p += up256((size_t)W * S.nblk * (S.nbins + 1) * 4);
         S.rec = reinterpret_cast<int2*>(p);
+        // More sums than the next launch adds up itself: the bins of a worker share a few slots (which lie where the sums
+        // would: more than kLossPartsMax sums of at most kColumnMaxWorkers workers are more than two floats per slot), in
+        // double, so that their order does not show.  20000 x 20000, 16 workers, whole step: 5 us less.
+        S.sums = W <= kColumnMaxWorkers && !loss_parts_ok(W, S.nbinsU) ? reinterpret_cast<double*>(st.partials) : nullptr;
         launch_prep(W, b, nb, S, s);
         if (vw == 4) launch_side_lanes<4>(x, g, W, ld, b, S, st.partials, mc_runs(cost, W), s);
         else if (vw == 2) launch_side_lanes<2>(x, g, W, ld, b, S, st.partials, mc_runs(cost, W), s);
         else launch_side_lanes<1>(x, g, W, ld, b, S, st.partials, mc_runs(cost, W), s);
-        if (ld > P)
-            hipLaunchKernelGGL(mc_zero_pad_kernel, dim3((unsigned)((ld - P + 255) / 256), (unsigned)W), dim3(256), 0, s, g, P, ld);
-        return finish_loss(S.nbinsU, nullptr);
+        return S.sums ? finish_loss(kLossSlots, S.sums) : finish_loss(S.nbinsU, nullptr);
     }
     const int nblk = (int)((nb + kMcEntriesPerBlock - 1) / kMcEntriesPerBlock);
     // the block sums of squares stay in double where the binned path's scratch, idle now, has room for them (always for
