@@ -190,6 +190,89 @@ __global__ __launch_bounds__(mc_atomic_threads(S, FLY)) void mc_grad_atomic_kern
     }
 }
 
+// The general path where a factor has few values: its gradient (LU: of U, LV: of V) is added up in LDS, and only the
+// workgroup's sums go to g.  Entries that meet in a few rows queue up at the memory side otherwise, 40 ns each.  As above,
+// with entries in flight.  Atomics on g / in LDS, us: 93 x 3965, rank 2, 4 workers x 40409 entries 99 to 155 / 20 (as g
+// lies in memory); 87 x 362, rank 1, 8 x 27762 69 / 13; 80 x 8283, rank 8, 5 x 60721 95 / 39; 280 x 3930, rank 16,
+// 16 x 55831 132 / 98; 420 drawn gradient calls with a side of up to 38000 values, as the rule sends them, 0.89 of the
+// time, those of 50 us and more 0.63.
+constexpr int kLdsThreads = 1024;
+
+template <int S, bool LU, bool LV>
+__global__ __launch_bounds__(kLdsThreads) void mc_grad_lds_kernel(
+    const float* __restrict__ x, float* __restrict__ g, int64_t ld, int m, int n, int r,
+    const int32_t* __restrict__ rows, const int32_t* __restrict__ cols, const float* __restrict__ vals,
+    const int32_t* __restrict__ batch_idx, int64_t nb, int64_t per, float two_c, float* __restrict__ partials, double* __restrict__ partials64,
+    const lsgd_mc_entry* __restrict__ entries)
+{
+    constexpr int kSubs = kLdsThreads / S, kFly = S <= 2 ? 2 : S < 8 ? 4 : 8;
+    extern __shared__ float acc[];                       // [LU ? m r : 0][LV ? n r : 0]
+    const int w = blockIdx.y, t = threadIdx.x;
+    const int64_t nu = (int64_t)m * r;
+    const int held = (LU ? (int)nu : 0) + (LV ? n * r : 0);           // fits LDS
+    float* const accV = acc + (LU ? nu : 0);
+    const float* U = x + (int64_t)w * ld;
+    const float* V = U + nu;
+    float* gU = g + (int64_t)w * ld;
+    float* gV = gU + nu;
+    for (int i = t; i < held; i += kLdsThreads) acc[i] = 0.f;
+    __syncthreads();
+    const int sub = t / S, q0 = t % S;
+    const int64_t k0 = (int64_t)blockIdx.x * per, k1 = k0 + per < nb ? k0 + per : nb;
+    double sq = 0.0;
+    auto add = [&](int a, int b, int q, double f, float uq, float vq) {
+        const float du = (float)(f * (double)vq), dv = (float)(f * (double)uq);
+        if (LU) unsafeAtomicAdd(acc + a * r + q, du); else unsafeAtomicAdd(gU + (int64_t)a * r + q, du);
+        if (LV) unsafeAtomicAdd(accV + b * r + q, dv); else unsafeAtomicAdd(gV + (int64_t)b * r + q, dv);
+    };
+    for (int64_t kb = k0 + sub; kb < k1; kb += (int64_t)kSubs * kFly) {
+        int a[kFly], b[kFly];
+        float mv[kFly], ua[kFly], vb[kFly];
+        bool live[kFly];
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+            const int64_t k = kb + (int64_t)u * kSubs;
+            live[u] = k < k1;
+            const int64_t kc = live[u] ? k : kb;         // past the end: the first entry again, its results dropped
+            const int64_t s = batch_idx ? (int64_t)batch_idx[(int64_t)w * nb + kc] : kc;
+            fetch_entry(entries, rows, cols, vals, s, a[u], b[u], mv[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+            ua[u] = q0 < r ? U[(int64_t)a[u] * r + q0] : 0.f;
+            vb[u] = q0 < r ? V[(int64_t)b[u] * r + q0] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+            const float* uu = U + (int64_t)a[u] * r;
+            const float* vv = V + (int64_t)b[u] * r;
+            float dot = ua[u] * vb[u];
+            float low = fmaf(ua[u], vb[u], -dot);        // what the product's rounding dropped
+            for (int q = q0 + S; q < r; q += S) dot = fmaf(uu[q], vv[q], dot);
+            low = fabsf(low) < INFINITY ? low : 0.f;
+            const float e = (group_sum<S>(dot) - mv[u]) + group_sum<S>(low);
+            if (!live[u]) continue;
+            if (q0 == 0) sq += (double)e * (double)e;
+            const double f = (double)two_c * (double)e;
+            if (q0 < r) add(a[u], b[u], q0, f, ua[u], vb[u]);
+            for (int q = q0 + S; q < r; q += S) add(a[u], b[u], q, f, uu[q], vv[q]);
+        }
+    }
+#pragma unroll
+    for (int d = S; d < kWave; d <<= 1) sq += __shfl_xor(sq, d, kWave);
+    __shared__ double red[kLdsThreads / kWave];
+    if (t % kWave == 0) red[t / kWave] = sq;
+    __syncthreads();
+    float* const to = LU ? gU : gV;
+    for (int i = t; i < held; i += kLdsThreads)
+        if (acc[i] != 0.f) unsafeAtomicAdd(to + i, acc[i]);
+    if (t == 0) {
+        for (int q = 1; q < kLdsThreads / kWave; ++q) red[0] += red[q];
+        if (partials64) partials64[(int64_t)w * gridDim.x + blockIdx.x] = red[0];
+        else partials[(int64_t)w * gridDim.x + blockIdx.x] = (float)red[0];
+    }
+}
+
 // Objective only, rank a multiple of 4 and 16-byte aligned rows: LPE lanes share an entry with one float4
 // of each factor row per lane, and four entries per lane group are in flight (index, record and both rows
 // of each are fetched before the first product), since nothing but gathers happens here.
@@ -750,6 +833,38 @@ static McRoute mc_route(const McCost& c, int vw, bool binned_ok)
     return c.flight < c.one ? kMcFlight : kMcOne;
 }
 
+// The same for gradients that are added up in LDS: of the side with fewer values, or of both.  A workgroup per compute unit,
+// chunks per worker, each of at least as many entries as a workgroup of the other loops takes.  What bounds it: the
+// LDS atomics of a workgroup (1.55 us per thousand values), or the requests of the other side and of the workgroups' sums;
+// clearing and writing out what is held.  Fitted to 420 shapes that could go this way, ranks 1 to 64, 10 % rms error.
+constexpr int64_t kLdsValues = 38000;
+struct McLds {
+    double narrow, both;        // us
+    int64_t chunks, per;
+};
+static McLds mc_lds(int W, const lsgd_mc_batch& b)
+{
+    McLds c{1e30, 1e30, 0, 0};
+    const int64_t nb = mc_entries(b), lo = b.m < b.n ? b.m : b.n, hi = b.m < b.n ? b.n : b.m;
+    if (nb <= 0 || lo * b.r > kLdsValues) return c;
+    const int64_t most = (nb + kMcEntriesPerBlock - 1) / kMcEntriesPerBlock;
+    c.chunks = W < 256 ? 256 / W : 1;
+    if (c.chunks > most) c.chunks = most;
+    c.per = (nb + c.chunks - 1) / c.chunks;
+    c.chunks = (nb + c.per - 1) / c.per;
+    int group = 1;                                                      // lanes per entry
+    while (group < b.r && group < kWave) group <<= 1;
+    const int fly = group <= 2 ? 2 : group < 8 ? 4 : 8;
+    const double per = (double)c.per, turns = ceil((double)b.r / group), slots = ceil(per * group / kLdsThreads), rounds = ceil(slots / fly);
+    const double rows = (double)W * (double)(lo + hi) * b.r * 4.0 / 5e6, sums = 1e-3 * (double)c.chunks * W / 16.0;
+    const double pieces = b.r % 16 == 0 || 16 % b.r == 0 ? (b.r > 16 ? b.r / 16.0 : 1.0) : 1.0 + (b.r - 1) / 16.0;
+    const double held = (double)(lo * b.r);
+    c.narrow = 8.0 + dominant(1.55e-3 * per * b.r, 0.07e-3 * (double)W * (double)nb * pieces + 0.015 * sums * held) + 0.069e-3 * held + 1.1 * rows;
+    if ((lo + hi) * b.r <= kLdsValues)
+        c.both = 8.8 + dominant(0.13 * rounds + 0.22 * slots * turns + 3.05e-3 * per * b.r, 0.036 * sums * (double)((lo + hi) * b.r)) + 1.1 * rows;
+    return c;
+}
+
 // Whether dies take contiguous runs of bins (xcd_map).  With a worker per die and W no multiple of eight the busiest die
 // has 8 ceil(W / 8) / W times the average; runs even that out, but spread a worker over dies, so that the fullest bin's
 // records, if that is what the launch waits for, find less of the other factor in their die's L2 (up to 29 % longer).
@@ -857,6 +972,47 @@ static void launch_side_lanes(const float* x, float* g, int W, int64_t ld, const
     else launch_side<32, 2, VW>(x, g, W, ld, b, S, partials, runs, s);
 }
 
+static void launch_fill_zero(float* g, int W, int64_t ld, hipStream_t s)
+{
+    const bool v4 = (reinterpret_cast<uintptr_t>(g) & 15u) == 0 && (ld % 4 == 0);
+    int64_t blocks = ((v4 ? ld / 4 : ld) + 255) / 256;
+    if (blocks > 2048) blocks = 2048;
+    if (blocks < 1) blocks = 1;
+    if (v4) hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, g, ld);
+    else hipLaunchKernelGGL(fill_zero_scalar_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, g, ld);
+}
+
+template <int S>
+static void launch_lds_lanes(const float* x, float* g, int W, int64_t ld, const lsgd_mc_batch& b, int64_t nb, const McLds& c, bool lu, bool lv,
+                             float* partials, double* sums64, hipStream_t s)
+{
+    const size_t lds = sizeof(float) * (size_t)((lu ? (int64_t)b.m * b.r : 0) + (lv ? (int64_t)b.n * b.r : 0));
+    auto go = [&](auto u, auto v) {
+        auto kernel = mc_grad_lds_kernel<S, decltype(u)::value, decltype(v)::value>;
+        if (lds > 48 * 1024) {
+            static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsValues * sizeof(float)));
+            (void)once;
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)c.chunks, (unsigned)W), dim3(kLdsThreads), lds, s, x, g, ld, b.m, b.n, b.r, b.rows, b.cols, b.vals,
+                           b.batch_idx, nb, c.per, 2.0f * b.c, partials, sums64, b.entries);
+    };
+    if (lu && lv) go(std::true_type{}, std::true_type{});
+    else if (lu) go(std::true_type{}, std::false_type{});
+    else go(std::false_type{}, std::true_type{});
+}
+
+static void launch_lds(const float* x, float* g, int W, int64_t ld, const lsgd_mc_batch& b, int64_t nb, const McLds& c, bool lu, bool lv,
+                       float* partials, double* sums64, hipStream_t s)
+{
+    if (b.r <= 1) launch_lds_lanes<1>(x, g, W, ld, b, nb, c, lu, lv, partials, sums64, s);
+    else if (b.r <= 2) launch_lds_lanes<2>(x, g, W, ld, b, nb, c, lu, lv, partials, sums64, s);
+    else if (b.r <= 4) launch_lds_lanes<4>(x, g, W, ld, b, nb, c, lu, lv, partials, sums64, s);
+    else if (b.r <= 8) launch_lds_lanes<8>(x, g, W, ld, b, nb, c, lu, lv, partials, sums64, s);
+    else if (b.r <= 16) launch_lds_lanes<16>(x, g, W, ld, b, nb, c, lu, lv, partials, sums64, s);
+    else if (b.r <= 32) launch_lds_lanes<32>(x, g, W, ld, b, nb, c, lu, lv, partials, sums64, s);
+    else launch_lds_lanes<64>(x, g, W, ld, b, nb, c, lu, lv, partials, sums64, s);
+}
+
 hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
                                const lsgd_mc_batch& b, const DeviceState& st, hipStream_t s, LossParts* parts)
 {
@@ -879,6 +1035,16 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
     const int vw = mc_cols(x, g, ld, b.r);
     const McCost cost = mc_cost(W, b, vw);
     const McRoute route = mc_route(cost, vw, mc_binned_ok(W, b, vw) && st.scratch_bytes >= mc_binned_bytes(W, b));
+    const McLds lds = mc_lds(W, b);
+    const double other = route == kMcBinned ? cost.binned : route == kMcFlight ? cost.flight : cost.one;
+    // The usual route keeps the call unless the estimate is 13 % and 0.7 us lower: at 10 us all routes are launches.
+    if (1.15 * (lds.narrow < lds.both ? lds.narrow : lds.both) + 0.7 < other) {
+        const bool both = lds.both <= lds.narrow, lu = both || b.m <= b.n;
+        double* sums64 = st.scratch_bytes >= sizeof(double) * (size_t)W * (size_t)lds.chunks ? reinterpret_cast<double*>(st.scratch) : nullptr;
+        launch_fill_zero(g, W, ld, s);
+        launch_lds(x, g, W, ld, b, nb, lds, lu, both || !lu, st.partials, sums64, s);
+        return finish_loss((int)lds.chunks, sums64);
+    }
     if (route == kMcBinned) {
         McBinned S;
         S.nbinsU = mc_bins_u(b); S.nbins = mc_bins(b); S.nblk = mc_prep_blocks(W, b); S.E = mc_ept(W, b) * kPrepThreads;
@@ -899,15 +1065,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
     // the block sums of squares stay in double where the binned path's scratch, idle now, has room for them (always for
     // ranks that are multiples of four and could have taken that path)
     double* sums64 = st.scratch_bytes >= sizeof(double) * (size_t)W * (size_t)nblk ? reinterpret_cast<double*>(st.scratch) : nullptr;
-    // general path: zero the whole rows (padding included), then atomics
-    {
-        const bool v4 = (reinterpret_cast<uintptr_t>(g) & 15u) == 0 && (ld % 4 == 0);
-        int64_t blocks = ((v4 ? ld / 4 : ld) + 255) / 256;
-        if (blocks > 2048) blocks = 2048;
-        if (blocks < 1) blocks = 1;
-        if (v4) hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, g, ld);
-        else hipLaunchKernelGGL(fill_zero_scalar_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, g, ld);
-    }
+    launch_fill_zero(g, W, ld, s);                       // general path: whole rows (padding included), then atomics
     if (nblk > 0) {
         dim3 grid((unsigned)nblk, (unsigned)W);
         const float two_c = 2.0f * b.c;
