@@ -30,6 +30,7 @@ struct GemmArgs {
     float* C; int64_t sC; int64_t ldc;            // EPI_DW, EPI_LOGITS: fp32 [M][N]
     // EPI_HEAD (out, outT: the output deltas [M][N] and [N][M], or NULL)
     const int32_t* y;                             // [M] per worker
+    uint16_t* dx; uint16_t* dxT;                  // the d-input product [M][K] and [K][M] (strides of out), or NULL
     double* loss_parts; int64_t sLoss; float* losses; // loss sums of the row tiles (sLoss doubles between workers), or the losses when one tile holds the batch
     float* pad; int64_t pad_from, pad_to;         // columns [pad_from, pad_to) of rows of pad_to floats to clear, or NULL
     FusedUpdate fu; int64_t colC;                 // EPI_DWU: update state; column of C[0][0] in the parameter row
@@ -210,5 +211,13 @@ bool launch_gemm_direct_any(const GemmArgs& g, int W, int epi, hipStream_t s);
 
 // Matrix products of any shape and alignment (mlp_gemm_ragged.hip).
 void launch_gemm_ragged(const GemmArgs& g, int W, int epi, hipStream_t s);
+
+// d-weight products (EPI_DW or EPI_DWU) of up to kGroupMax layers in one launch.
+constexpr int kGroupMax = 6;
+struct GemmGroup {
+    GemmArgs g[kGroupMax];
+    int n;
+};
+void launch_gemm_group(const GemmGroup& q, int W, int epi, hipStream_t s);
 
 } // namespace lsgd

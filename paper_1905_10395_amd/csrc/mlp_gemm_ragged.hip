@@ -122,8 +122,9 @@ struct RaggedShape {
     static constexpr size_t lds = operand_bytes > result_bytes ? operand_bytes : result_bytes;
 };
 
+// Tile `id` of a product's tiles_m x tiles_n x W.
 template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
-__global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1) void gemm_ragged_kernel(GemmArgs g, int tiles_m, int tiles_n, int W, int64_t per_xcd)
+__device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m, int tiles_n, int W, int64_t id)
 {
     using S = RaggedShape<BM, BN, WVM, WVN, WVK, BK, EPI>;
     using Sum = typename S::Sum;
@@ -143,11 +144,9 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int wk = wid % WVK, wn = (wid / WVK) % WVN, wm = wid / (WVK * WVN);
 
-    // A die (workgroup id modulo 8) takes a contiguous run of tiles.  Row tiles vary fastest, so that the tiles
-    // that share a weight tile, and the workgroups of a worker, which share its activations, run on one die.  In
-    // the fused update the workers vary fastest instead: they share the leader copies' tile.
-    const int64_t id = (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-    if (id >= (int64_t)tiles_m * tiles_n * W) return;
+    // Row tiles vary fastest, so that the tiles that share a weight tile, and the workgroups of a worker, which share
+    // its activations, run on one die.  In the fused update the workers vary fastest instead: they share the leader
+    // copies' tile.
     int w, tm, tn;
     if (EPI == EPI_DWU) {
         w = (int)(id % W);
@@ -397,6 +396,7 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
     if constexpr (EPI == EPI_HEAD) {
         static_assert(BM == 32 && THREADS >= 256, "eight lanes per sample");
         __shared__ double row_loss[BM];
+        __shared__ __attribute__((aligned(16))) uint16_t dl[BM][BN + 8];  // output deltas, zeros beyond M and N
         if (tid < 256) {
             const int r = tid >> 3, l = tid & 7, m = m0 + r;             // lane l of the sample's eight: classes l, l + 8, ...
             const int yb = m < M ? g.y[(int64_t)w * M + m] : -1;
@@ -424,20 +424,74 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
             for (int d = 1; d < 8; d <<= 1) { se += __shfl_xor(se, d, 64); zy += __shfl_xor(zy, d, 64); }
             const float lse = mx + logf(se);
             if (l == 0) row_loss[r] = m < M ? (double)(lse - zy) : 0.0;
-            if (m < M && g.out) {
+            if (g.out) {
                 const float inv = 1.0f / (float)M;
 #pragma unroll
                 for (int j = 0; j < BN / 8; ++j) {
                     const int c = l + 8 * j;
-                    if (c < N) {
-                        const uint16_t q = f32_to_bf16_rne((expf(z[j] - lse) - (c == yb ? 1.f : 0.f)) * inv);
-                        g.out[(int64_t)w * g.sOut + (int64_t)m * N + c] = q;
+                    uint16_t q = 0;
+                    if (m < M && c < N) {
+                        q = f32_to_bf16_rne((expf(z[j] - lse) - (c == yb ? 1.f : 0.f)) * inv);
+                        if (!g.dx) g.out[(int64_t)w * g.sOut + (int64_t)m * N + c] = q;
                         g.outT[(int64_t)w * g.sOut + (int64_t)c * M + m] = q;
                     }
+                    dl[r][c] = q;
                 }
             }
         }
         __syncthreads();
+        if (g.dx) {
+            // The d-input product of the classifier: its deltas are here.  A wavefront takes 32 columns at a time; lane
+            // (n = lane % 32, k-half = lane / 32) reads eight rows of W at column n.
+            bf16x8 af[BN / 16];
+#pragma unroll
+            for (int q = 0; q < BN / 16; ++q)
+                af[q] = *reinterpret_cast<const bf16x8*>(&dl[lane & 31][q * 16 + 8 * (lane >> 5)]);
+            uint16_t* const dx = g.dx + (int64_t)w * g.sOut + (int64_t)m0 * K;
+            uint16_t* const dxT = g.dxT + (int64_t)w * g.sOut + m0;
+            const uint16_t* const Am = A + (int64_t)m0 * g.lda;
+            int half = lane >> 5, left = M - m0 < BM ? M - m0 : BM;
+#pragma unroll 1
+            for (int c0 = wid * 32; c0 < K; c0 += THREADS / 2) {
+                asm("" : "+v"(half), "+v"(left));                        // or the loop carries a mask and an address per row
+                const int n = c0 + (lane & 31), nin = n < K ? n : K - 1;
+                uint16_t hv[16];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int r = half * 4 + 8 * (v >> 2) + (v & 3);
+                    hv[v] = Am[(uint32_t)((r < left ? r : left - 1) * (int)g.lda + nin)];
+                }
+                f32x16 d;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) d[v] = 0.f;
+#pragma unroll
+                for (int q = 0; q < BN / 16; ++q) {
+                    s16x8 b;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int c = q * 16 + 8 * half + e;             // past the last class: zero (a zero delta times infinity is not)
+                        const uint16_t wv = B[(uint32_t)((c < N ? c : N - 1) * (int)g.ldb + nin)];
+                        b[e] = c < N ? (short)wv : (short)0;
+                    }
+                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[q], __builtin_bit_cast(bf16x8, b), d, 0, 0, 0);
+                }
+                if (n >= K) continue;
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    const int r = half * 4 + 8 * p;
+                    uint32_t o[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        o[e] = hv[4 * p + e] == 0 ? 0u : (uint32_t)f32_to_bf16_rne(d[4 * p + e]);
+                        if (r + e < left) dx[(uint32_t)((r + e) * K + n)] = (uint16_t)o[e];
+                    }
+                    const u32x2 t = {o[0] | o[1] << 16, o[2] | o[3] << 16};
+                    uint16_t* const to = dxT + (int64_t)n * M + r;
+                    if (r + 4 <= left) *reinterpret_cast<u32x2_any*>(to) = t;
+                    else store_some(to, t, left - r);
+                }
+            }
+        }
         if (tid == 0) {
             double t = 0.0;
             for (int r = 0; r < BM; ++r) t += row_loss[r];
@@ -568,6 +622,56 @@ __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1)
     }
 }
 
+// A die (workgroup id modulo 8) takes a contiguous run of tiles.
+template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
+__global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1) void gemm_ragged_kernel(GemmArgs g, int tiles_m, int tiles_n, int W, int64_t per_xcd)
+{
+    const int64_t id = (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    if (id >= (int64_t)tiles_m * tiles_n * W) return;
+    gemm_ragged_tile<BM, BN, WVM, WVN, WVK, BK, EPI>(g, tiles_m, tiles_n, W, id);
+}
+
+// Tiles of several products, of BM rows, or of 32 where a product has no more.  Every die takes a run of each product,
+// the last product first (layer 1, mostly the largest: the short tiles of the classifier fill the end).  A launch of a
+// few us per layer otherwise: 784-300-100-10, 8 workers, batch 50, 14 -> 7 us; with one run of all tiles per die, and
+// so the short tiles on some dies only, 256-4096-10, 16 x 32, took 63 us for a gradient instead of 57.
+template <int BM>
+__host__ __device__ inline int64_t group_tiles(const GemmArgs& g, int W, int& tiles_m, int& tiles_n)
+{
+    tiles_m = g.M > 32 ? (g.M + BM - 1) / BM : 1;
+    tiles_n = (g.N + 63) / 64;
+    return (int64_t)tiles_m * tiles_n * W;
+}
+
+template <int BM, int EPI>
+__global__ __launch_bounds__(256, 2) void gemm_group_kernel(GemmGroup q, int W)
+{
+    int64_t l = blockIdx.x / kXcds;
+    for (int i = q.n - 1; i >= 0; --i) {                                 // uniform
+        int tiles_m, tiles_n;
+        const int64_t tiles = group_tiles<BM>(q.g[i], W, tiles_m, tiles_n), run = (tiles + kXcds - 1) / kXcds;
+        if (l < run) {
+            const int64_t id = (int64_t)(blockIdx.x % kXcds) * run + l;
+            if (id >= tiles) return;
+            if (q.g[i].M > 32) gemm_ragged_tile<BM, 64, 2, 2, 1, 64, EPI>(q.g[i], tiles_m, tiles_n, W, id);
+            else gemm_ragged_tile<32, 64, 1, 2, 2, 64, EPI>(q.g[i], tiles_m, tiles_n, W, id);
+            return;
+        }
+        l -= run;
+    }
+}
+
+template <int BM, int EPI>
+void launch_tiles(const GemmGroup& q, int W, hipStream_t s)
+{
+    constexpr size_t big = RaggedShape<BM, 64, 2, 2, 1, 64, EPI>::lds, small = RaggedShape<32, 64, 1, 2, 2, 64, EPI>::lds;
+    static_assert(big <= 64 * 1024 && small <= 64 * 1024, "no attribute set");
+    int64_t runs = 0;
+    int tm, tn;
+    for (int i = 0; i < q.n; ++i) runs += (group_tiles<BM>(q.g[i], W, tm, tn) + kXcds - 1) / kXcds;
+    hipLaunchKernelGGL((gemm_group_kernel<BM, EPI>), dim3((unsigned)(runs * kXcds)), dim3(256), big > small ? big : small, s, q, W);
+}
+
 template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
 void launch_tile(const GemmArgs& g, int W, hipStream_t s)
 {
@@ -633,7 +737,27 @@ void launch_epi(const GemmArgs& g, int W, hipStream_t s)
     }
 }
 
+template <int EPI>
+void launch_group_epi(const GemmGroup& q, int W, hipStream_t s)
+{
+    int64_t tiles = 0;                                       // of 128 rows
+    int widest = 0, tm, tn;
+    for (int i = 0; i < q.n; ++i) {
+        tiles += group_tiles<128>(q.g[i], W, tm, tn);
+        if (q.g[i].M > widest) widest = q.g[i].M;
+    }
+    if (widest > 64 && tiles >= 256) launch_tiles<128, EPI>(q, W, s);
+    else launch_tiles<64, EPI>(q, W, s);
+}
+
 } // namespace
+
+void launch_gemm_group(const GemmGroup& q, int W, int epi, hipStream_t s)
+{
+    if (q.n == 1) launch_gemm_ragged(q.g[0], W, epi, s);
+    else if (epi == EPI_DW) launch_group_epi<EPI_DW>(q, W, s);
+    else launch_group_epi<EPI_DWU>(q, W, s);
+}
 
 void launch_gemm_ragged(const GemmArgs& g, int W, int epi, hipStream_t s)
 {

@@ -558,6 +558,20 @@ hipError_t launch_mlp_grad_loss(const uint16_t* xb, const float* x, float* g, fl
     return launch_mlp_backward(xb, x, g, W, P, ld, b, st, nullptr, s);
 }
 
+// Whether the launch of the classifier also forms its d-input product, on its W B / 32 workgroups alone: a launch less,
+// but fewer workgroups than the product of its own has, and wavefronts that take more and more columns each.  Whole
+// gradient calls and steps, own launch = 1: 10 classes behind 64 units 0.85 to 0.88, 256 0.94, 512 0.95, 768 0.97, 1024
+// 1.01 to 1.07, 4096 1.07 to 1.5; behind 1024 to 4096 with 256 workgroups 0.92; 60 classes (four wavefronts) behind 512
+// units 1.08.
+static bool head_forms_dx(const lsgd_mlp_batch& b, int W)
+{
+    const int L = b.n_layers;
+    if (L < 2 || b.dims[L] > 64) return false;
+    const int64_t units = b.dims[L - 1];
+    if (b.dims[L] > 32) return units <= 256;
+    return units <= 768 || (units <= 4096 && (int64_t)W * ((b.B + 31) / 32) >= 256);
+}
+
 hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
                               const lsgd_mlp_batch& b, const DeviceState& st, bool backward, LossParts* parts, hipStream_t s)
 {
@@ -602,6 +616,7 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, floa
             // the tiles' loss sums lie where the worker's logits would (4 B C bytes hold B / 32 doubles)
             a.loss_parts = reinterpret_cast<double*>(logits); a.sLoss = p.per_worker / 8;
             if (backward) { a.out = sc16 + p.d[L]; a.outT = sc16 + p.dT[L]; a.sOut = sW16; }
+            if (backward && head_forms_dx(b, W)) { a.dx = sc16 + p.d[L - 1]; a.dxT = sc16 + p.dT[L - 1]; }
             a.pad = ld > P ? g : nullptr; a.pad_from = P; a.pad_to = ld;
             launch_gemm_ragged(a, W, EPI_HEAD, s);
             if (tiles > 1 && loss_parts_ok(W, tiles)) {        // one order, whoever adds them up
@@ -625,7 +640,7 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, floa
 }
 
 // Backward pass.  Per layer, from the top: delta_{k-1} first (it reads W_k, which the fused update
-// of dW_k overwrites), then dW_k and db_k.
+// of dW_k overwrites), then dW_k and db_k; those without an aligned tile in one launch at the end.
 hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int W, int64_t P, int64_t ld,
                                const lsgd_mlp_batch& b, const DeviceState& st, const FusedUpdate* fu_in, hipStream_t s)
 {
@@ -643,12 +658,14 @@ hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int
     // fp32 inputs: the forward pass of this step left their bf16 copy in the scratch
     const uint16_t* X0 = b.x_is_fp32 ? sc16 + p.x0 : static_cast<const uint16_t*>(b.X);
     const int64_t sX0 = b.x_is_fp32 ? sW16 : (int64_t)B * b.dims[0];
+    const int epi = fused ? EPI_DWU : EPI_DW;
+    GemmGroup rest{};
     for (int k = L; k >= 1; --k) {
         const int din = b.dims[k - 1], dout = b.dims[k];
         const uint16_t* Hin = (k == 1) ? X0 : sc16 + p.h[k - 1];
         const int64_t sHin = (k == 1) ? sX0 : sW16;
         // delta_{k-1}
-        if (k > 1) {
+        if (k > 1 && !(k == L && head_forms_dx(b, W))) {
             GemmArgs a{};
             a.A = sc16 + p.d[k]; a.sA = sW16; a.lda = dout;
             a.B = xb + woff[k]; a.sB = ld; a.ldb = din;
@@ -666,10 +683,11 @@ hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int
             a.M = dout; a.N = din; a.K = B;
             a.C = g + woff[k]; a.sC = ld; a.ldc = din;
             a.fu = fu; a.colC = woff[k];
-            if (!(fused ? try_mfma<true, EPI_DWU>(a, W, s) : try_mfma<true, EPI_DW>(a, W, s)))
-                launch_gemm_ragged(a, W, fused ? EPI_DWU : EPI_DW, s);
+            if (!(fused ? try_mfma<true, EPI_DWU>(a, W, s) : try_mfma<true, EPI_DW>(a, W, s))) rest.g[rest.n++] = a;
+            if (rest.n == kGroupMax) { launch_gemm_group(rest, W, epi, s); rest.n = 0; }
         }
     }
+    if (rest.n) launch_gemm_group(rest, W, epi, s);
     return hipGetLastError();
 }
 
