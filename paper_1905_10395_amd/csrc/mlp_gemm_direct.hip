@@ -1,5 +1,5 @@
 // Forward and d-input products of the MLP path on 16-byte aligned operands with more than 64 samples per worker:
-// operands go from global memory straight to LDS, three K steps deep.
+// operands go from global memory straight to LDS, three or four K steps deep.
 //
 //   forward   out[m][n] = bf16(relu(<A[m,:], B[n,:]> + bias[n]))      A = h_{k-1}, B = W_k       (both [.][k])
 //   d-input   out[m][n] = bf16(sum_k A[m][k] B[k][n]) * [mask != 0]   A = delta_k, B = W_k       (B as [k][n]); outT transposed
@@ -7,7 +7,7 @@
 // What bounds these products is what reaches the compute units (a batch of 128 to 256 rows per weight: 17 TB/s of
 // tiles out of L2 measured without the products), and for the largest the chip's power limit: 256 x 4096 x 4096, 8
 // workers, takes 68 us on zeros and 80 us on normal values, at 1.8 to 2.1 instead of 2.4 GHz, in every tile and wavefront
-// shape.  Loads that go straight to LDS need no registers, so three K steps are under way per workgroup, and no vector
+// shape.  Loads that go straight to LDS need no registers, so three K steps or more are under way per workgroup, and no vector
 // instructions to store them.  A wavefront's load writes 64 consecutive 16-byte pieces, so rows cannot be padded: the
 // pieces of a row are stored in another order instead (exclusive or with the row number), which spreads the fragment
 // reads over all banks.  Fragments are read a quarter step ahead of their products, across the barrier too.
@@ -29,7 +29,6 @@ namespace lsgd {
 namespace {
 
 constexpr int kBK = 64;              // contraction per K step: one 128-byte line of every row
-constexpr int ST = 3;                // K steps in LDS
 
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef const __attribute__((address_space(1))) void* global_ptr;
@@ -54,7 +53,8 @@ __device__ __forceinline__ void for_each(const F& f)
     if constexpr (I < N) { f(std::integral_constant<int, I>{}); for_each<N, I + 1>(f); }
 }
 
-template <int BM, int BN, int WVM, int WVN, bool TRANS_B, int EPI, bool ANY>
+// ST: K steps in LDS
+template <int BM, int BN, int WVM, int WVN, int ST, bool TRANS_B, int EPI, bool ANY>
 __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g, int tiles_m, int tiles_n)
 {
     constexpr int THREADS = 64 * WVM * WVN;
@@ -63,8 +63,12 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
     constexpr int NCH = BN / 8;                                       // pieces of a [k][n] row
     constexpr int TILE = (BM + BN) * kBK;
     // separate objects, so that the compiler sees that a read of one does not wait for loads into another
-    __shared__ __attribute__((aligned(16))) uint16_t buf0[TILE], buf1[TILE], buf2[TILE];
-    auto bufs = [&](int q) -> uint16_t* { return q == 0 ? buf0 : q == 1 ? buf1 : buf2; };
+    __shared__ __attribute__((aligned(16))) uint16_t buf0[TILE], buf1[TILE], buf2[TILE], buf3[ST > 3 ? TILE : 8];
+    static_assert(ST == 3 || ST == 4, "buffers");
+    auto bufs = [&](int q) -> uint16_t* {
+        if constexpr (ST > 3) { if (q == 3) return buf3; }
+        return q == 0 ? buf0 : q == 1 ? buf1 : buf2;
+    };
 
     const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wid / WVN, wn = wid % WVN;
@@ -297,13 +301,21 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
     }
 }
 
-template <int BM, int BN, int WVM, int WVN, bool ANY>
+template <int BM, int BN, int WVM, int WVN, int ST>
+void launch_forward(const GemmArgs& g, int W, hipStream_t s)
+{
+    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+    hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, ST, false, EPI_FWD, true>), dim3((unsigned)(tiles_m * tiles_n * W)),
+                       dim3(64 * WVM * WVN), 0, s, g, tiles_m, tiles_n);
+}
+
+template <int BM, int BN, int WVM, int WVN, int ST, bool ANY>
 void launch_direct(const GemmArgs& g, int W, int epi, hipStream_t s)
 {
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     const dim3 grid((unsigned)(tiles_m * tiles_n * W)), block(64 * WVM * WVN);
-    if (epi == EPI_FWD) hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, false, EPI_FWD, ANY>), grid, block, 0, s, g, tiles_m, tiles_n);
-    else hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, true, EPI_DX, ANY>), grid, block, 0, s, g, tiles_m, tiles_n);
+    if (epi == EPI_FWD) hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, ST, false, EPI_FWD, ANY>), grid, block, 0, s, g, tiles_m, tiles_n);
+    else hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, ST, true, EPI_DX, ANY>), grid, block, 0, s, g, tiles_m, tiles_n);
 }
 
 // 128 columns as long as that leaves few compute units without a tile (forward 500 x 300 x 784, 16 workers, 192 tiles of
@@ -319,9 +331,9 @@ bool wide_tile(const GemmArgs& g, int W, int epi)
 void launch_gemm_direct(const GemmArgs& g, int W, int epi, hipStream_t s)
 {
     // a 256-row tile covers a whole batch of 256: the weights are then read once
-    if (g.M % 256 == 0 && g.N % 128 == 0 && (int64_t)(g.M / 256) * (g.N / 128) * W >= 256) launch_direct<256, 128, 4, 2, false>(g, W, epi, s);
-    else if (g.N % 128 == 0 && wide_tile(g, W, epi)) launch_direct<128, 128, 2, 4, false>(g, W, epi, s);
-    else launch_direct<128, 64, 2, 2, false>(g, W, epi, s);
+    if (g.M % 256 == 0 && g.N % 128 == 0 && (int64_t)(g.M / 256) * (g.N / 128) * W >= 256) launch_direct<256, 128, 4, 2, 3, false>(g, W, epi, s);
+    else if (g.N % 128 == 0 && wide_tile(g, W, epi)) launch_direct<128, 128, 2, 4, 3, false>(g, W, epi, s);
+    else launch_direct<128, 64, 2, 2, 3, false>(g, W, epi, s);
 }
 
 bool launch_gemm_direct_any(const GemmArgs& g, int W, int epi, hipStream_t s)
@@ -332,8 +344,12 @@ bool launch_gemm_direct_any(const GemmArgs& g, int W, int epi, hipStream_t s)
     // Only where the any-shape kernel takes 128-row tiles too: its smaller tiles round less often (and with fewer
     // workgroups than compute units they are the faster ones, 128 x 1000 x 784, 4 workers: 8.5 against 10.9 us).
     if (g.M <= 64 || (int64_t)((g.M + 127) / 128) * ((g.N + 63) / 64) * W < 256) return false;
-    if (wide_tile(g, W, epi)) launch_direct<128, 128, 2, 4, true>(g, W, epi, s);
-    else launch_direct<128, 64, 2, 2, true>(g, W, epi, s);
+    // One K step more in LDS where the contraction is long: with double sums a step takes longer than its loads, and the
+    // 128 x 128 tile has a compute unit to itself (forward 500 x 3072 x 1024, 16 workers, 79.5 -> 76.8 us; whole tiles and
+    // the 64-column tile, two workgroups per compute unit, gain nothing, contractions of 256 lose 2 %).
+    if (wide_tile(g, W, epi) && g.K >= 1024 && epi == EPI_FWD) launch_forward<128, 128, 2, 4, 4>(g, W, s);
+    else if (wide_tile(g, W, epi)) launch_direct<128, 128, 2, 4, 3, true>(g, W, epi, s);
+    else launch_direct<128, 64, 2, 2, 3, true>(g, W, epi, s);
     return true;
 }
 
