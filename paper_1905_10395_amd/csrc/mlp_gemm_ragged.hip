@@ -702,11 +702,13 @@ void launch_tile(const GemmArgs& g, int W, hipStream_t s)
 // Row tile: a batch of up to 32 / 64 fits one tile; larger ones take 128 rows, unless that leaves compute units
 // without a workgroup.  When there are few tiles and a long contraction (the classifier layer, a narrow first
 // layer), sixteen wavefronts split the contraction of a 32 x 32 tile, 64 KB of operands per K step: logits of
-// 4096 -> 10, 8 workers, batch 256 25 -> 17 us, of 1024 -> 10, 16 workers, batch 128 11 -> 8 us.
+// 4096 -> 10, 8 workers, batch 256 25 -> 17 us, of 1024 -> 10, 16 workers, batch 128 11 -> 8 us; whole gradients of
+// 256-73-377-10, 16 x 16, 36.7 -> 34.0 us, of 100-353-2, 15 x 128, 27.1 -> 25.0; at 256 units half the K step would be
+// empty (256-256-10, 4 x 200, 12.4 -> 14.1).
 void launch_head(const GemmArgs& g, int W, hipStream_t s)
 {
     const int64_t tiles = (int64_t)W * ((g.M + 31) / 32);
-    if (g.N <= 32 && g.K >= 512 && tiles <= 512) launch_tile<32, 32, 1, 1, 16, 512, EPI_HEAD>(g, W, s);
+    if (g.N <= 32 && g.K > 256 && tiles <= 512) launch_tile<32, 32, 1, 1, 16, 512, EPI_HEAD>(g, W, s);
     else if (g.N <= 32) launch_tile<32, 32, 1, 1, 4, 128, EPI_HEAD>(g, W, s);
     else launch_tile<32, 64, 1, 1, 4, 128, EPI_HEAD>(g, W, s);
 }

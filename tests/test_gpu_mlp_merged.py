@@ -15,6 +15,7 @@ SHAPES = [
     ([40, 1, 2], 2, 1), ([24, 31, 3], 3, 31), ([24, 33, 16], 3, 33), ([24, 513, 17], 3, 65),
     ([24, 767, 10], 5, 32), ([24, 768, 32], 5, 34), ([24, 769, 10], 5, 32),
     ([24, 255, 33], 4, 40), ([24, 256, 64], 4, 95), ([24, 257, 64], 4, 40),
+    ([24, 256, 10], 3, 33), ([24, 257, 10], 3, 33), ([24, 300, 32], 3, 50),
     ([24, 1030, 10], 128, 34), ([24, 4096, 32], 16, 500),        # 256 workgroups: wider layers
     ([200, 300, 40], 16, 50), ([500, 2000, 10], 16, 33), ([64, 20, 65], 3, 50),
 ]
