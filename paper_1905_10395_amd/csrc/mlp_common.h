@@ -23,6 +23,7 @@ struct GemmArgs {
     const uint16_t* A; int64_t sA; int64_t lda;   // [M][K], per-worker stride sA (elements)
     const uint16_t* B; int64_t sB; int64_t ldb;   // TRANS_B ? [K][N] : [N][K]
     int M, N, K;
+    const float* A32; uint16_t* copy; int64_t sCopy; // EPI_FWD on fp32 inputs (in place of A, strides sA and lda): where their bf16 copy [M][K] goes, or NULL
     const float* bias; int64_t sBias;             // EPI_FWD: fp32 [N]
     const uint16_t* mask; int64_t sMask; int64_t ldmask; // EPI_DX: h_{k-1} [M][N]
     uint16_t* out; int64_t sOut; int64_t ldout;   // EPI_FWD: h [M][N]; EPI_DX: delta [M][N]
@@ -211,6 +212,9 @@ bool launch_gemm_direct_any(const GemmArgs& g, int W, int epi, hipStream_t s);
 
 // Matrix products of any shape and alignment (mlp_gemm_ragged.hip).
 void launch_gemm_ragged(const GemmArgs& g, int W, int epi, hipStream_t s);
+// Forward product of fp32 inputs g.A32, rounded to bf16 on their way; false (nothing launched) where a launch that converts
+// them first is the better way.
+bool launch_gemm_ragged_f32(const GemmArgs& g, int W, hipStream_t s);
 
 // d-weight products (EPI_DW or EPI_DWU) of up to kGroupMax layers in one launch.
 constexpr int kGroupMax = 6;

@@ -3,7 +3,8 @@
 //
 //   forward   out[m][n] = bf16(relu(<A[m,:], B[n,:]> + bias[n]))      A = h_{k-1}, B = W_k       (both [.][k])
 //   logits    C[m][n]   = <A[m,:], B[n,:]> + bias[n]
-//   head      the same for up to 64 classes, kept in LDS: softmax cross-entropy, its sum per row tile, output deltas
+//   head      the same for up to 64 classes, kept in LDS: softmax cross-entropy, its sum per row tile, output deltas, and
+//             the classifier's d-input product where the caller asks for it
 //   d-input   out[m][n] = bf16(sum_k A[m][k] B[k][n]) * [mask != 0]   A = delta_k, B = W_k       (B as [k][n])
 //   d-weight  C[m][n]   = sum_k A[m][k] B[k][n]                       A = delta_k^T, B = h_{k-1}  (or the update)
 //
@@ -27,9 +28,8 @@
 // become the limit (5.7e-8; 105 against 81 us without sums on 500 x 3072 x 1024, 16 workers).
 //
 // Measured (whole passes, against one-thread-per-output vector-ALU kernels that re-read an operand per output):
-// gradients of 3072-1024-512-10, 16 workers, batch 32: 19.7 ms -> 0.10 ms; objective of 3072-1024-10, 16 workers,
-// batch 500: 16.2 -> 0.09 ms (first product 0.087 ms = 570 TFLOP/s); whole step of 784-300-100-10, 8 workers,
-// batch 50: 1.26 -> 0.062 ms (3 to 6 us per product: launch and fill, not work).
+// gradients of 3072-1024-512-10, 16 workers, batch 32: 19.7 ms -> 0.10 ms; whole step of 784-300-100-10, 8 workers,
+// batch 50: 1.26 -> 0.052 ms (4 to 9 us per product: launch and fill, not work).
 #include <type_traits>
 
 #include "mlp_common.h"
@@ -128,8 +128,21 @@ struct RaggedShape {
     static constexpr size_t lds = bytes(2);
 };
 
-// Tile `id` of a product's tiles_m x tiles_n x W.
-template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
+// A 16-byte piece of a row of A, or the eight fp32 values that become one.
+struct F32Piece { f32x4 lo, hi; };
+__device__ __forceinline__ u32x4 as_piece(const F32Piece& v)
+{
+    return (u32x4){f32x2_to_bf16x2(v.lo.x, v.lo.y), f32x2_to_bf16x2(v.lo.z, v.lo.w), f32x2_to_bf16x2(v.hi.x, v.hi.y), f32x2_to_bf16x2(v.hi.z, v.hi.w)};
+}
+__device__ __forceinline__ void load_piece(u32x4& v, const uint16_t* p) { v = load16(p); }
+__device__ __forceinline__ void load_piece(F32Piece& v, const float* p)
+{
+    v.lo = *reinterpret_cast<const f32x4_any*>(p);
+    v.hi = *reinterpret_cast<const f32x4_any*>(p + 4);
+}
+
+// Tile `id` of a product's tiles_m x tiles_n x W.  F32A: A in fp32, rows of at least 8 values.
+template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI, bool F32A = false>
 __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m, int tiles_n, int W, int64_t id)
 {
     using S = RaggedShape<BM, BN, WVM, WVN, WVK, BK, EPI>;
@@ -164,9 +177,13 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
         tn = (int)(r % tiles_n); w = (int)(r / tiles_n);
     }
     const int m0 = tm * BM, n0 = tn * BN, M = g.M, N = g.N, K = g.K;
-    const uint16_t* A = g.A + (int64_t)w * g.sA;
+    using AElem = typename std::conditional<F32A, float, uint16_t>::type;
+    using APiece = typename std::conditional<F32A, F32Piece, u32x4>::type;
+    const AElem* A;
+    if constexpr (F32A) A = g.A32 + (int64_t)w * g.sA;
+    else A = g.A + (int64_t)w * g.sA;
     const uint16_t* B = g.B + (int64_t)w * g.sB;
-    const bool short_k = K < 8, short_n = TRANS_B && N < 8;             // uniform
+    const bool short_k = !F32A && K < 8, short_n = TRANS_B && N < 8;             // uniform
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -202,7 +219,7 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
     // this thread's pieces: column piece kc of rows ra0 + c * A_STEP (a [k][n] operand: piece nc of rows kr0 + c * B_STEP)
     const int kc = (tid % KCH) * 8, ra0 = tid / KCH;
     const int nc = (tid % NCH) * 8, kr0 = tid / NCH;
-    const uint16_t* arow[A_CHUNKS];
+    const AElem* arow[A_CHUNKS];
     const uint16_t* brow[B_CHUNKS];
 #pragma unroll
     for (int c = 0; c < A_CHUNKS; ++c) {
@@ -220,10 +237,10 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
     const int bshift = bcol - bcol_in < 8 ? bcol - bcol_in : 8;
     const bool edge_n = n0 + BN > N;                                     // uniform
 
-    auto load_global = [&](int kt, u32x4* ra, u32x4* rb) {               // rows of at least 8 elements
+    auto load_global = [&](int kt, APiece* ra, u32x4* rb) {              // rows of at least 8 elements
         const int k = kt * BK + kc, kin = k < K - 8 ? k : K - 8;
 #pragma unroll
-        for (int c = 0; c < A_CHUNKS; ++c) ra[c] = load16(arow[c] + kin);
+        for (int c = 0; c < A_CHUNKS; ++c) load_piece(ra[c], arow[c] + kin);
 #pragma unroll
         for (int c = 0; c < B_CHUNKS; ++c) {
             if (TRANS_B) {
@@ -236,6 +253,7 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
         }
     };
     auto load_global_short = [&](int kt, u32x4* ra, u32x4* rb) {         // any length
+        if constexpr (!F32A) {
         const int k = kt * BK + kc, n = K - k < 0 ? 0 : K - k;
 #pragma unroll
         for (int c = 0; c < A_CHUNKS; ++c) ra[c] = load_short(arow[c] + k, n);
@@ -247,6 +265,7 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
             } else {
                 rb[c] = load_short(brow[c] + k, n);
             }
+        }
         }
     };
     auto store_lds = [&](int buf, int kt, u32x4* ra, u32x4* rb, bool shift) {
@@ -275,6 +294,27 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
         } else {
 #pragma unroll
             for (int c = 0; c < B_CHUNKS; ++c) *reinterpret_cast<u32x4*>(bs + (ra0 + c * A_STEP) * LDA + kc) = rb[c];
+        }
+    };
+    // The first tile column of a product on fp32 inputs also leaves their bf16 copy (pieces that were moved back, and rows
+    // past the end, write what is there already).
+    uint16_t* const copy = F32A && g.copy && tn == 0 ? g.copy + (int64_t)w * g.sCopy : nullptr;      // uniform
+    auto store_step = [&](int buf, int kt, APiece* pa, u32x4* rb) {
+        if constexpr (F32A) {
+            u32x4 ra[A_CHUNKS];
+            const int k = kt * BK + kc, kin = k < K - 8 ? k : K - 8;
+#pragma unroll
+            for (int c = 0; c < A_CHUNKS; ++c) ra[c] = as_piece(pa[c]);
+            if (copy) {
+#pragma unroll
+                for (int c = 0; c < A_CHUNKS; ++c) {
+                    const int r = m0 + ra0 + c * A_STEP;
+                    *reinterpret_cast<u32x4_any*>(copy + (int64_t)(r < M ? r : M - 1) * K + kin) = ra[c];
+                }
+            }
+            store_lds(buf, kt, ra, rb, true);
+        } else {
+            store_lds(buf, kt, pa, rb, true);
         }
     };
     // the first tile column of a d-weight product also sums its rows of delta^T: the bias gradients
@@ -330,22 +370,23 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
             __syncthreads();
         }
     } else {
-        u32x4 ra[A_CHUNKS], rb[B_CHUNKS], qa[A_CHUNKS], qb[B_CHUNKS];
+        APiece ra[A_CHUNKS], qa[A_CHUNKS];
+        u32x4 rb[B_CHUNKS], qb[B_CHUNKS];
         int kt = 0;
         load_global(0, ra, rb);
         if (nk > 4) {
             load_global(1, qa, qb);
             __builtin_amdgcn_sched_barrier(0);           // the two stages' loads in the order in which the loop waits for them
-            store_lds(0, 0, ra, rb, true);
+            store_step(0, 0, ra, rb);
             load_global(2, ra, rb);
             __syncthreads();
             // no conditional load in here: behind a branch around loads the compiler waits for all loads in flight
             for (; kt + 4 < nk; kt += 2) {
-                store_lds(1, kt + 1, qa, qb, true);
+                store_step(1, kt + 1, qa, qb);
                 load_global(kt + 3, qa, qb);
                 compute(0);
                 __syncthreads();
-                store_lds(0, kt + 2, ra, rb, true);
+                store_step(0, kt + 2, ra, rb);
                 load_global(kt + 4, ra, rb);
                 compute(1);
                 promote_pair();
@@ -353,23 +394,23 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
             }
         } else {
             if (nk > 1) load_global(1, qa, qb);
-            store_lds(0, 0, ra, rb, true);
+            store_step(0, 0, ra, rb);
             if (nk > 2) load_global(2, ra, rb);
             __syncthreads();
         }
         const int left = nk - kt;                                        // 1 .. 4 steps, the first already in buffer 0
-        if (left > 1) store_lds(1, kt + 1, qa, qb, true);
+        if (left > 1) store_step(1, kt + 1, qa, qb);
         if (left > 3) load_global(kt + 3, qa, qb);
         compute(0);
         __syncthreads();
         if (left > 1) {
-            if (left > 2) store_lds(0, kt + 2, ra, rb, true);
+            if (left > 2) store_step(0, kt + 2, ra, rb);
             compute(1);
             promote_pair();
             __syncthreads();
         }
         if (left > 2) {
-            if (left > 3) store_lds(1, kt + 3, qa, qb, true);
+            if (left > 3) store_step(1, kt + 3, qa, qb);
             compute(0);
             __syncthreads();
         }
@@ -629,12 +670,12 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
 }
 
 // A die (workgroup id modulo 8) takes a contiguous run of tiles.
-template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
+template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI, bool F32A = false>
 __global__ __launch_bounds__(64 * WVM * WVN * WVK, WVM * WVN * WVK == 4 ? 2 : 1) void gemm_ragged_kernel(GemmArgs g, int tiles_m, int tiles_n, int W, int64_t per_xcd)
 {
     const int64_t id = (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
     if (id >= (int64_t)tiles_m * tiles_n * W) return;
-    gemm_ragged_tile<BM, BN, WVM, WVN, WVK, BK, EPI>(g, tiles_m, tiles_n, W, id);
+    gemm_ragged_tile<BM, BN, WVM, WVN, WVK, BK, EPI, F32A>(g, tiles_m, tiles_n, W, id);
 }
 
 // Tiles of several products, of BM rows, or of 32 where a product has no more.  Every die takes a run of each product,
@@ -683,11 +724,11 @@ void launch_tiles(const GemmGroup& q, int W, hipStream_t s)
     hipLaunchKernelGGL((gemm_group_kernel<BM, EPI>), dim3((unsigned)(runs * kXcds)), dim3(256), big > small ? big : small, s, q, W);
 }
 
-template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI>
+template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI, bool F32A = false>
 void launch_tile(const GemmArgs& g, int W, hipStream_t s)
 {
     using S = RaggedShape<BM, BN, WVM, WVN, WVK, BK, EPI>;
-    auto kernel = gemm_ragged_kernel<BM, BN, WVM, WVN, WVK, BK, EPI>;
+    auto kernel = gemm_ragged_kernel<BM, BN, WVM, WVN, WVK, BK, EPI, F32A>;
     static_assert(S::FORWARD || S::THREADS / (BN / 4) <= BM, "the other epilogues use every thread");
     if (S::lds > 64 * 1024) {
         static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -713,11 +754,15 @@ void launch_head(const GemmArgs& g, int W, hipStream_t s)
     else launch_tile<32, 64, 1, 1, 4, 128, EPI_HEAD>(g, W, s);
 }
 
+// Whether a product has enough tiles of 64 columns and `rows` rows for every compute unit; whether it has so few, and so
+// long a contraction, that sixteen wavefronts split one.
+bool fills(const GemmArgs& g, int W, int rows) { return (int64_t)((g.N + 63) / 64) * W * ((g.M + rows - 1) / rows) >= 256; }
+bool long_and_few(const GemmArgs& g, int W) { return g.K >= 1024 && (int64_t)((g.N + 63) / 64) * W * ((g.M + 31) / 32) <= 128; }
+
 template <int EPI>
 void launch_epi(const GemmArgs& g, int W, hipStream_t s)
 {
-    const int64_t cols = (int64_t)((g.N + 63) / 64) * W;
-    const bool fill64 = cols * ((g.M + 63) / 64) >= 256, fill128 = cols * ((g.M + 127) / 128) >= 256;
+    const bool fill64 = fills(g, W, 64), fill128 = fills(g, W, 128);
     if constexpr (EPI == EPI_DW || EPI == EPI_DWU) {
         if (g.M > 64 && fill128) launch_tile<128, 64, 2, 2, 1, 64, EPI>(g, W, s);
         else if (g.M > 32) launch_tile<64, 64, 2, 2, 1, 64, EPI>(g, W, s);
@@ -732,7 +777,7 @@ void launch_epi(const GemmArgs& g, int W, hipStream_t s)
             }
         }
         if constexpr (EPI == EPI_FWD || EPI == EPI_LOGITS) {
-            if (g.K >= 1024 && cols * ((g.M + 31) / 32) <= 128) {
+            if (long_and_few(g, W)) {
                 launch_tile<32, 32, 1, 1, 16, 512, EPI>(g, W, s);
                 return;
             }
@@ -770,6 +815,17 @@ void launch_gemm_group(const GemmGroup& q, int W, int epi, hipStream_t s)
     if (q.n == 1) launch_gemm_ragged(q.g[0], W, epi, s);
     else if (epi == EPI_DW) launch_group_epi<EPI_DW>(q, W, s);
     else launch_group_epi<EPI_DWU>(q, W, s);
+}
+
+// The 32-row tile converts as it goes: its products are small enough that a launch for the conversion counts and reading
+// the inputs in fp32 once per 64 columns does not.  Objective of 617-132-10, 3 workers, batch 16, 14.2 -> 12.4 us, step of
+// 784-300-100-10, 8 x 50, 51.9 -> 50.6; 47 drawn calls, part of them of this size, 0.966 of the time.  The larger tiles have no registers
+// for fp32 pieces in flight.
+bool launch_gemm_ragged_f32(const GemmArgs& g, int W, hipStream_t s)
+{
+    if (g.K < 8 || long_and_few(g, W) || (g.M > 32 && fills(g, W, 64)) || (g.M > 64 && fills(g, W, 128))) return false;
+    launch_tile<32, 64, 1, 1, 4, 128, EPI_FWD, true>(g, W, s);
+    return true;
 }
 
 void launch_gemm_ragged(const GemmArgs& g, int W, int epi, hipStream_t s)

@@ -10,9 +10,11 @@
 //             delta_{k-1} = bf16((delta_k W_k) .* [h_{k-1} > 0])
 //
 // The three matrix products are dense contractions and run on the matrix
-// cores (v_mfma_f32_32x32x16_bf16): with the kernel in this file when the
-// shapes are multiples of its tile sizes and the rows 16-byte aligned, with the
-// any-shape kernel (mlp_gemm_ragged.hip) otherwise, the narrow classifier layer included.
+// cores (v_mfma_f32_32x32x16_bf16).  Shapes that are multiples of the tile sizes
+// with 16-byte aligned rows: d-weight products, and forward and d-input products that
+// fill the chip with 256 x 256 tiles, with the kernel in this file, other forward and
+// d-input products with mlp_gemm_direct.hip, which also takes other sizes of aligned rows;
+// the rest with the any-shape kernel (mlp_gemm_ragged.hip), the narrow classifier layer included.
 //
 // Operand layouts for the MFMA kernel.  A lane feeds the matrix core eight
 // consecutive values along the contraction index:
@@ -588,15 +590,27 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, floa
     // ---- forward ----
     const uint16_t* X0 = static_cast<const uint16_t*>(b.X);
     int64_t sX0 = (int64_t)B * b.dims[0];
+    bool first_done = false;
     if (b.x_is_fp32) {                                     // the bf16 copy both passes read
+        if (L > 1 && (b.B % 128 || b.dims[1] % 64 || b.dims[0] % kBK)) {      // (whole tiles: the aligned kernels)
+            GemmArgs a{};
+            a.A32 = static_cast<const float*>(b.X); a.sA = sX0; a.lda = b.dims[0];
+            if (backward) { a.copy = sc16 + p.x0; a.sCopy = sW16; }
+            a.B = xb + woff[1]; a.sB = ld; a.ldb = b.dims[0];
+            a.M = B; a.N = b.dims[1]; a.K = b.dims[0];
+            a.bias = x + woff[1] + (int64_t)b.dims[1] * b.dims[0]; a.sBias = ld;
+            a.out = sc16 + p.h[1]; a.sOut = sW16; a.ldout = b.dims[1];
+            first_done = launch_gemm_ragged_f32(a, W, s);
+        }
         const int64_t n = (int64_t)B * b.dims[0];
         int64_t blocks = (n + 255) / 256;
         if (blocks > 4096) blocks = 4096;
-        hipLaunchKernelGGL(cast_input_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, static_cast<const float*>(b.X), n,
-                           sc16 + p.x0, sW16);
+        if (!first_done)
+            hipLaunchKernelGGL(cast_input_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, static_cast<const float*>(b.X), n,
+                               sc16 + p.x0, sW16);
         X0 = sc16 + p.x0; sX0 = sW16;
     }
-    for (int k = 1; k <= L; ++k) {
+    for (int k = first_done ? 2 : 1; k <= L; ++k) {
         const int din = b.dims[k - 1], dout = b.dims[k];
         const uint16_t* Hin = (k == 1) ? X0 : sc16 + p.h[k - 1];
         const int64_t sHin = (k == 1) ? sX0 : sW16;
