@@ -9,8 +9,8 @@
 // workers, takes 68 us on zeros and 80 us on normal values, at 1.8 to 2.1 instead of 2.4 GHz, in every tile and wavefront
 // shape.  Loads that go straight to LDS need no registers, so three K steps or more are under way per workgroup, and no vector
 // instructions to store them.  A wavefront's load writes 64 consecutive 16-byte pieces, so rows cannot be padded: the
-// pieces of a row are stored in another order instead (exclusive or with the row number), which spreads the fragment
-// reads over all banks.  Fragments are read a quarter step ahead of their products, across the barrier too.
+// pieces of a row are stored in another order instead (exclusive or with half the row number: two rows fill the banks
+// once), which spreads the fragment reads over all banks (with the row number itself half of the LDS cycles were conflicts).  Fragments are read a quarter step ahead of their products, across the barrier too.
 //
 // ANY: any M and N, K a multiple of 8.  Row numbers past the end are clamped to the last row, pieces past the end of a
 // row to its last piece (fragments past K become zeros in the last step).  Sums are carried as in the any-shape kernel's
@@ -80,9 +80,9 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
     const uint16_t* A = g.A + (int64_t)w * g.sA;
     const uint16_t* B = g.B + (int64_t)w * g.sB;
 
-    // this thread's pieces: where they come from.  [.][k]: row tid / 8 + c * THREADS / 8, piece (tid % 8) ^ (row % 8)
+    // this thread's pieces: where they come from.  [.][k]: row tid / 8 + c * THREADS / 8, piece (tid % 8) ^ (row / 2 % 8)
     const uint16_t *pa[A_OPS], *pb[B_OPS];
-    const int kc = ((tid & 7) ^ ((tid >> 3) & 7)) * 8;
+    const int kc = ((tid & 7) ^ ((tid >> 4) & 7)) * 8;
 #pragma unroll
     for (int c = 0; c < A_OPS; ++c) {
         int r = m0 + (tid >> 3) + c * (THREADS / 8);
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
     };
 
     const int half = lane >> 5, l16 = lane & 15;
-    const int sw = half ^ (lane & 7);                                 // piece of k step 0, swizzled
+    const int sw = half ^ ((lane >> 1) & 7);                          // piece of k step 0, swizzled
     const int arow = (wm * WTM + (lane & 31)) * kBK, brow = (BM + wn * WTN + (lane & 31)) * kBK;
     struct Frags { bf16x8 a[TM], b[TN]; };
     // (offsets are summed up first: behind a longer chain of address steps the compiler loses track of which buffer is read)
