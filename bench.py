@@ -35,9 +35,9 @@ import workloads as wl
 # Bytes between the L2 caches and memory per launch, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by
 # reference kernels of known size (profiles/*_hbm_traffic.md).  Valid only for the kernel sources they were
 # taken on: reported as null once the code of any of these files (comments and white space aside) differs.
-PULL_TRAFFIC = {"files": ("pull_update.hip", "pull_common.h", "update_math.h"), "code_sha256_16": "32c416ddd7e5bca5", "bytes_per_launch": 7.666e9,
+PULL_TRAFFIC = {"files": ("pull_update.hip", "pull_common.h", "update_math.h"), "code_sha256_16": "bdf23d1a5237443a", "bytes_per_launch": 7.666e9,
                 "key": (32, 11_689_512)}
-MC_TRAFFIC = {"files": ("mc_grad.hip",), "code_sha256_16": "9b605e87ba23fe57", "bytes_per_launch": 3.935e8,
+MC_TRAFFIC = {"files": ("mc_grad.hip",), "code_sha256_16": "018dfea31ab6a293", "bytes_per_launch": 3.992e8,
               "key": (16, 65536, 20000, 20000, 32)}
 CSRC = os.path.join(ROOT, "paper_1905_10395_amd", "csrc")
 
@@ -289,7 +289,7 @@ def run_c2(L, steps, warmup, data):
         "workload": f"matrix completion LSGD: 20000x20000 rank 32, 1% observed ({prob.n_obs}), W={W} in {G} groups, "
                     f"B={B}/worker/step, eta={eta}, lam_L={lamL}, lam_G={lamG}, leaders every {tau} steps",
         "value": W * steps / secs, "unit": "worker-steps/s", "ms_per_step": secs / steps * 1e3,
-        "roofline": {"kernel": "lsgd_grad_loss stage: mc_prep + mc_side + mc_loss_finish kernels", "bound": "hbm", "achieved": ach,
+        "roofline": {"kernel": "lsgd_grad_loss stage: mc_prep + mc_side + loss_parts kernels", "bound": "hbm", "achieved": ach,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
                      "traffic": _traffic(MC_TRAFFIC, (W, B, prob.m, prob.n, prob.r)),
                      "bytes_per_launch": grad_bytes, "ms_per_launch": ms_grad},

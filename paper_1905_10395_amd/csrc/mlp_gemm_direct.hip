@@ -18,7 +18,7 @@
 //
 // Measured, us, through registers -> straight to LDS: objective of 3072-1024-10, 16 workers, batch 128: 42 -> 32;
 // gradients of 1024-2048-2048-10, 8 workers, batch 256: 169 -> 159; 256-512-512-10, 8 workers, batch 128: 46.5 -> 43.
-// ANY: forward 500 x 1024 x 3072, 16 workers, 95 -> 80, 128 x 1912 x 1208 35 -> 23; d-input 200 x 1912 x 1208 72 -> 43,
+// ANY: forward 500 x 1024 x 3072, 16 workers, 95 -> 77, 128 x 1912 x 1208 35 -> 23; d-input 200 x 1912 x 1208 72 -> 43,
 // 256 x 1000 x 784 32 -> 20.
 #include <type_traits>
 
