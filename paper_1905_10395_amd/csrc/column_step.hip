@@ -258,6 +258,7 @@ __device__ __forceinline__ void stream_columns(const ColumnDev& s, const Leaders
                 if (COMM) {
                     crow = cfresh ? clead : -1;
                     cc.cL = cfresh ? s.commL : 0.0f;
+                    zlc = zero_of(V());                  // (the last group's may be infinite: not even times zero)
                     if (cfresh) {
                         zlc = nlx;
                         if (s.update) update_vec<KIND, V>(zlc, nlg, nlm, zl, zg, c);
@@ -349,6 +350,7 @@ __device__ __forceinline__ void regs_comm(const ColumnDev& s, const Leaders& L, 
                 lead = __builtin_amdgcn_readfirstlane(L.lead[j]);
                 fresh = L.fresh[j] != 0;
                 c.cL = fresh ? s.commL : 0.0f;
+                zl = zero_of(V());                       // (the last group's may be infinite: not even times zero)
                 if (fresh) {                             // (no row of the group has moved yet)
                     zl = row_of<VEC, NR>(r, lead);
                     if (a.Z) st_vec(at(a.Z, a.ld, j, col), zl);

@@ -31,7 +31,7 @@ def assert_update_elementwise(new_gpu, new_ora, old, what="", k_self=2.0, k_row=
     disp = np.abs(new_ora - old)
     bound = k_self * EPS32 * np.abs(new_ora) + k_row * EPS32 * disp.max(axis=-1, keepdims=True) + 1e-37
     err = np.abs(new_gpu - new_ora)
-    bad = err > bound
+    bad = ~(err <= bound)                                    # (NaN is no agreement)
     if bad.any():
         i = np.unravel_index(np.argmax(err / bound), err.shape)
         raise AssertionError(f"{what}: {int(bad.sum())} elements beyond fp32 rounding; worst at {i}: gpu {new_gpu[i]!r} "

@@ -2,11 +2,15 @@
 rows stream whatever group they are in (batches of 8 rows at one column per thread, of 4 at two or four), iterations with up
 to 4 or 8 rows in registers, elastic averaging with up to 8, 16 or 32, columns left over for the last workgroup.  Bit for bit
 against row streams and against the calls that a step is made of; elastic averaging against the oracle."""
+import numpy as np
 import pytest
+import torch
 
 import paper_1905_10395_amd as L
 import test_gpu_column_step as column
 import test_gpu_easgd as easgd
+import workloads as wl
+from gpu_util import Pair, assert_update_elementwise
 
 pytestmark = pytest.mark.gpu
 
@@ -63,3 +67,32 @@ def test_easgd_rows_in_registers_or_twice(W, P, ld):
 @pytest.mark.parametrize("W,G,P,ld", [(6, 2, 1_000_003, 1_000_064), (13, 1, 500_003, 500_032), (20, 4, 500_003, 500_032), (32, 4, 1031, 1031)])
 def test_easgd_without_momentum(W, G, P, ld):
     easgd.test_easgd_update_matches_oracle(W, G, P, ld, 0.0, 0, 1e-4)
+
+
+@pytest.mark.parametrize("call", ["step_alg1", "leader_pull"])
+@pytest.mark.parametrize("W,off", [(2, ones(2)), (4, [0, 1, 4]), (8, [0, 3, 8]), (9, [0, 4, 9]), (13, [0, 5, 6, 13]), (32, ones(32)), (40, [0, 9, 40])])
+def test_group_that_does_not_communicate_takes_nothing_from_the_one_before(W, off, call):
+    """Group 0 has diverged and communicates; the others are only pulled to the global leader, which is in the last group:
+    the infinite leader takes no part in their rows, not even times zero."""
+    P, G = 257, len(off) - 1
+    x0, g0, _ = wl.stress_state(W, P, P, seed=W)
+    x0[:off[1]] = np.inf
+    pr = Pair(x0, off)
+    losses = (np.arange(W, 0, -1) / W).astype(np.float32)
+    losses[:off[1]] = np.nan
+    pr.set_grad(g0, losses)
+    mask = [1] + [0] * (G - 1)
+    if call == "step_alg1":
+        pr.ora.update(0.05, 0.0, 0.0)
+        pr.pop.step_alg1(L.ExternalBatch(pr.losses_dev), 0.05, 0.0, 0.0, 0.1, 0.07, L.COMM_LOCAL | L.COMM_GLOBAL, mask)
+    else:
+        pr.pop.select_leaders(pr.losses_dev, mask, 1)
+        pr.pop.leader_pull(0.1, 0.07)
+    rl = np.array(mask, np.uint8)
+    pr.ora.select(rl, 1); pr.ora.leader_pull(0.1, 0.07, rl, 1)
+    torch.cuda.synchronize()
+    rest = slice(off[1], W)
+    got, Z = pr.x.cpu().numpy()[rest], pr.Z.cpu().numpy()
+    assert np.all(np.isfinite(pr.ora.x[rest])) and np.all(np.isfinite(got))
+    assert_update_elementwise(got, pr.ora.x[rest], x0[rest])
+    assert not np.any(np.isfinite(Z[0])) and np.all(np.isfinite(Z[G]))
