@@ -61,8 +61,11 @@ def test_infinite_weight_past_the_last_class_stays_out():
     """Three classes on tiles of sixteen: what follows the classifier's weights in memory takes no part."""
     dims, W, B = [16, 48, 3], 2, 20
     pr, batch, Xb, y, P, _ = make(dims, W, B, seed=1)
+    pr.pop.sync_shadow()                                         # or the gradient call writes the copy anew
     pr.xb[:, P - 3:] = float("inf")                              # the classifier's biases are read in fp32
     pr.ora.grad_loss_mlp(dims, Xb, y)
     pr.pop.grad_loss(batch)
     torch.cuda.synchronize()
+    assert torch.all(torch.isinf(pr.xb[:, P - 3:P]))
+    assert torch.all(torch.isfinite(pr.g[:, :P]))
     check_grads(pr.g.cpu().numpy()[:, :P], pr.ora.g[:, :P], dims)
