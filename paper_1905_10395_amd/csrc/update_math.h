@@ -12,7 +12,8 @@ struct Coef {
 
 // One parameter (V = float) or several (V = a vector), element-wise.  The fused multiply-adds are written out, so that
 // every kernel rounds alike wherever this is inlined: the one-launch update works out a leader's new value a second time
-// and the paths are compared bit for bit.
+// and the paths are compared bit for bit.  Of the two pulls one product is rounded by itself: the global one's, whose
+// coefficient is the smaller in use (the other way round the error of the momentum grows by 1 %).
 // KIND 0: gradient step, 1: gradient step with momentum, 2: Algorithm 1's communication pull
 // (x <- x - cL (x - zl), then x <- x - cG (x - zg); no gradient, momentum untouched).
 template <class V>
@@ -29,7 +30,7 @@ __device__ __forceinline__ void update_vec(V& x, const V g, V& m, const V zl, co
         return;
     }
     V d = mul_add(c.wd, x, g);
-    const V pull = mul_add(c.cG, x - zg, c.cL * (x - zl));
+    const V pull = mul_add(c.cL, x - zl, c.cG * (x - zg));
     V step;
     if (MOM) {
         if (c.grad_only) {
