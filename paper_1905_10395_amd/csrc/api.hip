@@ -373,12 +373,13 @@ lsgd_status check_pull_state(const lsgd_population* p, float eta, float lamL, fl
     return LSGD_OK;
 }
 
-bool any_pending(const lsgd_population* p)
+// Groups whose leader was re-selected since the last update.
+int pending_groups(const lsgd_population* p)
 {
-    bool any = p->pending_global;
-    for (int j = 0; j < p->cfg.n_groups; ++j) any = any || p->pending_local[(size_t)j];
-    return any;
+    return (int)(p->pending_local.size() - (size_t)std::count(p->pending_local.begin(), p->pending_local.end(), 0));
 }
+
+bool any_pending(const lsgd_population* p) { return p->pending_global || pending_groups(p) > 0; }
 
 // Bookkeeping of a selection: which groups are re-selected (sel) and which count as re-selected since the last
 // update afterwards (cap).
@@ -492,11 +493,17 @@ lsgd_status do_pull(lsgd_population* p, float eta, float lamL, float lamG, bool 
     hipError_t e;
     // One launch where row streams take two: re-selected leaders are to be captured (16 x 60 000 behind a selection of its
     // own, us, row streams / column owners: 13.9 / 13.1, 32 x 10 000 10.4 / 13.1, 32 x 140 000 23 / 19; without any 6.8 / 10).
+    // Row streams too where everybody is pulled to the global leader, and few of many groups of one to their own (16 x 40 001,
+    // one of 16: 14 / 16; half of them 18 / 17; 32 x 140 001, one 23 / 34, half 36 / 37).
     const double bytes = 12.0 * (double)p->cfg.W * (double)p->cfg.P;
-    if (any_pending(p) && column_step(p, true) && (p->cfg.W <= 16 || bytes >= 30e6)) {
+    const int G = p->cfg.n_groups;
+    const bool ones = comm && p->cfg.W == G && G > 8 && p->pending_global && 2 * pending_groups(p) < G;
+    if (any_pending(p) && column_step(p, true) && !ones && (p->cfg.W <= 16 || bytes >= 30e6)) {
         ColumnStep c{};
         c.pull = q;
         c.update = !comm; c.comm = comm; c.commL = lamL; c.commG = lamG;
+        for (int j = 0; j < G; ++j) c.cap |= (uint64_t)(p->pending_local[(size_t)j] != 0) << j;
+        c.capG = p->pending_global;
         e = launch_column_step(c, p->st, p->stream);
     } else {
         e = launch_pull_update(q, p->st, p->stream);

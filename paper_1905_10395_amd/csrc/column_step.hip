@@ -15,7 +15,7 @@
 // 24.6 -> 16.5; 16 x 250 000 with momentum 30.0 -> 17.3;
 // 16 x 1 250 000 without 62.5 -> 41.5; elastic averaging, 16 x 1 250 000 with momentum 85.3 -> 73.3.
 //
-// Four ways through the rows (launch_column_step), by what a thread has to wait for:
+// The ways through the rows (launch_column_step), by what a thread has to wait for:
 //   the update of groups of several workers     group by group, the next rows' loads under way (update_columns)
 //   ... of groups of one, and Algorithm 1's     one pass over all rows, two batches ahead, whatever group they are in
 //   iterations of more than 8 workers           (stream_columns): groups one after the other would leave a single row in
@@ -24,6 +24,8 @@
 //                                               16 workers in 4 groups x 1 250 001 74 -> 60, of 24 144 -> 79
 //   Algorithm 1's iterations of up to 8         every row in registers (regs_update, regs_comm): 8 workers in 2 groups x
 //                                               2 500 000 81 -> 57
+//   its communication pull alone                as its iterations where everybody moves, else group by group (pull_columns):
+//                                               the other ways read every row, whoever communicates
 //   elastic averaging                           every row in registers, x read once: 4 x 1003 6.5 -> 4.0, 16 x 1 250 001
 //                                               without momentum 54 -> 46, 32 x 140 001 34 -> 17 (but for many rows with
 //                                               momentum out of HBM: two passes)
@@ -366,6 +368,40 @@ __device__ __forceinline__ void regs_comm(const ColumnDev& s, const Leaders& L, 
         }
 }
 
+// A communication pull alone, group by group: rows of groups that do not communicate are not touched at all.
+template <int VEC>
+__device__ __forceinline__ void pull_columns(const ColumnDev& s, const Leaders& L, int64_t col)
+{
+    using V = typename Vec<VEC>::type;
+    const PullDev& a = s.a;
+    Coef c = make_coef<V>(a);
+    c.cG = L.freshG ? s.commG : 0.0f;
+    V zg = zero_of(V());
+    if (L.freshG) {
+        zg = ld_vec<VEC>(a.x + (int64_t)L.gl * a.ld + col);
+        if (a.Z) st_vec(a.Z + (int64_t)a.G * a.ld + col, zg);
+    }
+    for (int j = 0; j < a.G; ++j) {
+        const int lead = L.lead[j];
+        const bool fresh = L.fresh[j] != 0;
+        V zl = zero_of(V());
+        if (fresh) {                                     // (no row of the group has moved yet)
+            zl = ld_vec<VEC>(a.x + (int64_t)lead * a.ld + col);
+            if (a.Z) st_vec(a.Z + (int64_t)j * a.ld + col, zl);
+        }
+        c.cL = fresh ? s.commL : 0.0f;
+        if (c.cL == 0.0f && c.cG == 0.0f) continue;
+        for (int i = a.offsets[j]; i < a.offsets[j + 1]; ++i) {
+            if (fresh && i == lead && c.cG == 0.0f) continue;        // a leader's pull to itself is zero
+            const int64_t o = (int64_t)i * a.ld + col;
+            V xv = ld_vec<VEC>(a.x + o), none = zero_of(V());
+            update_vec<2, V>(xv, none, none, zl, zg, c);
+            st_vec(a.x + o, xv);
+            if (a.xb) st_bf16(a.xb + o, xv);
+        }
+    }
+}
+
 // A communication pull with both coefficients zero: nobody moves, the re-selected leaders are copied to Z, eight rows of loads in
 // flight.
 template <int VEC>
@@ -575,7 +611,7 @@ __global__ __launch_bounds__(kThreads) void capture_kernel(ColumnDev s)
     }
 }
 
-enum { kUpdate, kUpdateOnes, kComm, kCommRegs, kCenter, kCenterRegs };
+enum { kUpdate, kUpdateOnes, kComm, kCommRegs, kCenter, kCenterRegs, kPull };
 
 // What one thread does at its columns.  Loads are under way during the selection.  NR: rows in registers (*Regs).
 template <int VEC, int KIND, bool NT, int MODE, int NR>
@@ -591,6 +627,9 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
         if (!live) return;
         if (CENTER) center_columns<VEC>(s, col);
         update_columns<VEC, KIND, NT, CENTER>(s, before, col, first);
+    } else if constexpr (MODE == kPull) {
+        choose_leaders(s, now, chosen);
+        if (live) pull_columns<VEC>(s, after, col);
     } else if constexpr (MODE == kUpdateOnes || MODE == kComm) {
         RowBatch<VEC> cur, next;
         if (live) {
@@ -633,8 +672,11 @@ void launch_vec(const ColumnDev& s, bool nt, hipStream_t st)
 {
     const int64_t cols = s.a.col1 - s.a.col0, per = (int64_t)kThreads * VEC, whole = cols / VEC * VEC;
     const dim3 grid((unsigned)((whole + per - 1) / per + (whole < cols)));
-    if (nt) hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR>), grid, dim3(kThreads), 0, st, s);
-    else hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR>), grid, dim3(kThreads), 0, st, s);
+    // (a group's rows are read again, and rows of groups that do not move live on in the caches: plain accesses)
+    if constexpr (MODE != kPull) {
+        if (nt) { hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR>), grid, dim3(kThreads), 0, st, s); return; }
+    }
+    hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR>), grid, dim3(kThreads), 0, st, s);
 }
 
 // vec: columns per thread wished for; no more than the registers hold.
@@ -653,6 +695,21 @@ void launch_mode(const ColumnDev& s, int vec, bool mom, bool nt, hipStream_t st)
         if (vec >= 2) launch_vec<2, 0, MODE, NR>(s, nt, st);
         else launch_vec<1, 0, MODE, NR>(s, nt, st);
     }
+}
+
+// A pull alone: whether one pass over all rows beats a walk group by group, which touches only rows that move.  One pass / by
+// groups, us, selection included: 8 workers in 2 groups x 400 001 one group communicates 9.0 / 9.2, both 10.3 / 12.9, the global
+// leader too 11.6 / 14.7; 16 in 4 x 140 001 one 11.3 / 7.6, all 13.2 / 15.5, x 1 000 001 all 31 / 25; 32 in 8 x 400 001 one 20 / 9,
+// all 27 / 30; 16 in 8 x 40 001 all 13.1 / 12.1, x 400 001 23 / 20.  Over 1190 pulls, 2 to 32 workers in 1 to 32 groups, 1003 to
+// 3 million columns, none more than 5 % slower than with the walk (row streams for groups of one), 13 % faster together.
+bool pull_in_one_pass(const ColumnStep& q)
+{
+    const PullParams& p = q.pull;
+    const double bytes = 12.0 * (double)p.W * (double)p.P;
+    const bool large_groups = p.W >= 4 * p.G;
+    if (p.W <= 8) return q.capG && (p.W > 4 || p.W < 2 * p.G || bytes <= 100e6);        // 4 in 2 x 2 500 000 25.6 / 23.8
+    if (!q.capG && !(large_groups && __builtin_popcountll(q.cap) == p.G)) return false;
+    return large_groups ? p.W > 16 || bytes <= 70e6 : bytes <= 40e6;
 }
 
 } // namespace
@@ -688,7 +745,8 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     // Many rows with momentum out of HBM: reading x twice costs less than registers for sixteen rows of three values (16 x
     // 1 250 001, 400 MB: 71 us against 78; 12 x 1 250 001, 300 MB, 60 against 59, 8 x 2 500 000, 400 MB, 83 against 76).
     const int mode = q.center ? (mom && p.W > 12 && bytes > 300e6 && p.W <= 16 ? kCenter : kCenterRegs)
-                   : q.comm ? (p.W <= 8 ? kCommRegs : kComm) : p.W == p.G ? kUpdateOnes : kUpdate;
+                   : !q.comm ? (p.W == p.G ? kUpdateOnes : kUpdate)
+                   : !q.update && !pull_in_one_pass(q) ? kPull : p.W <= 8 ? kCommRegs : kComm;
     // Columns per thread: one, so that small rows still make enough wavefronts; more once there are plenty.  Update: 16
     // workers without momentum, 600 000 columns 27.0 / 25.6 / 24.5 us with 1 / 2 / 4, 250 000 columns 13.8 / 13.7 / 14.1;
     // with momentum two columns are never more than 2 % ahead, four mostly behind.  Algorithm 1's iteration, 8 workers in 2
@@ -726,6 +784,11 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     case kUpdate: launch_mode<kUpdate>(s, vec, mom, nt, stream); break;
     case kUpdateOnes: launch_mode<kUpdateOnes>(s, vec, mom, nt, stream); break;
     case kComm: launch_mode<kComm>(s, vec, mom, nt, stream); break;
+    case kPull:
+        if (vec == 4) launch_vec<4, 0, kPull, 0>(s, false, stream);
+        else if (vec == 2) launch_vec<2, 0, kPull, 0>(s, false, stream);
+        else launch_vec<1, 0, kPull, 0>(s, false, stream);
+        break;
     case kCommRegs:
         if (p.W <= 4) launch_mode<kCommRegs, 4>(s, vec, mom, nt, stream);
         else launch_mode<kCommRegs, 8>(s, vec, mom, nt, stream);

@@ -93,7 +93,7 @@ struct ColumnStep {
     float commL, commG;
     int select;              // 0: none, 1: before the update, 2: between the update and the communication pull
     uint64_t sel, cap;       // groups to re-select / whose leader counts as re-selected afterwards
-    int selG, capG;
+    int selG, capG;          // (a call that does not select: cap, capG are the leaders re-selected before it)
     const float* losses;     // ignored when parts.n > 0
     float* losses_out;       // also receives the losses, or NULL
     LossParts parts;

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import paper_1905_10395_amd as L
+import test_gpu_alg1 as alg1
 import test_gpu_column_step as column
 import test_gpu_easgd as easgd
 import workloads as wl
@@ -67,6 +68,13 @@ def test_easgd_rows_in_registers_or_twice(W, P, ld):
 @pytest.mark.parametrize("W,G,P,ld", [(6, 2, 1_000_003, 1_000_064), (13, 1, 500_003, 500_032), (20, 4, 500_003, 500_032), (32, 4, 1031, 1031)])
 def test_easgd_without_momentum(W, G, P, ld):
     easgd.test_easgd_update_matches_oracle(W, G, P, ld, 0.0, 0, 1e-4)
+
+
+# pulls alone, some or all groups communicating: groups of one up to 8 workers and above, pairs, large groups above 16 workers
+# and 30 MB, four workers above 100 MB
+@pytest.mark.parametrize("W,G,P,ld", [(8, 8, 301, 320), (12, 12, 1031, 1031), (16, 8, 1030, 1088), (24, 4, 120_003, 120_064), (4, 2, 2_100_003, 2_100_032)])
+def test_pulls_alone_match_the_oracle(W, G, P, ld):
+    alg1.test_leader_pull_matches_oracle(W, G, P, ld)
 
 
 @pytest.mark.parametrize("call", ["step_alg1", "leader_pull"])
