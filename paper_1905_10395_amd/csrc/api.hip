@@ -433,11 +433,20 @@ bool column_step(const lsgd_population* p, bool selects)
 
 // The same for an iteration of Algorithm 1 that communicates, which takes four launches otherwise: 16 x 1 250 001, 4 groups,
 // 105 / 62 us, 24 x 1 250 001 (360 MB) 145 / 79, 12 x 2 500 000 (360 MB) 144 / 89; of any group size (8 groups of one x
-// 1 250 001 75 / 44).
-bool column_alg1(const lsgd_population* p)
+// 1 250 001 75 / 44).  Not for many groups of one of which few communicate: 32 x 140 001, two, 39 / 27, half of them with
+// momentum 57 / 44, 20 x 1 000 001, one, 90 / 69, 32 x 40 001, two, 29 / 23 (x 1003 21 / 26); to the global leader alone 29 / 25
+// there, with momentum 25 / 26.
+bool column_alg1(const lsgd_population* p, int communicating, bool global)
 {
-    const double bytes = (p->cfg.momentum != 0.0f ? 20.0 : 12.0) * (double)p->cfg.W * (double)p->cfg.P;
-    return p->cfg.W <= 32 && bytes <= 450e6;
+    const int W = p->cfg.W, G = p->cfg.n_groups;
+    const double bytes = (p->cfg.momentum != 0.0f ? 20.0 : 12.0) * (double)W * (double)p->cfg.P;
+    if (W == G) {
+        const bool wide = W > 24 && p->cfg.P >= 5000;
+        if (global ? wide && 8 * communicating < W && bytes < 20e6
+                   : (W > 16 && bytes >= 30e6 && 2 * communicating <= W) || (wide && 4 * communicating <= W))
+            return false;
+    }
+    return W <= 32 && bytes <= 450e6;
 }
 
 // The same for elastic averaging, two launches and a copy of the losses otherwise: 4 x 1003 11.5 / 4.0, 16 x 271 117 with
@@ -697,11 +706,11 @@ lsgd_status lsgd_step_alg1(lsgd_population* pop, const lsgd_batch* batch, float 
     st = check_pull_state(pop, eta, gamma_L, gamma_G, nullptr, false, false);
     if (st != LSGD_OK) return st;
     const int G = pop->cfg.n_groups;
-    bool any_local = false;
+    int local = 0;                                       // groups that communicate
     if (comm & LSGD_COMM_LOCAL) {
-        for (int j = 0; j < G; ++j) any_local = any_local || !comm_local_mask || comm_local_mask[j];
+        for (int j = 0; j < G; ++j) local += !comm_local_mask || comm_local_mask[j];
     }
-    const bool communicate = any_local || (comm & LSGD_COMM_GLOBAL);
+    const bool global = (comm & LSGD_COMM_GLOBAL) != 0, communicate = local > 0 || global;
     std::vector<uint8_t> none;
     const uint8_t* mask = comm_local_mask;
     if (!(comm & LSGD_COMM_LOCAL)) {
@@ -710,17 +719,17 @@ lsgd_status lsgd_step_alg1(lsgd_population* pop, const lsgd_batch* batch, float 
     }
     // one launch for update, selection and communication pull; the workgroups then read only leaders that this call
     // does not re-record, so not while a selection is pending or the recorded leaders are exempt
-    if (communicate && column_alg1(pop) && !any_pending(pop) && !(pop->cfg.flags & LSGD_LEADER_EXEMPT)) {
+    if (communicate && column_alg1(pop, local, global) && !any_pending(pop) && !(pop->cfg.flags & LSGD_LEADER_EXEMPT)) {
         ColumnStep c{};
         st = column_losses(pop, batch, &c);
         if (st != LSGD_OK) return st;
         c.pull = pull_params(pop, eta, gamma_L, gamma_G, true, false);
         note_pull(pop, gamma_L, gamma_G, false);
         RefreshBits sel, cap;
-        note_selection(pop, mask, (comm & LSGD_COMM_GLOBAL) != 0, &sel, &cap);
+        note_selection(pop, mask, global, &sel, &cap);
         c.update = c.comm = 1; c.commL = lambda_L; c.commG = lambda_G;
         c.select = 2; c.sel = sel.w[0]; c.cap = cap.w[0];
-        c.selG = c.capG = (comm & LSGD_COMM_GLOBAL) != 0;
+        c.selG = c.capG = global;
         hipError_t e = launch_column_step(c, pop->st, pop->stream);
         if (e != hipSuccess) return fail(LSGD_ERR_HIP, "step_alg1: %s", hipGetErrorString(e));
         note_pull(pop, lambda_L, lambda_G, true);
@@ -731,7 +740,7 @@ lsgd_status lsgd_step_alg1(lsgd_population* pop, const lsgd_batch* batch, float 
     st = do_pull(pop, eta, gamma_L, gamma_G, true, false);
     if (st != LSGD_OK) return st;
     if (!communicate) return LSGD_OK;
-    st = do_select(pop, nullptr, mask, (comm & LSGD_COMM_GLOBAL) != 0);
+    st = do_select(pop, nullptr, mask, global);
     if (st != LSGD_OK) return st;
     return do_pull(pop, 0.0f, lambda_L, lambda_G, false, true);
 }

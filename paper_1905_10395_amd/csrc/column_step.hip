@@ -24,8 +24,8 @@
 //                                               16 workers in 4 groups x 1 250 001 74 -> 60, of 24 144 -> 79
 //   Algorithm 1's iterations of up to 8         every row in registers (regs_update, regs_comm): 8 workers in 2 groups x
 //                                               2 500 000 81 -> 57
-//   its communication pull alone                as its iterations where everybody moves, else group by group (pull_columns):
-//                                               the other ways read every row, whoever communicates
+//   iterations and pulls in which few           group by group (pull_columns): the other ways read or work on every row,
+//   groups communicate                          whoever communicates
 //   elastic averaging                           every row in registers, x read once: 4 x 1003 6.5 -> 4.0, 16 x 1 250 001
 //                                               without momentum 54 -> 46, 32 x 140 001 34 -> 17 (but for many rows with
 //                                               momentum out of HBM: two passes)
@@ -368,7 +368,7 @@ __device__ __forceinline__ void regs_comm(const ColumnDev& s, const Leaders& L, 
         }
 }
 
-// A communication pull alone, group by group: rows of groups that do not communicate are not touched at all.
+// A communication pull group by group, alone or behind update_columns: rows of groups that do not communicate are not touched at all.
 template <int VEC>
 __device__ __forceinline__ void pull_columns(const ColumnDev& s, const Leaders& L, int64_t col)
 {
@@ -611,7 +611,7 @@ __global__ __launch_bounds__(kThreads) void capture_kernel(ColumnDev s)
     }
 }
 
-enum { kUpdate, kUpdateOnes, kComm, kCommRegs, kCenter, kCenterRegs, kPull };
+enum { kUpdate, kUpdateOnes, kComm, kCommRegs, kCenter, kCenterRegs, kPull, kUpdatePull };
 
 // What one thread does at its columns.  Loads are under way during the selection.  NR: rows in registers (*Regs).
 template <int VEC, int KIND, bool NT, int MODE, int NR>
@@ -619,7 +619,7 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
 {
     const Leaders& before = s.select == 1 ? chosen : now;
     const Leaders& after = s.select ? chosen : now;
-    if constexpr (MODE == kUpdate || MODE == kCenter) {
+    if constexpr (MODE == kUpdate || MODE == kCenter || MODE == kUpdatePull) {
         constexpr bool CENTER = MODE == kCenter;
         RowBatch<VEC> first;
         if (live) load_rows<VEC, KIND, NT>(s.a, 0, pass_end<CENTER>(s.a, 0), col, first);
@@ -627,6 +627,7 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
         if (!live) return;
         if (CENTER) center_columns<VEC>(s, col);
         update_columns<VEC, KIND, NT, CENTER>(s, before, col, first);
+        if (MODE == kUpdatePull) pull_columns<VEC>(s, after, col);
     } else if constexpr (MODE == kPull) {
         choose_leaders(s, now, chosen);
         if (live) pull_columns<VEC>(s, after, col);
@@ -673,7 +674,7 @@ void launch_vec(const ColumnDev& s, bool nt, hipStream_t st)
     const int64_t cols = s.a.col1 - s.a.col0, per = (int64_t)kThreads * VEC, whole = cols / VEC * VEC;
     const dim3 grid((unsigned)((whole + per - 1) / per + (whole < cols)));
     // (a group's rows are read again, and rows of groups that do not move live on in the caches: plain accesses)
-    if constexpr (MODE != kPull) {
+    if constexpr (MODE != kPull && MODE != kUpdatePull) {
         if (nt) { hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR>), grid, dim3(kThreads), 0, st, s); return; }
     }
     hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR>), grid, dim3(kThreads), 0, st, s);
@@ -712,6 +713,24 @@ bool pull_in_one_pass(const ColumnStep& q)
     return large_groups ? p.W > 16 || bytes <= 70e6 : bytes <= 40e6;
 }
 
+// An iteration of Algorithm 1: whether its pull is better walked group by group behind the update, which reads rows a second
+// time, but only those that move.  One pass / behind the update, us: 24 workers in 4 groups x 1003 one group communicates
+// 10.6 / 9.5, three 11.1 / 11.6, x 400 001 (115 MB) one 29.4 / 28.7, two 29.7 / 31.9; 16 in 8 x 1 000 001 (192 MB) one 55 / 41,
+// all 65 / 59; with momentum 32 in 8 x 140 001 (90 MB) one 31 / 27, all 36 / 34, 16 in 8 (45 MB) all 25.8 / 23.2.  To a global
+// leader everybody moves: 24 in 4 x 140 001 18.0 / 19.6, but 16 in 8 with momentum 26.6 / 24.8.  Registers of eight rows with momentum are slower than a walk while
+// rows are short: 8 in 1 x 40 001 7.5 / 6.7, x 140 001 9.3 / 9.5.
+bool pull_behind_update(const ColumnStep& q, double bytes)
+{
+    const PullParams& p = q.pull;
+    const int fresh = __builtin_popcountll(q.cap);
+    const bool mom = p.mu != 0.0f, large_groups = p.W >= 4 * p.G;
+    if (p.W <= 8) return mom && p.W > 4 && p.P < 100000 && large_groups && (p.G == 1 || (!q.capG && 2 * fresh <= p.G));
+    if (p.W < 2 * p.G || bytes > 300e6) return false;
+    if (mom && bytes >= 30e6 && bytes < (q.capG ? 60e6 : 95e6) && (!q.capG || (fresh == p.G && p.W <= 16))) return true;
+    if (q.capG) return false;
+    return large_groups ? fresh * (bytes < 100e6 ? 2 : 4) <= p.G : p.W <= 16 && bytes >= (2 * fresh <= p.G ? 70e6 : 150e6);
+}
+
 } // namespace
 
 hipError_t launch_loss_parts(const LossParts& parts, int W, float* losses, hipStream_t stream)
@@ -744,16 +763,17 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     const double bytes = (mom ? 20.0 : 12.0) * (double)p.W * (double)p.P;
     // Many rows with momentum out of HBM: reading x twice costs less than registers for sixteen rows of three values (16 x
     // 1 250 001, 400 MB: 71 us against 78; 12 x 1 250 001, 300 MB, 60 against 59, 8 x 2 500 000, 400 MB, 83 against 76).
+    const bool by_groups = q.comm && (q.update ? pull_behind_update(q, bytes) : !pull_in_one_pass(q));
     const int mode = q.center ? (mom && p.W > 12 && bytes > 300e6 && p.W <= 16 ? kCenter : kCenterRegs)
                    : !q.comm ? (p.W == p.G ? kUpdateOnes : kUpdate)
-                   : !q.update && !pull_in_one_pass(q) ? kPull : p.W <= 8 ? kCommRegs : kComm;
+                   : by_groups ? (q.update ? kUpdatePull : kPull) : p.W <= 8 ? kCommRegs : kComm;
     // Columns per thread: one, so that small rows still make enough wavefronts; more once there are plenty.  Update: 16
     // workers without momentum, 600 000 columns 27.0 / 25.6 / 24.5 us with 1 / 2 / 4, 250 000 columns 13.8 / 13.7 / 14.1;
     // with momentum two columns are never more than 2 % ahead, four mostly behind.  Algorithm 1's iteration, 8 workers in 2
     // groups: 140 001 columns 8.8 / 9.4 / 10.0, 1 250 001 37 / 35 / 32.  Groups of one, 8 x 271 117, 13.6 / 12.8 / 12.5.
     // Elastic averaging, 16 x 271 117 with momentum, 18.3 / 21.1, 4 x 1 250 001 without 18.8 / 17.8 / 16.3.
     int vec = 1;
-    if (mode == kUpdate || mode == kCenter) {
+    if (mode == kUpdate || mode == kUpdatePull || mode == kCenter) {
         if (!mom && p.P >= 500000) vec = p.P >= 1000000 ? 4 : 2;
         // (a bf16 copy is written two bytes per lane with one column: 8 workers x 266 610 columns, whole step 62.9 -> 61.0 us)
         if (p.xb && p.P >= 100000 && vec < 2) vec = 2;
@@ -784,6 +804,7 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     case kUpdate: launch_mode<kUpdate>(s, vec, mom, nt, stream); break;
     case kUpdateOnes: launch_mode<kUpdateOnes>(s, vec, mom, nt, stream); break;
     case kComm: launch_mode<kComm>(s, vec, mom, nt, stream); break;
+    case kUpdatePull: launch_mode<kUpdatePull>(s, vec, mom, nt, stream); break;
     case kPull:
         if (vec == 4) launch_vec<4, 0, kPull, 0>(s, false, stream);
         else if (vec == 2) launch_vec<2, 0, kPull, 0>(s, false, stream);

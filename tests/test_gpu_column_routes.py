@@ -70,6 +70,27 @@ def test_easgd_without_momentum(W, G, P, ld):
     easgd.test_easgd_update_matches_oracle(W, G, P, ld, 0.0, 0, 1e-4)
 
 
+# Algorithm 1's iterations whose pull is walked group by group behind the update (a few of large groups communicate; pairs above
+# 150 MB, or 70 with half of them; with momentum between 30 and 95 MB; a group of 5 to 8 with momentum), those beside them that are not, and many
+# groups of one of which few communicate (row streams: more than 24, or more than 16 above 30 MB)
+@pytest.mark.parametrize("mu", [0.0, 0.9])
+@pytest.mark.parametrize("W,G,P,ld", [(8, 1, 1031, 1031), (8, 2, 301, 320), (4, 2, 301, 320), (12, 3, 1031, 1031), (16, 4, 100_003, 100_032), (24, 4, 301, 320),
+                                      (16, 8, 800_003, 800_032), (28, 28, 5003, 5003), (20, 20, 130_003, 130_048)])
+def test_iterations_with_few_groups_match_the_oracle(W, G, P, ld, mu):
+    x0, g0, _ = wl.stress_state(W, P, ld, seed=W)
+    pr = Pair(x0, wl.equal_group_offsets(W, G), P=P, momentum=mu)
+    one, most = np.zeros(G, np.uint8), np.ones(G, np.uint8)
+    one[G - 1], most[0] = 1, G == 1
+    for t, (rl, rg) in enumerate([(np.ones(G, np.uint8), 1), (one, 0), (most, 0), (np.zeros(G, np.uint8), 1), (one, 1)]):
+        pr.set_grad(g0, wl.stress_losses(W, t, seed=G))
+        before = pr.follow_gpu()
+        alg1.alg1_oracle_iteration(pr.ora, 0.05, 0.02 * (t > 0), 0.01 * (t > 0), 0.1, 0.07, rl, rg)
+        comm = (L.COMM_LOCAL if rl.any() else 0) | (L.COMM_GLOBAL if rg else 0)
+        pr.pop.step_alg1(L.ExternalBatch(pr.losses_dev), 0.05, 0.02 * (t > 0), 0.01 * (t > 0), 0.1, 0.07, comm, rl)
+        assert pr.check_leaders(rl, rg)
+        pr.check_step_elementwise(before, f"iteration {t}", k_self=4.0)
+
+
 # pulls alone, some or all groups communicating: groups of one up to 8 workers and above, pairs, large groups above 16 workers
 # and 30 MB, four workers above 100 MB
 @pytest.mark.parametrize("W,G,P,ld", [(8, 8, 301, 320), (12, 12, 1031, 1031), (16, 8, 1030, 1088), (24, 4, 120_003, 120_064), (4, 2, 2_100_003, 2_100_032)])
