@@ -420,12 +420,20 @@ lsgd_status do_select(lsgd_population* p, const float* losses, const uint8_t* re
 // the lines are interpolated; 240 drawn populations (1 to 64 workers, 500 to 8 million columns, all the calls that come
 // this way) against row streams alone: half of them change, by a third on average, and none gets more than 5 % slower.
 // Groups of one worker are walked together instead: 16 x 140 001 36 / 16 us, 16 x 1 250 001 with momentum (400 MB) 126 / 90,
-// half of the leaders kept 90 / 88, none re-selected 43 / 46 (8 x 1 250 001).
-bool column_step(const lsgd_population* p, bool selects)
+// half of the leaders kept 90 / 88, none re-selected 43 / 46 (8 x 1 250 001).  Every row is then waited for alike, so that row
+// streams, which hold nothing up for a kept leader, come back in where few are re-selected: one of 32 x 140 001 27 / 37, 8 of
+// them 34 / 36, one of 16 x 400 001 29 / 30 (as a whole step, which takes two launches more by row streams, 32 / 29), one of 8 x
+// 2 500 000 with momentum (400 MB) 89 / 102; not for rows so short that the copies' launch counts (one of 16 x 1003 16 / 13).
+// fresh: groups re-selected since the last update; whole: the call also selects.
+bool column_step(const lsgd_population* p, bool selects, int fresh, bool whole)
 {
     const int W = p->cfg.W, G = p->cfg.n_groups;
     const double bytes = (p->cfg.momentum != 0.0f ? 20.0 : 12.0) * (double)W * (double)p->cfg.P;
-    if (W == G && W > 1) return selects && W <= 32 && bytes <= (W >= 8 ? 450e6 : 300e6);   // 4 x 5 000 000, three kept: 94 / 105
+    if (W == G && W > 1) {
+        if (!selects || W > 32) return false;
+        if (bytes > 300e6) return W >= 8 && bytes <= 450e6 && 2 * fresh >= W;               // 4 x 5 000 000, three kept: 94 / 105
+        return W <= 8 || 4 * fresh >= W || p->cfg.P < 5000 || (whole && W <= 16);
+    }
     if (W > 32 || bytes > 300e6) return false;
     if (selects) return W >= 4 * G || (W <= 16 && W >= 2 * G);
     return W >= 4 * G && (W <= 16 || bytes >= 30e6);                   // 32 x 30 000, 8 groups: 12.3 / 13.5
@@ -507,7 +515,7 @@ lsgd_status do_pull(lsgd_population* p, float eta, float lamL, float lamG, bool 
     const double bytes = 12.0 * (double)p->cfg.W * (double)p->cfg.P;
     const int G = p->cfg.n_groups;
     const bool ones = comm && p->cfg.W == G && G > 8 && p->pending_global && 2 * pending_groups(p) < G;
-    if (any_pending(p) && column_step(p, true) && !ones && (p->cfg.W <= 16 || bytes >= 30e6)) {
+    if (any_pending(p) && column_step(p, true, comm ? G : pending_groups(p), false) && !ones && (p->cfg.W <= 16 || bytes >= 30e6)) {
         ColumnStep c{};
         c.pull = q;
         c.update = !comm; c.comm = comm; c.commL = lamL; c.commG = lamG;
@@ -657,9 +665,9 @@ lsgd_status lsgd_step(lsgd_population* pop, const lsgd_batch* batch, float eta, 
     if (st != LSGD_OK) return st;
     if ((pop->cfg.flags & LSGD_FUSED_MLP_UPDATE) && batch->kind == LSGD_BATCH_MLP)
         return do_fused_mlp_step(pop, batch, eta, lambda_L, lambda_G, refresh_local, refresh_global);
-    bool selects = any_pending(pop) || refresh_global != 0 || !refresh_local;
-    for (int j = 0; j < pop->cfg.n_groups && !selects; ++j) selects = refresh_local[j] != 0;
-    if (column_step(pop, selects)) {
+    int fresh = 0;
+    for (int j = 0; j < pop->cfg.n_groups; ++j) fresh += !refresh_local || refresh_local[j] || pop->pending_local[(size_t)j];
+    if (column_step(pop, fresh > 0 || pop->pending_global || refresh_global != 0, fresh, true)) {
         ColumnStep c{};
         st = column_losses(pop, batch, &c);
         if (st != LSGD_OK) return st;

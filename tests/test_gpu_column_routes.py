@@ -53,6 +53,26 @@ def test_groups_of_one_match_the_oracle(W, off, P, ld, mu, flags, wd):
     column.test_whole_step_matches_oracle(W, off, P, ld, mu, flags, wd)
 
 
+# few of many re-selected: row streams from 5000 columns and 17 workers (9, as separate calls) on
+@pytest.mark.parametrize("W,P,ld", [(8, 5003, 5056), (16, 5003, 5056), (20, 4999, 4999), (20, 5003, 5056)])
+def test_few_groups_of_one_re_selected_match_the_oracle(W, P, ld):
+    x0, g0, _ = wl.stress_state(W, P, ld, seed=W)
+    pr = Pair(x0, ones(W), P=P, momentum=0.9)
+    one, none, every = np.eye(W, dtype=np.uint8)[W // 2], np.zeros(W, np.uint8), np.ones(W, np.uint8)
+    for t, (rl, rg) in enumerate([(every, 1), (one, 0), (none, 1), (one, 1)]):
+        for whole in (True, False):
+            pr.set_grad(g0, wl.stress_losses(W, 2 * t + whole, seed=W))
+            before = pr.follow_gpu()
+            pr.ora.select(rl, rg); pr.ora.update(0.05, 0.1, 0.05, rl, rg)
+            if whole:
+                pr.pop.step(L.ExternalBatch(pr.losses_dev), 0.05, 0.1, 0.05, rl, rg)
+            else:
+                pr.pop.select_leaders(pr.losses_dev, rl, rg); pr.pop.pull_update(0.05, 0.1, 0.05)
+            assert pr.check_leaders(rl, rg)
+            pr.check_step_elementwise(before, f"step {t}")
+            np.testing.assert_array_equal(pr.Z.cpu().numpy()[:, :P], pr.ora.Z[:, :P])
+
+
 @pytest.mark.parametrize("mu", [0.0, 0.9])
 @pytest.mark.parametrize("W,off,P,ld", ALG1)
 def test_one_call_equals_separate_calls(W, off, P, ld, mu):
