@@ -276,7 +276,7 @@ __device__ __forceinline__ void stream_columns(const ColumnDev& s, const Leaders
                     }
                 }
             }
-                        if (s.update) {
+            if (s.update) {
                 Coef cr = c;
                 if (exempt) {
                     if (pullL && row == uni(before.lead[j])) cr.cL = 0.0f;
@@ -489,7 +489,7 @@ __device__ __forceinline__ void regs_easgd(const ColumnDev& s, uint32_t col, Row
 #pragma unroll
     for (int u = 0; u < NR; ++u)
         if (u < a.W) {
-                        update_vec<KIND, V>(r.x[u], r.g[u], r.m[u], none, zg, c);
+            update_vec<KIND, V>(r.x[u], r.g[u], r.m[u], none, zg, c);
             if (NT) st_stream(at(a.x, a.ld, u, col), r.x[u]); else st_vec(at(a.x, a.ld, u, col), r.x[u]);
             if (KIND == 1) { if (NT) st_stream(at(a.m, a.ld, u, col), r.m[u]); else st_vec(at(a.m, a.ld, u, col), r.m[u]); }
             if (a.xb) st_bf16(at(a.xb, a.ld, u, col), r.x[u]);
@@ -673,11 +673,12 @@ void launch_vec(const ColumnDev& s, bool nt, hipStream_t st)
 {
     const int64_t cols = s.a.col1 - s.a.col0, per = (int64_t)kThreads * VEC, whole = cols / VEC * VEC;
     const dim3 grid((unsigned)((whole + per - 1) / per + (whole < cols)));
-    // (a group's rows are read again, and rows of groups that do not move live on in the caches: plain accesses)
-    if constexpr (MODE != kPull && MODE != kUpdatePull) {
-        if (nt) { hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR>), grid, dim3(kThreads), 0, st, s); return; }
-    }
-    hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR>), grid, dim3(kThreads), 0, st, s);
+    // one kernel where a way has but one kind of accesses: what is walked group by group is read again, rows in registers and
+    // the two passes of elastic averaging stream
+    constexpr bool PLAIN = MODE == kPull || MODE == kUpdatePull, STREAMS = MODE == kCommRegs || MODE == kCenter;
+    if constexpr (!PLAIN)
+        if (nt || STREAMS) { hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR>), grid, dim3(kThreads), 0, st, s); return; }
+    if constexpr (!STREAMS) hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR>), grid, dim3(kThreads), 0, st, s);
 }
 
 // vec: columns per thread wished for; no more than the registers hold.
@@ -791,7 +792,7 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     // (26 MB) 13.6 / 17.3, 16 x 1 250 001 with momentum (400 MB) 106 / 90; with most of them kept 8 x 1 250 001 (120 MB) 43 / 39.
     const bool all_fresh = q.select == 1 && (q.cap & (~0ull >> (64 - p.G))) == (~0ull >> (64 - p.G));
     const bool nt = mode == kUpdateOnes ? (all_fresh ? bytes > 200e6 : true)
-                  : mode == kCommRegs ? true : bytes >= 16e6 && (bytes < 90e6 || bytes > 280e6);
+                  : bytes >= 16e6 && (bytes < 90e6 || bytes > 280e6);
     if (!q.update && q.comm && q.commL == 0.0f && q.commG == 0.0f) {
         const int64_t tiles = (p.P + (int64_t)kThreads * vec - 1) / ((int64_t)kThreads * vec);
         const dim3 grid((unsigned)(tiles < 2048 ? tiles : 2048));
@@ -814,7 +815,7 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
         if (p.W <= 4) launch_mode<kCommRegs, 4>(s, vec, mom, nt, stream);
         else launch_mode<kCommRegs, 8>(s, vec, mom, nt, stream);
         break;
-    case kCenter: launch_vec<1, 1, kCenter, 0>(s, true, stream); break;
+    case kCenter: launch_vec<1, 1, kCenter, 0>(s, nt, stream); break;
     case kCenterRegs:
         if (p.W <= 8) launch_mode<kCenterRegs, 8>(s, vec, mom, nt, stream);
         else if (p.W <= 16) launch_mode<kCenterRegs, 16>(s, vec, mom, nt, stream);
