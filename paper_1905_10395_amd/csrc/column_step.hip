@@ -9,8 +9,9 @@
 // one also records its result for the calls that follow.
 //
 // Which path.  A launch costs about 3 to 5 us here whatever it does, while a workgroup that hops between W rows gets
-// less out of HBM than the row-streaming kernels (5.2 against 5.9 TB/s at 1.6 GB per update); up to about 300 MB read
-// and written per update (the caller's rule) the saved launches weigh more.  Measured, whole lsgd_step on external
+// less out of HBM than the row-streaming kernels (5.2 against 5.9 TB/s at 1.6 GB per update); up to 300 MB read and
+// written per update, 450 for groups of one and Algorithm 1, 650 for elastic averaging (the caller's rules), the saved
+// launches weigh more.  Measured, whole lsgd_step on external
 // gradients, row streams -> this kernel, us: 4 x 1003 14.6 -> 4.5; 12 x 271 117 with momentum and kept leaders
 // 24.6 -> 16.5; 16 x 250 000 with momentum 30.0 -> 17.3;
 // 16 x 1 250 000 without 62.5 -> 41.5; elastic averaging, 16 x 1 250 000 with momentum 85.3 -> 73.3.
@@ -139,7 +140,7 @@ __device__ __forceinline__ void update_columns(const ColumnDev& s, const Leaders
 }
 
 // A thread's columns of row i of p: the row's address is the same in every lane, the column's is an offset of 32 bits
-// (launch_column_step sees to that), which keeps addresses out of the vector registers.
+// (launch_column_step refuses more), which keeps addresses out of the vector registers.
 template <class T>
 __device__ __forceinline__ T* at(T* p, int64_t ld, int i, uint32_t col)
 {
@@ -773,6 +774,7 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     // with momentum two columns are never more than 2 % ahead, four mostly behind.  Algorithm 1's iteration, 8 workers in 2
     // groups: 140 001 columns 8.8 / 9.4 / 10.0, 1 250 001 37 / 35 / 32.  Groups of one, 8 x 271 117, 13.6 / 12.8 / 12.5.
     // Elastic averaging, 16 x 271 117 with momentum, 18.3 / 21.1, 4 x 1 250 001 without 18.8 / 17.8 / 16.3.
+    if (p.P > ((int64_t)1 << 30)) return hipErrorInvalidValue;         // (at(): far beyond any caller's limit)
     int vec = 1;
     if (mode == kUpdate || mode == kUpdatePull || mode == kCenter) {
         if (!mom && p.P >= 500000) vec = p.P >= 1000000 ? 4 : 2;
