@@ -774,7 +774,6 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     // with momentum two columns are never more than 2 % ahead, four mostly behind.  Algorithm 1's iteration, 8 workers in 2
     // groups: 140 001 columns 8.8 / 9.4 / 10.0, 1 250 001 37 / 35 / 32.  Groups of one, 8 x 271 117, 13.6 / 12.8 / 12.5.
     // Elastic averaging, 16 x 271 117 with momentum, 18.3 / 21.1, 4 x 1 250 001 without 18.8 / 17.8 / 16.3.
-    if (p.P > ((int64_t)1 << 30)) return hipErrorInvalidValue;         // (at(): far beyond any caller's limit)
     int vec = 1;
     if (mode == kUpdate || mode == kUpdatePull || mode == kCenter) {
         if (!mom && p.P >= 500000) vec = p.P >= 1000000 ? 4 : 2;
@@ -803,6 +802,8 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
         else hipLaunchKernelGGL((capture_kernel<1>), grid, dim3(kThreads), 0, stream, s);
         return hipGetLastError();
     }
+    // (captures alone, above, take any number of columns)
+    if (p.P > ((int64_t)1 << 30) && mode != kUpdate && mode != kPull && mode != kUpdatePull && mode != kCenter) return hipErrorInvalidValue;
     switch (mode) {
     case kUpdate: launch_mode<kUpdate>(s, vec, mom, nt, stream); break;
     case kUpdateOnes: launch_mode<kUpdateOnes>(s, vec, mom, nt, stream); break;
