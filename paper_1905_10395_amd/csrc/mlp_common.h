@@ -206,7 +206,8 @@ __device__ __forceinline__ void store_bias_grad(const GemmArgs& g, int w, int m,
 }
 
 // Forward and d-input products of 16-byte aligned operands (mlp_gemm_direct.hip): M a multiple of 128, N and K of 64;
-// or, if it returns true, other sizes.
+// or, if it returns true, other sizes.  better_direct: whether it is the faster way for a product of more than two K steps.
+bool better_direct(const GemmArgs& g, int W, int epi);
 void launch_gemm_direct(const GemmArgs& g, int W, int epi, hipStream_t s);
 bool launch_gemm_direct_any(const GemmArgs& g, int W, int epi, hipStream_t s);
 

@@ -30,6 +30,8 @@ namespace {
 
 constexpr int kBK = 64;              // contraction per K step: one 128-byte line of every row
 
+constexpr int kNonTemporal = 2;      // cache policy of a load
+
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef const __attribute__((address_space(1))) void* global_ptr;
 
@@ -53,8 +55,8 @@ __device__ __forceinline__ void for_each(const F& f)
     if constexpr (I < N) { f(std::integral_constant<int, I>{}); for_each<N, I + 1>(f); }
 }
 
-// ST: K steps in LDS
-template <int BM, int BN, int WVM, int WVN, int ST, bool TRANS_B, int EPI, bool ANY>
+// ST: K steps in LDS; NT: B past the caches
+template <int BM, int BN, int WVM, int WVN, int ST, bool TRANS_B, int EPI, bool ANY, bool NT>
 __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g, int tiles_m, int tiles_n)
 {
     constexpr int THREADS = 64 * WVM * WVN;
@@ -120,7 +122,7 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
             } else {
                 p = pb[c] + k;
             }
-            __builtin_amdgcn_global_load_lds((global_ptr)p, (lds_ptr)(buf + (BM * kBK + (c * THREADS + wid * 64) * 8)), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((global_ptr)p, (lds_ptr)(buf + (BM * kBK + (c * THREADS + wid * 64) * 8)), 16, 0, NT ? kNonTemporal : 0);
         }
     };
 
@@ -301,21 +303,30 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
     }
 }
 
-template <int BM, int BN, int WVM, int WVN, int ST>
+// Whether a forward product reads its weights past the caches: more than about half of the memory-side cache holds of one
+// layer's weights will not be there again at the next pass, and takes the room of what the passes behind it write.
+// Plain / past the caches, us: 16 workers, batch 128, 3072-2048-10, objective 56.9 / 52.5, gradients 162 / 150, fused step 314 /
+// 309; batch 100, 3072-2000-1000-10, gradients 286 / 260; 3072-1536-10 (151 MB) 51.7 / 48.2, 135 / 127; but 2048-1536-10 (101 MB)
+// 31.5 / 36.4, 90 / 94, batch 100, 1000-3000-10 (96 MB) 43.7 / 55.  With a second row tile the L2s are to keep them: batch 200,
+// 3072-2000-1000-10, 114 / 119, fused step 685 / 708.
+bool streams(const GemmArgs& g, int W, int rows) { return g.M <= rows && 2.0 * W * (double)g.N * g.K > 120e6; }
+
+template <int BM, int BN, int WVM, int WVN, int ST, bool ANY>
 void launch_forward(const GemmArgs& g, int W, hipStream_t s)
 {
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, ST, false, EPI_FWD, true>), dim3((unsigned)(tiles_m * tiles_n * W)),
-                       dim3(64 * WVM * WVN), 0, s, g, tiles_m, tiles_n);
+    const dim3 grid((unsigned)(tiles_m * tiles_n * W)), block(64 * WVM * WVN);
+    if (streams(g, W, BM)) hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, ST, false, EPI_FWD, ANY, true>), grid, block, 0, s, g, tiles_m, tiles_n);
+    else hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, ST, false, EPI_FWD, ANY, false>), grid, block, 0, s, g, tiles_m, tiles_n);
 }
 
 template <int BM, int BN, int WVM, int WVN, int ST, bool ANY>
 void launch_direct(const GemmArgs& g, int W, int epi, hipStream_t s)
 {
+    if (epi == EPI_FWD) { launch_forward<BM, BN, WVM, WVN, ST, ANY>(g, W, s); return; }
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    const dim3 grid((unsigned)(tiles_m * tiles_n * W)), block(64 * WVM * WVN);
-    if (epi == EPI_FWD) hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, ST, false, EPI_FWD, ANY>), grid, block, 0, s, g, tiles_m, tiles_n);
-    else hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, ST, true, EPI_DX, ANY>), grid, block, 0, s, g, tiles_m, tiles_n);
+    hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WVM, WVN, ST, true, EPI_DX, ANY, false>), dim3((unsigned)(tiles_m * tiles_n * W)),
+                       dim3(64 * WVM * WVN), 0, s, g, tiles_m, tiles_n);
 }
 
 // 128 columns as long as that leaves few compute units without a tile (forward 500 x 300 x 784, 16 workers, 192 tiles of
@@ -327,6 +338,14 @@ bool wide_tile(const GemmArgs& g, int W, int epi)
 }
 
 } // namespace
+
+// One row tile per weight tile and more tiles than compute units: nothing is used twice, and a second workgroup on a compute
+// unit is worth more than loads that take no registers.  Through registers / straight to LDS, us, 16 workers, batch 128: objective
+// of 1024-4096-10 47 / 52, of 3072-4096-10 97 / 103, gradients 283 / 291; 256 tiles (3072-2048-10) 54 / 52.
+bool better_direct(const GemmArgs& g, int W, int epi)
+{
+    return !(epi == EPI_FWD && g.M == 128 && g.N % 128 == 0 && (int64_t)(g.N / 128) * W > 256 && streams(g, W, 128));
+}
 
 void launch_gemm_direct(const GemmArgs& g, int W, int epi, hipStream_t s)
 {
@@ -347,7 +366,7 @@ bool launch_gemm_direct_any(const GemmArgs& g, int W, int epi, hipStream_t s)
     // One K step more in LDS where the contraction is long: with double sums a step takes longer than its loads, and the
     // 128 x 128 tile has a compute unit to itself (forward 500 x 3072 x 1024, 16 workers, 79.5 -> 76.8 us; whole tiles and
     // the 64-column tile, two workgroups per compute unit, gain nothing, contractions of 256 lose 2 %).
-    if (wide_tile(g, W, epi) && g.K >= 1024 && epi == EPI_FWD) launch_forward<128, 128, 2, 4, 4>(g, W, s);
+    if (wide_tile(g, W, epi) && g.K >= 1024 && epi == EPI_FWD) launch_forward<128, 128, 2, 4, 4, true>(g, W, s);
     else if (wide_tile(g, W, epi)) launch_direct<128, 128, 2, 4, 3, true>(g, W, epi, s);
     else launch_direct<128, 64, 2, 2, 3, true>(g, W, epi, s);
     return true;

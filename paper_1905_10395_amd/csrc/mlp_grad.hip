@@ -12,8 +12,8 @@
 // The three matrix products are dense contractions and run on the matrix
 // cores (v_mfma_f32_32x32x16_bf16).  Shapes that are multiples of the tile sizes
 // with 16-byte aligned rows: d-weight products, and forward and d-input products of one or two
-// K steps or that fill the chip with 256 x 256 tiles, with the kernel in this file, other forward
-// and d-input products with mlp_gemm_direct.hip, which also takes other sizes of aligned rows;
+// K steps, with large weights that are used once, or that fill the chip with 256 x 256 tiles, with
+// the kernel in this file, other forward and d-input products with mlp_gemm_direct.hip, which also takes other sizes of aligned rows;
 // the rest with the any-shape kernel (mlp_gemm_ragged.hip), the narrow classifier layer included.
 //
 // Operand layouts for the MFMA kernel.  A lane feeds the matrix core eight
@@ -434,7 +434,7 @@ static bool try_mfma(const GemmArgs& g, int W, hipStream_t s)
     // forward and d-input products of more than two K steps go straight to LDS; shorter ones end before its three steps are
     // under way (objective of 64-64-64-64-10, 4 workers, batch 128, 18.5 us that way, 16.4 this way; 128-128-10, batch 1024,
     // 8 workers, 11.2 / 10.7; 192-64-10 11.0 / 11.2)
-    if ((EPI == EPI_FWD || EPI == EPI_DX) && g.K > 2 * kBK) { launch_gemm_direct(g, W, EPI, s); return true; }
+    if ((EPI == EPI_FWD || EPI == EPI_DX) && g.K > 2 * kBK && better_direct(g, W, EPI)) { launch_gemm_direct(g, W, EPI, s); return true; }
     if (g.N % 128 == 0 && blocks128 >= 256) launch_gemm<128, 128, 2, 2, TRANS_B, EPI>(g, W, s);
     else launch_gemm<128, 64, 2, 2, TRANS_B, EPI>(g, W, s);
     return true;
