@@ -223,6 +223,7 @@ struct GemmGroup {
     GemmArgs g[kGroupMax];
     int n;
 };
+bool gemm_joins_group(const GemmArgs& g, int W, int epi);     // whether the product does not lose by it
 void launch_gemm_group(const GemmGroup& q, int W, int epi, hipStream_t s);
 
 } // namespace lsgd

@@ -724,6 +724,11 @@ void launch_tiles(const GemmGroup& q, int W, hipStream_t s)
     hipLaunchKernelGGL((gemm_group_kernel<BM, EPI>), dim3((unsigned)(runs * kXcds)), dim3(256), big > small ? big : small, s, q, W);
 }
 
+// A gradient of one K step so large that three or four workgroups per compute unit, each writing its rows, are too many streams
+// for the memory; from sixteen workers on.  Two / more, whole gradients, us, batch 32: 3072-2048-10, 16 workers, 128 / 139,
+// 3072-1536-10 105 / 113, 3072-1024-10, 32 workers, 124 / 132; but 8 workers 3072-2048-10 85 / 81, 16 with 2048-1024-10 (134 MB) 76 / 70.
+bool crowds(const GemmArgs& g, int W) { return W >= 16 && 4.0 * W * (double)g.M * g.N > 240e6; }
+
 template <int BM, int BN, int WVM, int WVN, int WVK, int BK, int EPI, bool F32A = false>
 void launch_tile(const GemmArgs& g, int W, hipStream_t s)
 {
@@ -737,7 +742,7 @@ void launch_tile(const GemmArgs& g, int W, hipStream_t s)
     }
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     const int64_t per_xcd = ((int64_t)tiles_m * tiles_n * W + kXcds - 1) / kXcds;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(per_xcd * kXcds)), dim3(S::THREADS), S::bytes(g.K > BK ? 2 : 1), s, g, tiles_m, tiles_n, W, per_xcd);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(per_xcd * kXcds)), dim3(S::THREADS), S::bytes(g.K > BK || (EPI == EPI_DW && crowds(g, W)) ? 2 : 1), s, g, tiles_m, tiles_n, W, per_xcd);
 }
 
 // Row tile: a batch of up to 32 / 64 fits one tile; larger ones take 128 rows, unless that leaves compute units
@@ -809,6 +814,15 @@ void launch_group_epi(const GemmGroup& q, int W, hipStream_t s)
 }
 
 } // namespace
+
+// Large products are better off alone: the launch that a group saves is nothing to them, and with more than one K step its kernel is
+// the slower one.  Alone / in a group with the classifier's, whole gradients, us, 16 workers, batch 100: 3072-2000-10 (393 MB of
+// gradients) 174 / 191, 3072-1000-10 (197 MB) 99 / 104, but 3072-512-10 (100 MB) 65.5 / 64.7, 1000-2000-10 (128 MB) 97 / 96.
+bool gemm_joins_group(const GemmArgs& g, int W, int epi)
+{
+    const double bytes = 4.0 * W * (double)g.M * g.N;
+    return g.K > 64 ? bytes <= 150e6 : !(epi == EPI_DW && crowds(g, W));
+}
 
 void launch_gemm_group(const GemmGroup& q, int W, int epi, hipStream_t s)
 {

@@ -408,9 +408,9 @@ static bool aligned_for_mfma(const GemmArgs& g)
     return a16(g.A) && a16(g.B) && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sA % 8 == 0 && g.sB % 8 == 0;
 }
 
-// Picks the largest tile whose grid still fills the chip; returns false when no MFMA tile fits the shape.
+// Whether the shape is whole tiles of aligned rows.
 template <bool TRANS_B, int EPI>
-static bool try_mfma(const GemmArgs& g, int W, hipStream_t s)
+static bool mfma_fits(const GemmArgs& g)
 {
     if (g.K % kBK || g.M % 128 || g.N % 64 || !aligned_for_mfma(g)) return false;
     if (EPI == EPI_DX && (g.ldoutT % 4 || (reinterpret_cast<uintptr_t>(g.outT) & 7u) || g.sOutT % 4)) return false;
@@ -425,6 +425,14 @@ static bool try_mfma(const GemmArgs& g, int W, hipStream_t s)
             (reinterpret_cast<uintptr_t>(g.fu.xb) & 7u))
             return false;
     }
+    return true;
+}
+
+// Picks the largest tile whose grid still fills the chip; returns false when no MFMA tile fits the shape.
+template <bool TRANS_B, int EPI>
+static bool try_mfma(const GemmArgs& g, int W, hipStream_t s)
+{
+    if (!mfma_fits<TRANS_B, EPI>(g)) return false;
     const int64_t blocks256 = (g.M % 256 == 0 && g.N % 256 == 0) ? (int64_t)(g.M / 256) * (g.N / 256) * W : 0;
     const int64_t blocks128 = (int64_t)(g.M / 128) * (g.N / 128) * W;
     // the fused update keeps two batches of x, m and leader values in registers: no room beside a 256x256 tile
@@ -653,7 +661,7 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, floa
 }
 
 // Backward pass.  Per layer, from the top: delta_{k-1} first (it reads W_k, which the fused update
-// of dW_k overwrites), then dW_k and db_k; those without an aligned tile in one launch at the end.
+// of dW_k overwrites), then dW_k and db_k; small ones without an aligned tile that follow each other in one launch.
 hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int W, int64_t P, int64_t ld,
                                const lsgd_mlp_batch& b, const DeviceState& st, const FusedUpdate* fu_in, hipStream_t s)
 {
@@ -696,8 +704,13 @@ hipError_t launch_mlp_backward(const uint16_t* xb, const float* x, float* g, int
             a.M = dout; a.N = din; a.K = B;
             a.C = g + woff[k]; a.sC = ld; a.ldc = din;
             a.fu = fu; a.colC = woff[k];
-            if (!(fused ? try_mfma<true, EPI_DWU>(a, W, s) : try_mfma<true, EPI_DW>(a, W, s))) rest.g[rest.n++] = a;
-            if (rest.n == kGroupMax) { launch_gemm_group(rest, W, epi, s); rest.n = 0; }
+            // (what waits goes before an aligned product: it is small, and its operands are in the caches)
+            const bool whole = fused ? mfma_fits<true, EPI_DWU>(a) : mfma_fits<true, EPI_DW>(a);
+            if (rest.n && (whole || rest.n == kGroupMax)) { launch_gemm_group(rest, W, epi, s); rest.n = 0; }
+            if (!whole && gemm_joins_group(a, W, epi)) rest.g[rest.n++] = a;
+            else if (!whole) launch_gemm_ragged(a, W, epi, s);
+            else if (fused) try_mfma<true, EPI_DWU>(a, W, s);
+            else try_mfma<true, EPI_DW>(a, W, s);
         }
     }
     if (rest.n) launch_gemm_group(rest, W, epi, s);
