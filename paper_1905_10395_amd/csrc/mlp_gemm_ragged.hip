@@ -833,10 +833,13 @@ void launch_gemm_group(const GemmGroup& q, int W, int epi, hipStream_t s)
 
 // The 32-row tile converts as it goes: its products are small enough that a launch for the conversion counts and reading
 // the inputs in fp32 once per 64 columns does not.  Objective of 617-132-10, 3 workers, batch 16, 14.2 -> 12.4 us, step of
-// 784-300-100-10, 8 x 50, 51.9 -> 50.6; 47 drawn calls, part of them of this size, 0.966 of the time.  The larger tiles have no registers
-// for fp32 pieces in flight.
+// 784-300-100-10, 8 x 50, 51.9 -> 50.6; 47 drawn calls, part of them of this size, 0.966 of the time.  Where every 64 columns read
+// more than 90 MB a second time in all, the launch is the cheaper way: gradients, launch of its own / as it goes, us, batch 32,
+// 3072-4096-10, 16 workers (201 MB) 278 / 288, 8 (101 MB) 155.7 / 158.5; 3072-2048-10, 16 (101 MB) 148 / 150, 8 (50 MB) 86.9 / 86.6.
+// The larger tiles have no registers for fp32 pieces in flight.
 bool launch_gemm_ragged_f32(const GemmArgs& g, int W, hipStream_t s)
 {
+    if (2.0 * W * (double)g.M * g.K * ((g.N + 63) / 64) > 90e6) return false;
     if (g.K < 8 || long_and_few(g, W) || (g.M > 32 && fills(g, W, 64)) || (g.M > 64 && fills(g, W, 128))) return false;
     launch_tile<32, 64, 1, 1, 4, 128, EPI_FWD, true>(g, W, s);
     return true;
