@@ -28,8 +28,8 @@
 //   iterations and pulls in which few           group by group (pull_columns): the other ways read or work on every row,
 //   groups communicate                          whoever communicates
 //   elastic averaging                           every row in registers, x read once: 4 x 1003 6.5 -> 4.0, 16 x 1 250 001
-//                                               without momentum 54 -> 46, 32 x 140 001 34 -> 17 (but for many rows with
-//                                               momentum out of HBM: two passes)
+//                                               without momentum 54 -> 46, 32 x 140 001 34 -> 17 (two passes for 13 to
+//                                               16 rows with momentum between 300 and 430 MB)
 #include "pull_common.h"
 #include "select_common.h"
 
@@ -763,10 +763,12 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
                (!p.Z || aligned(p.Z, 4 * v)) && (!p.xb || aligned(p.xb, 2 * v)) && (!q.center || aligned(q.center, 4 * v));
     };
     const double bytes = (mom ? 20.0 : 12.0) * (double)p.W * (double)p.P;
-    // Many rows with momentum out of HBM: reading x twice costs less than registers for sixteen rows of three values (16 x
-    // 1 250 001, 400 MB: 71 us against 78; 12 x 1 250 001, 300 MB, 60 against 59, 8 x 2 500 000, 400 MB, 83 against 76).
+    // 13 to 16 rows with momentum, while much of x is still in the memory-side cache at its second reading: twice costs less than
+    // registers for sixteen rows of three values.  Twice / once, us: 16 x 1 250 001 (400 MB) 73 / 79, 15 x 1 250 001 69 / 74, 14 x
+    // 1 250 001 65 / 68, 13 x 1 250 001 (325 MB) 62 / 65, 15 x 1 400 001 (420 MB) 82 / 83; 16 x 1 400 001 (448 MB) 89 / 90, 14 x
+    // 1 666 667 (467 MB) 94 / 87, 16 x 1 866 667 (597 MB) 135 / 123, 13 x 2 000 001 109 / 94; 12 x 1 250 001 (300 MB) 60 / 59.
     const bool by_groups = q.comm && (q.update ? pull_behind_update(q, bytes) : !pull_in_one_pass(q));
-    const int mode = q.center ? (mom && p.W > 12 && bytes > 300e6 && p.W <= 16 ? kCenter : kCenterRegs)
+    const int mode = q.center ? (mom && p.W > 12 && p.W <= 16 && bytes > 300e6 && bytes <= 430e6 ? kCenter : kCenterRegs)
                    : !q.comm ? (p.W == p.G ? kUpdateOnes : kUpdate)
                    : by_groups ? (q.update ? kUpdatePull : kPull) : p.W <= 8 ? kCommRegs : kComm;
     // Columns per thread: one, so that small rows still make enough wavefronts; more once there are plenty.  Update: 16
