@@ -825,7 +825,7 @@ static McCost mc_cost(int W, const lsgd_mc_batch& b, int vw)
 //   100 x 20000   rank 5    4 x 62000   84 / 144 / 605      9468 x 466      rank 2   16 x 62000  180 / 194 / 134
 //   6001 x 3517   rank 10   8 x  4096   34 /  16 /  20      6001 x 3517     rank 10   8 x 16384   38 /  34 /  26
 //   1000 x 800    rank 64   8 x   256   89 /  18 /  15      20000 x 20000   rank 32  16 x 32768  128 / 136 /  77
-enum McRoute { kMcOne, kMcFlight, kMcBinned };
+enum McRoute { kMcOne, kMcFlight, kMcBinned, kMcLds };
 static McRoute mc_route(const McCost& c, int vw, bool binned_ok)
 {
     const double atomics = c.flight < c.one ? c.flight : c.one;
@@ -915,6 +915,38 @@ size_t mc_scratch_bytes(int W, const lsgd_mc_batch& b)
     const int vw = mc_cols(b.r);
     if (!mc_binned_ok(W, b, vw) || (b.r % 4 != 0 && mc_route(mc_cost(W, b, vw), vw, true) != kMcBinned)) return 0;
     return mc_binned_bytes(W, b);
+}
+
+// The route of a call whose rows allow vw columns per lane, with scratch_bytes of scratch; what else the launch needs of it.
+struct McPath {
+    McRoute route;
+    McCost cost;
+    McLds lds;                  // kMcLds: gradients held in LDS, of U, of V
+    bool lu, lv;
+};
+static McPath mc_path(int W, const lsgd_mc_batch& b, int vw, size_t scratch_bytes)
+{
+    McPath p{};
+    p.cost = mc_cost(W, b, vw);
+    p.route = mc_route(p.cost, vw, mc_binned_ok(W, b, vw) && scratch_bytes >= mc_binned_bytes(W, b));
+    p.lds = mc_lds(W, b);
+    const double other = p.route == kMcBinned ? p.cost.binned : p.route == kMcFlight ? p.cost.flight : p.cost.one;
+    // The usual route keeps the call unless the estimate is 13 % and 0.7 us lower: at 10 us all routes are launches.
+    if (1.15 * (p.lds.narrow < p.lds.both ? p.lds.narrow : p.lds.both) + 0.7 < other) {
+        const bool both = p.lds.both <= p.lds.narrow;
+        p.route = kMcLds;
+        p.lu = both || b.m <= b.n; p.lv = both || !p.lu;
+    }
+    return p;
+}
+
+// What mc_path says, for tests: route, factors held in LDS, and where binned the prepare workgroups and their entries.
+void mc_describe_path(int W, const lsgd_mc_batch& b, int vw, size_t scratch_bytes, int out[5])
+{
+    const McPath p = mc_path(W, b, vw, scratch_bytes);
+    out[0] = p.route; out[1] = p.lu; out[2] = p.lv;
+    out[3] = p.route == kMcBinned ? mc_prep_blocks(W, b) : 0;
+    out[4] = p.route == kMcBinned ? mc_ept(W, b) * kPrepThreads : 0;
 }
 
 // The binned path's scratch is a condition only for ranks that are multiples of four; with others a workspace
@@ -1033,16 +1065,13 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         return hipGetLastError();
     };
     const int vw = mc_cols(x, g, ld, b.r);
-    const McCost cost = mc_cost(W, b, vw);
-    const McRoute route = mc_route(cost, vw, mc_binned_ok(W, b, vw) && st.scratch_bytes >= mc_binned_bytes(W, b));
-    const McLds lds = mc_lds(W, b);
-    const double other = route == kMcBinned ? cost.binned : route == kMcFlight ? cost.flight : cost.one;
-    // The usual route keeps the call unless the estimate is 13 % and 0.7 us lower: at 10 us all routes are launches.
-    if (1.15 * (lds.narrow < lds.both ? lds.narrow : lds.both) + 0.7 < other) {
-        const bool both = lds.both <= lds.narrow, lu = both || b.m <= b.n;
+    const McPath path = mc_path(W, b, vw, st.scratch_bytes);
+    const McRoute route = path.route;
+    if (route == kMcLds) {
+        const McLds& lds = path.lds;
         double* sums64 = st.scratch_bytes >= sizeof(double) * (size_t)W * (size_t)lds.chunks ? reinterpret_cast<double*>(st.scratch) : nullptr;
         launch_fill_zero(g, W, ld, s);
-        launch_lds(x, g, W, ld, b, nb, lds, lu, both || !lu, st.partials, sums64, s);
+        launch_lds(x, g, W, ld, b, nb, lds, path.lu, path.lv, st.partials, sums64, s);
         return finish_loss((int)lds.chunks, sums64);
     }
     if (route == kMcBinned) {
@@ -1056,9 +1085,9 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         // double, so that their order does not show.  20000 x 20000, 16 workers, whole step: 5 us less.
         S.sums = W <= kColumnMaxWorkers && !loss_parts_ok(W, S.nbinsU) ? reinterpret_cast<double*>(st.partials) : nullptr;
         launch_prep(W, b, nb, S, s);
-        if (vw == 4) launch_side_lanes<4>(x, g, W, ld, b, S, st.partials, mc_runs(cost, W), s);
-        else if (vw == 2) launch_side_lanes<2>(x, g, W, ld, b, S, st.partials, mc_runs(cost, W), s);
-        else launch_side_lanes<1>(x, g, W, ld, b, S, st.partials, mc_runs(cost, W), s);
+        if (vw == 4) launch_side_lanes<4>(x, g, W, ld, b, S, st.partials, mc_runs(path.cost, W), s);
+        else if (vw == 2) launch_side_lanes<2>(x, g, W, ld, b, S, st.partials, mc_runs(path.cost, W), s);
+        else launch_side_lanes<1>(x, g, W, ld, b, S, st.partials, mc_runs(path.cost, W), s);
         return S.sums ? finish_loss(kLossSlots, S.sums) : finish_loss(S.nbinsU, nullptr);
     }
     const int nblk = (int)((nb + kMcEntriesPerBlock - 1) / kMcEntriesPerBlock);

@@ -41,9 +41,12 @@ def test_pack_entries_is_an_exact_copy():
     (70, 90, 12, 0.50, 2, 900),            # four lanes per row, one of them idle
     (40, 30, 128, 0.50, 2, 300),           # 32 lanes per row: the sum crosses 16-lane rows
     (300, 10, 8, 0.50, 3, 2000),           # two lanes per row; one short side
-    (128, 128, 4, 0.90, 1, 300_000),       # 293 prepare workgroups of 1024 entries: more segments than one round collects
-    (128, 96, 8, 0.90, 4, 300_000),        # 2048 entries per prepare workgroup; thousands of records per bin
-    (128, 96, 8, 0.90, 8, 300_000),        # 4096 entries per prepare workgroup
+    (128, 128, 4, 0.90, 1, 300_000),       # sums in LDS: thousands of entries per row
+    (128, 96, 8, 0.90, 4, 300_000),
+    (128, 96, 8, 0.90, 8, 300_000),
+    (5400, 4400, 4, 0.01, 2, 263_000),     # binned, 257 prepare workgroups of 1024 entries: more segments than one round collects
+    (3100, 2900, 4, 0.02, 4, 263_000),     # ... 2048 entries per prepare workgroup; thousands of records per bin
+    (1700, 1500, 4, 0.05, 8, 263_000),     # ... 4096
 ])
 def test_mc_grad_loss_matches_oracle(m, n, r, frac, W, B, packed):
     prob = upload(wl.mc_problem(m, n, r, frac, 1.0, noise_std=0.01, seed=m + r))

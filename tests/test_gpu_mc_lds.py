@@ -10,9 +10,14 @@ from gpu_util import Pair, dev, rel_l2_rows
 
 pytestmark = pytest.mark.gpu
 
-BOTH = [(60, 50, r, 8, 40001) for r in (1, 2, 3, 5, 8, 17, 33, 67)] + [(150, 90, 5, 300, 6001), (7, 9, 4, 1, 30000)]
+# small factors (the rule holds either or both; both at wide groups of many workers only), one narrow side
+BOTH = [(60, 50, r, 8, 40001) for r in (1, 2, 3, 5, 8, 17, 33, 67)] + [(150, 90, 5, 300, 6001), (7, 9, 4, 1, 30000)] + \
+       [(9, 1, 9, 2384, 14), (2, 2, 17, 2018, 15), (6, 3, 38, 1017, 11)]
 NARROW = [(90, 9000, 1, 4, 40007), (70, 9001, 4, 5, 60007), (61, 9000, 16, 9, 40000), (41, 9000, 33, 16, 30001),
-          (9000, 53, 7, 9, 40000), (9000, 37, 64, 4, 60001), (9000, 500, 67, 8, 40000), (9000, 3, 2, 300, 5000)]
+          (9000, 53, 7, 9, 40000), (9000, 37, 64, 4, 60001), (9000, 500, 67, 8, 40000), (9000, 3, 2, 300, 5000),
+          (8, 500, 67, 4, 40001), (500, 8, 64, 4, 20001)]
+# of these, what the rule sends by the other routes
+BEYOND = [(60, 50, 67, 8, 40001), (150, 90, 5, 300, 6001), (9000, 37, 64, 4, 60001), (9000, 500, 67, 8, 40000)]
 
 
 @pytest.mark.parametrize("packed,listed,odd", [(False, True, False), (True, True, True), (True, False, False)])

@@ -1,5 +1,6 @@
-"""GPU parity of the two routes of the matrix-completion gradient (binned, atomics) at every width of a lane's part of a
-factor row, on shapes that the size rule sends to either, and on workspaces without room for the binned route."""
+"""GPU parity of the routes of the matrix-completion gradient (binned, atomics an entry at a time and with entries in flight;
+sums in LDS have a file of their own) at every width of a lane's part of a factor row, on shapes that the size rule sends to
+each (test_mc_paths.py sees to that), and on workspaces without room for the binned route."""
 import numpy as np
 import pytest
 import torch
@@ -28,7 +29,8 @@ def problem(m, n, r, n_obs, W, B, seed, ld=None, pop_kw=None, G=1):
 
 
 # bins of 128 rows: one row past a bin, several bins; ranks with lanes of four, two and one column, exact and not;
-# 40000 entries per worker so that the binned route is the faster one by the rule, 300 so that it is not
+# 40000 entries per worker so that the binned route is the faster one by the rule (ranks 1 and 2: sums in LDS), 300 so that it is
+# not, but for rank 64
 @pytest.mark.parametrize("B", [300, 40000])
 @pytest.mark.parametrize("r", [1, 2, 3, 4, 5, 6, 10, 12, 33, 50, 64])
 def test_both_routes_match_oracle(r, B):
@@ -43,7 +45,25 @@ def test_both_routes_match_oracle(r, B):
     assert np.all(g[:, P:] == 0)
 
 
-# one side of few rows, many entries: the atomics an entry at a time
+# W, m, n, r, entries: the atomics an entry at a time, groups of 4, 8, 16, 32 and 64 lanes (1 and 2 above)
+ONE_AT_A_TIME = [(4, 210, 580, 3, 12_000), (2, 3300, 520, 5, 50_000), (4, 980, 2300, 9, 44_000), (8, 1220, 1400, 17, 34_400), (9, 4000, 61, 64, 40_000)]
+# binned at the lowest ranks
+BINNED = [(4, 5600, 4600, 1, 36_000), (7, 5800, 2600, 2, 18_000)]
+
+
+@pytest.mark.parametrize("W,m,n,r,B", ONE_AT_A_TIME + BINNED)
+def test_route_matches_oracle(W, m, n, r, B):
+    pr, batch, P = problem(m, n, r, 60000, W, B, seed=r)
+    pr.g.fill_(float("nan"))
+    pr.pop.grad_loss(batch)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(pr.pop.get_losses(), pr.ora.losses, rtol=1e-5)
+    g = pr.g.cpu().numpy()
+    assert rel_l2_rows(g[:, :P], pr.ora.g[:, :P]).max() <= 1e-5
+    assert np.all(g[:, P:] == 0)
+
+
+# one side of few rows, many entries: sums in LDS up to rank 33, atomics above
 @pytest.mark.parametrize("W,m,n", [(4, 90, 4000), (9, 4000, 61)])     # (628 and 1413 loss sums)
 @pytest.mark.parametrize("r", [1, 2, 3, 5, 6, 7, 9, 16, 17, 33, 64, 67])
 def test_narrow_side_matches_oracle(r, W, m, n):

@@ -1,5 +1,6 @@
-"""The size rule that chooses the matrix-completion route, seen from the host: for ranks that are no multiples of four the
-workspace holds the binned route's records exactly where that route is taken."""
+"""The size rule that chooses between binned and atomics, seen from the host: for ranks that are no multiples of four the
+workspace holds the binned route's records exactly where that route is the better of the two (sums in LDS may be better than
+either)."""
 import pytest
 import torch
 
@@ -21,7 +22,7 @@ def binned(m, n, r, W, B):
     (3000, 4001, 5, 16, 62000, True),      # 137 / 79
     (6001, 3517, 10, 8, 16384, True),      # 34 / 26
     (1000, 800, 1, 32, 50000, True),       # 123 / 64
-    (100, 20000, 5, 4, 62000, False),      # 84 / 605: one workgroup walks every record of the narrow side
+    (100, 20000, 5, 4, 62000, False),      # 84 / 605: one workgroup walks every record of the narrow side (LDS is taken)
     (100, 100, 5, 16, 62000, False),       # 151 / 589
     (466, 9468, 2, 4, 62000, False),       # 66 / 105
     (6001, 3517, 10, 8, 4096, False),      # 16 / 20: launches
