@@ -23,6 +23,7 @@ struct GemmArgs {
     const uint16_t* A; int64_t sA; int64_t lda;   // [M][K], per-worker stride sA (elements)
     const uint16_t* B; int64_t sB; int64_t ldb;   // TRANS_B ? [K][N] : [N][K]
     int M, N, K;
+    int updated;                                  // EPI_FWD: a fused update goes over all weights between two passes
     const float* A32; uint16_t* copy; int64_t sCopy; // EPI_FWD on fp32 inputs (in place of A, strides sA and lda): where their bf16 copy [M][K] goes, or NULL
     const float* bias; int64_t sBias;             // EPI_FWD: fp32 [N]
     const uint16_t* mask; int64_t sMask; int64_t ldmask; // EPI_DX: h_{k-1} [M][N]

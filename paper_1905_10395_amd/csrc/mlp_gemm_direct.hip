@@ -308,8 +308,9 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
 // Plain / past the caches, us: 16 workers, batch 128, 3072-2048-10, objective 56.9 / 52.5, gradients 162 / 150, fused step 314 /
 // 309; batch 100, 3072-2000-1000-10, gradients 286 / 260; 3072-1536-10 (151 MB) 51.7 / 48.2, 135 / 127; but 2048-1536-10 (101 MB)
 // 31.5 / 36.4, 90 / 94, batch 100, 1000-3000-10 (96 MB) 43.7 / 55.  With a second row tile the L2s are to keep them: batch 200,
-// 3072-2000-1000-10, 114 / 119, fused step 685 / 708.
-bool streams(const GemmArgs& g, int W, int rows) { return g.M <= rows && 2.0 * W * (double)g.N * g.K > 120e6; }
+// 3072-2000-1000-10, 114 / 119, fused step 685 / 708.  A fused update's own streams have pushed out smaller weights too: batch 128,
+// 3072-1024-10 (101 MB), fused step with momentum 262.2 / 260.6.
+bool streams(const GemmArgs& g, int W, int rows) { return g.M <= rows && 2.0 * W * (double)g.N * g.K > (g.updated ? 95e6 : 120e6); }
 
 template <int BM, int BN, int WVM, int WVN, int ST, bool ANY>
 void launch_forward(const GemmArgs& g, int W, hipStream_t s)

@@ -629,6 +629,7 @@ hipError_t launch_mlp_forward(const uint16_t* xb, const float* x, float* g, floa
         a.bias = bias; a.sBias = ld;
         if (k < L) {
             a.out = sc16 + p.h[k]; a.sOut = sW16; a.ldout = dout;
+            a.updated = backward && !g;
             if (!try_mfma<false, EPI_FWD>(a, W, s) && !launch_gemm_direct_any(a, W, EPI_FWD, s)) launch_gemm_ragged(a, W, EPI_FWD, s);
         } else if (dout <= 64) {                               // logits, loss and output delta in one launch
             const int tiles = (B + 31) / 32;
