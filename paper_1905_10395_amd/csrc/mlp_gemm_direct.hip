@@ -6,20 +6,22 @@
 //
 // What bounds these products is what reaches the compute units (a batch of 128 to 256 rows per weight: 17 TB/s of
 // tiles out of L2 measured without the products), and for the largest the chip's power limit: 256 x 4096 x 4096, 8
-// workers, takes 68 us on zeros and 80 us on normal values, at 1.8 to 2.1 instead of 2.4 GHz, in every tile and wavefront
-// shape.  Loads that go straight to LDS need no registers, so three K steps or more are under way per workgroup, and no vector
-// instructions to store them.  A wavefront's load writes 64 consecutive 16-byte pieces, so rows cannot be padded: the
-// pieces of a row are stored in another order instead (exclusive or with half the row number: two rows fill the banks
-// once), which spreads the fragment reads over all banks (with the row number itself half of the LDS cycles were conflicts).  Fragments are read a quarter step ahead of their products, across the barrier too.
+// workers, takes 68 us on zeros and 80 us on normal values, at 1.8 to 2.1 instead of 2.4 GHz, in every tile and
+// wavefront shape.  Loads that go straight to LDS need no registers, so three K steps or more are under way per
+// workgroup, and no vector instructions to store them.  A wavefront's load writes 64 consecutive 16-byte pieces, so
+// rows cannot be padded: the pieces of a row are stored in another order instead (exclusive or with half the row
+// number: two rows fill the banks once), which spreads the fragment reads over all banks (with the row number itself
+// half of the LDS cycles were conflicts).  Fragments are read a quarter step ahead of their products, across the
+// barrier too.
 //
 // ANY: any M and N, K a multiple of 8.  Row numbers past the end are clamped to the last row, pieces past the end of a
 // row to its last piece (fragments past K become zeros in the last step).  Sums are carried as in the any-shape kernel's
 // 128-row tiles, in double after every eight matrix instructions, bit for bit.  !ANY: whole tiles, one fp32 chain.
 //
-// Measured, us, through registers -> straight to LDS: objective of 3072-1024-10, 16 workers, batch 128: 42 -> 32;
+// Measured, us, through registers -> straight to LDS: objective of 3072-1024-10, 16 workers, batch 128: 38 -> 32;
 // gradients of 1024-2048-2048-10, 8 workers, batch 256: 169 -> 159; 256-512-512-10, 8 workers, batch 128: 46.5 -> 43.
-// ANY: forward 500 x 1024 x 3072, 16 workers, 95 -> 77, 128 x 1912 x 1208 35 -> 23; d-input 200 x 1912 x 1208 72 -> 43,
-// 256 x 1000 x 784 32 -> 20.
+// ANY, kernels alone: forward 500 x 1024 x 3072, 16 workers, 91 -> 76, 128 x 1912 x 1208 34 -> 22; d-input 200 x 1912 x
+// 1208 72 -> 44, 256 x 784 x 1000 34 -> 22.
 #include <type_traits>
 
 #include "mlp_common.h"

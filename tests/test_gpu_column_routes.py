@@ -1,7 +1,9 @@
 """The ways through the rows of the one-launch update at their edges: groups of one and iterations of Algorithm 1 whose
 rows stream whatever group they are in (batches of 8 rows at one column per thread, of 4 at two or four), iterations with up
-to 4 or 8 rows in registers, elastic averaging with up to 8, 16 or 32, columns left over for the last workgroup.  Bit for bit
-against row streams and against the calls that a step is made of; elastic averaging against the oracle."""
+to 4 or 8 rows in registers, iterations and pulls walked group by group, elastic averaging with up to 8, 16 or 32 rows in
+registers, columns left over for the last workgroup.  Steps bit for bit against row streams; iterations bit for bit against
+the calls that they are made of, whose pulls go another way or the same by size, and like pulls against the oracle; elastic
+averaging against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -90,9 +92,9 @@ def test_easgd_without_momentum(W, G, P, ld):
     easgd.test_easgd_update_matches_oracle(W, G, P, ld, 0.0, 0, 1e-4)
 
 
-# Algorithm 1's iterations whose pull is walked group by group behind the update (a few of large groups communicate; pairs above
-# 150 MB, or 70 with half of them; with momentum between 30 and 95 MB; a group of 5 to 8 with momentum), those beside them that are not, and many
-# groups of one of which few communicate (row streams: more than 24, or more than 16 above 30 MB)
+# Algorithm 1's iterations whose pull is walked group by group behind the update (a few of large groups communicate; pairs
+# above 150 MB, or 70 with half of them; with momentum between 30 and 95 MB; a group of 5 to 8 with momentum), those beside them
+# that are not, and many groups of one of which few communicate (row streams: more than 24, or more than 16 above 30 MB)
 @pytest.mark.parametrize("mu", [0.0, 0.9])
 @pytest.mark.parametrize("W,G,P,ld", [(8, 1, 1031, 1031), (8, 2, 301, 320), (4, 2, 301, 320), (12, 3, 1031, 1031), (16, 4, 100_003, 100_032), (24, 4, 301, 320),
                                       (16, 8, 800_003, 800_032), (28, 28, 5003, 5003), (20, 20, 130_003, 130_048)])

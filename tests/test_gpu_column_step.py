@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 # W, group offsets, P, ld
 SHAPES = [
     (1, [0, 1], 1, 1),                               # row streams: one worker, one column
-    (2, [0, 1, 2], 255, 256),                        # row streams: groups of one
+    (2, [0, 1, 2], 255, 256),                        # groups of one: one launch where something is re-selected
     (2, [0, 2], 1, 1),                               # one column
     (4, [0, 4], 255, 256),                           # one thread short of a workgroup
     (2, [0, 2], 257, 257),                           # one thread past it, odd stride: one column per thread
@@ -125,8 +125,8 @@ def test_ties_nan_and_infinite_losses_select_alike():
 
 @pytest.mark.parametrize("W,P,ld", [(5, 1030, 1088), (16, 1030, 1088), (17, 1030, 1088), (16, 60_001, 60_032), (17, 240_001, 240_064), (20, 220_003, 220_032)])
 def test_easgd_both_routes(W, P, ld):
-    """Center and rows, one launch (up to 16 workers; more between 80 and 250 MB; streaming accesses at 60 001 columns) or
-    two: center bit-exact (one order of the sum, one rounding)."""
+    """Center and rows, one launch (up to 32 workers and 650 MB; streaming accesses from 16 MB on) or two: center bit-exact
+    (one order of the sum, one rounding)."""
     x0, g0, _ = wl.stress_state(W, P, ld, seed=W)
     pr = Pair(x0, [0, W], P=P, momentum=0.9)
     c0 = x0[0].astype(np.float32).copy()
