@@ -13,11 +13,20 @@
 // written per update, 450 for groups of one and Algorithm 1, 650 for elastic averaging (the caller's rules), the saved
 // launches weigh more.  Measured, whole lsgd_step on external
 // gradients, row streams -> this kernel, us: 4 x 1003 14.6 -> 4.5; 12 x 271 117 with momentum and kept leaders
-// 24.6 -> 16.5; 16 x 250 000 with momentum 30.0 -> 17.3;
+// 24.6 -> 15.3; 16 x 250 000 with momentum 30.0 -> 17.3;
 // 16 x 1 250 000 without 62.5 -> 41.5; elastic averaging, 16 x 1 250 000 with momentum 85.3 -> 73.3.
 //
+// What bounds a small call is not memory but one wavefront's instructions, 2.7 ns each, and the loads that it waits for
+// one after the other.  So what the selection reads is asked for first, all at once and by the wavefront that selects
+// alone; the selection scans by data-parallel-primitive moves; and where rows are held in registers a row is one addition
+// to a 32-bit offset.  Against a chain of dependent loads, scans by LDS shuffles and 64-bit row addresses: 4 x 1003 4.5 ->
+// 3.6 us, 16 in 4 groups x 40 001 with momentum 10.1 -> 6.5.
+//
 // The ways through the rows (launch_column_step), by what a thread has to wait for:
-//   the update of groups of several workers     group by group, the next rows' loads under way (update_columns)
+//   the update of groups of several workers     every row in registers, leaders found in an LDS copy (held_update); nothing but
+//                                               the selection is waited for twice: 12 in 3 groups x 271 117 with momentum 18.2 ->
+//                                               15.4, pairs, 16 x 140 001, 18.5 -> 8.7
+//   ... of more than 16 workers beyond 100 MB   group by group, the next rows' loads under way (update_columns)
 //   ... of groups of one, and Algorithm 1's     one pass over all rows, two batches ahead, whatever group they are in
 //   iterations of more than 8 workers           (stream_columns): groups one after the other would leave a single row in
 //                                               flight, and a communication pull behind the update would read x again.
@@ -49,6 +58,8 @@ struct ColumnDev {
     int select;                  // 0: leaders as recorded, 1: selection before the update, 2: after it
     uint64_t sel, cap;           // groups re-selected now / captured by the next stage
     int selG, capG;
+    uint32_t pitch;              // bytes from row to row, for the ways that hold every row
+    int group_inv;               // 65536 / rows of a group, rounded up, where all groups are alike, else 0
     const float* losses;
     float* losses_out;           // the population's own loss buffer when the losses come from elsewhere, else NULL
     LossParts parts;             // partial sums to finish instead
@@ -62,6 +73,7 @@ struct Leaders {
     int lead[kColumnMaxWorkers]; // of each group
     int fresh[kColumnMaxWorkers];
     int gl, freshG;
+    alignas(16) int row[kColumnMaxWorkers];  // kUpdateRegs: a word per row (row_word)
 };
 
 // A few rows of one group.
@@ -98,15 +110,16 @@ __device__ __forceinline__ void update_columns(const ColumnDev& s, const Leaders
     using V = typename Vec<VEC>::type;
     const PullDev& a = s.a;
     const bool pullL = a.lamL != 0.0f, pullG = a.lamG != 0.0f;
-    const bool exempt = (a.flags & LSGD_LEADER_EXEMPT) != 0;
+    const bool exempt = !CENTER && (a.flags & LSGD_LEADER_EXEMPT) != 0;
     const Coef c = make_coef<V>(a);
     // a re-selected leader's row belongs to the group that reads it, and the global leader's is read before any row
     // is written: both are as they were
     auto local_leader = [&](int j) { return ld_vec<VEC>((L.fresh[j] ? a.x + (int64_t)L.lead[j] * a.ld : a.Z + (int64_t)j * a.ld) + col); };
     V zg = zero_of(V()), zl = zero_of(V());
-    if (pullG) zg = ld_vec<VEC>((L.freshG ? a.x + (int64_t)L.gl * a.ld : a.Z + (int64_t)a.G * a.ld) + col);
+    const bool freshG = !CENTER && L.freshG;             // (elastic averaging pulls to the center and has no leaders)
+    if (pullG) zg = ld_vec<VEC>((freshG ? a.x + (int64_t)L.gl * a.ld : a.Z + (int64_t)a.G * a.ld) + col);
     if (pullL) zl = local_leader(0);
-    if (pullG && L.freshG && a.Z) st_vec(a.Z + (int64_t)a.G * a.ld + col, zg);
+    if (pullG && freshG && a.Z) st_vec(a.Z + (int64_t)a.G * a.ld + col, zg);
     RowBatch<VEC> cur = first, next;
     const int passes = CENTER && !pullL ? 1 : a.G;
     int j = 0, i = 0, end = pass_end<CENTER>(a, 0);
@@ -140,12 +153,25 @@ __device__ __forceinline__ void update_columns(const ColumnDev& s, const Leaders
 }
 
 // A thread's columns of row i of p: the row's address is the same in every lane, the column's is an offset of 32 bits
-// (launch_column_step refuses more), which keeps addresses out of the vector registers.
+// (launch_column_step refuses more), which keeps addresses out of the vector registers.  (Bytes are added to a pointer:
+// through an integer the compiler loses that it is global memory, and its flat loads are waited for with every LDS
+// access and scalar load.)
 template <class T>
 __device__ __forceinline__ T* at(T* p, int64_t ld, int i, uint32_t col)
 {
-    T* const row = p + (int64_t)i * ld;
-    return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(row) + (uintptr_t)(col * (uint32_t)sizeof(T)));
+    using B = std::conditional_t<std::is_const_v<T>, const char, char>;
+    return reinterpret_cast<T*>(reinterpret_cast<B*>(p + (int64_t)i * ld) + col * (uint32_t)sizeof(T));
+}
+
+// The same where whole matrices span less than 4 GB (launch_column_step sees to it): the matrix's address is the same for
+// all of a call's accesses, a row is one addition to a lane's offset in bytes.  (With 64-bit row addresses a row of an
+// update took 30 scalar instructions, and a small call is the instructions of one wavefront.)
+template <class T>
+__device__ __forceinline__ T* at(T* p, uint32_t off)
+{
+    static_assert(sizeof(T) == 4 || sizeof(T) == 2, "");
+    using B = std::conditional_t<std::is_const_v<T>, const char, char>;
+    return reinterpret_cast<T*>(reinterpret_cast<B*>(p) + (sizeof(T) == 4 ? off : off / 2));
 }
 
 // Every row's values at a thread's columns.
@@ -154,7 +180,32 @@ struct Rows {
     typename Vec<VEC>::type x[NR], g[NR], m[NR];
 };
 
-template <int VEC, int KIND, bool NT, int NR>
+template <int VEC, int KIND, bool NT>
+__device__ __forceinline__ void load_row(const ColumnDev& s, int i, uint32_t col, typename Vec<VEC>::type& x, typename Vec<VEC>::type& g,
+                                         typename Vec<VEC>::type& m)
+{
+    using V = typename Vec<VEC>::type;
+    const PullDev& a = s.a;
+    x = NT ? ld_stream<VEC>(at(a.x, a.ld, i, col)) : ld_vec<VEC>(at(a.x, a.ld, i, col));
+    g = s.update ? ld_stream<VEC>(at(a.g, a.ld, i, col)) : zero_of(V());
+    m = (KIND == 1) ? (NT ? ld_stream<VEC>(at(a.m, a.ld, i, col)) : ld_vec<VEC>(at(a.m, a.ld, i, col))) : zero_of(V());
+}
+
+// Row u of p, by either way of addressing.
+template <bool LONG, class T>
+__device__ __forceinline__ T* row_at(const ColumnDev& s, T* p, int u, uint32_t col)
+{
+    if constexpr (LONG) return at(p, s.a.ld, u, col);
+    else return at(p, col * 4u + (uint32_t)u * s.pitch);
+}
+// Loads one behind the other, 64 clocks apart and by the longer addresses, where requests for eight rows in one go were
+// slower, us, before / in one go / so: Algorithm 1's iteration without momentum, 8 workers in 2 groups x 1 250 001 26.5 /
+// 30.3 / 26.9, groups of one 35.1 / 40.5 / 35.7, one group x 40 001 6.3 / 6.9 / 6.2.  (Two columns per thread: x 600 001
+// 16.1 / 14.6 / 17.5.)
+template <int VEC, int KIND, int NR> constexpr bool kPaced = KIND == 0 && NR == 8 && VEC != 2;
+
+// UPDATE: gradients and momentum too (asked for each row's, a call that may have none takes twice the time).
+template <int VEC, int KIND, bool NT, bool PACED, bool UPDATE, int NR>
 __device__ __forceinline__ void load_rows(const ColumnDev& s, uint32_t col, Rows<VEC, NR>& r)
 {
     using V = typename Vec<VEC>::type;
@@ -162,9 +213,11 @@ __device__ __forceinline__ void load_rows(const ColumnDev& s, uint32_t col, Rows
 #pragma unroll
     for (int u = 0; u < NR; ++u)
         if (u < a.W) {
-            r.x[u] = NT ? ld_stream<VEC>(at(a.x, a.ld, u, col)) : ld_vec<VEC>(at(a.x, a.ld, u, col));
-            r.g[u] = s.update ? ld_stream<VEC>(at(a.g, a.ld, u, col)) : zero_of(V());
-            r.m[u] = (KIND == 1) ? (NT ? ld_stream<VEC>(at(a.m, a.ld, u, col)) : ld_vec<VEC>(at(a.m, a.ld, u, col))) : zero_of(V());
+            if (PACED && u) __builtin_amdgcn_s_sleep(1);
+            r.x[u] = NT ? ld_stream<VEC>(row_at<PACED>(s, a.x, u, col)) : ld_vec<VEC>(row_at<PACED>(s, a.x, u, col));
+            r.g[u] = r.m[u] = zero_of(V());
+            if (UPDATE) r.g[u] = ld_stream<VEC>(row_at<PACED>(s, a.g, u, col));
+            if (UPDATE && KIND == 1) r.m[u] = NT ? ld_stream<VEC>(row_at<PACED>(s, a.m, u, col)) : ld_vec<VEC>(row_at<PACED>(s, a.m, u, col));
         }
 }
 
@@ -179,17 +232,6 @@ __device__ __forceinline__ typename Vec<VEC>::type row_of(const Rows<VEC, NR>& r
         v = u == i ? at : v;
     }
     return v;
-}
-
-template <int VEC, int KIND, bool NT>
-__device__ __forceinline__ void load_row(const ColumnDev& s, int i, uint32_t col, typename Vec<VEC>::type& x, typename Vec<VEC>::type& g,
-                                         typename Vec<VEC>::type& m)
-{
-    using V = typename Vec<VEC>::type;
-    const PullDev& a = s.a;
-    x = NT ? ld_stream<VEC>(at(a.x, a.ld, i, col)) : ld_vec<VEC>(at(a.x, a.ld, i, col));
-    g = s.update ? ld_stream<VEC>(at(a.g, a.ld, i, col)) : zero_of(V());
-    m = (KIND == 1) ? (NT ? ld_stream<VEC>(at(a.m, a.ld, i, col)) : ld_vec<VEC>(at(a.m, a.ld, i, col))) : zero_of(V());
 }
 
 template <int VEC, int KIND, bool NT>
@@ -304,8 +346,106 @@ __device__ __forceinline__ void stream_columns(const ColumnDev& s, const Leaders
     }
 }
 
-// Algorithm 1's iteration, or a communication pull alone, with every row in registers.  The update's leaders are kept copies.
+// The update with every row in registers.  Nothing that is loaded waits for the selection: rows and kept copies are on
+// their way before it, and a leader is then found among them by its number, in an LDS copy of the thread's own columns
+// (rows 0 .. W-1, behind them the groups' kept copies).  No barrier for that: a thread reads only what it wrote.
+// What a row has to know is one word: its local leader's place in that copy, its group, and
+constexpr int kRowCaptureL = 1 << 8, kRowCaptureG = 1 << 9;     // it is a leader to be captured
+constexpr int kRowExemptL = 1 << 10, kRowExemptG = 1 << 11;     // it is a leader that takes no pull
+constexpr int kRowGroupShift = 16;
+
+template <int NR> constexpr int kHeldGroups = NR / 2;           // at most
+
+template <int VEC, int NR>
+struct HeldRows {
+    typename Vec<VEC>::type x[NR], g[NR], m[NR], kept[kHeldGroups<NR>], keptG;
+};
+
 template <int VEC, int KIND, bool NT, int NR>
+__device__ __forceinline__ void held_load(const ColumnDev& s, uint32_t off, HeldRows<VEC, NR>& r)
+{
+    using V = typename Vec<VEC>::type;
+    const PullDev& a = s.a;
+    uint32_t o = off;                                    // (no branch around a load: past the end the last row again)
+#pragma unroll
+    for (int u = 0; u < NR; ++u) {
+        r.x[u] = NT ? ld_stream<VEC>(at(a.x, o)) : ld_vec<VEC>(at(a.x, o));
+        r.g[u] = ld_stream<VEC>(at(a.g, o));
+        r.m[u] = (KIND == 1) ? (NT ? ld_stream<VEC>(at(a.m, o)) : ld_vec<VEC>(at(a.m, o))) : zero_of(V());
+        o += u + 1 < a.W ? s.pitch : 0u;
+    }
+    if (a.lamL != 0.0f) {
+#pragma unroll
+        for (int j = 0; j < kHeldGroups<NR>; ++j)
+            if (j < a.G && !((s.cap >> j) & 1ull)) r.kept[j] = ld_vec<VEC>(at(a.Z, off + (uint32_t)j * s.pitch));
+    }
+    if (a.lamG != 0.0f && !s.capG) r.keptG = ld_vec<VEC>(at(a.Z, off + (uint32_t)a.G * s.pitch));
+}
+
+template <int VEC, int KIND, bool NT, int NR>
+__device__ __forceinline__ void held_update(const ColumnDev& s, const Leaders& L, uint32_t off, HeldRows<VEC, NR>& r)
+{
+    using V = typename Vec<VEC>::type;
+    const PullDev& a = s.a;
+    extern __shared__ __align__(16) char held_lds[];
+    V* const own = reinterpret_cast<V*>(held_lds) + threadIdx.x;
+    const bool pullL = a.lamL != 0.0f, pullG = a.lamG != 0.0f;
+    const Coef c = make_coef<V>(a);
+#pragma unroll
+    for (int u = 0; u < NR; ++u)
+        if (u < a.W) own[u * kThreads] = r.x[u];
+    if (pullL) {
+#pragma unroll
+        for (int j = 0; j < kHeldGroups<NR>; ++j)
+            if (j < a.G && !((s.cap >> j) & 1ull)) own[(a.W + j) * kThreads] = r.kept[j];
+    }
+    V zg = zero_of(V());
+    if (pullG) zg = s.capG ? own[__builtin_amdgcn_readfirstlane(L.gl) * kThreads] : r.keptG;
+    uint32_t o = off;
+#pragma unroll
+    for (int i = 0; i < NR; i += 4) {
+        if (i >= a.W) break;
+        const int4 words = *reinterpret_cast<const int4*>(L.row + i);
+        const int word[4] = {words.x, words.y, words.z, words.w};
+        int row[4];
+        V zl[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            row[u] = __builtin_amdgcn_readfirstlane(word[u]);
+            zl[u] = pullL ? own[(row[u] & 0xff) * kThreads] : zero_of(V());
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v, o += s.pitch) {
+            const int u = i + v;
+            if (u >= a.W) break;
+            Coef cr = c;
+            if (row[v] & (kRowCaptureL | kRowCaptureG | kRowExemptL | kRowExemptG)) {
+                if (row[v] & kRowCaptureL) st_vec(at(a.Z, off + (uint32_t)(row[v] >> kRowGroupShift) * s.pitch), r.x[u]);
+                if (row[v] & kRowCaptureG) st_vec(at(a.Z, off + (uint32_t)a.G * s.pitch), r.x[u]);
+                if (row[v] & kRowExemptL) cr.cL = 0.0f;
+                if (row[v] & kRowExemptG) cr.cG = 0.0f;
+            }
+            update_vec<KIND, V>(r.x[u], r.g[u], r.m[u], zl[v], zg, cr);
+            if (NT) st_stream(at(a.x, o), r.x[u]); else st_vec(at(a.x, o), r.x[u]);
+            if (KIND == 1) { if (NT) st_stream(at(a.m, o), r.m[u]); else st_vec(at(a.m, o), r.m[u]); }
+            if (a.xb) st_bf16(at(a.xb, o), r.x[u]);
+        }
+    }
+}
+
+// The word of row `lane`, pulled to `own`, the global leader being `gl`.
+__device__ __forceinline__ int row_word(const ColumnDev& s, int lane, int gid, int own, int gl)
+{
+    const PullDev& a = s.a;
+    const bool fresh = (s.cap >> gid) & 1ull, pullL = a.lamL != 0.0f, pullG = a.lamG != 0.0f, exempt = (a.flags & LSGD_LEADER_EXEMPT) != 0;
+    int word = (fresh ? own : a.W + gid) | gid << kRowGroupShift;
+    if (pullL && own == lane) word |= (fresh && a.Z ? kRowCaptureL : 0) | (exempt ? kRowExemptL : 0);
+    if (pullG && gl == lane) word |= (s.capG && a.Z ? kRowCaptureG : 0) | (exempt ? kRowExemptG : 0);
+    return word;
+}
+
+// Algorithm 1's iteration, or a communication pull alone, with every row in registers.  The update's leaders are kept copies.
+template <int VEC, int KIND, bool NT, bool PACED, int NR>
 __device__ __forceinline__ void regs_update(const ColumnDev& s, uint32_t col, Rows<VEC, NR>& r)
 {
     using V = typename Vec<VEC>::type;
@@ -313,9 +453,9 @@ __device__ __forceinline__ void regs_update(const ColumnDev& s, uint32_t col, Ro
     const bool pullL = a.lamL != 0.0f, pullG = a.lamG != 0.0f;
     const Coef c = make_coef<V>(a);
     V zg = zero_of(V()), zl = zero_of(V()), nzl = zero_of(V());
-    if (pullG) zg = ld_vec<VEC>(at(a.Z, a.ld, a.G, col));
-    if (pullL) zl = ld_vec<VEC>(at(a.Z, a.ld, 0, col));
-    if (pullL && a.G > 1) nzl = ld_vec<VEC>(at(a.Z, a.ld, 1, col));
+    if (pullG) zg = ld_vec<VEC>(row_at<PACED>(s, a.Z, a.G, col));
+    if (pullL) zl = ld_vec<VEC>(row_at<PACED>(s, a.Z, 0, col));
+    if (pullL && a.G > 1) nzl = ld_vec<VEC>(row_at<PACED>(s, a.Z, 1, col));
     int j = 0, end = a.offsets[1];
 #pragma unroll
     for (int u = 0; u < NR; ++u)
@@ -323,14 +463,14 @@ __device__ __forceinline__ void regs_update(const ColumnDev& s, uint32_t col, Ro
             if (u == end) {                              // the next group
                 ++j; end = a.offsets[j + 1];
                 zl = nzl;
-                if (pullL && j + 1 < a.G) nzl = ld_vec<VEC>(at(a.Z, a.ld, j + 1, col));
+                if (pullL && j + 1 < a.G) nzl = ld_vec<VEC>(row_at<PACED>(s, a.Z, j + 1, col));
             }
             update_vec<KIND, V>(r.x[u], r.g[u], r.m[u], zl, zg, c);
-            if (KIND == 1) { if (NT) st_stream(at(a.m, a.ld, u, col), r.m[u]); else st_vec(at(a.m, a.ld, u, col), r.m[u]); }
+            if (KIND == 1) { if (NT) st_stream(row_at<PACED>(s, a.m, u, col), r.m[u]); else st_vec(row_at<PACED>(s, a.m, u, col), r.m[u]); }
         }
 }
 
-template <int VEC, bool NT, int NR>
+template <int VEC, bool NT, bool PACED, int NR>
 __device__ __forceinline__ void regs_comm(const ColumnDev& s, const Leaders& L, uint32_t col, Rows<VEC, NR>& r)
 {
     using V = typename Vec<VEC>::type;
@@ -340,7 +480,7 @@ __device__ __forceinline__ void regs_comm(const ColumnDev& s, const Leaders& L, 
     V zg = zero_of(V());
     if (L.freshG) {
         zg = row_of<VEC, NR>(r, __builtin_amdgcn_readfirstlane(L.gl));
-        if (a.Z) st_vec(at(a.Z, a.ld, a.G, col), zg);
+        if (a.Z) st_vec(row_at<PACED>(s, a.Z, a.G, col), zg);
     }
     int j = -1, end = 0, lead = 0;
     bool fresh = false;
@@ -356,15 +496,15 @@ __device__ __forceinline__ void regs_comm(const ColumnDev& s, const Leaders& L, 
                 zl = zero_of(V());                       // (the last group's may be infinite: not even times zero)
                 if (fresh) {                             // (no row of the group has moved yet)
                     zl = row_of<VEC, NR>(r, lead);
-                    if (a.Z) st_vec(at(a.Z, a.ld, j, col), zl);
+                    if (a.Z) st_vec(row_at<PACED>(s, a.Z, j, col), zl);
                 }
             }
             const bool moves = (c.cL != 0.0f && !(fresh && u == lead)) || c.cG != 0.0f;   // (a leader's pull to itself is zero)
             V none = zero_of(V());
             if (moves) update_vec<2, V>(r.x[u], none, none, zl, zg, c);
             if (moves || s.update) {
-                if (NT) st_stream(at(a.x, a.ld, u, col), r.x[u]); else st_vec(at(a.x, a.ld, u, col), r.x[u]);
-                if (a.xb) st_bf16(at(a.xb, a.ld, u, col), r.x[u]);
+                if (NT) st_stream(row_at<PACED>(s, a.x, u, col), r.x[u]); else st_vec(row_at<PACED>(s, a.x, u, col), r.x[u]);
+                if (a.xb) st_bf16(row_at<PACED>(s, a.xb, u, col), r.x[u]);
             }
         }
 }
@@ -464,11 +604,11 @@ __device__ __forceinline__ void center_columns(const ColumnDev& s, int64_t col)
 
 // The same with every row's values in registers.
 template <int VEC, int KIND, bool NT, int NR>
-__device__ __forceinline__ void regs_easgd(const ColumnDev& s, uint32_t col, Rows<VEC, NR>& r)
+__device__ __forceinline__ void regs_easgd(const ColumnDev& s, uint32_t off, Rows<VEC, NR>& r)
 {
     using V = typename Vec<VEC>::type;
     const PullDev& a = s.a;
-    const V old = ld_vec<VEC>(at(s.center, 0, 0, col));
+    const V old = ld_vec<VEC>(at(s.center, off));
     V next;
     {
 #pragma clang fp contract(off)      // (1-a)*c + a*mean as two products and a sum, rounded like the plain expression
@@ -482,8 +622,8 @@ __device__ __forceinline__ void regs_easgd(const ColumnDev& s, uint32_t col, Row
                 (float)((1.0 - s.center_rate) * (double)reinterpret_cast<const float*>(&old)[v] + s.center_rate * (sum / (double)a.W));
         }
     }
-    st_vec(at(a.Z, a.ld, a.G, col), old);
-    st_vec(at(s.center, 0, 0, col), next);
+    st_vec(at(a.Z, off + (uint32_t)a.G * s.pitch), old);
+    st_vec(at(s.center, off), next);
     const Coef c = make_coef<V>(a);
     const V none = zero_of(V());
     const V zg = a.lamG != 0.0f ? old : none;
@@ -491,26 +631,53 @@ __device__ __forceinline__ void regs_easgd(const ColumnDev& s, uint32_t col, Row
     for (int u = 0; u < NR; ++u)
         if (u < a.W) {
             update_vec<KIND, V>(r.x[u], r.g[u], r.m[u], none, zg, c);
-            if (NT) st_stream(at(a.x, a.ld, u, col), r.x[u]); else st_vec(at(a.x, a.ld, u, col), r.x[u]);
-            if (KIND == 1) { if (NT) st_stream(at(a.m, a.ld, u, col), r.m[u]); else st_vec(at(a.m, a.ld, u, col), r.m[u]); }
-            if (a.xb) st_bf16(at(a.xb, a.ld, u, col), r.x[u]);
+            if (NT) st_stream(at(a.x, off + (uint32_t)u * s.pitch), r.x[u]); else st_vec(at(a.x, off + (uint32_t)u * s.pitch), r.x[u]);
+            if (KIND == 1) { if (NT) st_stream(at(a.m, off + (uint32_t)u * s.pitch), r.m[u]); else st_vec(at(a.m, off + (uint32_t)u * s.pitch), r.m[u]); }
+            if (a.xb) st_bf16(at(a.xb, off + (uint32_t)u * s.pitch), r.x[u]);
         }
 }
 
+// What the selection reads, requested before anything else: loads return in order, so that it waits for none of the rows'.
+struct Pick {
+    float loss;                  // of row `lane`
+    int gid;                     // its group
+    int lead, fresh;             // of group `lane`, as recorded
+    int gl, freshG;
+    uint64_t part[4];            // partial sums of the losses, as they lie in memory
+};
+
 // The losses from their partial sums: a team of 4 to 256 lanes per worker, in double, in an order that depends on the
 // number of workers alone.  All kThreads threads; at most kColumnMaxWorkers workers.
-__device__ __forceinline__ void finish_losses(const LossParts& parts, int W, float* losses)
+__device__ __forceinline__ int parts_team(int W)
 {
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
     int team = kThreads;
     while (team * W > kThreads) team >>= 1;
-    const int w = tid / team, l = tid % team;
+    return team;
+}
+__device__ __forceinline__ void load_parts(const LossParts& parts, int W, uint64_t (&part)[4], int first)
+{
+    const int team = parts_team(W), w = (int)threadIdx.x / team, l = first + (int)threadIdx.x % team;
+    const int64_t row = (w < W ? w : 0) * parts.stride;
+    if (parts.sums64) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) part[u] = reinterpret_cast<const uint64_t*>(parts.sums64)[row + (l + u * team < parts.n ? l + u * team : 0)];
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) part[u] = reinterpret_cast<const uint32_t*>(parts.sums)[row + (l + u * team < parts.n ? l + u * team : 0)];
+    }
+}
+__device__ __forceinline__ void finish_losses(const LossParts& parts, int W, uint64_t (&part)[4], float* losses)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), team = parts_team(W), w = tid / team, l = tid % team;
     double acc = 0.0;
-    if (w < W)
-        for (int i = l; i < parts.n; i += team) {
-            const int64_t at = (int64_t)w * parts.stride + i;
-            acc += parts.sums64 ? parts.sums64[at] : (double)parts.sums[at];
+    for (int first = 0; first < parts.n; first += 4 * team) {
+        if (first) load_parts(parts, W, part, first);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double v = parts.sums64 ? __longlong_as_double((long long)part[u]) : (double)__uint_as_float((uint32_t)part[u]);
+            if (w < W && first + l + u * team < parts.n) acc += v;
         }
+    }
     if (team > kWave) {                                  // one or two workers
         __shared__ double cross[kThreads / kWave];
 #pragma unroll
@@ -525,54 +692,112 @@ __device__ __forceinline__ void finish_losses(const LossParts& parts, int W, flo
     if (w < W && l == 0) losses[w] = (float)(parts.c * acc / (double)parts.div);
 }
 
-__global__ __launch_bounds__(kThreads) void loss_parts_kernel(LossParts parts, int W, float* losses) { finish_losses(parts, W, losses); }
+__global__ __launch_bounds__(kThreads) void loss_parts_kernel(LossParts parts, int W, float* losses)
+{
+    uint64_t part[4];
+    load_parts(parts, W, part, 0);
+    finish_losses(parts, W, part, losses);
+}
+
+// By the wavefront that selects, and no more than it needs: every workgroup asks for the same few lines, which holds up
+// the rows' loads behind them.  Leaders as recorded count where a call does not select, or captures one that an earlier call
+// selected, or exempts kept leaders, and for what the first workgroup records.
+__device__ __forceinline__ void load_pick(const ColumnDev& s, Pick& p)
+{
+    if (s.parts.n > 0) load_parts(s.parts, s.a.W, p.part, 0);
+    if (threadIdx.x >= kWave) return;
+    const int lane = threadIdx.x, W = s.a.W, G = s.a.G;
+    const int i = lane < W ? lane : W - 1, j = lane < G ? lane : G - 1;
+    p.loss = 0.f;
+    if (s.select && s.parts.n == 0) p.loss = s.losses[i];
+    if (s.group_inv) p.gid = (i * s.group_inv) >> 16;
+    else p.gid = s.a.group_of[i];
+    p.lead = p.gl = p.fresh = p.freshG = 0;
+    if (blockIdx.x == 0 || !s.select || (s.cap & ~s.sel) || (s.capG && !s.selG) || (s.a.flags & LSGD_LEADER_EXEMPT)) {
+        p.lead = s.a.lead[j];
+        p.gl = s.a.glead[0];
+    }
+    if (s.a.use_refreshed && s.select != 1) {
+        p.fresh = s.a.refreshed[j];
+        p.freshG = s.a.refreshed[G];
+    }
+}
+
+// One step of a segmented minimum scan: the key of the lane that CTRL names counts if it is of the same group.  Lanes
+// that have none keep theirs (ROWS: the rows of 16 lanes that take part).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t scan_min(uint32_t key, int gid)
+{
+    const uint32_t ok = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)key, CTRL, ROWS, 0xF, false);
+    const int og = __builtin_amdgcn_update_dpp(-1, gid, CTRL, ROWS, 0xF, false);
+    return og == gid && ok < key ? ok : key;
+}
+
+// Every row's local leader, in its lane, and the global leader: selected from the losses, or as recorded.  The smallest
+// key of a group stands in its last lane after a scan (keys are the losses alone: of equal ones the lowest lane is taken),
+// by data-parallel-primitive moves: a scan by LDS shuffles waits for twelve of them one after the other.
+__device__ __forceinline__ void pick_leaders(const ColumnDev& s, const Pick& p, float loss, int& own, int& gl, bool& starts)
+{
+    const int lane = threadIdx.x & (kWave - 1), W = s.a.W;
+    const bool row = lane < W;
+    const uint32_t key = row ? (uint32_t)(loss_key(loss, 0) >> 32) : ~0u;
+    auto scan = [&](uint32_t v, int gid) {
+        v = scan_min<0x111, 0xF>(v, gid);                // row_shr:1, 2, 4, 8
+        v = scan_min<0x112, 0xF>(v, gid);
+        v = scan_min<0x114, 0xF>(v, gid);
+        v = scan_min<0x118, 0xF>(v, gid);
+        v = scan_min<0x142, 0xA>(v, gid);                // lane 15 of a row to the row behind it
+        return scan_min<0x143, 0xC>(v, gid);             // lane 31 to the upper half
+    };
+    const int before = __builtin_amdgcn_update_dpp(-1, p.gid, 0x138, 0xF, 0xF, false);      // wave_shr:1
+    starts = row && before != p.gid;
+    const uint64_t lanes = ~0ull >> (kWave - W), starting = __ballot(starts);
+    const int start = kWave - 1 - __builtin_clzll((starting & (~0ull >> (kWave - 1 - lane))) | 1ull);
+    const uint64_t later = ((starting | ~lanes) >> lane) >> 1;
+    const int last = later ? lane + __builtin_ctzll(later) : kWave - 1;
+    const uint32_t seg = scan(key, row ? p.gid : -2), all = scan(key, 0);
+    // (no branch from here on: behind one that only rows take, lane 63 would not have the scan's last step)
+    const uint32_t least = (uint32_t)__builtin_amdgcn_ds_bpermute(last * 4, (int)seg);
+    const uint32_t leastG = (uint32_t)__builtin_amdgcn_readlane((int)all, kWave - 1);
+    const uint64_t best = __ballot(key == least) & lanes, bestG = __ballot(key == leastG) & lanes;
+    const int picked = start + __builtin_ctzll((best >> start) | (1ull << (kWave - 1)));
+    const int recorded = __builtin_amdgcn_ds_bpermute(p.gid * 4, p.lead);
+    own = s.select && ((s.sel >> p.gid) & 1ull) ? picked : recorded;
+    gl = s.select && s.selG ? __builtin_ctzll(bestG) : p.gl;
+}
 
 // Leaders as recorded by earlier calls (now) and, when the call selects, as they stand after the selection (chosen);
 // the first workgroup records the latter, and the losses.  All threads; ends behind a barrier.
-__device__ __forceinline__ void choose_leaders(const ColumnDev& s, Leaders& now, Leaders& chosen)
+template <bool WORDS = false>
+__device__ __forceinline__ void choose_leaders(const ColumnDev& s, Pick& p, Leaders& now, Leaders& chosen)
 {
     __shared__ float loss_s[kColumnMaxWorkers];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int W = s.a.W, G = s.a.G;
     if (s.parts.n > 0) {                                 // every workgroup adds up the partial sums itself
-        finish_losses(s.parts, W, loss_s);
+        finish_losses(s.parts, W, p.part, loss_s);
         __syncthreads();
     }
     if (tid < kWave) {
         if (lane < G) {                                  // as recorded by earlier calls
-            now.lead[lane] = s.a.lead[lane];
-            now.fresh[lane] = s.a.use_refreshed ? s.a.refreshed[lane] : 0;
+            now.lead[lane] = p.lead;
+            now.fresh[lane] = p.fresh;
         }
         if (lane == 0) {
-            now.gl = s.a.glead[0];
-            now.freshG = s.a.use_refreshed ? s.a.refreshed[G] : 0;
+            now.gl = p.gl;
+            now.freshG = p.freshG;
         }
         if (s.select) {
-            uint64_t key = ~0ull;
-            int gid = -1;
-            if (lane < W) {
-                key = loss_key(s.parts.n > 0 ? loss_s[lane] : s.losses[lane], lane);
-                gid = s.a.group_of[lane];
-            }
-            uint64_t seg = key;                          // segmented inclusive minimum: keys of the lane's own group only
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) {
-                const uint64_t ok = shfl_up_u64(seg, d);
-                const int og = __shfl_up(gid, d, kWave);
-                if (lane >= d && og == gid && ok < seg) seg = ok;
-            }
-            const uint64_t all = wave_min_u64(key);
-            const int next_gid = __shfl_down(gid, 1, kWave);
-            if (lane < G) {
-                chosen.lead[lane] = now.lead[lane];
-                chosen.fresh[lane] = (int)((s.cap >> lane) & 1ull);
-            }
+            int own, gl;
+            bool starts;
+            pick_leaders(s, p, s.parts.n > 0 ? loss_s[lane < W ? lane : 0] : p.loss, own, gl, starts);
+            if (starts) chosen.lead[p.gid] = own;
+            if (WORDS) chosen.row[lane] = lane < W ? row_word(s, lane, p.gid, own, gl) : 0;
+            if (lane < G) chosen.fresh[lane] = (int)((s.cap >> lane) & 1ull);
             if (lane == 0) {
-                chosen.gl = s.selG ? (int32_t)(uint32_t)all : now.gl;
+                chosen.gl = gl;
                 chosen.freshG = s.capG;
             }
-            __builtin_amdgcn_wave_barrier();
-            if (lane < W && (lane == W - 1 || next_gid != gid) && ((s.sel >> gid) & 1ull)) chosen.lead[gid] = (int32_t)(uint32_t)seg;
         }
     }
     __syncthreads();
@@ -587,7 +812,7 @@ __device__ __forceinline__ void choose_leaders(const ColumnDev& s, Leaders& now,
             s.refreshed[G] = chosen.freshG;
         }
         if (tid < W) {
-            const int j = s.a.group_of[tid];
+            const int j = p.gid;
             RowPlan r;
             r.ll = chosen.lead[j]; r.gl = chosen.gl; r.freshL = chosen.fresh[j]; r.freshG = chosen.freshG; r.j = j;
             r.pad[0] = r.pad[1] = r.pad[2] = 0;
@@ -602,7 +827,9 @@ template <int VEC>
 __global__ __launch_bounds__(kThreads) void capture_kernel(ColumnDev s)
 {
     __shared__ Leaders now, chosen;
-    choose_leaders(s, now, chosen);
+    Pick pick;
+    load_pick(s, pick);
+    choose_leaders(s, pick, now, chosen);
     const Leaders& L = s.select ? chosen : now;
     for (int64_t col = s.a.col0 + ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VEC; col < s.a.col1;
          col += (int64_t)gridDim.x * kThreads * VEC) {
@@ -612,7 +839,7 @@ __global__ __launch_bounds__(kThreads) void capture_kernel(ColumnDev s)
     }
 }
 
-enum { kUpdate, kUpdateOnes, kComm, kCommRegs, kCenter, kCenterRegs, kPull, kUpdatePull };
+enum { kUpdate, kUpdateOnes, kComm, kCommRegs, kCenter, kCenterRegs, kPull, kUpdatePull, kUpdateRegs };
 
 // What one thread does at its columns.  Loads are under way during the selection.  NR: rows in registers (*Regs).
 template <int VEC, int KIND, bool NT, int MODE, int NR>
@@ -620,17 +847,25 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
 {
     const Leaders& before = s.select == 1 ? chosen : now;
     const Leaders& after = s.select ? chosen : now;
+    Pick pick;
+    if ((MODE != kCenter && MODE != kCenterRegs) || blockIdx.x == 0) load_pick(s, pick);
     if constexpr (MODE == kUpdate || MODE == kCenter || MODE == kUpdatePull) {
         constexpr bool CENTER = MODE == kCenter;
         RowBatch<VEC> first;
         if (live) load_rows<VEC, KIND, NT>(s.a, 0, pass_end<CENTER>(s.a, 0), col, first);
-        choose_leaders(s, now, chosen);
+        if (!CENTER || blockIdx.x == 0) choose_leaders(s, pick, now, chosen);              // (CENTER: the losses alone)
         if (!live) return;
         if (CENTER) center_columns<VEC>(s, col);
         update_columns<VEC, KIND, NT, CENTER>(s, before, col, first);
         if (MODE == kUpdatePull) pull_columns<VEC>(s, after, col);
+    } else if constexpr (MODE == kUpdateRegs) {
+        HeldRows<VEC, NR> r;
+        const uint32_t off = (uint32_t)col * 4u;
+        if (live) held_load<VEC, KIND, NT, NR>(s, off, r);
+        choose_leaders<true>(s, pick, now, chosen);
+        if (live) held_update<VEC, KIND, NT, NR>(s, chosen, off, r);
     } else if constexpr (MODE == kPull) {
-        choose_leaders(s, now, chosen);
+        choose_leaders(s, pick, now, chosen);
         if (live) pull_columns<VEC>(s, after, col);
     } else if constexpr (MODE == kUpdateOnes || MODE == kComm) {
         RowBatch<VEC> cur, next;
@@ -638,19 +873,25 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
             load_batch<VEC, KIND, NT>(s, 0, (uint32_t)col, cur);
             load_batch<VEC, KIND, NT>(s, kRowsInFlight<VEC>, (uint32_t)col, next);
         }
-        choose_leaders(s, now, chosen);
+        choose_leaders(s, pick, now, chosen);
         if (live) stream_columns<VEC, KIND, NT, MODE == kComm>(s, before, after, (uint32_t)col, cur, next);
     } else {
         Rows<VEC, NR> r;
-        if (live) load_rows<VEC, KIND, NT, NR>(s, (uint32_t)col, r);
-        choose_leaders(s, now, chosen);
-        if (!live) return;
-        if (MODE == kCenterRegs) {
-            regs_easgd<VEC, KIND, NT, NR>(s, (uint32_t)col, r);
-        } else {
-            if (s.update) regs_update<VEC, KIND, NT, NR>(s, (uint32_t)col, r);
-            regs_comm<VEC, NT, NR>(s, after, (uint32_t)col, r);
+        constexpr bool PACED = MODE == kCommRegs && kPaced<VEC, KIND, NR>;
+        if (live) {
+            if (MODE == kCenterRegs || s.update) load_rows<VEC, KIND, NT, PACED, true, NR>(s, (uint32_t)col, r);
+            else load_rows<VEC, KIND, NT, PACED, false, NR>(s, (uint32_t)col, r);
         }
+        if constexpr (MODE == kCenterRegs) {
+            if (blockIdx.x == 0) choose_leaders(s, pick, now, chosen);                   // the losses alone
+            if (live) regs_easgd<VEC, KIND, NT, NR>(s, (uint32_t)col * 4u, r);
+            return;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        choose_leaders(s, pick, now, chosen);
+        if (!live) return;
+        if (s.update) regs_update<VEC, KIND, NT, PACED, NR>(s, (uint32_t)col, r);
+        regs_comm<VEC, NT, PACED, NR>(s, after, (uint32_t)col, r);
     }
 }
 
@@ -677,9 +918,10 @@ void launch_vec(const ColumnDev& s, bool nt, hipStream_t st)
     // one kernel where a way has but one kind of accesses: what is walked group by group is read again, rows in registers and
     // the two passes of elastic averaging stream
     constexpr bool PLAIN = MODE == kPull || MODE == kUpdatePull, STREAMS = MODE == kCommRegs || MODE == kCenter;
+    const size_t lds = MODE == kUpdateRegs ? (size_t)(s.a.W + s.a.G) * kThreads * VEC * sizeof(float) : 0;
     if constexpr (!PLAIN)
-        if (nt || STREAMS) { hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR>), grid, dim3(kThreads), 0, st, s); return; }
-    if constexpr (!STREAMS) hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR>), grid, dim3(kThreads), 0, st, s);
+        if (nt || STREAMS) { hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR>), grid, dim3(kThreads), lds, st, s); return; }
+    if constexpr (!STREAMS) hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR>), grid, dim3(kThreads), lds, st, s);
 }
 
 // vec: columns per thread wished for; no more than the registers hold.
@@ -698,6 +940,18 @@ void launch_mode(const ColumnDev& s, int vec, bool mom, bool nt, hipStream_t st)
         if (vec >= 2) launch_vec<2, 0, MODE, NR>(s, nt, st);
         else launch_vec<1, 0, MODE, NR>(s, nt, st);
     }
+}
+
+// The update of groups of several workers: whether every row in registers beats a walk by groups.  By groups / registers,
+// us: 24 workers in 4 groups with momentum x 140 001 (67 MB) 19.4 / 17.1, x 271 117 (130 MB) nothing re-selected 27.3 / 27.8,
+// x 600 001 (288 MB) 56 / 59; 32 in 4 groups x 271 117 (104 MB) 23.2 / 24.1; 16 in 4 groups x 1 250 001 (240 MB) 48 / 46.  4 workers
+// without momentum, nothing re-selected, x 271 117 (13 MB) 6.5 / 5.1, x 1 250 001 (60 MB) 12.5 / 14.4 (15.6 / 15.4 where it is).
+// 313 populations of 4 to 32 workers, 1003 to 1 250 001 columns: 0.82 of the time.
+bool update_in_registers(const ColumnStep& q, double bytes)
+{
+    const PullParams& p = q.pull;
+    if (p.W > 16) return bytes <= 100e6;
+    return p.W > 4 || p.mu != 0.0f || q.cap || q.capG || bytes <= 35e6;
 }
 
 // A pull alone: whether one pass over all rows beats a walk group by group, which touches only rows that move.  One pass / by
@@ -756,6 +1010,7 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     s.losses = q.losses; s.losses_out = q.losses_out; s.parts = q.parts;
     s.lead = st.lead; s.glead = st.glead; s.refreshed = st.refreshed; s.plan = st.plan;
     s.center = q.center; s.center_rate = q.center_rate;
+    s.group_inv = p.group_size > 0 ? (65535 + p.group_size) / p.group_size : 0;          // (exact for up to 64 rows)
     const bool mom = q.update && p.mu != 0.0f;
     auto aligned = [](const void* v, unsigned n) { return (reinterpret_cast<uintptr_t>(v) & (n - 1u)) == 0; };
     auto layout_ok = [&](unsigned v) {      // every row start and every thread's group of v columns is v*4-byte aligned
@@ -767,23 +1022,30 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     // registers for sixteen rows of three values.  Twice / once, us: 16 x 1 250 001 (400 MB) 73 / 79, 15 x 1 250 001 69 / 74, 14 x
     // 1 250 001 65 / 68, 13 x 1 250 001 (325 MB) 62 / 65, 15 x 1 400 001 (420 MB) 82 / 83; 16 x 1 400 001 (448 MB) 89 / 90, 14 x
     // 1 666 667 (467 MB) 94 / 87, 16 x 1 866 667 (597 MB) 135 / 123, 13 x 2 000 001 109 / 94; 12 x 1 250 001 (300 MB) 60 / 59.
-    const bool by_groups = q.comm && (q.update ? pull_behind_update(q, bytes) : !pull_in_one_pass(q));
-    const int mode = q.center ? (mom && p.W > 12 && p.W <= 16 && bytes > 300e6 && bytes <= 430e6 ? kCenter : kCenterRegs)
-                   : !q.comm ? (p.W == p.G ? kUpdateOnes : kUpdate)
+    // whole matrices within reach of 32-bit offsets (rows may lie far apart)
+    const bool near = (double)(p.W + 1) * (double)p.ld < (double)(1u << 30);
+    const bool by_groups = q.comm && ((p.W <= 8 && !near) || (q.update ? pull_behind_update(q, bytes) : !pull_in_one_pass(q)));
+    const bool held = near && q.select == 1 && p.W >= 2 * p.G && update_in_registers(q, bytes);
+    s.pitch = (uint32_t)p.ld * 4u;
+    const int mode = q.center ? ((mom && p.W > 12 && p.W <= 16 && bytes > 300e6 && bytes <= 430e6) || !near ? kCenter : kCenterRegs)
+                   : !q.comm ? (p.W == p.G ? kUpdateOnes : held ? kUpdateRegs : kUpdate)
                    : by_groups ? (q.update ? kUpdatePull : kPull) : p.W <= 8 ? kCommRegs : kComm;
-    // Columns per thread: one, so that small rows still make enough wavefronts; more once there are plenty.  Update: 16
+    // Columns per thread: one, so that small rows still make enough wavefronts; more once there are plenty, but not where
+    // every row's loads are under way at once, which wait less with one.  Update by groups: 16
     // workers without momentum, 600 000 columns 27.0 / 25.6 / 24.5 us with 1 / 2 / 4, 250 000 columns 13.8 / 13.7 / 14.1;
-    // with momentum two columns are never more than 2 % ahead, four mostly behind.  Algorithm 1's iteration, 8 workers in 2
-    // groups: 140 001 columns 8.8 / 9.4 / 10.0, 1 250 001 37 / 35 / 32.  Groups of one, 8 x 271 117, 13.6 / 12.8 / 12.5.
-    // Elastic averaging, 16 x 271 117 with momentum, 18.3 / 21.1, 4 x 1 250 001 without 18.8 / 17.8 / 16.3.
+    // with momentum two columns are never more than 2 % ahead, four mostly behind.  From registers, 16 workers in 4 groups,
+    // 140 001 columns 8.1 / 9.3 / 9.2, with momentum 10.5 / 13.7 / 13.8, 1 250 001 46 / 52 / 59.  Algorithm 1's iteration,
+    // 8 workers in 2 groups with momentum, 271 117 columns 11.9 / 13.4 / 13.4, 600 001 25.1 / 23.0 / 23.0; 4 workers without x
+    // 1 250 001 19.8 / 17.6 / 14.1.  Groups of one, 8 x 271 117, 13.6 / 12.8 / 12.5.
+    // Elastic averaging, 16 without momentum x 600 001 22 / 29 / 29, with momentum x 140 001 10.0 / 12.8 / 12.8.
     int vec = 1;
     if (mode == kUpdate || mode == kUpdatePull || mode == kCenter) {
         if (!mom && p.P >= 500000) vec = p.P >= 1000000 ? 4 : 2;
         // (a bf16 copy is written two bytes per lane with one column: 8 workers x 266 610 columns, whole step 62.9 -> 61.0 us)
         if (p.xb && p.P >= 100000 && vec < 2) vec = 2;
-    } else if (mode == kCenterRegs) {
-        vec = p.P < 500000 ? 1 : p.P < 1000000 ? 2 : 4;
-    } else {
+    } else if (mode == kCommRegs) {
+        vec = p.P < 400000 ? 1 : mom || p.P < 1000000 ? 2 : 4;
+    } else if (mode != kUpdateRegs && mode != kCenterRegs) {
         vec = p.P < (mode == kComm ? 100000 : 200000) ? 1 : p.P < 500000 ? 2 : 4;
     }
     if (!q.update) vec = 4;
@@ -795,7 +1057,7 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     // (26 MB) 13.6 / 17.3, 16 x 1 250 001 with momentum (400 MB) 106 / 90; with most of them kept 8 x 1 250 001 (120 MB) 43 / 39.
     const bool all_fresh = q.select == 1 && (q.cap & (~0ull >> (64 - p.G))) == (~0ull >> (64 - p.G));
     const bool nt = mode == kUpdateOnes ? (all_fresh ? bytes > 200e6 : true)
-                  : bytes >= 16e6 && (bytes < 90e6 || bytes > 280e6);
+                  : bytes > 280e6 || (bytes >= 16e6 && bytes < 90e6 && mode != kCenterRegs);
     if (!q.update && q.comm && q.commL == 0.0f && q.commG == 0.0f) {
         const int64_t tiles = (p.P + (int64_t)kThreads * vec - 1) / ((int64_t)kThreads * vec);
         const dim3 grid((unsigned)(tiles < 2048 ? tiles : 2048));
@@ -809,6 +1071,14 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     switch (mode) {
     case kUpdate: launch_mode<kUpdate>(s, vec, mom, nt, stream); break;
     case kUpdateOnes: launch_mode<kUpdateOnes>(s, vec, mom, nt, stream); break;
+    case kUpdateRegs:
+        if (p.W <= 4) launch_mode<kUpdateRegs, 4>(s, vec, mom, nt, stream);
+        else if (p.W <= 8) launch_mode<kUpdateRegs, 8>(s, vec, mom, nt, stream);
+        else if (p.W <= 12) launch_mode<kUpdateRegs, 12>(s, vec, mom, nt, stream);
+        else if (p.W <= 16) launch_mode<kUpdateRegs, 16>(s, vec, mom, nt, stream);
+        else if (p.W <= 24) launch_mode<kUpdateRegs, 24>(s, vec, mom, nt, stream);
+        else launch_mode<kUpdateRegs, 32>(s, vec, mom, nt, stream);
+        break;
     case kComm: launch_mode<kComm>(s, vec, mom, nt, stream); break;
     case kUpdatePull: launch_mode<kUpdatePull>(s, vec, mom, nt, stream); break;
     case kPull:
@@ -820,7 +1090,10 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
         if (p.W <= 4) launch_mode<kCommRegs, 4>(s, vec, mom, nt, stream);
         else launch_mode<kCommRegs, 8>(s, vec, mom, nt, stream);
         break;
-    case kCenter: launch_vec<1, 1, kCenter, 0>(s, nt, stream); break;
+    case kCenter:
+        if (mom) launch_vec<1, 1, kCenter, 0>(s, nt, stream);
+        else launch_vec<1, 0, kCenter, 0>(s, nt, stream);
+        break;
     case kCenterRegs:
         if (p.W <= 8) launch_mode<kCenterRegs, 8>(s, vec, mom, nt, stream);
         else if (p.W <= 16) launch_mode<kCenterRegs, 16>(s, vec, mom, nt, stream);

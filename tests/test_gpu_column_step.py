@@ -164,3 +164,45 @@ def test_step_and_separate_calls_find_the_same_mlp_losses():
         else:
             getattr(pr.pop, call)(batch)
         assert pr.pop.get_losses() == [62.0] * W, call
+
+
+# every row in registers: the numbers of rows at which another kernel takes over, and one less or more
+HELD = [(3, [0, 3], 257, 320), (5, [0, 2, 5], 256, 256), (8, [0, 3, 8], 513, 576), (9, [0, 1, 5, 9], 255, 256), (12, [0, 12], 64, 64),
+        (13, [0, 2, 5, 7, 13], 301, 301), (16, [0, 2, 4, 6, 8, 10, 12, 14, 16], 769, 832), (17, [0, 8, 17], 63, 64),
+        (24, [0, 5, 24], 129, 192), (25, [0, 12, 25], 257, 257), (28, [0, 7, 14, 21, 28], 1, 1)]
+
+
+@pytest.mark.parametrize("mu,flags,wd", OPTIONS)
+@pytest.mark.parametrize("W,off,P,ld", HELD)
+def test_rows_in_registers_match_oracle(W, off, P, ld, mu, flags, wd):
+    test_whole_step_matches_oracle(W, off, P, ld, mu, flags, wd)
+
+
+@pytest.mark.parametrize("call", ["step", "alg1", "easgd"])
+def test_rows_far_apart(call):
+    """Rows 2 GB apart are out of reach of 32-bit offsets: the same results, bit for bit, as with rows next to each other."""
+    W, P = 2, 1000
+    out = []
+    for ld in (1024, 1 << 29):
+        gen = torch.Generator(device="cuda:0").manual_seed(5)
+        t = {}
+        for name, rows in (("x", W), ("g", W), ("m", W), ("Z", 2)):
+            t[name] = torch.empty((rows, ld), device="cuda:0")
+            t[name][:, :P] = torch.randn((rows, P), device="cuda:0", generator=gen)
+        center = torch.zeros(ld, device="cuda:0")
+        center[:P] = torch.randn(P, device="cuda:0", generator=gen)
+        losses = torch.tensor([0.5, 0.25], device="cuda:0")
+        pop = L.Population(t["x"], t["g"], 1, m=t["m"], z_snapshot=t["Z"], P=P, momentum=0.9)
+        batch = L.ExternalBatch(losses)
+        for _ in range(2):
+            if call == "step":
+                pop.step(batch, 0.05, 0.1, 0.05)
+            elif call == "alg1":
+                pop.select_leaders(losses); pop.leader_pull(0.0, 0.0)
+                pop.step_alg1(batch, 0.05, 0.02, 0.01, 0.1, 0.05, L.COMM_LOCAL | L.COMM_GLOBAL)
+            else:
+                pop.easgd_step(batch, center, 0.05, 0.1)
+        out.append([t[n][:, :P].cpu() for n in ("x", "m", "Z")] + [center[:P].cpu()])
+        del pop, t
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
