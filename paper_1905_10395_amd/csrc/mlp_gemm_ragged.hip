@@ -13,7 +13,7 @@
 // bytes and shifted into place (zeros behind it) on its way to LDS, so the K loop has no branches per lane.
 //
 // Tiles.  These shapes are small or have few rows per weight, so what counts is to have enough bytes in flight on
-// enough compute units, not flops per LDS byte: BN = 64 columns, 32 / 64 / 128 rows.  With 32 rows, and in the forward
+// enough compute units, not flops per LDS byte: BN = 64 columns (32 where tiles are few), 32 / 64 / 128 rows.  With 32 rows, and in the forward
 // and d-input products with 64 (a whole small batch), the wavefronts split the contraction of one tile among them (K
 // steps of 128, a quarter or a half each; 64 where the contraction is one step) instead of splitting the rows.  Few tiles
 // with a long contraction take 32 x 32 tiles of sixteen wavefronts and K steps of 512, large forward batches 128 x 128
@@ -764,6 +764,18 @@ void launch_head(const GemmArgs& g, int W, hipStream_t s)
 bool fills(const GemmArgs& g, int W, int rows) { return (int64_t)((g.N + 63) / 64) * W * ((g.M + rows - 1) / rows) >= 256; }
 bool long_and_few(const GemmArgs& g, int W) { return g.K >= 1024 && (int64_t)((g.N + 63) / 64) * W * ((g.M + 31) / 32) <= 128; }
 
+// Whether 32 rows go with 32 columns instead of 64.  What a workgroup of so few rows waits for is its own chain of K steps,
+// most of it additions to the double sums, of which half as many columns have half; twice as many workgroups load A again.
+// So with compute units to spare, and where tiles of 64 columns would fill a second round of them badly.  64 / 32 columns, us
+// (the same bits): objective of 784-300-100-10, 8 workers, batch 50, 21.7 / 18.7, of 3072-1500-10, 12 x 16 (288 tiles of 64)
+// 39.2 / 36.0; 118 objectives and gradients: up to 160 tiles 0.93 of the time, 161 to 256 0.99 forward but 1.03 to 1.04
+// d-input, 257 to 400 0.94, more than that 1.05 to 1.10.
+bool narrow(const GemmArgs& g, int W)
+{
+    const int64_t tiles = (int64_t)((g.N + 63) / 64) * W * ((g.M + 31) / 32);
+    return tiles <= 160 || (tiles > 256 && tiles <= 400);
+}
+
 template <int EPI>
 void launch_epi(const GemmArgs& g, int W, hipStream_t s)
 {
@@ -796,6 +808,7 @@ void launch_epi(const GemmArgs& g, int W, hipStream_t s)
         }
         if (g.M > 64 && fill128) launch_tile<128, 64, 2, 2, 1, 64, EPI>(g, W, s);
         else if (g.M > 32 && fill64) launch_tile<64, 64, 1, 2, 2, 128, EPI>(g, W, s);
+        else if (narrow(g, W)) launch_tile<32, 32, 1, 1, 4, 128, EPI>(g, W, s);
         else launch_tile<32, 64, 1, 1, 4, 128, EPI>(g, W, s);
     }
 }
@@ -841,7 +854,8 @@ bool launch_gemm_ragged_f32(const GemmArgs& g, int W, hipStream_t s)
 {
     if (2.0 * W * (double)g.M * g.K * ((g.N + 63) / 64) > 90e6) return false;
     if (g.K < 8 || long_and_few(g, W) || (g.M > 32 && fills(g, W, 64)) || (g.M > 64 && fills(g, W, 128))) return false;
-    launch_tile<32, 64, 1, 1, 4, 128, EPI_FWD, true>(g, W, s);
+    if (narrow(g, W)) launch_tile<32, 32, 1, 1, 4, 128, EPI_FWD, true>(g, W, s);
+    else launch_tile<32, 64, 1, 1, 4, 128, EPI_FWD, true>(g, W, s);
     return true;
 }
 

@@ -28,6 +28,9 @@ SHAPES = [
     ([257, 1030, 100], 16, 50),   # 64-row tiles, forward and d-input (double sums every other instruction)
     ([300, 1030], 16, 50),        # logits of more than 64 classes: 64-row tiles
     ([137, 1030], 16, 130),       # ... 128-row tiles, two of them
+    ([130, 300, 10], 16, 70),     # 32 rows: 64 columns where tiles fill the compute units once,
+    ([257, 1500, 10], 12, 16),    # 32 where they would fill them twice,
+    ([70, 1030, 10], 13, 33),     # 64 again beyond
 ]
 
 
