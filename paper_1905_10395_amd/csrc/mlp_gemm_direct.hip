@@ -21,7 +21,9 @@
 // Measured, us, through registers -> straight to LDS: objective of 3072-1024-10, 16 workers, batch 128: 38 -> 32;
 // gradients of 1024-2048-2048-10, 8 workers, batch 256: 169 -> 159; 256-512-512-10, 8 workers, batch 128: 46.5 -> 43.
 // ANY, kernels alone: forward 500 x 1024 x 3072, 16 workers, 91 -> 76, 128 x 1912 x 1208 34 -> 22; d-input 200 x 1912 x
-// 1208 72 -> 44, 256 x 784 x 1000 34 -> 22.
+// 1208 72 -> 44, 256 x 784 x 1000 34 -> 22.  With four buffers the additions to the double sums run beside the next two
+// steps' matrix instructions, which go into other accumulators: objective of 3072-1024-10, 16 x 500, 85.8 -> 82.9 us, of
+// 3072-1000-10, 8 x 1000, 84.7 -> 81.3 (same bits).
 #include <type_traits>
 
 #include "mlp_common.h"
@@ -139,6 +141,28 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
                 acc[i][j][v] = 0.f;
                 if (ANY) sum[i][j][v] = 0.0;
             }
+    // DEFER (an even number of buffers): the accumulators of two K steps are added to the sums while the next two are
+    // multiplied into others, a quarter at a time
+    constexpr bool DEFER = ANY && ST % 2 == 0;
+    f32x16 old[DEFER ? TM : 1][DEFER ? TN : 1];
+    auto put_off = [&]() {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                old[DEFER ? i : 0][DEFER ? j : 0] = acc[i][j];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            }
+    };
+    auto add_old = [&](int part) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 4 * part; v < 4 * part + 4; ++v) sum[ANY ? i : 0][ANY ? j : 0][v] += (double)old[DEFER ? i : 0][DEFER ? j : 0][v];
+    };
     auto promote = [&]() {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -194,9 +218,13 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
         constexpr bool LAST = decltype(last_steps)::value;
         const uint16_t* const buf = bufs(q);
         const int live = K - kt * kBK;
+        constexpr bool ADD = DEFER && decltype(q)::value % 2 == 0;    // (before the first step there are only zeros to add)
         read(buf, 1, f1); if (ANY && LAST) clear_past(f0, 0, live); multiply(f0);
+        if (ADD) add_old(0);
         read(buf, 2, f0); if (ANY && LAST) clear_past(f1, 1, live); multiply(f1);
+        if (ADD) add_old(1);
         read(buf, 3, f1); if (ANY && LAST) clear_past(f0, 2, live); multiply(f0);
+        if (ADD) add_old(2);
         __builtin_amdgcn_sched_barrier(0);
         wait_loads<decltype(in_flight)::value * OPS>();
         step_barrier();
@@ -205,8 +233,14 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
         read(bufs((q + 1) % ST), 0, f0);
         __builtin_amdgcn_sched_barrier(0);
         multiply(f1);
-        if (ANY && ((kt & 1) || (LAST && kt == nk - 1))) promote();
+        if (DEFER) {
+            if (ADD) add_old(3);
+            if (decltype(q)::value % 2 == 1) put_off();
+        } else if (ANY && ((kt & 1) || (LAST && kt == nk - 1))) {
+            promote();
+        }
     };
+    if (DEFER) put_off();
     for_each<ST>([&](auto q) { issue(q < nk ? q : nk - 1, bufs(q)); });
     wait_loads<(ST - 1) * OPS>();
     step_barrier();
@@ -219,6 +253,10 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_direct_kernel(GemmArgs g,
         constexpr int after = ST - 2 - decltype(q)::value;
         if (q == 0 || kt + q < nk) step(q, kt + q, std::integral_constant<int, (after > 0 ? after : 0)>{}, std::true_type{});
     });
+    if (DEFER) {
+        if (!(nk & 1)) for_each<4>([&](auto part) { add_old(part); });
+        else promote();
+    }
     wait_loads<0>();
     __syncthreads();
 
