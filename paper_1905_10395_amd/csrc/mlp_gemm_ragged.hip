@@ -452,6 +452,8 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
 #pragma unroll
             for (int j = 0; j < BN / 8; ++j) {
                 const int c = l + 8 * j;
+                z[j] = -INFINITY;
+                if (BN == 32 && 8 * j >= N) continue;                    // uniform: no such classes (here and below; with 64 columns the branches cost more)
                 Sum v = T[r * LDC + c];
 #pragma unroll
                 for (int q = 1; q < WVK; ++q) v += T[(q * BM + r) * LDC + c];
@@ -464,6 +466,7 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
 #pragma unroll
             for (int j = 0; j < BN / 8; ++j) {
                 const int c = l + 8 * j;
+                if (BN == 32 && 8 * j >= N) continue;
                 if (c < N) se += expf(z[j] - mx);
                 if (c < N && c == yb) zy = z[j];
             }
@@ -477,6 +480,7 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
                 for (int j = 0; j < BN / 8; ++j) {
                     const int c = l + 8 * j;
                     uint16_t q = 0;
+                    if (BN == 32 && 8 * j >= N) { dl[r][c] = 0; continue; }
                     if (m < M && c < N) {
                         q = f32_to_bf16_rne((expf(z[j] - lse) - (c == yb ? 1.f : 0.f)) * inv);
                         if (!g.dx) g.out[(int64_t)w * g.sOut + (int64_t)m * N + c] = q;
@@ -513,6 +517,7 @@ __device__ __forceinline__ void gemm_ragged_tile(const GemmArgs& g, int tiles_m,
                 for (int v = 0; v < 16; ++v) d[v] = 0.f;
 #pragma unroll
                 for (int q = 0; q < BN / 16; ++q) {
+                    if (BN == 32 && 16 * q >= N) break;
                     s16x8 b;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
