@@ -67,6 +67,25 @@ __device__ __forceinline__ float group_sum(float v)
     return v;
 }
 
+// Inclusive sum over the lanes of a wavefront, by data-parallel-primitive adds (lane shuffles take an LDS round each).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add(int v) { return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false); }
+__device__ __forceinline__ int wave_scan(int v)
+{
+    v = dpp_add<0x111, 0xF>(v);               // row_shr:1, 2, 4, 8
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);               // lane 15 of a row to the row behind it
+    return dpp_add<0x143, 0xC>(v);            // lane 31 to the upper half
+}
+// Sum of the first n of up to 16 values in LDS (the same in every lane).
+__device__ __forceinline__ int sum_first(const int* v, int of, int n)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    return __builtin_amdgcn_readlane(wave_scan(lane < (n < of ? n : of) ? v[lane] : 0), 15);
+}
+
 // General path: S lanes cooperate on one entry (S = power of two >= min(r, 64)),
 // residual by a sum over the lanes, gradient rows accumulated with hardware fp32
 // atomics into the zero-filled g.  Any r, m, n.  GRAD = false evaluates the
@@ -376,6 +395,8 @@ __global__ __launch_bounds__(256) void mc_loss_finish_kernel(const T* __restrict
 // which keeps the worker's factors, 5 MB at rank 32, in that die's L2.  This placement only
 // affects speed, never results.
 // ------------------------------------------------------------------------------------------
+typedef __attribute__((address_space(3))) void* lds_ptr;
+typedef const __attribute__((address_space(1))) void* global_ptr;
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 // a lane's part of a factor row: four, two or one of its columns, by the rank and the alignment of the rows
@@ -464,23 +485,28 @@ __global__ __launch_bounds__(kPrepThreads) void mc_prep_kernel(
     const int per = (S.nbins + kPrepThreads - 1) / kPrepThreads;     // <= kMaxBins / 1024
     int loc[kMaxBins / kPrepThreads];
     int tot = 0;
+    if (per == 1) {
+        tot = t < S.nbins ? lhist[t] : 0;
+    } else {
 #pragma unroll
-    for (int q = 0; q < kMaxBins / kPrepThreads; ++q) {
-        const int i = t * per + q;
-        loc[q] = (q < per && i < S.nbins) ? lhist[i] : 0;
-        tot += loc[q];
+        for (int q = 0; q < kMaxBins / kPrepThreads; ++q) {
+            const int i = t * per + q;
+            loc[q] = (q < per && i < S.nbins) ? lhist[i] : 0;
+            tot += loc[q];
+        }
     }
-    int inc = tot;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d, 64); if (lane >= d) inc += v; }
+    const int inc = wave_scan(tot);
     if (lane == 63) wsum[wv] = inc;
     __syncthreads();
-    int run = inc - tot;
-    for (int q = 0; q < wv; ++q) run += wsum[q];
+    int run = inc - tot + sum_first(wsum, kPrepThreads / 64, wv);
+    if (per == 1) {
+        if (t < S.nbins) lhist[t] = run;
+    } else {
 #pragma unroll
-    for (int q = 0; q < kMaxBins / kPrepThreads; ++q) {
-        const int i = t * per + q;
-        if (q < per && i < S.nbins) { lhist[i] = run; run += loc[q]; }
+        for (int q = 0; q < kMaxBins / kPrepThreads; ++q) {
+            const int i = t * per + q;
+            if (q < per && i < S.nbins) { lhist[i] = run; run += loc[q]; }
+        }
     }
     if (t == 0) lhist[S.nbins] = 2 * cnt_here;
     __syncthreads();
@@ -506,6 +532,11 @@ __global__ __launch_bounds__(kPrepThreads) void mc_prep_kernel(
 // each lane group owns whole rows: it walks the row's records, four gathers of the other factor's
 // rows in flight, forms each record's residual against its own row, accumulates in registers and
 // writes the gradient row once (scaled by 2c).  Rows without records are written as zeros.
+// A workgroup is a chain of dependent steps (bounds, records, counts, places, gathers), 16 us of it at 20000^2, rank 32, four
+// after each other on a compute unit, so what counts is the chain's length: own rows go straight to LDS while the bounds
+// are on their way (a loop of load, wait and store took four latencies), scans are data-parallel-primitive adds.  Gradient
+// of 16 workers x 65536 entries 82.3 -> 77.1 us, x 16384 59.8 -> 53.6, 8 x 16384 at 6001 x 3517, rank 10, 18.7 -> 17.6.  (Six
+// workgroups per compute unit instead of five, at 80 registers: 76 to 77, other ranks up to 4 % slower.)
 constexpr int kSideThreads = 256;
 constexpr int kRedCap = 1024;                     // records staged per pass
 constexpr int kSegCap = kSideThreads;             // segments collected at a time
@@ -556,9 +587,7 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
     auto scan_rows = [&]() {
         if (kBinRows > 64 || t < 64) {
             const int cc = (t < kBinRows) ? cnt[t] : 0;
-            int in2 = cc;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(in2, d, 64); if (lane >= d) in2 += v; }
+            int in2 = wave_scan(cc);
             if (kBinRows > 64) {
                 if (lane == 63) wtot[wv] = in2;
                 __syncthreads();
@@ -617,6 +646,35 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
         }
     };
 
+    // The bin's own rows, which lie in one piece, to the tile.  No loop that loads, waits and stores: straight to LDS where
+    // a lane's columns are 16 bytes, else a few loads at a time.
+    auto own_rows = [&]() {
+        const int live = (nrows - row0 < kBinRows ? nrows - row0 : kBinRows) * rv;
+        const V* src = reinterpret_cast<const V*>(own + (int64_t)row0 * r);
+        if constexpr (VW == 4) {
+            const int wave0 = __builtin_amdgcn_readfirstlane(t & ~63);
+            auto piece = [&](int at) {                                // 64 lanes from `at` on; past the end the last again
+                __builtin_amdgcn_global_load_lds((global_ptr)(src + (at + lane < live ? at + lane : live - 1)), (lds_ptr)(tile + at), 16, 0, 0);
+            };
+            if constexpr (EXACT) {
+#pragma unroll
+                for (int i = 0; i < kBinRows * LPE * NV; i += kSideThreads)
+                    if (LPE * NV * kBinRows >= kSideThreads || wave0 < LPE * NV * kBinRows) piece(i + wave0);
+            } else {
+                for (int i = wave0; i < kBinRows * rv; i += kSideThreads) piece(i);
+            }
+        } else {
+            for (int i = t; i < live; i += 4 * kSideThreads) {
+                V v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = src[i + u * kSideThreads < live ? i + u * kSideThreads : i];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (i + u * kSideThreads < live) tile[i + u * kSideThreads] = v[u];
+            }
+        }
+    };
+
     // A team of lanes per segment reads its bounds and its records, as many as the registers hold; no list of all records
     // in between.
     int team = kSideThreads;
@@ -624,11 +682,15 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
     bool teams = team * S.nblk <= kSideThreads && (int64_t)S.nblk * S.E * kBinRows <= (int64_t)kRedCap * nrows;   // uniform; on average they fit
     int2 mine[PER];
     int len = 0;                                                      // records of this lane
+    const int blk = t / team, l = t % team;
+    const int32_t* sp = segs + (int64_t)(blk < S.nblk ? blk : 0) * (S.nbins + 1);
+    const int s0 = sp[0], s1 = sp[1];
+    __builtin_amdgcn_sched_barrier(0);                                // (the bounds first: loads return in order)
+    own_rows();
+    __builtin_amdgcn_sched_barrier(0);
     if (teams) {
-        const int blk = t / team, l = t % team;
         if (blk < S.nblk) {
-            const int32_t* sp = segs + (int64_t)blk * (S.nbins + 1);
-            const int s0 = sp[0], left = sp[1] - s0 - l;
+            const int left = s1 - s0 - l;
             const int2* src = rec + (int64_t)blk * (2 * S.E) + s0 + l;
 #pragma unroll
             for (int u = 0; u < PER; ++u)
@@ -636,13 +698,9 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
             len = left > 0 ? (left + team - 1) / team : 0;
         }
     }
-    {
-        const int live = (nrows - row0 < kBinRows ? nrows - row0 : kBinRows) * rv;
-        const V* src = reinterpret_cast<const V*>(own + (int64_t)row0 * r);
-        for (int i = t; i < live; i += kSideThreads) tile[i] = src[i];
-    }
     if (t < kBinRows) cnt[t] = 0;
     if (t == 0) crowded = 0;
+    __builtin_amdgcn_s_waitcnt(0x0F70);                               // vmcnt 0: the tile is there
     __syncthreads();
     if (teams) {
         if (len > PER) crowded = 1;
@@ -674,13 +732,10 @@ __global__ __launch_bounds__(kSideThreads) void mc_side_kernel(const float* __re
             c = sp[1] - s0;
             segbase[t] = blk * (2 * S.E) + s0;
         }
-        int inc = c;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d, 64); if (lane >= d) inc += v; }
+        const int inc = wave_scan(c);
         if (lane == 63) wtot[wv] = inc;
         __syncthreads();
-        int before = 0;
-        for (int q = 0; q < wv; ++q) before += wtot[q];
+        const int before = sum_first(wtot, kSideThreads / 64, wv);
         segoff[t + 1] = before + inc;
         if (t == 0) segoff[0] = 0;
         __syncthreads();
