@@ -17,8 +17,10 @@ namespace lsgd {
 constexpr int kMcThreads = 256;
 constexpr int kMcEntriesPerBlock = 256;
 
-__global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ g, int64_t ld)
+// sums: n doubles per row to clear too, or NULL
+__global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ g, int64_t ld, double* __restrict__ sums, int n)
 {
+    if (sums && blockIdx.x == 0 && threadIdx.x < n) sums[blockIdx.y * n + threadIdx.x] = 0.0;
     float* row = g + (int64_t)blockIdx.y * ld;
     const int64_t n4 = ld >> 2;
     float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -26,8 +28,9 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ g, i
         reinterpret_cast<float4*>(row)[c] = z;
     if (blockIdx.x == 0 && threadIdx.x < (ld & 3)) row[(n4 << 2) + threadIdx.x] = 0.f;
 }
-__global__ __launch_bounds__(256) void fill_zero_scalar_kernel(float* __restrict__ g, int64_t ld)
+__global__ __launch_bounds__(256) void fill_zero_scalar_kernel(float* __restrict__ g, int64_t ld, double* __restrict__ sums, int n)
 {
+    if (sums && blockIdx.x == 0 && threadIdx.x < n) sums[blockIdx.y * n + threadIdx.x] = 0.0;
     float* row = g + (int64_t)blockIdx.y * ld;
     for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < ld; c += (int64_t)gridDim.x * blockDim.x)
         row[c] = 0.f;
@@ -105,9 +108,14 @@ __device__ __forceinline__ int sum_first(const int* v, int of, int n)
 // is rounded once.  Relative error of gradient / losses, 8 workers x 256 entries on
 // 1000 x 800, rank 8: 5.6e-8 / 1.6e-8, binned 5.8e-8 / 1.8e-8, with all of it in
 // 32 bits 6.2e-8 / 3.9e-8, at the same time per call.
+//   FEW   FLY where workgroups of 256 entries would leave compute units idle: a lane group goes through its entries one
+//         after the other once they are there, so it takes two, and there are as many more workgroups (mc_few).  Whole
+//         steps, 4 workers x 3000 entries of 100 x 100, rank 5, 12.8 -> 11.5 us, 4 x 256 of 1000 x 800 11.9 -> 9.9, rank 50,
+//         2 x 400 of 300 x 200, 21.0 -> 10.9, rank 12, 8 x 5000 of 600 x 900 (160 workgroups of 256) 17.9 -> 16.5.
 constexpr int mc_atomic_threads(int S, bool FLY) { return !FLY || S <= 8 ? 256 : S == 16 ? 512 : 1024; }
+constexpr int mc_few_entries(int S) { return 2 * mc_atomic_threads(S, true) / S; }
 
-template <int S, bool GRAD, bool FLY>
+template <int S, bool GRAD, bool FLY, bool FEW = false>
 __global__ __launch_bounds__(mc_atomic_threads(S, FLY)) void mc_grad_atomic_kernel(
     const float* __restrict__ x, float* __restrict__ g, int64_t ld, int m, int n, int r,
     const int32_t* __restrict__ rows, const int32_t* __restrict__ cols, const float* __restrict__ vals,
@@ -122,8 +130,9 @@ __global__ __launch_bounds__(mc_atomic_threads(S, FLY)) void mc_grad_atomic_kern
     float* gV = GRAD ? gU + (int64_t)m * r : nullptr;
     const int sub = threadIdx.x / S, q0 = threadIdx.x % S;
     constexpr int kSubs = kThreads / S;
-    const int64_t k0 = (int64_t)blockIdx.x * kMcEntriesPerBlock;
-    const int64_t k1 = (k0 + kMcEntriesPerBlock < nb) ? k0 + kMcEntriesPerBlock : nb;
+    constexpr int kPer = FEW ? mc_few_entries(S) : kMcEntriesPerBlock;
+    const int64_t k0 = (int64_t)blockIdx.x * kPer;
+    const int64_t k1 = (k0 + kPer < nb) ? k0 + kPer : nb;
     double sq = 0.0;
     auto residual = [&](float dot, float low, float v) {
         low = fabsf(low) < INFINITY ? low : 0.f;         // (nothing, where the product is infinite)
@@ -154,7 +163,7 @@ __global__ __launch_bounds__(mc_atomic_threads(S, FLY)) void mc_grad_atomic_kern
             }
         }
     } else {
-        constexpr int kFly = S < 8 ? S : 8;              // entries of a lane group in flight
+        constexpr int kFly = FEW ? 2 : S < 8 ? S : 8;    // entries of a lane group in flight
         for (int64_t kb = k0 + sub; kb < k1; kb += (int64_t)kSubs * kFly) {
             int a[kFly], b[kFly];
             float mv[kFly], ua[kFly], vb[kFly];
@@ -204,7 +213,8 @@ __global__ __launch_bounds__(mc_atomic_threads(S, FLY)) void mc_grad_atomic_kern
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int q = 1; q < kThreads / kWave; ++q) red[0] += red[q];
-        if (partials64) partials64[(int64_t)w * nblk + blockIdx.x] = red[0];
+        if (FEW) unsafeAtomicAdd(partials64 + (int64_t)w * nblk + blockIdx.x % (unsigned)nblk, red[0]);   // (nblk: slots)
+        else if (partials64) partials64[(int64_t)w * nblk + blockIdx.x] = red[0];
         else partials[(int64_t)w * nblk + blockIdx.x] = (float)red[0];
     }
 }
@@ -846,6 +856,19 @@ struct McCost {
     double one, flight, binned; // atomics an entry at a time, atomics with entries in flight, binned
     double walk, stream;        // binned: the fullest bin's records, which one workgroup walks; all records and rows
 };
+// Requests of one worker that meet in the same 64 bytes, us.
+static double mc_meet(const lsgd_mc_batch& b)
+{
+    const double r = b.r, lo = b.m < b.n ? b.m : b.n;
+    return (double)mc_entries(b) / (lo * r > 16 ? lo * r / 16 : 1.0) * (0.0068 + 0.0045 * (r < 16 ? r : 16));
+}
+// Requests of 64 bytes, and where one side is narrow their queues at its few channels, us.
+static double mc_queue(int W, const lsgd_mc_batch& b)
+{
+    const double r = b.r, lo = b.m < b.n ? b.m : b.n, hi = b.m < b.n ? b.n : b.m;
+    const double pieces = b.r % 16 == 0 || 16 % b.r == 0 ? (r > 16 ? r / 16 : 1.0) : 1.0 + (r - 1) / 16;
+    return 1e-3 * (double)W * (double)mc_entries(b) * (0.093 * pieces + 0.017 * log(hi / lo) / (1 + 0.14 * r));
+}
 static double dominant(double a, double b, double c = 0.0) { return sqrt(sqrt(a * a * a * a + b * b * b * b + c * c * c * c)); }
 static McCost mc_cost(int W, const lsgd_mc_batch& b, int vw)
 {
@@ -854,9 +877,8 @@ static McCost mc_cost(int W, const lsgd_mc_batch& b, int vw)
     const double rows = (double)W * (lo + hi) * r * 4.0 / 5e6;          // one pass over all factor rows
     // Atomics: requests of 64 bytes and, where one side is narrow, their queues at its few channels; or the requests of
     // one worker that meet in the same 64 bytes; or the latency of the entries that a lane group takes one after the other.
-    const double pieces = b.r % 16 == 0 || 16 % b.r == 0 ? (r > 16 ? r / 16 : 1.0) : 1.0 + (r - 1) / 16;
-    const double queue = thousands * (0.093 * pieces + 0.017 * log(hi / lo) / (1 + 0.14 * r));
-    const double meet = nb / (lo * r > 16 ? lo * r / 16 : 1.0) * (0.0068 + 0.0045 * (r < 16 ? r : 16));
+    const double queue = mc_queue(W, b);
+    const double meet = mc_meet(b);
     int group = 1;                                                      // lanes per entry
     while (group < b.r && group < kWave) group <<= 1;
     const double turns = ceil(r / group);
@@ -959,6 +981,26 @@ size_t mc_partials(int W, const lsgd_mc_batch& b)
     return (size_t)W * (size_t)(nblk > 0 ? nblk : 1);
 }
 
+// Entries in flight, two per lane group: workgroups per worker, which share a few double slots (where the sums of larger workgroups
+// or of bins would lie); none: 0.  Where workgroups of 256 entries are no more than compute units and it is the chain of a lane
+// group's entries that the launch waits for, not requests that queue (5 x 12534 entries of 1911 x 919, rank 5, 16.7 / 18.6) or
+// meet in the same lines (2 x 29762 of 223 x 2125, rank 12, 19.0 / 22.9).  180 drawn gradients and steps of this size 0.91 of the time.
+struct McFew { int workgroups, slots; };
+static McFew mc_few(int W, const lsgd_mc_batch& b)
+{
+    McFew f{0, 0};
+    int group = 4;
+    while (group < b.r && group < kWave) group <<= 1;
+    const int64_t nb = mc_entries(b), blocks = (nb + kMcEntriesPerBlock - 1) / kMcEntriesPerBlock;
+    const int64_t room = (int64_t)(mc_partials(W, b) / (size_t)W) / 2;                   // doubles per worker
+    if (b.r <= 2 || nb <= 0 || (int64_t)W * blocks > 256 || room < 1 || W > kColumnMaxWorkers || mc_meet(b) > 5.0 ||
+        1.1 * mc_queue(W, b) > (group > 32 ? 8.6 : 4.3))
+        return f;
+    f.workgroups = (int)((nb + mc_few_entries(group) - 1) / mc_few_entries(group));
+    f.slots = (int)(room < kLossSlots ? room : kLossSlots);
+    return f;
+}
+
 static size_t mc_binned_bytes(int W, const lsgd_mc_batch& b)
 {
     const size_t slots = (size_t)mc_prep_blocks(W, b) * mc_ept(W, b) * kPrepThreads;
@@ -1059,14 +1101,14 @@ static void launch_side_lanes(const float* x, float* g, int W, int64_t ld, const
     else launch_side<32, 2, VW>(x, g, W, ld, b, S, partials, runs, s);
 }
 
-static void launch_fill_zero(float* g, int W, int64_t ld, hipStream_t s)
+static void launch_fill_zero(float* g, int W, int64_t ld, hipStream_t s, double* sums = nullptr, int n = 0)
 {
     const bool v4 = (reinterpret_cast<uintptr_t>(g) & 15u) == 0 && (ld % 4 == 0);
     int64_t blocks = ((v4 ? ld / 4 : ld) + 255) / 256;
     if (blocks > 2048) blocks = 2048;
     if (blocks < 1) blocks = 1;
-    if (v4) hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, g, ld);
-    else hipLaunchKernelGGL(fill_zero_scalar_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, g, ld);
+    if (v4) hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, g, ld, sums, n);
+    else hipLaunchKernelGGL(fill_zero_scalar_kernel, dim3((unsigned)blocks, (unsigned)W), dim3(256), 0, s, g, ld, sums, n);
 }
 
 template <int S>
@@ -1145,19 +1187,22 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
         else launch_side_lanes<1>(x, g, W, ld, b, S, st.partials, mc_runs(path.cost, W), s);
         return S.sums ? finish_loss(kLossSlots, S.sums) : finish_loss(S.nbinsU, nullptr);
     }
-    const int nblk = (int)((nb + kMcEntriesPerBlock - 1) / kMcEntriesPerBlock);
+    const McFew few = route == kMcFlight ? mc_few(W, b) : McFew{0, 0};
+    const int nblk = few.workgroups ? few.workgroups : (int)((nb + kMcEntriesPerBlock - 1) / kMcEntriesPerBlock);
     // the block sums of squares stay in double where the binned path's scratch, idle now, has room for them (always for
     // ranks that are multiples of four and could have taken that path)
-    double* sums64 = st.scratch_bytes >= sizeof(double) * (size_t)W * (size_t)nblk ? reinterpret_cast<double*>(st.scratch) : nullptr;
-    launch_fill_zero(g, W, ld, s);                       // general path: whole rows (padding included), then atomics
+    double* sums64 = few.workgroups ? reinterpret_cast<double*>(st.partials)
+                   : st.scratch_bytes >= sizeof(double) * (size_t)W * (size_t)nblk ? reinterpret_cast<double*>(st.scratch) : nullptr;
+    launch_fill_zero(g, W, ld, s, few.workgroups ? sums64 : nullptr, few.slots);   // general path: whole rows (padding included), then atomics
     if (nblk > 0) {
         dim3 grid((unsigned)nblk, (unsigned)W);
         const float two_c = 2.0f * b.c;
-#define LSGD_MC_LAUNCH_AS(S, FLY)                                                                               \
-    hipLaunchKernelGGL((mc_grad_atomic_kernel<S, true, FLY>), grid, dim3(mc_atomic_threads(S, FLY)), 0, s, x, g, ld, b.m, b.n, b.r, \
-                       b.rows, b.cols, b.vals, b.batch_idx, nb, two_c, st.partials, sums64, nblk, b.entries)
+#define LSGD_MC_LAUNCH_AS(S, FLY, FEW)                                                                          \
+    hipLaunchKernelGGL((mc_grad_atomic_kernel<S, true, FLY, FEW>), grid, dim3(mc_atomic_threads(S, FLY)), 0, s, x, g, ld, b.m, b.n, b.r, \
+                       b.rows, b.cols, b.vals, b.batch_idx, nb, two_c, st.partials, sums64, FEW ? few.slots : nblk, b.entries)
 // (ranks 1 and 2 have short chains anyway: the estimate never gives them entries in flight)
-#define LSGD_MC_LAUNCH(S) do { if (route == kMcFlight) LSGD_MC_LAUNCH_AS(S, (S > 2)); else LSGD_MC_LAUNCH_AS(S, false); } while (0)
+#define LSGD_MC_LAUNCH(S) do { if (few.workgroups) LSGD_MC_LAUNCH_AS(S, (S > 2), (S > 2)); else if (route == kMcFlight) LSGD_MC_LAUNCH_AS(S, (S > 2), false); \
+                               else LSGD_MC_LAUNCH_AS(S, false, false); } while (0)
         if (b.r <= 1) LSGD_MC_LAUNCH(1);
         else if (b.r <= 2) LSGD_MC_LAUNCH(2);
         else if (b.r <= 4) LSGD_MC_LAUNCH(4);
@@ -1168,7 +1213,7 @@ hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, i
 #undef LSGD_MC_LAUNCH
 #undef LSGD_MC_LAUNCH_AS
     }
-    return finish_loss(nblk, sums64);
+    return finish_loss(few.workgroups ? few.slots : nblk, sums64);
 }
 
 // Objective values only: the residual pass of the general path without its atomics, one partial sum per

@@ -189,3 +189,18 @@ def test_small_batch_overflow_stays_infinite(r):
     assert pr.pop.get_losses() == [float("inf")] * 2
     g = pr.g.cpu().numpy()[0, :600 * r].reshape(600, r)
     assert np.all(np.isposinf(g[[7, 307]])) and np.all(np.isfinite(np.delete(g, [7, 307], 0)))
+
+
+# entries in flight, two per lane group: every width of a group, remainders of its workgroups, one slot of sums and several
+@pytest.mark.parametrize("W,m,n,r,B", [(4, 200, 150, 3, 257), (3, 300, 140, 4, 500), (5, 1000, 800, 5, 256), (2, 400, 300, 9, 1), (4, 700, 600, 17, 1000),
+                                       (2, 300, 200, 50, 400), (16, 2000, 3000, 10, 1500), (1, 3000, 5000, 6, 12_000), (3, 129, 64, 7, 63)])
+def test_few_entries_in_flight_match_oracle(W, m, n, r, B):
+    pr, batch, P = problem(m, n, r, min(m * n, 5000), W, B, seed=r + B)
+    for _ in range(2):                                   # the slots of the sums are cleared by every call
+        pr.g.fill_(float("nan"))
+        pr.pop.grad_loss(batch)
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(pr.pop.get_losses(), pr.ora.losses, rtol=1e-6)
+        g = pr.g.cpu().numpy()
+        assert rel_l2_rows(g[:, :P], pr.ora.g[:, :P]).max() <= 1e-5
+        assert np.all(g[:, P:] == 0)
