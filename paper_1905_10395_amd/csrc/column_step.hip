@@ -924,20 +924,16 @@ void launch_vec(const ColumnDev& s, bool nt, hipStream_t st)
     if constexpr (!STREAMS) hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR>), grid, dim3(kThreads), lds, st, s);
 }
 
-// vec: columns per thread wished for; no more than the registers hold.
+// vec: columns per thread; with momentum no more than two.
 template <int MODE, int NR = 0>
 void launch_mode(const ColumnDev& s, int vec, bool mom, bool nt, hipStream_t st)
 {
     if (mom) {
-        if constexpr (NR <= 16) {
-            if (vec >= 2) { launch_vec<2, 1, MODE, NR>(s, nt, st); return; }
-        }
-        launch_vec<1, 1, MODE, NR>(s, nt, st);
+        if (vec >= 2) launch_vec<2, 1, MODE, NR>(s, nt, st);
+        else launch_vec<1, 1, MODE, NR>(s, nt, st);
     } else {
-        if constexpr (NR <= 16) {
-            if (vec == 4) { launch_vec<4, 0, MODE, NR>(s, nt, st); return; }
-        }
-        if (vec >= 2) launch_vec<2, 0, MODE, NR>(s, nt, st);
+        if (vec == 4) launch_vec<4, 0, MODE, NR>(s, nt, st);
+        else if (vec >= 2) launch_vec<2, 0, MODE, NR>(s, nt, st);
         else launch_vec<1, 0, MODE, NR>(s, nt, st);
     }
 }
@@ -952,6 +948,14 @@ bool update_in_registers(const ColumnStep& q, double bytes)
     const PullParams& p = q.pull;
     if (p.W > 16) return bytes <= 100e6;
     return p.W > 4 || p.mu != 0.0f || q.cap || q.capG || bytes <= 35e6;
+}
+
+// One column per thread.
+template <int MODE, int NR = 0>
+void launch_narrow(const ColumnDev& s, bool mom, bool nt, hipStream_t st)
+{
+    if (mom) launch_vec<1, 1, MODE, NR>(s, nt, st);
+    else launch_vec<1, 0, MODE, NR>(s, nt, st);
 }
 
 // A pull alone: whether one pass over all rows beats a walk group by group, which touches only rows that move.  One pass / by
@@ -1072,12 +1076,12 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     case kUpdate: launch_mode<kUpdate>(s, vec, mom, nt, stream); break;
     case kUpdateOnes: launch_mode<kUpdateOnes>(s, vec, mom, nt, stream); break;
     case kUpdateRegs:
-        if (p.W <= 4) launch_mode<kUpdateRegs, 4>(s, vec, mom, nt, stream);
-        else if (p.W <= 8) launch_mode<kUpdateRegs, 8>(s, vec, mom, nt, stream);
-        else if (p.W <= 12) launch_mode<kUpdateRegs, 12>(s, vec, mom, nt, stream);
-        else if (p.W <= 16) launch_mode<kUpdateRegs, 16>(s, vec, mom, nt, stream);
-        else if (p.W <= 24) launch_mode<kUpdateRegs, 24>(s, vec, mom, nt, stream);
-        else launch_mode<kUpdateRegs, 32>(s, vec, mom, nt, stream);
+        if (p.W <= 4) launch_narrow<kUpdateRegs, 4>(s, mom, nt, stream);
+        else if (p.W <= 8) launch_narrow<kUpdateRegs, 8>(s, mom, nt, stream);
+        else if (p.W <= 12) launch_narrow<kUpdateRegs, 12>(s, mom, nt, stream);
+        else if (p.W <= 16) launch_narrow<kUpdateRegs, 16>(s, mom, nt, stream);
+        else if (p.W <= 24) launch_narrow<kUpdateRegs, 24>(s, mom, nt, stream);
+        else launch_narrow<kUpdateRegs, 32>(s, mom, nt, stream);
         break;
     case kComm: launch_mode<kComm>(s, vec, mom, nt, stream); break;
     case kUpdatePull: launch_mode<kUpdatePull>(s, vec, mom, nt, stream); break;
@@ -1090,14 +1094,11 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
         if (p.W <= 4) launch_mode<kCommRegs, 4>(s, vec, mom, nt, stream);
         else launch_mode<kCommRegs, 8>(s, vec, mom, nt, stream);
         break;
-    case kCenter:
-        if (mom) launch_vec<1, 1, kCenter, 0>(s, nt, stream);
-        else launch_vec<1, 0, kCenter, 0>(s, nt, stream);
-        break;
+    case kCenter: launch_narrow<kCenter>(s, mom, nt, stream); break;
     case kCenterRegs:
-        if (p.W <= 8) launch_mode<kCenterRegs, 8>(s, vec, mom, nt, stream);
-        else if (p.W <= 16) launch_mode<kCenterRegs, 16>(s, vec, mom, nt, stream);
-        else launch_mode<kCenterRegs, 32>(s, vec, mom, nt, stream);
+        if (p.W <= 8) launch_narrow<kCenterRegs, 8>(s, mom, nt, stream);
+        else if (p.W <= 16) launch_narrow<kCenterRegs, 16>(s, mom, nt, stream);
+        else launch_narrow<kCenterRegs, 32>(s, mom, nt, stream);
         break;
     }
     return hipGetLastError();
