@@ -413,9 +413,11 @@ lsgd_status do_select(lsgd_population* p, const float* losses, const uint8_t* re
 // Whether the one-launch update by column owners is the faster one.  Up to 300 MB read and written per update the
 // launches it saves weigh more than what workgroups that hop between rows lose against row streams (whole step, all
 // leaders re-selected, us, row streams / column owners: 96 MB 31 / 22, 240 MB 62 / 45; 384 MB 81 / 74 but 66 / 75 with
-// none re-selected, 640 MB 137 / 142).  A thread walks the groups one after the other, at most four rows in flight, so
-// groups of one worker are the other end (16 x 250 000 with momentum, half of the leaders re-selected, 16 groups
-// 30 / 35, 4 groups 23 / 18), and so are pairs of many workers or with nothing re-selected (16 x 250 000, 8 groups: half
+// none re-selected, 640 MB 137 / 142).  Whole steps of groups of two and more
+// go from registers: 32 in pairs x 1003 with momentum 44 / 8.7, 18 in 6 groups x 250 001 with (90 MB) 36 / 21, one of 16 pairs x
+// 140 001 with 32 / 23, 16 in pairs x 140 001 with nothing re-selected 9.9 / 8.4; but not with nothing re-selected beyond 16
+// workers: 32 in 8 groups x 10 001 with momentum 7.2 / 8.9, x 40 001 7.2 / 8.5.  Separate updates, and larger ones, walk the
+// groups one after the other, at most four rows in flight, so pairs are their other end (16 x 250 000, 8 groups: half
 // re-selected 27 / 24, none 20 / 21; 32 x 100 000, 16 groups: 28 / 31, 17 / 27).  Between these sizes
 // the lines are interpolated; 240 drawn populations (1 to 64 workers, 500 to 8 million columns, all the calls that come
 // this way) against row streams alone: half of them change, by a third on average, and none gets more than 5 % slower.
@@ -435,7 +437,8 @@ bool column_step(const lsgd_population* p, bool selects, int fresh, bool whole)
         return W <= 8 || 4 * fresh >= W || p->cfg.P < 5000 || (whole && W <= 16);
     }
     if (W > 32 || bytes > 300e6) return false;
-    if (selects) return W >= 4 * G || (W <= 16 && W >= 2 * G);
+    if (selects) return W >= 4 * G || (W >= 2 * G && (W <= 16 || (whole && bytes <= 100e6)));
+    if (whole && W <= 16 && W >= 2 * G && bytes <= 100e6) return true;
     return W >= 4 * G && (W <= 16 || bytes >= 30e6);                   // 32 x 30 000, 8 groups: 12.3 / 13.5
 }
 
