@@ -13,7 +13,7 @@
 // written per update, 450 for groups of one and Algorithm 1, 650 for elastic averaging (the caller's rules), the saved
 // launches weigh more.  Measured, whole lsgd_step on external
 // gradients, row streams -> this kernel, us: 4 x 1003 14.6 -> 4.5; 12 x 271 117 with momentum and kept leaders
-// 24.6 -> 15.3; 16 x 250 000 with momentum 30.0 -> 17.3;
+// 24.6 -> 15.3; 16 x 250 000 with momentum 30.0 -> 17.3 (by groups);
 // 16 x 1 250 000 without 62.5 -> 41.5; elastic averaging, 16 x 1 250 000 with momentum 85.3 -> 73.3.
 //
 // What bounds a small call is not memory but one wavefront's instructions, 2.7 ns each, and the loads that it waits for
