@@ -771,14 +771,17 @@ bool long_and_few(const GemmArgs& g, int W) { return g.K >= 1024 && (int64_t)((g
 
 // Whether 32 rows go with 32 columns instead of 64.  What a workgroup of so few rows waits for is its own chain of K steps,
 // most of it additions to the double sums, of which half as many columns have half; twice as many workgroups load A again.
-// So with compute units to spare, and where tiles of 64 columns would fill a second round of them badly.  64 / 32 columns, us
-// (the same bits): objective of 784-300-100-10, 8 workers, batch 50, 21.7 / 18.7, of 3072-1500-10, 12 x 16 (288 tiles of 64)
-// 39.2 / 36.0; 118 objectives and gradients: up to 160 tiles 0.93 of the time, 161 to 256 0.99 forward but 1.03 to 1.04
-// d-input, 257 to 400 0.94, more than that 1.05 to 1.10.
+// So while every narrow tile has a compute unit of its own, and where two or three rounds of them replace wide tiles that fill a
+// second round badly; not where some units have two narrow tiles and would have had one wide one.  64 / 32 columns, us
+// (the same bits): objective of 784-300-100-10, 8 workers, batch 50, 21.7 / 18.7, of 3072-1500-10, 12 x 16 (576 narrow tiles)
+// 39.2 / 36.0; but with fp32 inputs of 2000-491-10, 20 x 32 (320 of them) 23.2 / 27.5, of 3072-1222-10, 10 x 64 (780) 46.5 / 55.0.
+// 260 objectives and gradients: up to 256 narrow tiles 0.91 of the time; 257 to 448 1.03 forward, 0.98 d-input; 513 to 768 0.95,
+// beyond 1.05.
+template <int EPI>
 bool narrow(const GemmArgs& g, int W)
 {
-    const int64_t tiles = (int64_t)((g.N + 63) / 64) * W * ((g.M + 31) / 32);
-    return tiles <= 160 || (tiles > 256 && tiles <= 400);
+    const int64_t tiles = (int64_t)((g.N + 31) / 32) * W * ((g.M + 31) / 32);
+    return tiles <= (EPI == EPI_DX ? 320 : 256) || (tiles > 512 && tiles <= 768);
 }
 
 template <int EPI>
@@ -813,7 +816,7 @@ void launch_epi(const GemmArgs& g, int W, hipStream_t s)
         }
         if (g.M > 64 && fill128) launch_tile<128, 64, 2, 2, 1, 64, EPI>(g, W, s);
         else if (g.M > 32 && fill64) launch_tile<64, 64, 1, 2, 2, 128, EPI>(g, W, s);
-        else if (narrow(g, W)) launch_tile<32, 32, 1, 1, 4, 128, EPI>(g, W, s);
+        else if (narrow<EPI>(g, W)) launch_tile<32, 32, 1, 1, 4, 128, EPI>(g, W, s);
         else launch_tile<32, 64, 1, 1, 4, 128, EPI>(g, W, s);
     }
 }
@@ -850,16 +853,20 @@ void launch_gemm_group(const GemmGroup& q, int W, int epi, hipStream_t s)
 }
 
 // The 32-row tile converts as it goes: its products are small enough that a launch for the conversion counts and reading
-// the inputs in fp32 once per 64 columns does not.  Objective of 617-132-10, 3 workers, batch 16, 14.2 -> 12.4 us, step of
+// the inputs in fp32 once per tile of columns does not.  Objective of 617-132-10, 3 workers, batch 16, 14.2 -> 12.4 us, step of
 // 784-300-100-10, 8 x 50, 51.9 -> 50.6; 47 drawn calls, part of them of this size, 0.966 of the time.  Where every 64 columns read
 // more than 90 MB a second time in all, the launch is the cheaper way: gradients, launch of its own / as it goes, us, batch 32,
 // 3072-4096-10, 16 workers (201 MB) 278 / 288, 8 (101 MB) 155.7 / 158.5; 3072-2048-10, 16 (101 MB) 148 / 150, 8 (50 MB) 86.9 / 86.6.
+// It is the 64 columns that are counted, also where tiles have 32 and read twice as much (objectives, launch of its own / 32 / 64
+// columns as it goes, 384 and 363 wide tiles: 3072-2048-10, 12 x 32 (75 MB by 64) 49.3 / 49.3 / 49.0; 3072-723-10, 32 x 32 (75 MB)
+// 54.4 / 47.4 / 47.0; the other way 4096-2666-10, 8 x 32 (88 MB) 55.4 / 59.9 / 59.2): what the launch saves depends on how often
+// an input is read, what it costs on how large the inputs are, and the volume is no more than their product.
 // The larger tiles have no registers for fp32 pieces in flight.
 bool launch_gemm_ragged_f32(const GemmArgs& g, int W, hipStream_t s)
 {
     if (2.0 * W * (double)g.M * g.K * ((g.N + 63) / 64) > 90e6) return false;
     if (g.K < 8 || long_and_few(g, W) || (g.M > 32 && fills(g, W, 64)) || (g.M > 64 && fills(g, W, 128))) return false;
-    if (narrow(g, W)) launch_tile<32, 32, 1, 1, 4, 128, EPI_FWD, true>(g, W, s);
+    if (narrow<EPI_FWD>(g, W)) launch_tile<32, 32, 1, 1, 4, 128, EPI_FWD, true>(g, W, s);
     else launch_tile<32, 64, 1, 1, 4, 128, EPI_FWD, true>(g, W, s);
     return true;
 }
