@@ -37,7 +37,7 @@ import workloads as wl
 # taken on: reported as null once the code of any of these files (comments and white space aside) differs.
 PULL_TRAFFIC = {"files": ("pull_update.hip", "pull_common.h", "update_math.h"), "code_sha256_16": "cbd6c737ce46389e", "bytes_per_launch": 7.666e9,
                 "key": (32, 11_689_512)}
-MC_TRAFFIC = {"files": ("mc_grad.hip",), "code_sha256_16": "0eee10f571f6aadf", "bytes_per_launch": 3.968e8,
+MC_TRAFFIC = {"files": ("mc_grad.hip",), "code_sha256_16": "be187dbfae2059a4", "bytes_per_launch": 3.970e8,
               "key": (16, 65536, 20000, 20000, 32)}
 CSRC = os.path.join(ROOT, "paper_1905_10395_amd", "csrc")
 

@@ -167,7 +167,10 @@ lsgd_status lsgd_destroy_population(lsgd_population* pop);
 /* Writes g[W, ld] (unused padding columns zeroed) and losses (device [W]; NULL =
  * the population's own loss buffer, the one lsgd_step uses).  For
  * LSGD_BATCH_EXTERNAL copies the given losses into the population's buffer when
- * `losses` is NULL, otherwise into `losses`.                                   */
+ * `losses` is NULL, otherwise into `losses`.  For LSGD_BATCH_MC gradients and
+ * losses are sums in no fixed order (losses in double, rounded once): equal
+ * calls can differ in the last bit, and workers of equal rows on equal entries
+ * need not tie.                                                                */
 lsgd_status lsgd_grad_loss(lsgd_population* pop, const lsgd_batch* batch, float* losses);
 
 /* Objective values only: losses[i] = f_i(x_i) on worker i's part of the batch at

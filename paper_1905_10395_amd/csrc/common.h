@@ -113,7 +113,7 @@ hipError_t launch_cast_shadow(const float* x, uint16_t* xb, int W, int64_t P, in
 size_t mc_scratch_bytes(int W, const lsgd_mc_batch& b);
 size_t mc_scratch_required(int W, const lsgd_mc_batch& b);   // without which a batch is refused
 size_t mc_partials(int W, const lsgd_mc_batch& b);
-void mc_describe_path(int W, const lsgd_mc_batch& b, int vw, size_t scratch_bytes, int out[5]);
+void mc_describe_path(int W, const lsgd_mc_batch& b, int vw, size_t scratch_bytes, int out[7]);
 // parts != NULL: the caller's next launch can finish the losses; if parts->n is 0 afterwards they are in `losses`
 hipError_t launch_mc_grad_loss(const float* x, float* g, float* losses, int W, int64_t P, int64_t ld,
                                const lsgd_mc_batch& b, const DeviceState& st, hipStream_t s, LossParts* parts);

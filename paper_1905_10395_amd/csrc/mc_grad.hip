@@ -205,7 +205,8 @@ __global__ __launch_bounds__(mc_atomic_threads(S, FLY)) void mc_grad_atomic_kern
             }
         }
     }
-    // block sum of squared residuals in a fixed order (one lane of a group holds its sum)
+    // block sum of squared residuals in a fixed order (one lane of a group holds its sum); FEW: several blocks then add theirs to
+    // one slot, in the order in which they come
 #pragma unroll
     for (int d = S; d < kWave; d <<= 1) sq += __shfl_xor(sq, d, kWave);
     __shared__ double red[kThreads / kWave];
@@ -876,7 +877,10 @@ static McCost mc_cost(int W, const lsgd_mc_batch& b, int vw)
     const double lo = b.m < b.n ? b.m : b.n, hi = b.m < b.n ? b.n : b.m;
     const double rows = (double)W * (lo + hi) * r * 4.0 / 5e6;          // one pass over all factor rows
     // Atomics: requests of 64 bytes and, where one side is narrow, their queues at its few channels; or the requests of
-    // one worker that meet in the same 64 bytes; or the latency of the entries that a lane group takes one after the other.
+    // one worker that meet in the same 64 bytes; or the latency of the entries that a lane group takes one after the other:
+    // eight of them.  (Batches of mc_few's range take two and less time, which the estimate does not know: of its constants
+    // that is the one that was not fitted again.  Up to rank 32 they go this way all the same; above, most go binned: 150 drawn
+    // ones of ranks 33 to 64 there 1.34 times as long as with two entries, 9.3 us against 10.5 to 17.)
     const double queue = mc_queue(W, b);
     const double meet = mc_meet(b);
     int group = 1;                                                      // lanes per entry
@@ -982,7 +986,7 @@ size_t mc_partials(int W, const lsgd_mc_batch& b)
 }
 
 // Entries in flight, two per lane group: workgroups per worker, which share a few double slots (where the sums of larger workgroups
-// or of bins would lie); none: 0.  Where workgroups of 256 entries are no more than compute units and it is the chain of a lane
+// or of bins would lie; the order of their additions is open, so that losses can differ in the last bit between calls); none: 0.  Where workgroups of 256 entries are no more than compute units and it is the chain of a lane
 // group's entries that the launch waits for, not requests that queue (5 x 12534 entries of 1911 x 919, rank 5, 16.7 / 18.6) or
 // meet in the same lines (2 x 29762 of 223 x 2125, rank 12, 19.0 / 22.9).  180 drawn gradients and steps of this size 0.91 of the time.
 struct McFew { int workgroups, slots; };
@@ -1037,13 +1041,16 @@ static McPath mc_path(int W, const lsgd_mc_batch& b, int vw, size_t scratch_byte
     return p;
 }
 
-// What mc_path says, for tests: route, factors held in LDS, and where binned the prepare workgroups and their entries.
-void mc_describe_path(int W, const lsgd_mc_batch& b, int vw, size_t scratch_bytes, int out[5])
+// What mc_path says, for tests: route, factors held in LDS, where binned the prepare workgroups and their entries, and where
+// lane groups take two entries each the workgroups per worker and the slots of their sums (mc_few).
+void mc_describe_path(int W, const lsgd_mc_batch& b, int vw, size_t scratch_bytes, int out[7])
 {
     const McPath p = mc_path(W, b, vw, scratch_bytes);
     out[0] = p.route; out[1] = p.lu; out[2] = p.lv;
     out[3] = p.route == kMcBinned ? mc_prep_blocks(W, b) : 0;
     out[4] = p.route == kMcBinned ? mc_ept(W, b) * kPrepThreads : 0;
+    const McFew few = p.route == kMcFlight ? mc_few(W, b) : McFew{0, 0};
+    out[5] = few.workgroups; out[6] = few.slots;
 }
 
 // The binned path's scratch is a condition only for ranks that are multiples of four; with others a workspace

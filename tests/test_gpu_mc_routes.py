@@ -192,8 +192,11 @@ def test_small_batch_overflow_stays_infinite(r):
 
 
 # entries in flight, two per lane group: every width of a group, remainders of its workgroups, one slot of sums and several
-@pytest.mark.parametrize("W,m,n,r,B", [(4, 200, 150, 3, 257), (3, 300, 140, 4, 500), (5, 1000, 800, 5, 256), (2, 400, 300, 9, 1), (4, 700, 600, 17, 1000),
-                                       (2, 300, 200, 50, 400), (16, 2000, 3000, 10, 1500), (1, 3000, 5000, 6, 12_000), (3, 129, 64, 7, 63)])
+FEW = [(4, 200, 150, 3, 257), (3, 300, 140, 4, 500), (5, 1000, 800, 5, 256), (2, 400, 300, 9, 1), (4, 700, 600, 17, 1000),
+       (2, 300, 200, 50, 400), (16, 2000, 3000, 10, 1500), (1, 3000, 5000, 6, 12_000), (3, 129, 64, 7, 63)]
+
+
+@pytest.mark.parametrize("W,m,n,r,B", FEW)
 def test_few_entries_in_flight_match_oracle(W, m, n, r, B):
     pr, batch, P = problem(m, n, r, min(m * n, 5000), W, B, seed=r + B)
     for _ in range(2):                                   # the slots of the sums are cleared by every call

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = [([8, 70, 4], 3, 5), ([9, 64, 10], 2, 1), ([7, 40, 3], 3, 33), ([15, 33, 20, 2], 5, 31), ([130, 65, 10], 4, 33),
           ([784, 300, 100, 10], 8, 50), ([617, 132, 10], 3, 64), ([1030, 40, 10], 2, 33), ([129, 600, 70], 8, 70),
           ([256, 128, 10], 3, 128), ([96, 64], 3, 20), ([200, 1030, 10], 16, 50), ([100, 300, 10], 16, 70),
-          ([64, 1500, 10], 12, 16)]
+          ([64, 1500, 10], 12, 16), ([200, 490, 10], 20, 32)]
 
 
 @pytest.mark.parametrize("dims,W,B", SHAPES)

@@ -31,6 +31,7 @@ SHAPES = [
     ([130, 300, 10], 16, 70),     # 32 rows: 64 columns where tiles fill the compute units once,
     ([257, 1500, 10], 12, 16),    # 32 where they would fill them twice,
     ([70, 1030, 10], 13, 33),     # 64 again beyond
+    ([200, 490, 10], 20, 32),     # forward 64 where narrow tiles would be two on some units and one on others, d-input 32
 ]
 
 

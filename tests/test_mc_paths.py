@@ -14,9 +14,18 @@ ONE, FLIGHT, BINNED, LDS = range(4)
 
 def path(W, m, n, r, B, vw=None):
     """Route, whether the gradients of U and of V are held in LDS, prepare workgroups and their entries (binned)."""
+    return describe(W, m, n, r, B, vw)[:5]
+
+
+def few(W, m, n, r, B):
+    """Workgroups per worker of two entries per lane group, and the slots that their loss sums share; 0, 0: another loop."""
+    return tuple(describe(W, m, n, r, B)[5:])
+
+
+def describe(W, m, n, r, B, vw=None):
     f = getattr(L.lib(), "_ZN4lsgd16mc_describe_pathEiRK13lsgd_mc_batchimPi")
     f.argtypes, f.restype = [C.c_int, C.POINTER(binding._MC), C.c_int, C.c_size_t, C.POINTER(C.c_int)], None
-    out = (C.c_int * 5)()
+    out = (C.c_int * 7)()
     d = binding._MC(m, n, r, None, None, None, B, 1, B, 1.0, None)      # (the rule reads sizes, no arrays)
     f(W, C.byref(d), vw or (4 if r % 4 == 0 else 2 if r % 2 == 0 else 1), 1 << 40, out)
     return list(out)
@@ -50,6 +59,16 @@ def test_bins_on_dies(W, m, n, B):
 @pytest.mark.parametrize("r", [4, 8, 10])
 def test_rows_of_any_alignment(r):
     assert path(9, 4001, 3000, r, 40000, vw=1 if r == 8 else 2)[0] == BINNED
+
+
+def test_two_entries_per_lane_group():
+    """Every shape of the GPU test goes this way: with one slot, with several and with all eight, fewer and more workgroups than
+    slots, at every width of a lane group but the narrowest two.  Not where requests queue or meet in the same lines."""
+    assert [few(*s) for s in routes.FEW] == [(3, 1), (4, 1), (4, 4), (1, 2), (16, 3), (13, 1), (24, 8), (188, 8), (1, 1)]
+    assert {min(64, 1 << (s[3] - 1).bit_length()) for s in routes.FEW} == {4, 8, 16, 32, 64}
+    assert few(1, 3000, 5000, 6, 30_000)[0] > 0 and few(1, 3000, 5000, 6, 35_000) == (0, 0)
+    assert few(5, 60, 5000, 12, 3_000)[0] > 0 and few(5, 60, 5000, 12, 5_000) == (0, 0)
+    assert few(4, 700, 600, 2, 256) == (0, 0)
 
 
 @pytest.mark.parametrize("m,n,r,W,B,blocks,entries", [(5400, 4400, 4, 2, 263_000, 257, 1024), (3100, 2900, 4, 4, 263_000, 129, 2048),
