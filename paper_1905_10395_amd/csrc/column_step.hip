@@ -191,33 +191,19 @@ __device__ __forceinline__ void load_row(const ColumnDev& s, int i, uint32_t col
     m = (KIND == 1) ? (NT ? ld_stream<VEC>(at(a.m, a.ld, i, col)) : ld_vec<VEC>(at(a.m, a.ld, i, col))) : zero_of(V());
 }
 
-// Row u of p, by either way of addressing.
-template <bool LONG, class T>
-__device__ __forceinline__ T* row_at(const ColumnDev& s, T* p, int u, uint32_t col)
-{
-    if constexpr (LONG) return at(p, s.a.ld, u, col);
-    else return at(p, col * 4u + (uint32_t)u * s.pitch);
-}
-// Loads one behind the other, 64 clocks apart and by the longer addresses, where requests for eight rows in one go were
-// slower, us, before / in one go / so: Algorithm 1's iteration without momentum, 8 workers in 2 groups x 1 250 001 26.5 /
-// 30.3 / 26.9, groups of one 35.1 / 40.5 / 35.7, one group x 40 001 6.3 / 6.9 / 6.2.  (Two columns per thread: x 600 001
-// 16.1 / 14.6 / 17.5.)
-template <int VEC, int KIND, int NR> constexpr bool kPaced = KIND == 0 && NR == 8 && VEC != 2;
-
-// UPDATE: gradients and momentum too (asked for each row's, a call that may have none takes twice the time).
-template <int VEC, int KIND, bool NT, bool PACED, bool UPDATE, int NR>
-__device__ __forceinline__ void load_rows(const ColumnDev& s, uint32_t col, Rows<VEC, NR>& r)
+// UPDATE: gradients and momentum too.
+template <int VEC, int KIND, bool NT, bool UPDATE, int NR>
+__device__ __forceinline__ void load_rows(const ColumnDev& s, uint32_t off, Rows<VEC, NR>& r)
 {
     using V = typename Vec<VEC>::type;
     const PullDev& a = s.a;
 #pragma unroll
     for (int u = 0; u < NR; ++u)
         if (u < a.W) {
-            if (PACED && u) __builtin_amdgcn_s_sleep(1);
-            r.x[u] = NT ? ld_stream<VEC>(row_at<PACED>(s, a.x, u, col)) : ld_vec<VEC>(row_at<PACED>(s, a.x, u, col));
+            r.x[u] = NT ? ld_stream<VEC>(at(a.x, off + (uint32_t)u * s.pitch)) : ld_vec<VEC>(at(a.x, off + (uint32_t)u * s.pitch));
             r.g[u] = r.m[u] = zero_of(V());
-            if (UPDATE) r.g[u] = ld_stream<VEC>(row_at<PACED>(s, a.g, u, col));
-            if (UPDATE && KIND == 1) r.m[u] = NT ? ld_stream<VEC>(row_at<PACED>(s, a.m, u, col)) : ld_vec<VEC>(row_at<PACED>(s, a.m, u, col));
+            if (UPDATE) r.g[u] = ld_stream<VEC>(at(a.g, off + (uint32_t)u * s.pitch));
+            if (UPDATE && KIND == 1) r.m[u] = NT ? ld_stream<VEC>(at(a.m, off + (uint32_t)u * s.pitch)) : ld_vec<VEC>(at(a.m, off + (uint32_t)u * s.pitch));
         }
 }
 
@@ -445,17 +431,17 @@ __device__ __forceinline__ int row_word(const ColumnDev& s, int lane, int gid, i
 }
 
 // Algorithm 1's iteration, or a communication pull alone, with every row in registers.  The update's leaders are kept copies.
-template <int VEC, int KIND, bool NT, bool PACED, int NR>
-__device__ __forceinline__ void regs_update(const ColumnDev& s, uint32_t col, Rows<VEC, NR>& r)
+template <int VEC, int KIND, bool NT, int NR>
+__device__ __forceinline__ void regs_update(const ColumnDev& s, uint32_t off, Rows<VEC, NR>& r)
 {
     using V = typename Vec<VEC>::type;
     const PullDev& a = s.a;
     const bool pullL = a.lamL != 0.0f, pullG = a.lamG != 0.0f;
     const Coef c = make_coef<V>(a);
     V zg = zero_of(V()), zl = zero_of(V()), nzl = zero_of(V());
-    if (pullG) zg = ld_vec<VEC>(row_at<PACED>(s, a.Z, a.G, col));
-    if (pullL) zl = ld_vec<VEC>(row_at<PACED>(s, a.Z, 0, col));
-    if (pullL && a.G > 1) nzl = ld_vec<VEC>(row_at<PACED>(s, a.Z, 1, col));
+    if (pullG) zg = ld_vec<VEC>(at(a.Z, off + (uint32_t)a.G * s.pitch));
+    if (pullL) zl = ld_vec<VEC>(at(a.Z, off));
+    if (pullL && a.G > 1) nzl = ld_vec<VEC>(at(a.Z, off + s.pitch));
     int j = 0, end = a.offsets[1];
 #pragma unroll
     for (int u = 0; u < NR; ++u)
@@ -463,24 +449,26 @@ __device__ __forceinline__ void regs_update(const ColumnDev& s, uint32_t col, Ro
             if (u == end) {                              // the next group
                 ++j; end = a.offsets[j + 1];
                 zl = nzl;
-                if (pullL && j + 1 < a.G) nzl = ld_vec<VEC>(row_at<PACED>(s, a.Z, j + 1, col));
+                if (pullL && j + 1 < a.G) nzl = ld_vec<VEC>(at(a.Z, off + (uint32_t)(j + 1) * s.pitch));
             }
             update_vec<KIND, V>(r.x[u], r.g[u], r.m[u], zl, zg, c);
-            if (KIND == 1) { if (NT) st_stream(row_at<PACED>(s, a.m, u, col), r.m[u]); else st_vec(row_at<PACED>(s, a.m, u, col), r.m[u]); }
+            if (KIND == 1) { if (NT) st_stream(at(a.m, off + (uint32_t)u * s.pitch), r.m[u]); else st_vec(at(a.m, off + (uint32_t)u * s.pitch), r.m[u]); }
         }
 }
 
-template <int VEC, bool NT, bool PACED, int NR>
-__device__ __forceinline__ void regs_comm(const ColumnDev& s, const Leaders& L, uint32_t col, Rows<VEC, NR>& r)
+template <int VEC, bool NT, bool UPDATE, int NR>
+__device__ __forceinline__ void regs_comm(const ColumnDev& s, const Leaders& L, uint32_t off, Rows<VEC, NR>& r)
 {
     using V = typename Vec<VEC>::type;
     const PullDev& a = s.a;
     Coef c = make_coef<V>(a);
     c.cG = L.freshG ? s.commG : 0.0f;
+    // (eight rows of one column: asked at run time, or their branches are joined: 8 workers x 95 180 7.3 us instead of 6.5)
+    const bool stores = UPDATE && (VEC > 1 || NR < 8 || s.update);
     V zg = zero_of(V());
     if (L.freshG) {
         zg = row_of<VEC, NR>(r, __builtin_amdgcn_readfirstlane(L.gl));
-        if (a.Z) st_vec(row_at<PACED>(s, a.Z, a.G, col), zg);
+        if (a.Z) st_vec(at(a.Z, off + (uint32_t)a.G * s.pitch), zg);
     }
     int j = -1, end = 0, lead = 0;
     bool fresh = false;
@@ -496,15 +484,15 @@ __device__ __forceinline__ void regs_comm(const ColumnDev& s, const Leaders& L, 
                 zl = zero_of(V());                       // (the last group's may be infinite: not even times zero)
                 if (fresh) {                             // (no row of the group has moved yet)
                     zl = row_of<VEC, NR>(r, lead);
-                    if (a.Z) st_vec(row_at<PACED>(s, a.Z, j, col), zl);
+                    if (a.Z) st_vec(at(a.Z, off + (uint32_t)j * s.pitch), zl);
                 }
             }
             const bool moves = (c.cL != 0.0f && !(fresh && u == lead)) || c.cG != 0.0f;   // (a leader's pull to itself is zero)
             V none = zero_of(V());
             if (moves) update_vec<2, V>(r.x[u], none, none, zl, zg, c);
-            if (moves || s.update) {
-                if (NT) st_stream(row_at<PACED>(s, a.x, u, col), r.x[u]); else st_vec(row_at<PACED>(s, a.x, u, col), r.x[u]);
-                if (a.xb) st_bf16(row_at<PACED>(s, a.xb, u, col), r.x[u]);
+            if (moves || stores) {
+                if (NT) st_stream(at(a.x, off + (uint32_t)u * s.pitch), r.x[u]); else st_vec(at(a.x, off + (uint32_t)u * s.pitch), r.x[u]);
+                if (a.xb) st_bf16(at(a.xb, off + (uint32_t)u * s.pitch), r.x[u]);
             }
         }
 }
@@ -723,6 +711,13 @@ __device__ __forceinline__ void load_pick(const ColumnDev& s, Pick& p)
     }
 }
 
+// The same behind the rows' loads, where registers are full while those are on their way.
+__device__ __forceinline__ void load_pick_behind(const ColumnDev& s, Pick& p)
+{
+    __builtin_amdgcn_sched_barrier(0);
+    load_pick(s, p);
+}
+
 // One step of a segmented minimum scan: the key of the lane that CTRL names counts if it is of the same group.  Lanes
 // that have none keep theirs (ROWS: the rows of 16 lanes that take part).
 template <int CTRL, int ROWS>
@@ -839,7 +834,7 @@ __global__ __launch_bounds__(kThreads) void capture_kernel(ColumnDev s)
     }
 }
 
-enum { kUpdate, kUpdateOnes, kComm, kCommRegs, kCenter, kCenterRegs, kPull, kUpdatePull, kUpdateRegs };
+enum { kUpdate, kUpdateOnes, kComm, kCommRegs, kCenter, kCenterRegs, kPull, kUpdatePull, kUpdateRegs, kPullRegs };
 
 // What one thread does at its columns.  Loads are under way during the selection.  NR: rows in registers (*Regs).
 template <int VEC, int KIND, bool NT, int MODE, int NR>
@@ -848,7 +843,10 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
     const Leaders& before = s.select == 1 ? chosen : now;
     const Leaders& after = s.select ? chosen : now;
     Pick pick;
-    if ((MODE != kCenter && MODE != kCenterRegs) || blockIdx.x == 0) load_pick(s, pick);
+    // (eight rows of four columns: with what the selection reads, and every row's offset kept from its load to its store, 100
+    // registers, one wavefront less per SIMD than with 96: 8 workers in 2 groups x 1 250 001 30.9 us instead of 27.6)
+    constexpr bool FULL = MODE == kCommRegs && VEC == 4 && NR == 8;
+    if (!FULL && ((MODE != kCenter && MODE != kCenterRegs) || blockIdx.x == 0)) load_pick(s, pick);
     if constexpr (MODE == kUpdate || MODE == kCenter || MODE == kUpdatePull) {
         constexpr bool CENTER = MODE == kCenter;
         RowBatch<VEC> first;
@@ -877,21 +875,23 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
         if (live) stream_columns<VEC, KIND, NT, MODE == kComm>(s, before, after, (uint32_t)col, cur, next);
     } else {
         Rows<VEC, NR> r;
-        constexpr bool PACED = MODE == kCommRegs && kPaced<VEC, KIND, NR>;
-        if (live) {
-            if (MODE == kCenterRegs || s.update) load_rows<VEC, KIND, NT, PACED, true, NR>(s, (uint32_t)col, r);
-            else load_rows<VEC, KIND, NT, PACED, false, NR>(s, (uint32_t)col, r);
-        }
         if constexpr (MODE == kCenterRegs) {
+            if (live) load_rows<VEC, KIND, NT, true, NR>(s, (uint32_t)col * 4u, r);
             if (blockIdx.x == 0) choose_leaders(s, pick, now, chosen);                   // the losses alone
             if (live) regs_easgd<VEC, KIND, NT, NR>(s, (uint32_t)col * 4u, r);
             return;
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        constexpr bool UPDATE = MODE == kCommRegs;
+        uint32_t off = (uint32_t)col * 4u;
+        if (live) load_rows<VEC, KIND, NT, UPDATE, NR>(s, off, r);
+        if constexpr (FULL) load_pick_behind(s, pick);
+        // (stores count in the same counter: with one column per thread rows that are waited for between them take 5 % longer)
+        if constexpr (VEC == 1) __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt 0
         choose_leaders(s, pick, now, chosen);
         if (!live) return;
-        if (s.update) regs_update<VEC, KIND, NT, PACED, NR>(s, (uint32_t)col, r);
-        regs_comm<VEC, NT, PACED, NR>(s, after, (uint32_t)col, r);
+        if constexpr (FULL) asm("" : "+v"(off));         // (the compiler works it out anew)
+        if constexpr (UPDATE) regs_update<VEC, KIND, NT, NR>(s, off, r);
+        regs_comm<VEC, NT, UPDATE, NR>(s, after, off, r);
     }
 }
 
@@ -917,7 +917,7 @@ void launch_vec(const ColumnDev& s, bool nt, hipStream_t st)
     const dim3 grid((unsigned)((whole + per - 1) / per + (whole < cols)));
     // one kernel where a way has but one kind of accesses: what is walked group by group is read again, rows in registers and
     // the two passes of elastic averaging stream
-    constexpr bool PLAIN = MODE == kPull || MODE == kUpdatePull, STREAMS = MODE == kCommRegs || MODE == kCenter;
+    constexpr bool PLAIN = MODE == kPull || MODE == kUpdatePull, STREAMS = MODE == kCommRegs || MODE == kPullRegs || MODE == kCenter;
     const size_t lds = MODE == kUpdateRegs ? (size_t)(s.a.W + s.a.G) * kThreads * VEC * sizeof(float) : 0;
     if constexpr (!PLAIN)
         if (nt || STREAMS) { hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR>), grid, dim3(kThreads), lds, st, s); return; }
@@ -956,6 +956,14 @@ void launch_narrow(const ColumnDev& s, bool mom, bool nt, hipStream_t st)
 {
     if (mom) launch_vec<1, 1, MODE, NR>(s, nt, st);
     else launch_vec<1, 0, MODE, NR>(s, nt, st);
+}
+
+template <int MODE, int NR>
+void launch_pull(const ColumnDev& s, int vec, hipStream_t st)
+{
+    if (vec == 4) launch_vec<4, 0, MODE, NR>(s, false, st);
+    else if (vec == 2) launch_vec<2, 0, MODE, NR>(s, false, st);
+    else launch_vec<1, 0, MODE, NR>(s, false, st);
 }
 
 // A pull alone: whether one pass over all rows beats a walk group by group, which touches only rows that move.  One pass / by
@@ -1022,18 +1030,18 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
                (!p.Z || aligned(p.Z, 4 * v)) && (!p.xb || aligned(p.xb, 2 * v)) && (!q.center || aligned(q.center, 4 * v));
     };
     const double bytes = (mom ? 20.0 : 12.0) * (double)p.W * (double)p.P;
-    // 13 to 16 rows with momentum, while much of x is still in the memory-side cache at its second reading: twice costs less than
-    // registers for sixteen rows of three values.  Twice / once, us: 16 x 1 250 001 (400 MB) 73 / 79, 15 x 1 250 001 69 / 74, 14 x
-    // 1 250 001 65 / 68, 13 x 1 250 001 (325 MB) 62 / 65, 15 x 1 400 001 (420 MB) 82 / 83; 16 x 1 400 001 (448 MB) 89 / 90, 14 x
-    // 1 666 667 (467 MB) 94 / 87, 16 x 1 866 667 (597 MB) 135 / 123, 13 x 2 000 001 109 / 94; 12 x 1 250 001 (300 MB) 60 / 59.
     // whole matrices within reach of 32-bit offsets (rows may lie far apart)
     const bool near = (double)(p.W + 1) * (double)p.ld < (double)(1u << 30);
     const bool by_groups = q.comm && ((p.W <= 8 && !near) || (q.update ? pull_behind_update(q, bytes) : !pull_in_one_pass(q)));
     const bool held = near && q.select == 1 && p.W >= 2 * p.G && update_in_registers(q, bytes);
     s.pitch = (uint32_t)p.ld * 4u;
+    // 13 to 16 rows with momentum, while much of x is still in the memory-side cache at its second reading: twice costs less than
+    // registers for sixteen rows of three values.  Twice / once, us: 16 x 1 250 001 (400 MB) 73 / 79, 15 x 1 250 001 69 / 74, 14 x
+    // 1 250 001 65 / 68, 13 x 1 250 001 (325 MB) 62 / 65, 15 x 1 400 001 (420 MB) 82 / 83; 16 x 1 400 001 (448 MB) 89 / 90, 14 x
+    // 1 666 667 (467 MB) 94 / 87, 16 x 1 866 667 (597 MB) 135 / 123, 13 x 2 000 001 109 / 94; 12 x 1 250 001 (300 MB) 60 / 59.
     const int mode = q.center ? ((mom && p.W > 12 && p.W <= 16 && bytes > 300e6 && bytes <= 430e6) || !near ? kCenter : kCenterRegs)
                    : !q.comm ? (p.W == p.G ? kUpdateOnes : held ? kUpdateRegs : kUpdate)
-                   : by_groups ? (q.update ? kUpdatePull : kPull) : p.W <= 8 ? kCommRegs : kComm;
+                   : by_groups ? (q.update ? kUpdatePull : kPull) : p.W <= 8 ? (q.update ? kCommRegs : kPullRegs) : kComm;
     // Columns per thread: one, so that small rows still make enough wavefronts; more once there are plenty, but not where
     // every row's loads are under way at once, which wait less with one.  Update by groups: 16
     // workers without momentum, 600 000 columns 27.0 / 25.6 / 24.5 us with 1 / 2 / 4, 250 000 columns 13.8 / 13.7 / 14.1;
@@ -1043,13 +1051,13 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     // 1 250 001 19.8 / 17.6 / 14.1.  Groups of one, 8 x 271 117, 13.6 / 12.8 / 12.5.
     // Elastic averaging, 16 without momentum x 600 001 22 / 29 / 29, with momentum x 140 001 10.0 / 12.8 / 12.8.
     int vec = 1;
-    if (mode == kUpdate || mode == kUpdatePull || mode == kCenter) {
+    if (mode == kUpdate || mode == kUpdatePull) {
         if (!mom && p.P >= 500000) vec = p.P >= 1000000 ? 4 : 2;
         // (a bf16 copy is written two bytes per lane with one column: 8 workers x 266 610 columns, whole step 62.9 -> 61.0 us)
         if (p.xb && p.P >= 100000 && vec < 2) vec = 2;
     } else if (mode == kCommRegs) {
         vec = p.P < 400000 ? 1 : mom || p.P < 1000000 ? 2 : 4;
-    } else if (mode != kUpdateRegs && mode != kCenterRegs) {
+    } else if (mode != kUpdateRegs && mode != kCenterRegs && mode != kCenter) {
         vec = p.P < (mode == kComm ? 100000 : 200000) ? 1 : p.P < 500000 ? 2 : 4;
     }
     if (!q.update) vec = 4;
@@ -1085,14 +1093,14 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
         break;
     case kComm: launch_mode<kComm>(s, vec, mom, nt, stream); break;
     case kUpdatePull: launch_mode<kUpdatePull>(s, vec, mom, nt, stream); break;
-    case kPull:
-        if (vec == 4) launch_vec<4, 0, kPull, 0>(s, false, stream);
-        else if (vec == 2) launch_vec<2, 0, kPull, 0>(s, false, stream);
-        else launch_vec<1, 0, kPull, 0>(s, false, stream);
-        break;
+    case kPull: launch_pull<kPull, 0>(s, vec, stream); break;
     case kCommRegs:
         if (p.W <= 4) launch_mode<kCommRegs, 4>(s, vec, mom, nt, stream);
         else launch_mode<kCommRegs, 8>(s, vec, mom, nt, stream);
+        break;
+    case kPullRegs:
+        if (p.W <= 4) launch_pull<kPullRegs, 4>(s, vec, stream);
+        else launch_pull<kPullRegs, 8>(s, vec, stream);
         break;
     case kCenter: launch_narrow<kCenter>(s, mom, nt, stream); break;
     case kCenterRegs:
