@@ -13,7 +13,7 @@
 // written per update, 450 for groups of one and Algorithm 1, 650 for elastic averaging (the caller's rules), the saved
 // launches weigh more.  Measured, whole lsgd_step on external
 // gradients, row streams -> this kernel, us: 4 x 1003 14.6 -> 4.5; 12 x 271 117 with momentum and kept leaders
-// 24.6 -> 15.3; 16 x 250 000 with momentum 30.0 -> 17.3 (by groups);
+// 24.6 -> 13.3; 16 x 250 000 with momentum 30.0 -> 17.3 (by groups);
 // 16 x 1 250 000 without 62.5 -> 41.5; elastic averaging, 16 x 1 250 000 with momentum 85.3 -> 73.3.
 //
 // What bounds a small call is not memory but one wavefront's instructions, 2.7 ns each, and the loads that it waits for
@@ -22,10 +22,13 @@
 // to a 32-bit offset.  Against a chain of dependent loads, scans by LDS shuffles and 64-bit row addresses: 4 x 1003 4.5 ->
 // 3.6 us, 16 in 4 groups x 40 001 with momentum 10.1 -> 6.5.
 //
+// Medium calls whose workgroups are all resident at once hold their stores back until the chip has read its rows
+// (holds_stores_*): reads among stores come slower.
+//
 // The ways through the rows (launch_column_step), by what a thread has to wait for:
 //   the update of groups of several workers     every row in registers, leaders found in an LDS copy (held_update); nothing but
 //                                               the selection is waited for twice: 12 in 3 groups x 271 117 with momentum 18.2 ->
-//                                               15.4, pairs, 16 x 140 001, 18.5 -> 8.7
+//                                               15.5 (13.3 with stores held back), pairs, 16 x 140 001, 18.5 -> 8.7
 //   ... of more than 16 workers beyond 100 MB   group by group, the next rows' loads under way (update_columns)
 //   ... of groups of one, and Algorithm 1's     one pass over all rows, two batches ahead, whatever group they are in
 //   iterations of more than 8 workers           (stream_columns): groups one after the other would leave a single row in
@@ -50,6 +53,7 @@ namespace {
 
 constexpr int kThreads = 256;
 template <int VEC> constexpr int kRowsInFlight = VEC == 1 ? 8 : 4;
+constexpr int kHoldLoads = 3;
 
 struct ColumnDev {
     PullDev a;                   // the update (lamL, lamG: its coefficients)
@@ -711,10 +715,18 @@ __device__ __forceinline__ void load_pick(const ColumnDev& s, Pick& p)
     }
 }
 
-// The same behind the rows' loads, where registers are full while those are on their way.
+// The same behind the rows' loads, where registers are full while those are on their way; HOLD: and behind kHoldLoads loads
+// that go one after the other, which hold the call's stores back (holds_stores_*).
+template <bool HOLD>
 __device__ __forceinline__ void load_pick_behind(const ColumnDev& s, Pick& p)
 {
     __builtin_amdgcn_sched_barrier(0);
+    if (HOLD && threadIdx.x < kWave) {
+        for (int h = 0; h < kHoldLoads; ++h) {
+            const int v = s.a.lead[(int)threadIdx.x < s.a.G ? threadIdx.x : 0];
+            asm volatile("" :: "v"(v) : "memory");       // (here it has arrived)
+        }
+    }
     load_pick(s, p);
 }
 
@@ -837,7 +849,7 @@ __global__ __launch_bounds__(kThreads) void capture_kernel(ColumnDev s)
 enum { kUpdate, kUpdateOnes, kComm, kCommRegs, kCenter, kCenterRegs, kPull, kUpdatePull, kUpdateRegs, kPullRegs };
 
 // What one thread does at its columns.  Loads are under way during the selection.  NR: rows in registers (*Regs).
-template <int VEC, int KIND, bool NT, int MODE, int NR>
+template <int VEC, int KIND, bool NT, int MODE, int NR, bool HOLD>
 __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Leaders& chosen, int64_t col, bool live)
 {
     const Leaders& before = s.select == 1 ? chosen : now;
@@ -845,12 +857,13 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
     Pick pick;
     // (eight rows of four columns: with what the selection reads, and every row's offset kept from its load to its store, 100
     // registers, one wavefront less per SIMD than with 96: 8 workers in 2 groups x 1 250 001 30.9 us instead of 27.6)
-    constexpr bool FULL = MODE == kCommRegs && VEC == 4 && NR == 8;
-    if (!FULL && ((MODE != kCenter && MODE != kCenterRegs) || blockIdx.x == 0)) load_pick(s, pick);
+    constexpr bool FULL = MODE == kCommRegs && VEC == 4 && NR == 8, BEHIND = HOLD || FULL;
+    if (!BEHIND && ((MODE != kCenter && MODE != kCenterRegs) || blockIdx.x == 0)) load_pick(s, pick);
     if constexpr (MODE == kUpdate || MODE == kCenter || MODE == kUpdatePull) {
         constexpr bool CENTER = MODE == kCenter;
         RowBatch<VEC> first;
         if (live) load_rows<VEC, KIND, NT>(s.a, 0, pass_end<CENTER>(s.a, 0), col, first);
+        if constexpr (BEHIND) load_pick_behind<HOLD>(s, pick);
         if (!CENTER || blockIdx.x == 0) choose_leaders(s, pick, now, chosen);              // (CENTER: the losses alone)
         if (!live) return;
         if (CENTER) center_columns<VEC>(s, col);
@@ -860,6 +873,7 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
         HeldRows<VEC, NR> r;
         const uint32_t off = (uint32_t)col * 4u;
         if (live) held_load<VEC, KIND, NT, NR>(s, off, r);
+        if constexpr (BEHIND) load_pick_behind<HOLD>(s, pick);
         choose_leaders<true>(s, pick, now, chosen);
         if (live) held_update<VEC, KIND, NT, NR>(s, chosen, off, r);
     } else if constexpr (MODE == kPull) {
@@ -871,6 +885,7 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
             load_batch<VEC, KIND, NT>(s, 0, (uint32_t)col, cur);
             load_batch<VEC, KIND, NT>(s, kRowsInFlight<VEC>, (uint32_t)col, next);
         }
+        if constexpr (BEHIND) load_pick_behind<HOLD>(s, pick);
         choose_leaders(s, pick, now, chosen);
         if (live) stream_columns<VEC, KIND, NT, MODE == kComm>(s, before, after, (uint32_t)col, cur, next);
     } else {
@@ -884,7 +899,7 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
         constexpr bool UPDATE = MODE == kCommRegs;
         uint32_t off = (uint32_t)col * 4u;
         if (live) load_rows<VEC, KIND, NT, UPDATE, NR>(s, off, r);
-        if constexpr (FULL) load_pick_behind(s, pick);
+        if constexpr (BEHIND) load_pick_behind<HOLD>(s, pick);
         // (stores count in the same counter: with one column per thread rows that are waited for between them take 5 % longer)
         if constexpr (VEC == 1) __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt 0
         choose_leaders(s, pick, now, chosen);
@@ -896,45 +911,81 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
 }
 
 // The last workgroup takes the columns that are left over, one per thread, if there are any.
-template <int VEC, int KIND, bool NT, int MODE, int NR>
+// HOLD: stores are held back.
+template <int VEC, int KIND, bool NT, int MODE, int NR, bool HOLD>
 __global__ __launch_bounds__(kThreads) void column_step_kernel(ColumnDev s)
 {
     __shared__ Leaders now, chosen;
     const int64_t whole = s.a.col1 - (s.a.col1 - s.a.col0) % VEC, first = s.a.col0 + (int64_t)blockIdx.x * kThreads * VEC;
     if (VEC == 1 || first < whole) {
         const int64_t col = first + threadIdx.x * VEC;
-        step_thread<VEC, KIND, NT, MODE, NR>(s, now, chosen, col, col < whole);
+        step_thread<VEC, KIND, NT, MODE, NR, HOLD>(s, now, chosen, col, col < whole);
     } else {
         const int64_t col = whole + threadIdx.x;
-        step_thread<1, KIND, NT, MODE, NR>(s, now, chosen, col, col < s.a.col1);
+        step_thread<1, KIND, NT, MODE, NR, HOLD>(s, now, chosen, col, col < s.a.col1);
     }
 }
 
-template <int VEC, int KIND, int MODE, int NR>
-void launch_vec(const ColumnDev& s, bool nt, hipStream_t st)
+size_t held_bytes(int W, int G) { return (size_t)(W + G) * kThreads * sizeof(float); }     // (one column per thread)
+
+int64_t workgroups(int64_t cols, int vec)
 {
-    const int64_t cols = s.a.col1 - s.a.col0, per = (int64_t)kThreads * VEC, whole = cols / VEC * VEC;
-    const dim3 grid((unsigned)((whole + per - 1) / per + (whole < cols)));
+    const int64_t per = (int64_t)kThreads * vec, whole = cols / vec * vec;
+    return (whole + per - 1) / per + (whole < cols);
+}
+
+// Kernels that hold their stores back: those that ask for all rows, or all they have room for, before they store any, where the
+// rules below (holds_stores_*) can send a call to them.
+template <int VEC, int KIND, int MODE, int NR>
+constexpr bool kCanHold = MODE == kCommRegs ? (KIND ? 20.0 : 12.0) * NR * 1536 * kThreads * VEC >= 40e6
+                        : MODE == kUpdateOnes ? VEC == 4 || (VEC == 2 && KIND == 1)
+                        : MODE == kUpdateRegs ? NR > 4 : MODE == kUpdate && VEC == 4 && KIND == 0;
+
+// How many workgroups of a kernel that holds its stores back are resident at once, on 256 compute units: by its registers,
+// which are asked for once, and the LDS it is launched with.
+template <int VEC, int KIND, int MODE, int NR>
+int64_t resident(size_t lds)
+{
+    static const int by_registers = [] {
+        int n = 0;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, column_step_kernel<VEC, KIND, true, MODE, NR, true>, kThreads, 0) == hipSuccess ? n : 0;
+    }();
+    const int by_lds = (int)(160 * 1024 / (lds + 2048));
+    return 256 * (int64_t)(by_registers < by_lds ? by_registers : by_lds);
+}
+
+template <int VEC, int KIND, int MODE, int NR>
+void launch_vec(const ColumnDev& s, bool nt, bool hold, hipStream_t st)
+{
+    const dim3 grid((unsigned)workgroups(s.a.col1 - s.a.col0, VEC));
     // one kernel where a way has but one kind of accesses: what is walked group by group is read again, rows in registers and
-    // the two passes of elastic averaging stream
+    // the two passes of elastic averaging stream, and so does most of what holds its stores back
     constexpr bool PLAIN = MODE == kPull || MODE == kUpdatePull, STREAMS = MODE == kCommRegs || MODE == kPullRegs || MODE == kCenter;
-    const size_t lds = MODE == kUpdateRegs ? (size_t)(s.a.W + s.a.G) * kThreads * VEC * sizeof(float) : 0;
+    const size_t lds = MODE == kUpdateRegs ? held_bytes(s.a.W, s.a.G) : 0;
+    if constexpr (kCanHold<VEC, KIND, MODE, NR>) {
+        if (hold) {
+            if constexpr (MODE == kUpdateOnes)
+                if (!nt) { hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR, true>), grid, dim3(kThreads), lds, st, s); return; }
+            hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR, true>), grid, dim3(kThreads), lds, st, s);
+            return;
+        }
+    }
     if constexpr (!PLAIN)
-        if (nt || STREAMS) { hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR>), grid, dim3(kThreads), lds, st, s); return; }
-    if constexpr (!STREAMS) hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR>), grid, dim3(kThreads), lds, st, s);
+        if (nt || STREAMS) { hipLaunchKernelGGL((column_step_kernel<VEC, KIND, true, MODE, NR, false>), grid, dim3(kThreads), lds, st, s); return; }
+    if constexpr (!STREAMS) hipLaunchKernelGGL((column_step_kernel<VEC, KIND, false, MODE, NR, false>), grid, dim3(kThreads), lds, st, s);
 }
 
 // vec: columns per thread; with momentum no more than two.
 template <int MODE, int NR = 0>
-void launch_mode(const ColumnDev& s, int vec, bool mom, bool nt, hipStream_t st)
+void launch_mode(const ColumnDev& s, int vec, bool mom, bool nt, bool hold, hipStream_t st)
 {
     if (mom) {
-        if (vec >= 2) launch_vec<2, 1, MODE, NR>(s, nt, st);
-        else launch_vec<1, 1, MODE, NR>(s, nt, st);
+        if (vec >= 2) launch_vec<2, 1, MODE, NR>(s, nt, hold, st);
+        else launch_vec<1, 1, MODE, NR>(s, nt, hold, st);
     } else {
-        if (vec == 4) launch_vec<4, 0, MODE, NR>(s, nt, st);
-        else if (vec >= 2) launch_vec<2, 0, MODE, NR>(s, nt, st);
-        else launch_vec<1, 0, MODE, NR>(s, nt, st);
+        if (vec == 4) launch_vec<4, 0, MODE, NR>(s, nt, hold, st);
+        else if (vec >= 2) launch_vec<2, 0, MODE, NR>(s, nt, hold, st);
+        else launch_vec<1, 0, MODE, NR>(s, nt, hold, st);
     }
 }
 
@@ -950,20 +1001,72 @@ bool update_in_registers(const ColumnStep& q, double bytes)
     return p.W > 4 || p.mu != 0.0f || q.cap || q.capG || bytes <= 35e6;
 }
 
+// Holding stores back.  Where all workgroups of a launch are resident at once and ask for all their rows at once, those whose
+// rows come first would store while the others still wait for theirs, and reads among stores come slower: of 1221 workgroups
+// (4 workers x 1 250 001 without momentum, nothing re-selected) the last had its rows after 11.8 us, held back after 9.2.  So
+// the wavefront that selects first sends kHoldLoads loads one after the other.  They queue behind the rows of all: long while
+// the chip reads, short when it no longer does.  (A fixed number of clocks instead: 14.1 us and more where these take 12.7 and
+// nothing 13.9.  That the selection itself was once such a chain is why it was the faster one at these sizes.)  It costs about
+// 0.4 us where there is nothing to hold apart: smaller calls, or more workgroups than are resident, which store in turns anyway.
+//
+// Rows in registers, us, without / with: 12 in 3 groups x 271 117 with momentum (65 MB) 15.5 / 13.3, 8 in one x 271 117 with
+// (43 MB) 10.7 / 9.5, 16 in 4 x 170 001 with (54 MB, 665 workgroups) 12.5 / 11.4, 28 in 7 x 140 001 with (78 MB, 547) 20.2 / 17.2;
+// not 24 in 4 x 140 001 without (40 MB, 547) 10.6 / 11.0, 16 in 4 x 100 001 with (32 MB) 8.5 / 8.8, 16 in 4 x 450 001 without
+// (1758 workgroups on 1536 places) 20.1 / 20.9, 32 in 8 x 230 001 without (899 on 768) 21.9 / 23.6.
+template <int KIND, int NR>
+bool holds_stores_regs(const ColumnDev& s, double bytes)
+{
+    const int64_t n = workgroups(s.a.col1 - s.a.col0, 1);
+    return (bytes >= 55e6 || (bytes >= 40e6 && n >= 640)) && n <= resident<1, KIND, kUpdateRegs, NR>(held_bytes(s.a.W, s.a.G));
+}
+// By groups: only where one batch holds all rows (4 in 2 groups x 1 250 001 14.2 / 15.2).  4 in one x 1 250 001 13.9 / 12.8, x
+// 1 000 001 11.2 / 10.8, 3 x 1 250 001 11.3 / 10.3; not x 1 400 001 (1367 workgroups on 1280 places) 15.4 / 16.8.
+bool holds_stores_batch(const ColumnDev& s, int vec, double bytes)
+{
+    return s.select == 1 && vec == 4 && s.a.G == 1 && s.a.W <= kRowsInFlight<4> && bytes >= 36e6 &&
+           workgroups(s.a.col1 - s.a.col0, 4) <= resident<4, 0, kUpdate, 0>(0);
+}
+// Algorithm 1's iteration: 4 x 1 250 001 16.2 / 14.0, 4 x 700 001 with momentum 13.5 / 11.7, 8 in 2 groups x 600 001 with 23.6 /
+// 21.3, without 16.2 / 15.5, x 271 117 with (43 MB) 12.7 / 11.9; not 4 x 1 600 001 (1563 workgroups) 19.7 / 20.2, 4 x 271 117 with
+// (22 MB) 7.4 / 7.9, 8 in 2 x 140 001 with (547 workgroups) 8.9 / 9.3.
+bool holds_stores_comm(const ColumnDev& s, int vec, double bytes)
+{
+    const int64_t n = workgroups(s.a.col1 - s.a.col0, vec);
+    return bytes >= (vec == 4 ? 36e6 : 40e6) && n >= 768 && n <= 1536;
+}
+
+// Groups of one, while the batches ahead hold all rows: 8 x 800 001 without momentum (77 MB, 782 workgroups), one re-selected, 22.7 /
+// 20.5, x 400 001 with (64 MB) 19.3 / 17.6; not x 400 001 without (38 MB) 14.6 / 15.1, 4 x 1 250 001 without (1221 workgroups on
+// 1024 places) 17.1 / 18.9.
+template <int VEC, int KIND>
+bool holds_stores_ones(const ColumnDev& s, double bytes)
+{
+    return bytes >= 55e6 && bytes <= 100e6 && s.a.W <= 2 * kRowsInFlight<VEC> && workgroups(s.a.col1 - s.a.col0, VEC) <= resident<VEC, KIND, kUpdateOnes, 0>(0);
+}
+
 // One column per thread.
 template <int MODE, int NR = 0>
-void launch_narrow(const ColumnDev& s, bool mom, bool nt, hipStream_t st)
+void launch_narrow(const ColumnDev& s, bool mom, bool nt, bool hold, hipStream_t st)
 {
-    if (mom) launch_vec<1, 1, MODE, NR>(s, nt, st);
-    else launch_vec<1, 0, MODE, NR>(s, nt, st);
+    if (mom) launch_vec<1, 1, MODE, NR>(s, nt, hold, st);
+    else launch_vec<1, 0, MODE, NR>(s, nt, hold, st);
 }
 
 template <int MODE, int NR>
 void launch_pull(const ColumnDev& s, int vec, hipStream_t st)
 {
-    if (vec == 4) launch_vec<4, 0, MODE, NR>(s, false, st);
-    else if (vec == 2) launch_vec<2, 0, MODE, NR>(s, false, st);
-    else launch_vec<1, 0, MODE, NR>(s, false, st);
+    if (vec == 4) launch_vec<4, 0, MODE, NR>(s, false, false, st);
+    else if (vec == 2) launch_vec<2, 0, MODE, NR>(s, false, false, st);
+    else launch_vec<1, 0, MODE, NR>(s, false, false, st);
+}
+
+// The update of groups of several workers, every row in registers.
+template <int NR>
+void launch_held(const ColumnDev& s, bool mom, bool nt, double bytes, hipStream_t st)
+{
+    bool hold = false;
+    if constexpr (kCanHold<1, 0, kUpdateRegs, NR>) hold = nt && (mom ? holds_stores_regs<1, NR>(s, bytes) : holds_stores_regs<0, NR>(s, bytes));
+    launch_narrow<kUpdateRegs, NR>(s, mom, nt, hold, st);
 }
 
 // A pull alone: whether one pass over all rows beats a walk group by group, which touches only rows that move.  One pass / by
@@ -1056,7 +1159,7 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
         // (a bf16 copy is written two bytes per lane with one column: 8 workers x 266 610 columns, whole step 62.9 -> 61.0 us)
         if (p.xb && p.P >= 100000 && vec < 2) vec = 2;
     } else if (mode == kCommRegs) {
-        vec = p.P < 400000 ? 1 : mom || p.P < 1000000 ? 2 : 4;
+        vec = p.P < 400000 ? 1 : mom || p.P < 750000 ? 2 : 4;
     } else if (mode != kUpdateRegs && mode != kCenterRegs && mode != kCenter) {
         vec = p.P < (mode == kComm ? 100000 : 200000) ? 1 : p.P < 500000 ? 2 : 4;
     }
@@ -1080,33 +1183,36 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     }
     // (captures alone, above, take any number of columns)
     if (p.P > ((int64_t)1 << 30) && mode != kUpdate && mode != kPull && mode != kUpdatePull && mode != kCenter) return hipErrorInvalidValue;
+    const bool hold_comm = holds_stores_comm(s, mom && vec > 2 ? 2 : vec, bytes);
     switch (mode) {
-    case kUpdate: launch_mode<kUpdate>(s, vec, mom, nt, stream); break;
-    case kUpdateOnes: launch_mode<kUpdateOnes>(s, vec, mom, nt, stream); break;
-    case kUpdateRegs:
-        if (p.W <= 4) launch_narrow<kUpdateRegs, 4>(s, mom, nt, stream);
-        else if (p.W <= 8) launch_narrow<kUpdateRegs, 8>(s, mom, nt, stream);
-        else if (p.W <= 12) launch_narrow<kUpdateRegs, 12>(s, mom, nt, stream);
-        else if (p.W <= 16) launch_narrow<kUpdateRegs, 16>(s, mom, nt, stream);
-        else if (p.W <= 24) launch_narrow<kUpdateRegs, 24>(s, mom, nt, stream);
-        else launch_narrow<kUpdateRegs, 32>(s, mom, nt, stream);
+    case kUpdate: launch_mode<kUpdate>(s, vec, mom, nt, nt && !mom && holds_stores_batch(s, vec, bytes), stream); break;
+    case kUpdateOnes:
+        launch_mode<kUpdateOnes>(s, vec, mom, nt, mom ? vec >= 2 && holds_stores_ones<2, 1>(s, bytes) : vec == 4 && holds_stores_ones<4, 0>(s, bytes), stream);
         break;
-    case kComm: launch_mode<kComm>(s, vec, mom, nt, stream); break;
-    case kUpdatePull: launch_mode<kUpdatePull>(s, vec, mom, nt, stream); break;
+    case kUpdateRegs:
+        if (p.W <= 4) launch_held<4>(s, mom, nt, bytes, stream);
+        else if (p.W <= 8) launch_held<8>(s, mom, nt, bytes, stream);
+        else if (p.W <= 12) launch_held<12>(s, mom, nt, bytes, stream);
+        else if (p.W <= 16) launch_held<16>(s, mom, nt, bytes, stream);
+        else if (p.W <= 24) launch_held<24>(s, mom, nt, bytes, stream);
+        else launch_held<32>(s, mom, nt, bytes, stream);
+        break;
+    case kComm: launch_mode<kComm>(s, vec, mom, nt, false, stream); break;
+    case kUpdatePull: launch_mode<kUpdatePull>(s, vec, mom, nt, false, stream); break;
     case kPull: launch_pull<kPull, 0>(s, vec, stream); break;
     case kCommRegs:
-        if (p.W <= 4) launch_mode<kCommRegs, 4>(s, vec, mom, nt, stream);
-        else launch_mode<kCommRegs, 8>(s, vec, mom, nt, stream);
+        if (p.W <= 4) launch_mode<kCommRegs, 4>(s, vec, mom, nt, hold_comm, stream);
+        else launch_mode<kCommRegs, 8>(s, vec, mom, nt, hold_comm, stream);
         break;
     case kPullRegs:
         if (p.W <= 4) launch_pull<kPullRegs, 4>(s, vec, stream);
         else launch_pull<kPullRegs, 8>(s, vec, stream);
         break;
-    case kCenter: launch_narrow<kCenter>(s, mom, nt, stream); break;
+    case kCenter: launch_narrow<kCenter>(s, mom, nt, false, stream); break;
     case kCenterRegs:
-        if (p.W <= 8) launch_narrow<kCenterRegs, 8>(s, mom, nt, stream);
-        else if (p.W <= 16) launch_narrow<kCenterRegs, 16>(s, mom, nt, stream);
-        else launch_narrow<kCenterRegs, 32>(s, mom, nt, stream);
+        if (p.W <= 8) launch_narrow<kCenterRegs, 8>(s, mom, nt, false, stream);
+        else if (p.W <= 16) launch_narrow<kCenterRegs, 16>(s, mom, nt, false, stream);
+        else launch_narrow<kCenterRegs, 32>(s, mom, nt, false, stream);
         break;
     }
     return hipGetLastError();

@@ -19,7 +19,7 @@ SHAPES = [
     (2, [0, 2], 1, 1),                               # one column
     (4, [0, 4], 255, 256),                           # one thread short of a workgroup
     (2, [0, 2], 257, 257),                           # one thread past it, odd stride: one column per thread
-    (6, [0, 2, 4, 6], 301, 320),                     # pairs: one launch only where something is re-selected
+    (6, [0, 2, 4, 6], 301, 320),                     # pairs: one launch whether something is re-selected or not
     (7, [0, 1, 7], 257, 257),                        # groups of one and six
     (20, [0, 9, 20], 1, 1),                          # separate calls by row streams: small, more than 16 workers
     (20, [0, 9, 20], 255, 256),
@@ -169,7 +169,10 @@ def test_step_and_separate_calls_find_the_same_mlp_losses():
 # every row in registers: the numbers of rows at which another kernel takes over, and one less or more
 HELD = [(3, [0, 3], 257, 320), (5, [0, 2, 5], 256, 256), (8, [0, 3, 8], 513, 576), (9, [0, 1, 5, 9], 255, 256), (12, [0, 12], 64, 64),
         (13, [0, 2, 5, 7, 13], 301, 301), (16, [0, 2, 4, 6, 8, 10, 12, 14, 16], 769, 832), (17, [0, 8, 17], 63, 64),
-        (24, [0, 5, 24], 129, 192), (25, [0, 12, 25], 257, 257), (28, [0, 7, 14, 21, 28], 1, 1)]
+        (24, [0, 5, 24], 129, 192), (25, [0, 12, 25], 257, 257), (28, [0, 7, 14, 21, 28], 1, 1),
+        # more than 16 workers in pairs and triples: as many kept copies as the kernels have room for
+        (18, list(range(0, 19, 2)), 129, 192), (24, list(range(0, 25, 3)), 257, 320), (24, list(range(0, 25, 2)), 255, 256),
+        (31, [0, 3] + list(range(5, 32, 2)), 131, 192), (32, list(range(0, 33, 2)), 300, 320)]
 
 
 @pytest.mark.parametrize("mu,flags,wd", OPTIONS)
@@ -178,8 +181,14 @@ def test_rows_in_registers_match_oracle(W, off, P, ld, mu, flags, wd):
     test_whole_step_matches_oracle(W, off, P, ld, mu, flags, wd)
 
 
-@pytest.mark.parametrize("call", ["step", "alg1", "easgd"])
-def test_rows_far_apart(call):
+@pytest.mark.parametrize("mu,flags,wd", OPTIONS)
+@pytest.mark.parametrize("W,off,P,ld", HELD)
+def test_rows_in_registers_equal_row_streams(W, off, P, ld, mu, flags, wd):
+    test_step_equals_row_streams(W, off, P, ld, mu, flags, wd)
+
+
+@pytest.mark.parametrize("call,mu", [("step", 0.9), ("alg1", 0.9), ("easgd", 0.9), ("easgd", 0.0)])
+def test_rows_far_apart(call, mu):
     """Rows 2 GB apart are out of reach of 32-bit offsets: the same results, bit for bit, as with rows next to each other."""
     W, P = 2, 1000
     out = []
@@ -192,7 +201,7 @@ def test_rows_far_apart(call):
         center = torch.zeros(ld, device="cuda:0")
         center[:P] = torch.randn(P, device="cuda:0", generator=gen)
         losses = torch.tensor([0.5, 0.25], device="cuda:0")
-        pop = L.Population(t["x"], t["g"], 1, m=t["m"], z_snapshot=t["Z"], P=P, momentum=0.9)
+        pop = L.Population(t["x"], t["g"], 1, m=t["m"], z_snapshot=t["Z"], P=P, momentum=mu)
         batch = L.ExternalBatch(losses)
         for _ in range(2):
             if call == "step":
@@ -206,3 +215,67 @@ def test_rows_far_apart(call):
         del pop, t
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+# Sizes at which stores are held back behind all rows' loads (all workgroups resident at once): rows in registers of every kernel
+# with and without momentum, single batches, groups of one, iterations of Algorithm 1 with one, two and four columns per thread.
+def pairs(W): return list(range(0, W + 1, 2))
+HELD_BACK = [(8, [0, 3, 8], 420_001, 0.0), (12, [0, 4, 8, 12], 290_001, 0.0), (16, [0, 4, 8, 12, 16], 220_001, 0.0), (24, [0, 8, 16, 24], 195_001, 0.0),
+             (32, [0, 7, 16, 25, 32], 150_001, 0.0), (7, [0, 3, 7], 320_002, 0.9), (8, [0, 8], 260_001, 0.9), (12, pairs(12), 180_001, 0.9),
+             (16, pairs(16), 170_001, 0.9), (24, pairs(24), 120_001, 0.9), (32, pairs(32), 90_001, 0.9), (4, [0, 4], 1_000_001, 0.0),
+             (3, [0, 3], 1_250_003, 0.0), (8, list(range(9)), 800_001, 0.0), (8, list(range(9)), 600_002, 0.0), (8, list(range(9)), 400_001, 0.9),
+             (4, [0, 2, 4], 800_003, 0.0), (4, [0, 4], 500_001, 0.9), (6, [0, 2, 6], 600_001, 0.0)]
+
+
+@pytest.mark.parametrize("W,off,P,mu", HELD_BACK)
+def test_large_one_launch_calls_equal_separate_calls(W, off, P, mu):
+    """Steps in which all, some and no leaders are re-selected and iterations of Algorithm 1, against the separate calls, the
+    selection's by a kernel of its own: bit for bit."""
+    G, ld = len(off) - 1, (P + 63) // 64 * 64
+    gen = torch.Generator(device="cuda:0").manual_seed(W)
+    x0, g0 = (torch.randn((W, ld), device="cuda:0", generator=gen) for _ in range(2))
+    losses = [torch.rand(W, device="cuda:0", generator=gen) for _ in range(5)]
+    masks = [None, [1] + [0] * (G - 1), [0] * G]
+    res = []
+    for fused in (False, True):
+        x, g, Z = x0.clone(), g0.clone(), torch.zeros((G + 1, ld), device="cuda:0")
+        m = torch.zeros_like(x) if mu else None
+        pop = L.Population(x, g, G, m=m, z_snapshot=Z, P=P, momentum=mu, group_offsets=off)
+        for t, mask in enumerate(masks):
+            if fused:
+                pop.step(L.ExternalBatch(losses[t]), 0.05, 0.1, 0.05, mask, int(mask is None))
+            else:
+                pop.select_leaders(losses[t], mask, int(mask is None)); pop.pull_update(0.05, 0.1, 0.05)
+        for t in (3, 4):
+            comm = L.COMM_LOCAL | (L.COMM_GLOBAL if t == 3 else 0)
+            if fused:
+                pop.step_alg1(L.ExternalBatch(losses[t]), 0.05, 0.02, 0.01, 0.1, 0.07, comm, masks[t - 3])
+            else:
+                pop.step_alg1(L.ExternalBatch(losses[t]), 0.05, 0.02, 0.01, 0.1, 0.07, 0)
+                pop.select_leaders(None, masks[t - 3], int(t == 3)); pop.leader_pull(0.1, 0.07)
+        torch.cuda.synchronize()
+        res.append([v[:, :P].clone() for v in (x, Z) + ((m,) if mu else ())] + [pop.get_leaders(), pop.get_losses()])
+    a, b = res
+    assert a[-2:] == b[-2:] and all(torch.equal(u, v) for u, v in zip(a[:-2], b[:-2]))
+
+
+@pytest.mark.parametrize("W,P,mu", [(4, 600_001, 0.0), (2, 600_001, 0.9), (8, 271_117, 0.9), (16, 100_001, 0.9), (16, 250_001, 0.0)])
+def test_easgd_streaming_and_plain_accesses_agree(W, P, mu):
+    """The rows of a population around the sizes at which accesses change against the same rows alone in a small one, column by
+    column: the same bits."""
+    ld = (P + 63) // 64 * 64
+    gen = torch.Generator(device="cuda:0").manual_seed(W)
+    x0, g0 = (torch.randn((W, ld), device="cuda:0", generator=gen) for _ in range(2))
+    c0 = torch.randn(ld, device="cuda:0", generator=gen)
+    out = []
+    for cols in (slice(0, P), slice(P - 1000, P)):
+        n = cols.stop - cols.start
+        x, g, c = (torch.zeros((W, 1024) if n == 1000 else (W, ld), device="cuda:0") for _ in range(3))
+        x[:, :n] = x0[:, cols]; g[:, :n] = g0[:, cols]; c = c[0].clone(); c[:n] = c0[cols]
+        m, Z = torch.zeros_like(x) if mu else None, torch.zeros((2, x.shape[1]), device="cuda:0")
+        pop = L.Population(x, g, 1, m=m, z_snapshot=Z, P=n, momentum=mu)
+        for _ in range(2):
+            pop.easgd_step(L.ExternalBatch(torch.zeros(W, device="cuda:0")), c, 0.05, 0.1)
+        torch.cuda.synchronize()
+        out.append([v[..., n - 1000:n].clone() for v in (x, c, Z[1])])
+    assert all(torch.equal(u, v) for u, v in zip(*out))
