@@ -1170,9 +1170,13 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     // 600 000 (192 MB) 37.3 / 39.1, 1 250 000 (400 MB) 80.3 / 73.7, elastic averaging there 86.4 / 73.3; pairs of workers,
     // 16 x 250 000, 26.8 / 25.3.  Groups of one with their leaders re-selected write a copy of every row as well: 8 x 271 117
     // (26 MB) 13.6 / 17.3, 16 x 1 250 001 with momentum (400 MB) 106 / 90; with most of them kept 8 x 1 250 001 (120 MB) 43 / 39.
+    // Elastic averaging from registers reads x once and streams where that showed: 2 x 600 001 with momentum (24 MB) 7.1 / 6.3, 4 x
+    // 600 001 without 8.0 / 7.2, 8 x 271 117 with (43 MB) 9.8 / 9.3, 16 x 271 117 with (87 MB) 18.1 / 17.6; not 8 x 271 117 without
+    // (26 MB) 6.3 / 6.6, 6 x 200 001 with (24 MB) 5.7 / 6.0, 12 x 600 001 without (86 MB) 17.3 / 18.0, 4 x 1 250 001 without 14.0 / 14.4.
+    const bool center_streams = p.W <= 4 ? bytes >= 24e6 && p.P <= 1000000 : bytes >= 30e6 && p.P <= 500000;
     const bool all_fresh = q.select == 1 && (q.cap & (~0ull >> (64 - p.G))) == (~0ull >> (64 - p.G));
     const bool nt = mode == kUpdateOnes ? (all_fresh ? bytes > 200e6 : true)
-                  : bytes > 280e6 || (bytes >= 16e6 && bytes < 90e6 && mode != kCenterRegs);
+                  : bytes > 280e6 || (bytes >= 16e6 && bytes < 90e6 && (mode != kCenterRegs || center_streams));
     if (!q.update && q.comm && q.commL == 0.0f && q.commG == 0.0f) {
         const int64_t tiles = (p.P + (int64_t)kThreads * vec - 1) / ((int64_t)kThreads * vec);
         const dim3 grid((unsigned)(tiles < 2048 ? tiles : 2048));
