@@ -438,6 +438,8 @@ bool column_step(const lsgd_population* p, bool selects, int fresh, bool whole)
     }
     if (W > 32 || bytes > 300e6) return false;
     if (selects) return W >= 4 * G || (W >= 2 * G && (W <= 16 || (whole && bytes <= 100e6)));
+    // (nothing re-selected.  From registers, but for up to 4 workers without momentum from 35 MB on, which are walked by groups all
+    // the same: 4 in pairs x 800 001, row streams / walk, 13.9 / 12.2, x 1 250 001 16.4 / 14.3, x 2 000 001 (96 MB) 23.1 / 20.8)
     if (whole && W <= 16 && W >= 2 * G && bytes <= 100e6) return true;
     return W >= 4 * G && (W <= 16 || bytes >= 30e6);                   // 32 x 30 000, 8 groups: 12.3 / 13.5
 }
