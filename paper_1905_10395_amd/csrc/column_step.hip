@@ -715,18 +715,22 @@ __device__ __forceinline__ void load_pick(const ColumnDev& s, Pick& p)
     }
 }
 
-// The same behind the rows' loads, where registers are full while those are on their way; HOLD: and behind kHoldLoads loads
-// that go one after the other, which hold the call's stores back (holds_stores_*).
+// Loads one after the other, by the wavefront that selects, behind the rows' (holds_stores_*).
+__device__ __forceinline__ void hold_stores(const ColumnDev& s)
+{
+    if (threadIdx.x >= kWave) return;
+    for (int h = 0; h < kHoldLoads; ++h) {
+        const int v = s.a.lead[(int)threadIdx.x < s.a.G ? threadIdx.x : 0];
+        asm volatile("" :: "v"(v) : "memory");           // (here it has arrived)
+    }
+}
+
+// The selection's loads behind the rows', where registers are full while those are on their way, or stores are to be held back.
 template <bool HOLD>
 __device__ __forceinline__ void load_pick_behind(const ColumnDev& s, Pick& p)
 {
     __builtin_amdgcn_sched_barrier(0);
-    if (HOLD && threadIdx.x < kWave) {
-        for (int h = 0; h < kHoldLoads; ++h) {
-            const int v = s.a.lead[(int)threadIdx.x < s.a.G ? threadIdx.x : 0];
-            asm volatile("" :: "v"(v) : "memory");       // (here it has arrived)
-        }
-    }
+    if (HOLD) hold_stores(s);
     load_pick(s, p);
 }
 
@@ -858,7 +862,11 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
     // (eight rows of four columns: with what the selection reads, and every row's offset kept from its load to its store, 100
     // registers, one wavefront less per SIMD than with 96: 8 workers in 2 groups x 1 250 001 30.9 us instead of 27.6)
     constexpr bool FULL = MODE == kCommRegs && VEC == 4 && NR == 8, BEHIND = HOLD || FULL;
-    if (!BEHIND && ((MODE != kCenter && MODE != kCenterRegs) || blockIdx.x == 0)) load_pick(s, pick);
+    if (MODE == kCenter || MODE == kCenterRegs) {
+        if (blockIdx.x == 0) load_pick(s, pick);
+    } else if (!BEHIND) {
+        load_pick(s, pick);
+    }
     if constexpr (MODE == kUpdate || MODE == kCenter || MODE == kUpdatePull) {
         constexpr bool CENTER = MODE == kCenter;
         RowBatch<VEC> first;
@@ -892,6 +900,11 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
         Rows<VEC, NR> r;
         if constexpr (MODE == kCenterRegs) {
             if (live) load_rows<VEC, KIND, NT, true, NR>(s, (uint32_t)col * 4u, r);
+            if constexpr (HOLD) {
+                __builtin_amdgcn_sched_barrier(0);
+                hold_stores(s);
+                __syncthreads();
+            }
             if (blockIdx.x == 0) choose_leaders(s, pick, now, chosen);                   // the losses alone
             if (live) regs_easgd<VEC, KIND, NT, NR>(s, (uint32_t)col * 4u, r);
             return;
@@ -939,7 +952,7 @@ int64_t workgroups(int64_t cols, int vec)
 template <int VEC, int KIND, int MODE, int NR>
 constexpr bool kCanHold = MODE == kCommRegs ? (KIND ? 20.0 : 12.0) * NR * 1536 * kThreads * VEC >= 40e6
                         : MODE == kUpdateOnes ? VEC == 4 || (VEC == 2 && KIND == 1)
-                        : MODE == kUpdateRegs ? NR > 4 : MODE == kUpdate && VEC == 4 && KIND == 0;
+                        : MODE == kUpdateRegs ? NR > 4 : MODE == kCenterRegs || (MODE == kUpdate && VEC == 4 && KIND == 0);
 
 // How many workgroups of a kernel that holds its stores back are resident at once, on 256 compute units: by its registers,
 // which are asked for once, and the LDS it is launched with.
@@ -1044,6 +1057,17 @@ bool holds_stores_ones(const ColumnDev& s, double bytes)
     return bytes >= 55e6 && bytes <= 100e6 && s.a.W <= 2 * kRowsInFlight<VEC> && workgroups(s.a.col1 - s.a.col0, VEC) <= resident<VEC, KIND, kUpdateOnes, 0>(0);
 }
 
+// Elastic averaging with every row in registers, plain accesses without / streaming with: 4 x 400 001 with momentum 8.0 / 6.6, 5 x
+// 500 001 with 10.9 / 9.4, 8 x 400 001 without 9.1 / 8.3, with 13.8 / 11.8, 16 x 200 001 with 14.1 / 13.2, 32 x 140 001 with (90 MB, 547
+// workgroups) 19.3 / 18.5; not 32 x 140 001 without (54 MB) 12.1 / 12.6, 16 x 100 001 with (391 workgroups) 7.6 / 7.9, 4 x 600 001 with
+// (2344 on 2048 places), 4 x 1 250 001 without, and nothing gained below 24 MB.
+template <int KIND, int NR>
+bool holds_stores_center(const ColumnDev& s, double bytes)
+{
+    const int64_t n = workgroups(s.a.col1 - s.a.col0, 1);
+    return bytes >= 24e6 && bytes < 90e6 && n >= (bytes >= 55e6 ? 512 : 640) && n <= resident<1, KIND, kCenterRegs, NR>(0);
+}
+
 // One column per thread.
 template <int MODE, int NR = 0>
 void launch_narrow(const ColumnDev& s, bool mom, bool nt, bool hold, hipStream_t st)
@@ -1067,6 +1091,14 @@ void launch_held(const ColumnDev& s, bool mom, bool nt, double bytes, hipStream_
     bool hold = false;
     if constexpr (kCanHold<1, 0, kUpdateRegs, NR>) hold = nt && (mom ? holds_stores_regs<1, NR>(s, bytes) : holds_stores_regs<0, NR>(s, bytes));
     launch_narrow<kUpdateRegs, NR>(s, mom, nt, hold, st);
+}
+
+// Elastic averaging with every row in registers.
+template <int NR>
+void launch_center_regs(const ColumnDev& s, bool mom, bool nt, double bytes, hipStream_t st)
+{
+    const bool hold = mom ? holds_stores_center<1, NR>(s, bytes) : holds_stores_center<0, NR>(s, bytes);
+    launch_narrow<kCenterRegs, NR>(s, mom, nt || hold, hold, st);
 }
 
 // A pull alone: whether one pass over all rows beats a walk group by group, which touches only rows that move.  One pass / by
@@ -1170,10 +1202,10 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     // 600 000 (192 MB) 37.3 / 39.1, 1 250 000 (400 MB) 80.3 / 73.7, elastic averaging there 86.4 / 73.3; pairs of workers,
     // 16 x 250 000, 26.8 / 25.3.  Groups of one with their leaders re-selected write a copy of every row as well: 8 x 271 117
     // (26 MB) 13.6 / 17.3, 16 x 1 250 001 with momentum (400 MB) 106 / 90; with most of them kept 8 x 1 250 001 (120 MB) 43 / 39.
-    // Elastic averaging from registers reads x once and streams where that showed: 2 x 600 001 with momentum (24 MB) 7.1 / 6.3, 4 x
-    // 600 001 without 8.0 / 7.2, 8 x 271 117 with (43 MB) 9.8 / 9.3, 16 x 271 117 with (87 MB) 18.1 / 17.6; not 8 x 271 117 without
-    // (26 MB) 6.3 / 6.6, 6 x 200 001 with (24 MB) 5.7 / 6.0, 12 x 600 001 without (86 MB) 17.3 / 18.0, 4 x 1 250 001 without 14.0 / 14.4.
-    const bool center_streams = p.W <= 4 ? bytes >= 24e6 && p.P <= 1000000 : bytes >= 30e6 && p.P <= 500000;
+    // Elastic averaging from registers reads x once; beside the calls that hold their stores back those of few workers stream: 2 x
+    // 600 001 with momentum (24 MB) 7.1 / 6.3, 3 x 800 001 without 8.2 / 7.8, 4 x 600 001 without 8.0 / 7.2; not 12 x 600 001 without
+    // (86 MB) 17.3 / 18.0, 4 x 1 250 001 without 14.0 / 14.4.
+    const bool center_streams = p.W <= 4 && bytes >= 24e6 && p.P <= 1000000;
     const bool all_fresh = q.select == 1 && (q.cap & (~0ull >> (64 - p.G))) == (~0ull >> (64 - p.G));
     const bool nt = mode == kUpdateOnes ? (all_fresh ? bytes > 200e6 : true)
                   : bytes > 280e6 || (bytes >= 16e6 && bytes < 90e6 && (mode != kCenterRegs || center_streams));
@@ -1214,9 +1246,9 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
         break;
     case kCenter: launch_narrow<kCenter>(s, mom, nt, false, stream); break;
     case kCenterRegs:
-        if (p.W <= 8) launch_narrow<kCenterRegs, 8>(s, mom, nt, false, stream);
-        else if (p.W <= 16) launch_narrow<kCenterRegs, 16>(s, mom, nt, false, stream);
-        else launch_narrow<kCenterRegs, 32>(s, mom, nt, false, stream);
+        if (p.W <= 8) launch_center_regs<8>(s, mom, nt, bytes, stream);
+        else if (p.W <= 16) launch_center_regs<16>(s, mom, nt, bytes, stream);
+        else launch_center_regs<32>(s, mom, nt, bytes, stream);
         break;
     }
     return hipGetLastError();

@@ -259,9 +259,11 @@ def test_large_one_launch_calls_equal_separate_calls(W, off, P, mu):
     assert a[-2:] == b[-2:] and all(torch.equal(u, v) for u, v in zip(a[:-2], b[:-2]))
 
 
-@pytest.mark.parametrize("W,P,mu", [(4, 600_001, 0.0), (2, 600_001, 0.9), (8, 271_117, 0.9), (16, 100_001, 0.9), (16, 250_001, 0.0)])
+# (streaming, stores held back with 8, 16 and 32 rows, plain; the last columns alone are plain)
+@pytest.mark.parametrize("W,P,mu", [(4, 600_001, 0.0), (2, 600_001, 0.9), (8, 271_117, 0.9), (8, 400_001, 0.0), (16, 200_001, 0.9), (16, 250_001, 0.0),
+                                    (20, 150_001, 0.9), (32, 160_001, 0.0), (16, 100_001, 0.9), (32, 140_001, 0.0)])
 def test_easgd_streaming_and_plain_accesses_agree(W, P, mu):
-    """The rows of a population around the sizes at which accesses change against the same rows alone in a small one, column by
+    """The rows of a population around the sizes at which accesses and the order of loads change against the same rows alone in a small one, column by
     column: the same bits."""
     ld = (P + 63) // 64 * 64
     gen = torch.Generator(device="cuda:0").manual_seed(W)
@@ -277,5 +279,5 @@ def test_easgd_streaming_and_plain_accesses_agree(W, P, mu):
         for _ in range(2):
             pop.easgd_step(L.ExternalBatch(torch.zeros(W, device="cuda:0")), c, 0.05, 0.1)
         torch.cuda.synchronize()
-        out.append([v[..., n - 1000:n].clone() for v in (x, c, Z[1])])
+        out.append([v[..., n - 1000:n].clone() for v in (x, c, Z[1]) + ((m,) if mu else ())])
     assert all(torch.equal(u, v) for u, v in zip(*out))
