@@ -1018,49 +1018,49 @@ bool update_in_registers(const ColumnStep& q, double bytes)
 // rows come first would store while the others still wait for theirs, and reads among stores come slower: of 1221 workgroups
 // (4 workers x 1 250 001 without momentum, nothing re-selected) the last had its rows after 11.8 us, held back after 9.2.  So
 // the wavefront that selects first sends kHoldLoads loads one after the other.  They queue behind the rows of all: long while
-// the chip reads, short when it no longer does.  (A fixed number of clocks instead: 14.1 us and more where these take 12.7 and
-// nothing 13.9.  That the selection itself was once such a chain is why it was the faster one at these sizes.)  It costs about
-// 0.4 us where there is nothing to hold apart: smaller calls, or more workgroups than are resident, which store in turns anyway.
+// the chip reads, short when it no longer does.  (A fixed number of clocks instead: 14.1 us and more where these take 12.5 and
+// nothing 13.8.  That the selection itself was once such a chain is why it was the faster one at these sizes.)  It costs up to
+// 0.5 us where there is nothing to hold apart: smaller calls, or more workgroups than are resident, which store in turns anyway.
 //
-// Rows in registers, us, without / with: 12 in 3 groups x 271 117 with momentum (65 MB) 15.5 / 13.3, 8 in one x 271 117 with
-// (43 MB) 10.7 / 9.5, 16 in 4 x 170 001 with (54 MB, 665 workgroups) 12.5 / 11.4, 28 in 7 x 140 001 with (78 MB, 547) 20.2 / 17.2;
-// not 24 in 4 x 140 001 without (40 MB, 547) 10.6 / 11.0, 16 in 4 x 100 001 with (32 MB) 8.5 / 8.8, 16 in 4 x 450 001 without
-// (1758 workgroups on 1536 places) 20.1 / 20.9, 32 in 8 x 230 001 without (899 on 768) 21.9 / 23.6.
+// Rows in registers, us, without / with: 12 in 3 groups x 271 117 with momentum (65 MB) 15.9 / 13.5, 8 in one x 271 117 with
+// (43 MB) 10.5 / 9.4, 16 in 4 x 170 001 with (54 MB, 665 workgroups) 12.6 / 11.4, 28 in 7 x 140 001 with (78 MB, 547) 20.3 / 17.3;
+// not 24 in 4 x 140 001 without (40 MB, 547) 10.6 / 11.2, 16 in 4 x 100 001 with (32 MB) 8.5 / 9.0, 16 in 4 x 450 001 without
+// (1758 workgroups on 1536 places) 20.0 / 21.0, 32 in 8 x 230 001 without (899 on 768) 22.4 / 23.6.
 template <int KIND, int NR>
 bool holds_stores_regs(const ColumnDev& s, double bytes)
 {
     const int64_t n = workgroups(s.a.col1 - s.a.col0, 1);
     return (bytes >= 55e6 || (bytes >= 40e6 && n >= 640)) && n <= resident<1, KIND, kUpdateRegs, NR>(held_bytes(s.a.W, s.a.G));
 }
-// By groups: only where one batch holds all rows (4 in 2 groups x 1 250 001 14.2 / 15.2).  4 in one x 1 250 001 13.9 / 12.8, x
-// 1 000 001 11.2 / 10.8, 3 x 1 250 001 11.3 / 10.3; not x 1 400 001 (1367 workgroups on 1280 places) 15.4 / 16.8.
+// By groups: only where one batch holds all rows (4 in 2 groups x 1 250 001 14.2 / 15.2).  4 in one x 1 250 001 13.8 / 12.5, x
+// 1 000 001 11.2 / 10.6, 3 x 1 250 001 11.3 / 10.3; not x 1 400 001 (1367 workgroups on 1280 places) 15.5 / 17.0.
 bool holds_stores_batch(const ColumnDev& s, int vec, double bytes)
 {
     return s.select == 1 && vec == 4 && s.a.G == 1 && s.a.W <= kRowsInFlight<4> && bytes >= 36e6 &&
            workgroups(s.a.col1 - s.a.col0, 4) <= resident<4, 0, kUpdate, 0>(0);
 }
-// Algorithm 1's iteration: 4 x 1 250 001 16.2 / 14.0, 4 x 700 001 with momentum 13.5 / 11.7, 8 in 2 groups x 600 001 with 23.6 /
-// 21.3, without 16.2 / 15.5, x 271 117 with (43 MB) 12.7 / 11.9; not 4 x 1 600 001 (1563 workgroups) 19.7 / 20.2, 4 x 271 117 with
-// (22 MB) 7.4 / 7.9, 8 in 2 x 140 001 with (547 workgroups) 8.9 / 9.3.
+// Algorithm 1's iteration: 4 x 1 250 001 15.6 / 13.7, 4 x 700 001 with momentum 13.4 / 11.7, 8 in 2 groups x 600 001 with 23.0 /
+// 21.2, without 15.6 / 14.1, x 271 117 with (43 MB) 12.1 / 11.3; not 4 x 1 600 001 (1563 workgroups) 19.5 / 20.1, 8 in 2 x 140 001
+// with (547 workgroups) 8.3 / 8.6.
 bool holds_stores_comm(const ColumnDev& s, int vec, double bytes)
 {
     const int64_t n = workgroups(s.a.col1 - s.a.col0, vec);
     return bytes >= (vec == 4 ? 36e6 : 40e6) && n >= 768 && n <= 1536;
 }
 
-// Groups of one, while the batches ahead hold all rows: 8 x 800 001 without momentum (77 MB, 782 workgroups), one re-selected, 22.7 /
-// 20.5, x 400 001 with (64 MB) 19.3 / 17.6; not x 400 001 without (38 MB) 14.6 / 15.1, 4 x 1 250 001 without (1221 workgroups on
-// 1024 places) 17.1 / 18.9.
+// Groups of one, while the batches ahead hold all rows: 8 x 800 001 without momentum (77 MB, 782 workgroups), one re-selected, 23.1 /
+// 20.8, x 400 001 with (64 MB) 19.3 / 17.6; x 400 001 without (38 MB) no sure difference; not 4 x 1 250 001 without (1221 workgroups
+// on 1024 places) 17.1 / 19.1.
 template <int VEC, int KIND>
 bool holds_stores_ones(const ColumnDev& s, double bytes)
 {
     return bytes >= 55e6 && bytes <= 100e6 && s.a.W <= 2 * kRowsInFlight<VEC> && workgroups(s.a.col1 - s.a.col0, VEC) <= resident<VEC, KIND, kUpdateOnes, 0>(0);
 }
 
-// Elastic averaging with every row in registers, plain accesses without / streaming with: 4 x 400 001 with momentum 8.0 / 6.6, 5 x
-// 500 001 with 10.9 / 9.4, 8 x 400 001 without 9.1 / 8.3, with 13.8 / 11.8, 16 x 200 001 with 14.1 / 13.2, 32 x 140 001 with (90 MB, 547
-// workgroups) 19.3 / 18.5; not 32 x 140 001 without (54 MB) 12.1 / 12.6, 16 x 100 001 with (391 workgroups) 7.6 / 7.9, 4 x 600 001 with
-// (2344 on 2048 places), 4 x 1 250 001 without, and nothing gained below 24 MB.
+// Elastic averaging with every row in registers, plain accesses without / streaming with: 4 x 400 001 with momentum 7.8 / 6.8, 5 x
+// 500 001 with 11.1 / 9.4, 8 x 400 001 without 9.1 / 8.3, with 13.8 / 11.9, 16 x 200 001 with 14.1 / 13.2, 32 x 140 001 with (90 MB, 547
+// workgroups) 19.3 / 18.3; not 16 x 100 001 with (391 workgroups) 7.6 / 7.8, 4 x 600 001 with (2344 on 2048 places) 11.4 / 12.0, 4 x
+// 1 250 001 without 13.8 / 15.9, and nothing gained below 24 MB.
 template <int KIND, int NR>
 bool holds_stores_center(const ColumnDev& s, double bytes)
 {
