@@ -860,7 +860,7 @@ __device__ __forceinline__ void step_thread(const ColumnDev& s, Leaders& now, Le
     const Leaders& after = s.select ? chosen : now;
     Pick pick;
     // (eight rows of four columns: with what the selection reads, and every row's offset kept from its load to its store, 100
-    // registers, one wavefront less per SIMD than with 96: 8 workers in 2 groups x 1 250 001 30.9 us instead of 27.6)
+    // registers, one wavefront less per SIMD than with 96: 8 workers in 2 groups x 1 250 001 30.9 us instead of 28.0)
     constexpr bool FULL = MODE == kCommRegs && VEC == 4 && NR == 8, BEHIND = HOLD || FULL;
     if (MODE == kCenter || MODE == kCenterRegs) {
         if (blockIdx.x == 0) load_pick(s, pick);
@@ -1183,7 +1183,7 @@ hipError_t launch_column_step(const ColumnStep& q, const DeviceState& st, hipStr
     // with momentum two columns are never more than 2 % ahead, four mostly behind.  From registers, 16 workers in 4 groups,
     // 140 001 columns 8.1 / 9.3 / 9.2, with momentum 10.5 / 13.7 / 13.8, 1 250 001 46 / 52 / 59.  Algorithm 1's iteration,
     // 8 workers in 2 groups with momentum, 271 117 columns 11.9 / 13.4 / 13.4, 600 001 25.1 / 23.0 / 23.0; 4 workers without x
-    // 1 250 001 19.8 / 17.6 / 14.1.  Groups of one, 8 x 271 117, 13.6 / 12.8 / 12.5.
+    // 800 001 12.9 / 11.4 with 2 / 4, x 1 250 001 19.8 / 17.6 / 14.1.  Groups of one, 8 x 271 117, 13.6 / 12.8 / 12.5.
     // Elastic averaging, 16 without momentum x 600 001 22 / 29 / 29, with momentum x 140 001 10.0 / 12.8 / 12.8.
     int vec = 1;
     if (mode == kUpdate || mode == kUpdatePull) {
